@@ -112,38 +112,54 @@ struct RowSource {
     }
 };
 
-// The NACC sums a lane holds (columns chunk * NACC ... of bag (t, b)) to where they belong.
-template <bool HALF, bool CONCAT>
-__device__ inline void store_sums(const Acc<HALF> &acc, const PoolOut &out, int vec_ok, int b, int t,
-                                  int T, int D, int chunk)
+// N sums a lane holds (columns col ... of bag (t, b)) to where they belong.
+template <int N, bool CONCAT>
+__device__ inline void store_sums(const float *v, const PoolOut &out, int vec_ok, int b, int t, int T,
+                                  int D, int col)
 {
-    constexpr int NACC = HALF ? 8 : 4;
+    typedef __bf16 bvec __attribute__((ext_vector_type(N)));
     if (CONCAT) {
-        __bf16 *o = static_cast<__bf16 *>(out.z) + (long long)b * out.ldz + out.col0 + t * D + chunk * NACC;
+        __bf16 *o = static_cast<__bf16 *>(out.z) + (long long)b * out.ldz + out.col0 + t * D + col;
         if (vec_ok) {
-            if (HALF) {
-                bf16x8 v;
+            bvec h;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = (__bf16)acc.v[i];
-                *reinterpret_cast<bf16x8 *>(o) = v;
-            } else {
-                bf16x4 v;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = (__bf16)acc.v[i];
-                *reinterpret_cast<bf16x4 *>(o) = v;
-            }
+            for (int i = 0; i < N; ++i) h[i] = (__bf16)v[i];
+            *reinterpret_cast<bvec *>(o) = h;
         } else {
 #pragma unroll
-            for (int i = 0; i < NACC; ++i) o[i] = (__bf16)acc.v[i];
+            for (int i = 0; i < N; ++i) o[i] = (__bf16)v[i];
         }
     } else {
-        float *o = out.pooled + ((long long)b * T + t) * D + chunk * NACC;
+        constexpr int W = N < 4 ? N : 4;  // at most 16 bytes a store
+        typedef float wvec __attribute__((ext_vector_type(W)));
+        float *o = out.pooled + ((long long)b * T + t) * D + col;
 #pragma unroll
-        for (int i = 0; i < NACC; i += 4) {
-            f32x4 v = {acc.v[i], acc.v[i + 1], acc.v[i + 2], acc.v[i + 3]};
-            *reinterpret_cast<f32x4 *>(o + i) = v;
+        for (int i = 0; i < N; i += W) {
+            wvec w;
+#pragma unroll
+            for (int k = 0; k < W; ++k) w[k] = v[i + k];
+            *reinterpret_cast<wvec *>(o + i) = w;
         }
     }
+}
+
+// a <- a + (a of lane ^ M) in lanes that keep a, b + (b of lane ^ M) in the others
+// (lanes with bit M set), M = 32 or 16: one register swap and one add.
+template <int M>
+__device__ inline float fold_pair(float a, float b)
+{
+    const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
+    const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(ua, ub, false, false)
+                           : __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+// v + v of the lane R further on in its row of 16 lanes.
+template <int R>
+__device__ inline float add_ror(float v)
+{
+    const int x = __builtin_bit_cast(int, v);
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, x, 0x120 + R, 0xf, 0xf, false));
 }
 
 template <int LPR, bool HALF, bool CONCAT, bool STREAM, bool NARROW>
@@ -222,13 +238,32 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
         }
     }
 
-    // Fold the RPW partial sums: lanes l and l ^ m hold the same columns.
+    // Fold the RPW partial sums, lanes l and l ^ m holding the same columns.  While
+    // m is 32 or 16 a lane passes half of its columns to l ^ m and keeps the sum of
+    // the other half; within a row of 16 lanes the rest are rotate-and-add.  None of
+    // it goes through the LDS: folding with __shfl_xor, 24 of the 34 permutes a
+    // bag of 80 fp16 rows of 64 needed, queued on it.
+    float *v = acc.v;
+    int col = chunk * NACC;
+    constexpr int N1 = LPR <= 32 ? NACC / 2 : NACC, N2 = LPR <= 16 ? N1 / 2 : N1;
+    if constexpr (LPR <= 32) {
 #pragma unroll
-    for (int m = LPR; m < 64; m <<= 1) {
-#pragma unroll
-        for (int i = 0; i < NACC; ++i) acc.v[i] += __shfl_xor(acc.v[i], m, 64);
+        for (int i = 0; i < N1; ++i) v[i] = fold_pair<32>(v[i], v[i + N1]);
+        col += (lane >> 5) * N1;
     }
-    if (sub == 0) store_sums<HALF, CONCAT>(acc, out, vec_ok, b, t, T, D, chunk);
+    if constexpr (LPR <= 16) {
+#pragma unroll
+        for (int i = 0; i < N2; ++i) v[i] = fold_pair<16>(v[i], v[i + N2]);
+        col += (lane >> 4 & 1) * N2;
+    }
+#pragma unroll
+    for (int i = 0; i < N2; ++i) {
+        if (LPR <= 8) v[i] = add_ror<8>(v[i]);
+        if (LPR <= 4) v[i] = add_ror<4>(v[i]);
+        if (LPR <= 2) v[i] = add_ror<2>(v[i]);
+        if (LPR <= 1) v[i] = add_ror<1>(v[i]);
+    }
+    if (LPR > 8 || (lane & 15) < LPR) store_sums<N2, CONCAT>(v, out, vec_ok, b, t, T, D, col);
 }
 
 // SHORT_BAGS bags per group of LPR lanes, their load chains (offsets -> ids ->
@@ -313,7 +348,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_short_kernel(
     }
 #pragma unroll
     for (int g = 0; g < SHORT_BAGS; ++g)
-        if (live[g]) store_sums<HALF, CONCAT>(acc[g], out, vec_ok, b[g], t[g], T, D, chunk);
+        if (live[g]) store_sums<NACC, CONCAT>(acc[g].v, out, vec_ok, b[g], t[g], T, D, chunk * NACC);
 }
 
 template <int LPR, bool HALF, bool CONCAT>
