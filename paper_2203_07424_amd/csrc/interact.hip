@@ -7,8 +7,15 @@
 // narrowed to bf16 and zero padded to the GEMM's leading dimension -
 // concatenation and conversion are fused here (Sec. IV-A, operator fusion).
 //
-// LDS-tiled: a block stages X of a few samples in LDS and each wave computes
-// 16 x 16 tiles of the Gram matrix X X^T (blocks J <= I) on the matrix cores.
+// Two kernels.  interact_wave_kernel (D = 32 or 64, T <= 63, every model here):
+// one wave per sample with X in its operand registers.  It reads the pooled
+// vectors once and is bound by that: 42 MB at 40 tables x 4096 samples 13.0 ->
+// 11.8 us, 252 MB at 60 x 16384 62.1 -> 55.4 us (4.5 TB/s), 10 x 1024 fp32 (launch
+// bound) 41.5 -> 38.7 us per forward, against the LDS-tiled form; beside pooling,
+// where wave slots and barriers count, a pipelined batch of 40 x 4096 takes
+// 157 instead of 162.5 us.  interact_kernel takes the other shapes: a block
+// stages X of a few samples in LDS and each wave computes 16 x 16 tiles of the
+// Gram matrix X X^T (blocks J <= I) on the matrix cores.
 // The fp32 matrix instruction is slow (1/16 of the bf16 rate), and narrowing X
 // to bf16 would cost the interaction its fp32 accuracy, so X is split instead:
 // x = hi + lo with hi = bf16(x) and lo = bf16(x - hi), and
@@ -21,7 +28,7 @@
 // padded by 16 bytes (conflict-free 16-byte reads of 16 consecutive rows).
 // Results are collected in LDS as one bf16 output row per sample and written
 // out with full 16-byte stores.
-#include "rec_internal.h"
+#include "interact_body.h"
 
 namespace rec {
 
@@ -188,6 +195,40 @@ __global__ __launch_bounds__(IT_THREADS) void interact_kernel(const float *__res
                 *reinterpret_cast<const u32x4 *>(sO + s * ldo + 8 * c);
 }
 
+// One wave per sample, X in registers (interact_body.h); the output row is put
+// together in the wave's own LDS row.  Nothing is shared, so a wave waits for
+// nobody: the wait between its own LDS writes and reads is all there is.
+template <int NBLK, int KST>
+__global__ __launch_bounds__(IT_THREADS) void interact_wave_kernel(const float *__restrict__ x0, int ldx0,
+                                                                   const float *__restrict__ pooled, int B, int T,
+                                                                   __bf16 *__restrict__ out, int ldo)
+{
+    extern __shared__ __attribute__((aligned(16))) __bf16 s_mem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long b = (long long)blockIdx.x * IT_WAVES + wave;
+    if (b >= B) return;
+    __bf16 *z = s_mem + wave * ldo;
+    inter::RawRows<NBLK, KST> raw;
+    raw.load(x0 + b * ldx0, pooled + b * T * (32 * KST), T, lane);
+    inter::gram_row<NBLK, KST>(raw, T, z, ldo, lane);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int c = lane; c < ldo / 8; c += 64)
+        *reinterpret_cast<u32x4 *>(out + b * ldo + 8 * c) = *reinterpret_cast<const u32x4 *>(z + 8 * c);
+}
+
+template <int NBLK>
+hipError_t launch_wave(const float *x0, int ldx0, const float *pooled, int B, int T, int D, __bf16 *out, int ldo,
+                       hipStream_t s)
+{
+    const dim3 grid((B + IT_WAVES - 1) / IT_WAVES), block(IT_THREADS);
+    const size_t lds = IT_WAVES * (size_t)ldo * sizeof(__bf16);
+    if (D == 32)
+        hipLaunchKernelGGL((interact_wave_kernel<NBLK, 1>), grid, block, lds, s, x0, ldx0, pooled, B, T, out, ldo);
+    else
+        hipLaunchKernelGGL((interact_wave_kernel<NBLK, 2>), grid, block, lds, s, x0, ldx0, pooled, B, T, out, ldo);
+    return hipGetLastError();
+}
+
 // Concatenation model (no interaction operator): the dense part of each
 // Predict-FC input row, narrowed, and the zero padding behind the row.
 __global__ __launch_bounds__(256) void concat_dense_kernel(const float *__restrict__ x0, int ldx0, int w0,
@@ -223,13 +264,24 @@ hipError_t launch_interact(const float *x0, int ldx0, const float *pooled, int B
     const Geometry g = geometry(T, D);
     const size_t per = 2 * g.plane * sizeof(__bf16) + (size_t)ldo * 2;
     if (per > 64 * 1024) return hipErrorInvalidValue;  // rejected at model creation
+    __bf16 *o = static_cast<__bf16 *>(out_bf16);
+    // Up to four row blocks of up to 64 columns fit a wave's registers (100 VGPRs at
+    // most) and need aligned rows for the 16-byte loads.
+    if (inter::fits_wave(T, D) && ldx0 % 4 == 0 && reinterpret_cast<uintptr_t>(x0) % 16 == 0) {
+        switch ((T + 16) / 16) {
+        case 1: return launch_wave<1>(x0, ldx0, pooled, B, T, D, o, ldo, s);
+        case 2: return launch_wave<2>(x0, ldx0, pooled, B, T, D, o, ldo, s);
+        case 3: return launch_wave<3>(x0, ldx0, pooled, B, T, D, o, ldo, s);
+        default: return launch_wave<4>(x0, ldx0, pooled, B, T, D, o, ldo, s);
+        }
+    }
+    // Other shapes go through LDS.
     // Enough samples per block to give every wave about one tile; small blocks
     // (little LDS each) keep many of them resident, which hides the staging
     // latency of one behind the matrix work of the others.
     int spb = (IT_TILES_PER_WAVE * IT_WAVES + g.ntile - 1) / g.ntile;
     while (spb > 1 && spb * per > 32 * 1024) --spb;
     const dim3 grid((B + spb - 1) / spb), block(IT_THREADS);
-    __bf16 *o = static_cast<__bf16 *>(out_bf16);
     const size_t lds = spb * per;
     switch (g.ksteps) {
     case 1: hipLaunchKernelGGL(interact_kernel<1>, grid, block, lds, s, x0, ldx0, pooled, B, T, D, o, ldo, spb); break;

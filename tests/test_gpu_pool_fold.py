@@ -1,0 +1,47 @@
+"""The cross-lane fold of the pooling kernel for every row size it is compiled for
+(16 bytes to 1 KB, fp16 and fp32 rows), into the fp32 buffer and, narrowed, into
+the Predict-FC input of a concatenation model (aligned and unaligned columns)."""
+import numpy as np
+import pytest
+
+from oracle import rec_oracle as orc
+from paper_2203_07424_amd import synth
+
+import gpu_helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def binding():
+    from paper_2203_07424_amd import binding as b
+    return b
+
+
+@pytest.mark.parametrize("interaction,F", [("dot", 6), ("concat", 8), ("concat", 5)])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("rowbytes", [16, 32, 64, 128, 256, 512, 1024])
+def test_fold_of_every_row_size(binding, rowbytes, dtype, interaction, F):
+    print("fold case", rowbytes, np.dtype(dtype).name, interaction, F, flush=True)
+    D = rowbytes // np.dtype(dtype).itemsize
+    T, R, B = 2, 90, 21
+    g = np.random.default_rng(40 + rowbytes + F)
+    tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(dtype) for _ in range(T)]
+    lens = g.integers(0, 150, T * B).astype(np.int32)
+    lens[:3] = (0, 1, 64)
+    idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
+    layer = lambda n, k: [((g.standard_normal((n, k)) * k ** -0.5).astype(np.float32), np.zeros(n, np.float32))]
+    dot = interaction == "dot"
+    bottom = layer(D, F) if dot else []
+    width = D + T * (T + 1) // 2 if dot else F + T * D
+    m = H.make_model(binding, tabs, bottom, layer(1, width), B, idx.size, F, interaction=interaction)
+    H.run(m, synth.Batch(g.standard_normal((B, F)).astype(np.float32), idx, lens))
+    assert m.check() == (binding.REC_OK, -1)
+    P, A, nbad, _ = orc.pool(tabs, idx, lens, B, want_abs=True)
+    assert nbad == 0
+    if dot:
+        H.check_pooled(m.debug_pooled().cpu().numpy(), P, A)
+    else:  # one bf16 narrowing of a sum that is good to 1e-5 of the absolute sum
+        z = m.debug_interact().float().cpu().numpy().astype(np.float64)[:, F:F + T * D].reshape(B, T, D)
+        assert (np.abs(z - P) <= 2.0 ** -9 * np.abs(P) * 1.01 + 1.1e-5 * A + 1e-30).all()
+    m.close()
