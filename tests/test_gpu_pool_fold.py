@@ -41,7 +41,7 @@ def test_fold_of_every_row_size(binding, rowbytes, dtype, interaction, F):
     assert nbad == 0
     if dot:
         H.check_pooled(m.debug_pooled().cpu().numpy(), P, A)
-    else:  # one bf16 narrowing of a sum that is good to 1e-5 of the absolute sum
+    else:  # half an ulp of bf16's 8 significant bits (2^-8 of the value) on a sum good to 1e-5 of the absolute sum
         z = m.debug_interact().float().cpu().numpy().astype(np.float64)[:, F:F + T * D].reshape(B, T, D)
-        assert (np.abs(z - P) <= 2.0 ** -9 * np.abs(P) * 1.01 + 1.1e-5 * A + 1e-30).all()
+        assert (np.abs(z - P) <= 2.0 ** -8 * (np.abs(P) + 1e-5 * A) + 1e-5 * A + 1e-30).all()
     m.close()
