@@ -2,19 +2,28 @@
 // activations never leave the compute unit (the FC stacks of Sec. II-A and
 // Table I are narrow: a few hundred to a thousand units per layer).
 //
-// A block owns CH_ROWS samples.  Their input row is brought into LDS as bf16
-// once; every layer then reads its input from one LDS buffer and leaves its
-// output (bias, ReLU, narrowed to bf16) in the other, so between the first
-// read and the last write only weights move.  The weights come straight from
-// global memory (they stay in L2 across blocks) into the MFMA operand
-// registers: they are stored fragment by fragment, 64 lanes x 16 bytes each, so
-// every load of a wave is one contiguous KiB.  The product is computed
-// transposed, D[n][m] = sum_k W[n][k] X[m][k] on v_mfma_f32_32x32x16_bf16: a
-// lane then holds four consecutive outputs of one sample and stores them with
-// one instruction.
+// A block owns 32 samples, or 64 where that still gives (nearly) every compute
+// unit a block.  Their input row is brought into LDS as bf16 once; every layer
+// then reads its input from there and, once every wave has read it, leaves its
+// output (bias, ReLU, narrowed to bf16) in its place, so between the first read
+// and the last write only weights move.  The weights come straight from global
+// memory (they stay in L2 across blocks) into the MFMA operand registers: they
+// are stored fragment by fragment, 64 lanes x 16 bytes each, so every load of a
+// wave is one contiguous KiB.  The product is computed transposed,
+// D[n][m] = sum_k W[n][k] X[m][k] on v_mfma_f32_32x32x16_bf16: a lane then holds
+// four consecutive outputs of one sample and stores them with one instruction.
 //
-// Wave w of the eight takes the 32-column chunks w, w + 8, ... of a layer, two
-// at a time, each weight fragment requested CH_PF k-steps before it is used.
+// Wave w of the eight takes the 32-column chunks w, w + 8, ... of a layer, up to
+// four at a time.
+//
+// What bounds it: the weights of the run through each compute unit's L1.  A
+// read-only loop over the same fragments gets 53 bytes a clock and compute unit
+// on 128 of them and 48 on all; with its products this kernel gets 44.  With the
+// activation fragments read right where they are used it got 25 to 36 (0.4 MB of
+// weights, 4096 samples: 14.6 -> 10.8 us; the end of a 2560-wide Bottom-FC and
+// its Predict-FC as chains 104 -> 89 us per forward).  Two row tiles halve the
+// weights a sample asks for: four towers of 1024-512-256, 4096 samples 50 -> 32 us
+// behind the first layer (32.8 as launches of their own).
 //
 // The run ends in fp32 or bf16 rows in global memory, or - the Predict-FC's
 // one-output layer - in a dot product of the last activations (fp32, before
@@ -27,11 +36,18 @@ namespace {
 
 using namespace chain;
 
-template <bool A_F32>
-__global__ __launch_bounds__(CH_THREADS) void mlp_chain_kernel(const ChainProblem a)
+template <bool A_F32, int RT>
+__global__ __launch_bounds__(CH_THREADS) void mlp_chain_kernel(const ChainProblem a, int per_group)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    mlp_chain_block<A_F32>(a, smem, blockIdx.x, blockIdx.y, gridDim.x);
+    // Blocks run over the samples of stack 0, then stack 1, ...; XCD x (blocks are
+    // dealt round-robin) takes the x-th eighth of that list, so that its L2 holds
+    // the weights of one stack or two instead of all of them.
+    const bool eighths = (gridDim.x & 7) == 0;
+    const int v = eighths ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const int g = v / per_group, bx = v - g * per_group;
+    const int share = eighths ? min(32, min(per_group, (int)gridDim.x >> 3)) : touch_share(per_group);
+    mlp_chain_block<A_F32, RT>(a, smem, bx, g, (eighths ? bx : bx >> 3) % share, share);
 }
 
 // fp32 [N][K] -> bf16 fragments: element e of lane l of fragment (nc, ks) is
@@ -55,14 +71,33 @@ __global__ __launch_bounds__(256) void pack_chain_kernel(const float *__restrict
 
 bool chain_layer_fits(int Kpad, int Npad) { return Kpad <= CHAIN_MAX_WIDTH && Npad <= CHAIN_MAX_WIDTH; }
 
+namespace {
+
+template <bool A_F32, int RT>
+hipError_t prepare_as()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(mlp_chain_kernel<A_F32, RT>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)chain_lds_bytes<RT>(CHAIN_MAX_WIDTH + CH_LDS_PAD));
+}
+
+template <bool A_F32, int RT>
+hipError_t launch_as(const ChainProblem &a, hipStream_t s)
+{
+    const int per_group = (a.M + rows_of<RT>() - 1) / rows_of<RT>();
+    hipLaunchKernelGGL((mlp_chain_kernel<A_F32, RT>), dim3(per_group * a.groups), dim3(CH_THREADS),
+                       (chain_lds_bytes<RT>(a.ld_lds)), s, a, per_group);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t chain_prepare()
 {
-    const int most = (int)chain_lds_bytes(CHAIN_MAX_WIDTH + CH_LDS_PAD);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(mlp_chain_kernel<true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(mlp_chain_kernel<false>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    hipError_t e = prepare_as<true, 1>();
+    if (e == hipSuccess) e = prepare_as<false, 1>();
+    if (e == hipSuccess) e = prepare_as<false, 2>();
+    return e;
 }
 
 hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a)
@@ -74,7 +109,7 @@ hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a)
         if (p.Kpad[L] % PAD != 0 || p.Npad[L] % PAD != 0 || !chain_layer_fits(p.Kpad[L], p.Npad[L]))
             return hipErrorInvalidValue;
         if (L > 0 && p.Kpad[L] != p.Npad[L - 1]) return hipErrorInvalidValue;
-        widest = widest > p.Npad[L] ? widest : p.Npad[L];
+        if (L + 1 < p.n_layers) widest = widest > p.Npad[L] ? widest : p.Npad[L];
     }
     if (p.K > p.Kpad[0]) return hipErrorInvalidValue;
     a = p;
@@ -92,19 +127,19 @@ hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a)
     return hipSuccess;
 }
 
+bool chain_two_tiles(int groups, int M, int num_cus)
+{
+    return (long long)groups * ((M + 63) / 64) >= (long long)num_cus * 3 / 4;
+}
+
 hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s)
 {
     if (p.M <= 0) return hipSuccess;
     ChainProblem a;
     const hipError_t e = chain_finalize(p, a);
     if (e != hipSuccess) return e;
-    const dim3 grid((p.M + CH_ROWS - 1) / CH_ROWS, p.groups), block(CH_THREADS);
-    const size_t lds = chain_lds_bytes(a.ld_lds);
-    if (p.a_f32)
-        hipLaunchKernelGGL(mlp_chain_kernel<true>, grid, block, lds, s, a);
-    else
-        hipLaunchKernelGGL(mlp_chain_kernel<false>, grid, block, lds, s, a);
-    return hipGetLastError();
+    if (a.a_f32) return launch_as<true, 1>(a, s);
+    return chain_two_tiles(a.groups, a.M, a.num_cus) ? launch_as<false, 2>(a, s) : launch_as<false, 1>(a, s);
 }
 
 hipError_t launch_pack_chain(const float *W, int N, int K, int Npad, int Kpad, void *W_packed, hipStream_t s)

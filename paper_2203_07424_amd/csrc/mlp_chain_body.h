@@ -1,7 +1,8 @@
-// Body of the kernel that runs a stack of fully connected layers on chip
-// (csrc/mlp_chain.hip has the description), as a device function: the block
-// that calls it may be one of that kernel's own, or a spare block of another
-// launch that the stack rides along with.
+// Body of the kernels that run a stack of fully connected layers on chip
+// (csrc/mlp_chain.hip has the description), as device functions: the block that
+// calls them may be one of that kernel's own, a spare block of the scan that the
+// stack rides along with, or a block that has just put the stack's input
+// together in LDS itself (csrc/tail.hip).
 #ifndef REC_MLP_CHAIN_BODY_H
 #define REC_MLP_CHAIN_BODY_H
 #include "rec_internal.h"
@@ -9,11 +10,9 @@
 namespace rec {
 namespace chain {
 
-constexpr int CH_ROWS = 32;
 constexpr int CH_WAVES = 8;
 constexpr int CH_THREADS = CH_WAVES * 64;
-constexpr int CH_PF = 8;      // k-steps (of 16) a weight fragment is requested ahead
-static_assert(CH_PF == 8, "the tail of chunk_product assumes rounds of 8 and widths padded to 64");
+static_assert(CHAIN_MAX_WIDTH <= 4 * 32 * CH_WAVES, "a wave takes at most four chunks of 32 output columns");
 constexpr int CH_LDS_PAD = 8; // elements added to an LDS row: consecutive rows start 4 banks apart
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -22,220 +21,386 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// Input rows -> LDS as bf16, zero for rows >= M and columns >= K.
+// Rows of activations a block holds: RT tiles of 32.
+template <int RT>
+constexpr int rows_of() { return 32 * RT; }
+
+// Eight (bf16) or four (fp32) columns of an input row; zero from column K on.
 template <bool A_F32>
-__device__ inline void stage_input(const ChainProblem &a, int g, int row0, __bf16 *dst, int ld)
-{
-    const int Kpad = a.Kpad[0];
-    const int tid = threadIdx.x;
-    if (A_F32) {
-        const float *A = static_cast<const float *>(a.A) + (long long)g * a.a_stride;
-        if (a.a_vec) {  // four columns per thread
-            const int per_row = Kpad / 4;
-            for (int i = tid; i < CH_ROWS * per_row; i += CH_THREADS) {
-                const int r = i / per_row, k = (i - r * per_row) * 4;
-                f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (row0 + r < a.M && k < a.K)  // K is a multiple of 4 here
-                    v = *reinterpret_cast<const f32x4 *>(A + (long long)(row0 + r) * a.lda + k);
-                bf16x4 o;
+struct InVec;
+template <>
+struct InVec<true> {
+    static constexpr int W = 4;
+    f32x4 v;
+    __device__ inline void load(const float *p, int, int) { v = *reinterpret_cast<const f32x4 *>(p); }
+    __device__ inline void zero() { v = f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }
+    __device__ inline void store(__bf16 *d) const
+    {
+        bf16x4 o;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
-                *reinterpret_cast<bf16x4 *>(dst + r * ld + k) = o;
+        for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
+        *reinterpret_cast<bf16x4 *>(d) = o;
+    }
+};
+template <>
+struct InVec<false> {
+    static constexpr int W = 8;
+    bf16x8 v;
+    __device__ inline void load(const __bf16 *p, int k, int K)
+    {
+        v = *reinterpret_cast<const bf16x8 *>(p);
+        if (k + 8 > K) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (k + e >= K) v[e] = (__bf16)0.0f;
+        }
+    }
+    __device__ inline void zero()
+    {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.0f;
+    }
+    __device__ inline void store(__bf16 *d) const { *reinterpret_cast<bf16x8 *>(d) = v; }
+};
+
+// Input rows -> LDS as bf16, zero for rows >= M and columns >= K.  Each of the
+// `rows` (a power of two) has CH_THREADS / rows threads of its own; up to BATCH
+// loads of a thread are in flight.
+template <bool A_F32, int BATCH>
+__device__ inline void stage_input(const ChainProblem &a, int g, int row0, int rows, __bf16 *dst, int ld)
+{
+    typedef typename std::conditional<A_F32, float, __bf16>::type elem;
+    const int TPR = CH_THREADS / rows;
+    const int Kpad = a.Kpad[0];
+    const int r = threadIdx.x / TPR, c = threadIdx.x % TPR;
+    const bool live = row0 + r < a.M;
+    const elem *A = static_cast<const elem *>(a.A) + (long long)g * a.a_stride + (long long)(row0 + r) * a.lda;
+    __bf16 *row = dst + r * ld;
+    if (a.a_vec) {
+        typedef InVec<A_F32> Vec;
+        const int STEP = TPR * Vec::W;
+        for (int k0 = c * Vec::W; k0 < Kpad; k0 += BATCH * STEP) {
+            Vec v[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int k = k0 + u * STEP;
+                v[u].zero();
+                if (live && k < a.K) v[u].load(A + k, k, a.K);
             }
-        } else {
-            for (int i = tid; i < CH_ROWS * Kpad; i += CH_THREADS) {
-                const int r = i / Kpad, k = i - r * Kpad;
-                const float v = (row0 + r < a.M && k < a.K) ? A[(long long)(row0 + r) * a.lda + k] : 0.0f;
-                dst[r * ld + k] = (__bf16)v;
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int k = k0 + u * STEP;
+                if (k < Kpad) v[u].store(row + k);
             }
         }
     } else {
-        const __bf16 *A = static_cast<const __bf16 *>(a.A) + (long long)g * a.a_stride;
-        if (a.a_vec) {  // eight columns per thread
-            const int per_row = Kpad / 8;
-            for (int i = tid; i < CH_ROWS * per_row; i += CH_THREADS) {
-                const int r = i / per_row, k = (i - r * per_row) * 8;
-                bf16x8 v;
+        for (int k0 = c; k0 < Kpad; k0 += BATCH * TPR) {
+            float v[BATCH];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.0f;
-                if (row0 + r < a.M && k < a.K) {
-                    v = *reinterpret_cast<const bf16x8 *>(A + (long long)(row0 + r) * a.lda + k);
-                    if (k + 8 > a.K) {
+            for (int u = 0; u < BATCH; ++u) {
+                const int k = k0 + u * TPR;
+                v[u] = live && k < a.K ? (float)A[k] : 0.0f;
+            }
 #pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            if (k + e >= a.K) v[e] = (__bf16)0.0f;
-                    }
-                }
-                *reinterpret_cast<bf16x8 *>(dst + r * ld + k) = v;
-            }
-        } else {
-            for (int i = tid; i < CH_ROWS * Kpad; i += CH_THREADS) {
-                const int r = i / Kpad, k = i - r * Kpad;
-                dst[r * ld + k] = (row0 + r < a.M && k < a.K) ? A[(long long)(row0 + r) * a.lda + k] : (__bf16)0.0f;
-            }
+            for (int u = 0; u < BATCH; ++u)
+                if (k0 + u * TPR < Kpad) row[k0 + u * TPR] = (__bf16)v[u];
         }
     }
 }
 
-// acc_c += W_c X^T over all KS k-steps for NCH (1 or 2) chunks of 32 output
-// columns.  Straight-line code: every weight fragment is requested CH_PF steps
-// before its use, the requests past the end repeat the last fragment instead of
-// branching (a branch would make the compiler wait for all loads at every step).
-template <int NCH>
-__device__ inline void chunk_product(const u32x4 *w0, const u32x4 *w1, const __bf16 *xrow, int KS,
-                                     f32x16 &acc0, f32x16 &acc1)
-{
-    u32x4 q0[CH_PF], q1[CH_PF];
-    const int lastk = KS - 1;
-#pragma unroll
-    for (int p = 0; p < CH_PF; ++p) {
-        const int k = min(p, lastk);
-        q0[p] = w0[k * 64];
-        if (NCH == 2) q1[p] = w1[k * 64];
-    }
-    int ks = 0;
-    for (; ks + CH_PF <= KS; ks += CH_PF) {
-#pragma unroll
-        for (int p = 0; p < CH_PF; ++p) {
-            const bf16x8 x = *reinterpret_cast<const bf16x8 *>(xrow + (ks + p) * 16);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, q0[p]), x, acc0, 0, 0, 0);
-            if (NCH == 2)
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, q1[p]), x, acc1, 0, 0, 0);
-            const int k = min(ks + p + CH_PF, lastk);
-            q0[p] = w0[k * 64];
-            if (NCH == 2) q1[p] = w1[k * 64];
-            __builtin_amdgcn_sched_barrier(0);  // keep each request where it is written: CH_PF steps ahead
-        }
-    }
-    if (ks < KS) {  // KS is a multiple of 4: half a round is left, already in q[0..3]
-#pragma unroll
-        for (int p = 0; p < CH_PF / 2; ++p) {
-            const bf16x8 x = *reinterpret_cast<const bf16x8 *>(xrow + (ks + p) * 16);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, q0[p]), x, acc0, 0, 0, 0);
-            if (NCH == 2)
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, q1[p]), x, acc1, 0, 0, 0);
-        }
-    }
-}
+// k-steps (of 16) a weight fragment is requested before its use.
+template <int CNT>
+constexpr int fetch_ahead() { return CNT <= 2 ? 8 : 4; }
 
-// One block's share of the run: samples bx * CH_ROWS ... of stack g, bx out of
-// grid_x blocks.  `smem` is chain_lds_bytes(a.ld_lds) of dynamic LDS; all
-// CH_THREADS threads of the block take part.
-template <bool A_F32>
-__device__ inline void mlp_chain_block(const ChainProblem &a, unsigned char *smem, int bx, int g, int grid_x)
-{
-    const int ld = a.ld_lds;
-    // Two activation buffers of CH_ROWS rows; one base pointer and integer offsets,
-    // so that every access is compiled as an LDS access.
-    __bf16 *lds = reinterpret_cast<__bf16 *>(smem);
-    float *red = reinterpret_cast<float *>(smem + 2 * (size_t)CH_ROWS * ld * sizeof(__bf16));  // [CH_WAVES][CH_ROWS]
+// The weights of CNT chunks of 32 output columns on their way to the products:
+// fragments straight from global memory (L2) into operand registers, requested
+// fetch_ahead() steps before their use in straight-line code (a branch around a
+// request makes the compiler wait for all of them).
+template <int CNT>
+struct WeightStream {
+    static constexpr int PF = fetch_ahead<CNT>();
+    const char *w;   // chunk 0's first fragment (the same in all lanes), chunk c wstep bytes further on
+    unsigned wstep, lane16;
+    int KS;          // k-steps in all, a multiple of 4
+    u32x4 q[PF][CNT];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int row0 = bx * CH_ROWS;
-    const int m = lane & 31, half = lane >> 5;  // sample of this lane, and which 8 of a step's 16 k
-
-    // All blocks walk the weights in the same order at the same time, so a line
-    // missing in the L2 is missing for every block that wants it.  Before anything
-    // else the blocks that share an L2 (every eighth block, the XCDs taking blocks
-    // round-robin) each touch their slice of every layer's weights: one load per
-    // 128-byte line, all in flight together while the input rows are staged.
-    unsigned touched = 0;
+    __device__ inline u32x4 at(int c, int k) const
     {
-        const int share = min(16, max(1, grid_x >> 3));
-        const int mine = (bx >> 3) % share;
-        for (int L = 0; L < a.n_layers; ++L) {
-            const int lines = a.Kpad[L] * a.Npad[L] / 64;  // bf16: 64 elements per line
-            const int per = (lines + share - 1) / share;
-            const unsigned *w = static_cast<const unsigned *>(a.W[L][g]);
-            for (int i = mine * per + tid; i < min(lines, (mine + 1) * per); i += CH_THREADS)
-                touched |= w[(size_t)i * 32];
-        }
+        return *reinterpret_cast<const u32x4 *>(w + (c * wstep + (unsigned)k * 1024u) + lane16);
     }
-    stage_input<A_F32>(a, g, row0, lds, ld);
-    asm volatile("" ::"v"(touched));  // the loads above are issued, their values unused
-    __syncthreads();
+    __device__ inline WeightStream(const char *w_, unsigned wstep_, int KS_) : w(w_), wstep(wstep_), KS(KS_)
+    {
+        lane16 = (threadIdx.x & 63) * 16;
+#pragma unroll
+        for (int p = 0; p < PF; ++p)
+#pragma unroll
+            for (int c = 0; c < CNT; ++c) q[p][c] = at(c, min(p, KS - 1));
+    }
+};
 
-    float dot_part = 0.0f;
-    int cur = 0;
-    for (int L = 0; L < a.n_layers; ++L) {
-        const int KS = a.Kpad[L] / 16, NC = a.Npad[L] / 32;
-        const bool last = L + 1 == a.n_layers;
-        const bool relu = a.relu[L] != 0;
-        const u32x4 *W = static_cast<const u32x4 *>(a.W[L][g]);  // fragment (nc, ks) at W[(nc * KS + ks) * 64 + lane]
-        const float *bias = a.bias[L][g];
-        const __bf16 *xrow = lds + cur * CH_ROWS * ld + m * ld + half * 8;
-        __bf16 *yrow = lds + (cur ^ 1) * CH_ROWS * ld + m * ld;
+// acc[c][j] += W_c X_j^T over the KS k-steps of RT tiles of 32 samples; x is this
+// lane's part of row tile 0.  The activation fragments are read from LDS a group
+// of XG steps before their products, so that neither their latency nor the
+// weights' is met at a product.
+template <int CNT, int RT>
+__device__ inline void chunk_product(WeightStream<CNT> &ws, const __bf16 *x, int xstep, int KS,
+                                     f32x16 (&acc)[CNT][RT])
+{
+    constexpr int PF = WeightStream<CNT>::PF;
+    constexpr int XG = CNT * RT >= 8 ? 1 : CNT * RT >= 4 ? 2 : 4;
+    const auto rows = [&](bf16x8 (&f)[XG][RT], int k) {
+#pragma unroll
+        for (int p = 0; p < XG; ++p)
+#pragma unroll
+            for (int j = 0; j < RT; ++j) f[p][j] = *reinterpret_cast<const bf16x8 *>(x + j * xstep + (k + p) * 16);
+    };
+    bf16x8 xf[XG][RT];
+    rows(xf, 0);
 
-        for (int nc0 = wave; nc0 < NC; nc0 += 2 * CH_WAVES) {
-            const int nc1 = nc0 + CH_WAVES;
-            const bool two = nc1 < NC;  // wave-uniform
-            const u32x4 *w0 = W + (size_t)nc0 * KS * 64 + lane;
-            const u32x4 *w1 = W + (size_t)(two ? nc1 : nc0) * KS * 64 + lane;
-            f32x16 acc0, acc1;
+    int ks = 0;
+    for (; ks + PF < KS; ks += PF) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc0[r] = acc1[r] = 0.0f;
-            if (two)
-                chunk_product<2>(w0, w1, xrow, KS, acc0, acc1);
-            else
-                chunk_product<1>(w0, w1, xrow, KS, acc0, acc1);
-            // acc[r] is output column n = 32 nc + 8 (r / 4) + 4 half + r % 4 of sample m.
+        for (int g = 0; g < PF / XG; ++g) {
+            bf16x8 xn[XG][RT];
+            rows(xn, ks + XG * (g + 1));
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                if (c == 1 && !two) break;
-                const f32x16 &acc = c == 0 ? acc0 : acc1;
-                const int nbase = (c == 0 ? nc0 : nc1) * 32 + 4 * half;
+            for (int p = 0; p < XG; ++p) {
+                const int slot = XG * g + p;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n = nbase + 8 * q;
-                    const f32x4 bq = *reinterpret_cast<const f32x4 *>(bias + n);
-                    f32x4 v;
+                for (int c = 0; c < CNT; ++c)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        v[e] = acc[4 * q + e] + bq[e];
-                        if (relu) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
-                    }
-                    if (!last) {
-                        bf16x4 o;
+                    for (int j = 0; j < RT; ++j)
+                        acc[c][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ws.q[slot][c]),
+                                                                            xf[p][j], acc[c][j], 0, 0, 0);
+                const int k = min(ks + slot + PF, KS - 1);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
-                        *reinterpret_cast<bf16x4 *>(yrow + n) = o;
-                    } else if (a.out_mode == CHAIN_OUT_DOT) {
-                        const f32x4 wq = *reinterpret_cast<const f32x4 *>(a.dot_w[g] + n);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) dot_part += v[e] * wq[e];
-                    } else if (row0 + m < a.M) {
-                        const long long at = (long long)(row0 + m) * a.ldc + (long long)g * a.c_stride + n;
-                        if (a.out_mode == CHAIN_OUT_F32) {
-                            *reinterpret_cast<f32x4 *>(static_cast<float *>(a.C) + at) = v;
-                        } else {
-                            bf16x4 o;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
-                            *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.C) + at) = o;
-                        }
-                    }
-                }
+                for (int c = 0; c < CNT; ++c) ws.q[slot][c] = ws.at(c, k);
+                __builtin_amdgcn_sched_barrier(0);  // keep each request where it is written
             }
-        }
-        __syncthreads();
-        cur ^= 1;
-    }
-
-    if (a.out_mode == CHAIN_OUT_DOT) {
-        // Per sample: the two half-waves, then the waves in order.
-        dot_part += __shfl_xor(dot_part, 32, 64);
-        if (lane < 32) red[wave * CH_ROWS + m] = dot_part;
-        __syncthreads();
-        if (tid < CH_ROWS && row0 + tid < a.M) {
-            float sum = 0.0f;
 #pragma unroll
-            for (int w = 0; w < CH_WAVES; ++w) sum += red[w * CH_ROWS + tid];
-            a.dot_out[(long long)(row0 + tid) * a.dot_ld + g] = sum + a.dot_bias[g][0];
+            for (int p = 0; p < XG; ++p)
+#pragma unroll
+                for (int j = 0; j < RT; ++j) xf[p][j] = xn[p][j];
+        }
+    }
+    // The last up to PF steps, a multiple of 4: no weights are requested any more.
+#pragma unroll
+    for (int g = 0; g < PF / XG; ++g) {
+        if (ks + XG * g < KS) {
+            if (g > 0) rows(xf, ks + XG * g);
+#pragma unroll
+            for (int p = 0; p < XG; ++p)
+#pragma unroll
+                for (int c = 0; c < CNT; ++c)
+#pragma unroll
+                    for (int j = 0; j < RT; ++j)
+                        acc[c][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ws.q[XG * g + p][c]),
+                                                                            xf[p][j], acc[c][j], 0, 0, 0);
         }
     }
 }
 
-inline size_t chain_lds_bytes(int ld) { return 2 * (size_t)CH_ROWS * ld * sizeof(__bf16) + sizeof(float) * CH_WAVES * CH_ROWS; }
+// All blocks walk the weights in the same order at the same time, so a line missing
+// in the L2 is missing for every block that wants it, and one compute unit's
+// misses in flight are few.  So the blocks that share an L2 each touch a slice of
+// the weights up front, one load per 128-byte line, all in flight together.  The
+// caller consumes the result (done()) once it has something else to wait for.
+constexpr int TOUCH = 4;  // lines a thread touches at most
+struct Touched {
+    unsigned v[TOUCH];
+    __device__ inline void done() const
+    {
+#pragma unroll
+        for (int u = 0; u < TOUCH; ++u) asm volatile("" ::"v"(v[u]));
+    }
+};
+// Slice `mine` of `share` of the run's weights.
+__device__ inline Touched touch_weights(const ChainProblem &a, int g, int mine, int share)
+{
+    int total = 0;
+    for (int L = 0; L < a.n_layers; ++L) total += a.Kpad[L] * a.Npad[L] / 64;  // bf16: 64 elements per line
+    const int per = (total + share - 1) / share, end = min(total, (mine + 1) * per);
+    Touched t;
+#pragma unroll
+    for (int u = 0; u < TOUCH; ++u) t.v[u] = 0;
+    int base = 0;
+    for (int L = 0; L < a.n_layers; ++L) {
+        const unsigned *w = static_cast<const unsigned *>(a.W[L][g]);
+        const int lines = a.Kpad[L] * a.Npad[L] / 64;
+#pragma unroll
+        for (int u = 0; u < TOUCH; ++u) {
+            const int f = mine * per + u * CH_THREADS + (int)threadIdx.x;
+            if (f < end && f >= base && f < base + lines) t.v[u] = w[(size_t)(f - base) * 32];
+        }
+        base += lines;
+    }
+    return t;
+}
+// Blocks are dealt to the 8 XCDs round-robin.  Of a launch of n blocks, how many
+// share an XCD's touching; beyond 32 a slice is down to a few lines a wave.
+__device__ inline int touch_share(int n) { return min(32, max(1, n >> 3)); }
+
+// What the layers of a run share.
+struct RunCtx {
+    __bf16 *X;     // activations, bf16 [rows][ld]
+    float *x0s;    // fp32 copy of the last activations for the caller (or null), [rows][x0_ld]
+    int ld, x0_ld;
+    int g, row0;
+    int last_row;  // rows - 1: lanes past it work on copies and leave nothing behind
+};
+
+// One layer for a wave that has CNT chunks (first, first + 8, ...) of row tiles
+// tile .. tile + RT - 1: product, the block's barrier if the output goes back to
+// X, epilogue.  Adds the wave's part of the one-output layer behind the run to
+// dot_part.
+template <int CNT, int RT>
+__device__ inline void layer_pass(const ChainProblem &a, const RunCtx &t, int L, int first, int tile, float (&dot_part)[RT])
+{
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // else every address below is kept in registers across all layers
+    const int m = lane & 31, half = lane >> 5;  // sample of this lane in a row tile, and which 8 of a step's 16 k
+    const int KS = a.Kpad[L] / 16;
+    const bool last = L + 1 == a.n_layers, relu = a.relu[L] != 0;
+    // acc[c][j][r] is output column n = 32 (first + 8 c) + 8 (r / 4) + 4 half + r % 4
+    // of sample 32 (tile + j) + m.
+    f32x16 acc[CNT][RT];
+    f32x4 bv[CNT][4];
+    const auto load_bias = [&]() {
+        const float *bias = a.bias[L][t.g] + first * 32 + 4 * half;
+#pragma unroll
+        for (int c = 0; c < CNT; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bv[c][i] = *reinterpret_cast<const f32x4 *>(bias + c * CH_WAVES * 32 + 8 * i);
+    };
+    if (CNT <= 2) load_bias();  // early, where there are registers to keep it in
+#pragma unroll
+    for (int c = 0; c < CNT; ++c)
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[c][j][r] = 0.0f;
+    // fragment (nc, ks) is the KiB at W + (nc * KS + ks) * 1024
+    WeightStream<CNT> ws(static_cast<const char *>(a.W[L][t.g]) + (size_t)first * KS * 1024,
+                         (unsigned)(CH_WAVES * KS * 1024), KS);
+    chunk_product<CNT, RT>(ws, t.X + (tile * 32 + (m & t.last_row)) * t.ld + half * 8, 32 * t.ld, KS, acc);
+    if (CNT > 2) load_bias();
+    __builtin_amdgcn_sched_barrier(0);  // nothing of the epilogue into the product's registers
+    if (!last) __syncthreads();  // every wave has read the input: the output may replace it
+#pragma unroll
+    for (int c = 0; c < CNT; ++c) {
+#pragma unroll
+        for (int j = 0; j < RT; ++j) {
+            const int row = (tile + j) * 32 + m;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = (first + c * CH_WAVES) * 32 + 8 * q + 4 * half;
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float s = acc[c][j][4 * q + e] + bv[c][q][e];
+                    v[e] = relu && s < 0.0f ? 0.0f : s;
+                }
+                bf16x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
+                if (!last) {
+                    if (m <= t.last_row) *reinterpret_cast<bf16x4 *>(t.X + row * t.ld + n) = o;
+                } else if (a.out_mode == CHAIN_OUT_DOT) {
+                    const f32x4 wq = *reinterpret_cast<const f32x4 *>(a.dot_w[t.g] + n);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dot_part[j] += v[e] * wq[e];
+                } else if (m <= t.last_row) {
+                    if (t.x0s && n < t.x0_ld) *reinterpret_cast<f32x4 *>(t.x0s + row * t.x0_ld + n) = v;
+                    if (t.row0 + row < a.M) {
+                        const long long at = (long long)(t.row0 + row) * a.ldc + (long long)t.g * a.c_stride + n;
+                        if (a.out_mode == CHAIN_OUT_F32)
+                            *reinterpret_cast<f32x4 *>(static_cast<float *>(a.C) + at) = v;
+                        else
+                            *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.C) + at) = o;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// The layers of run `a` on the rows in t.X (the first layer's Kpad columns valid,
+// visible to the whole block).  Each layer's output replaces its input in place:
+// a wave keeps its sums in registers until every wave has read the input.  A
+// wave takes chunks wave, wave + 8, ... of 32 output columns for all RT row tiles,
+// or, with two row tiles and at most four chunks, one chunk of one tile.
+// red: [CH_WAVES][rows] floats of LDS.
+template <int RT>
+__device__ inline void run_layers(const ChainProblem &a, const RunCtx &t, float *red)
+{
+    constexpr int R = rows_of<RT>();
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float dot_part[RT];
+#pragma unroll
+    for (int j = 0; j < RT; ++j) dot_part[j] = 0.0f;
+    int tile = 0;
+    bool split = false;  // row tiles dealt to the waves too: a wave's sums belong to row tile `tile`
+    for (int L = 0; L < a.n_layers; ++L) {
+        const int NC = a.Npad[L] / 32;
+        split = RT == 2 && NC <= CH_WAVES / 2;
+        const int first = split ? wave & (CH_WAVES / 2 - 1) : wave;
+        tile = split ? wave / (CH_WAVES / 2) : 0;
+        const int cnt = first < NC ? (NC - first + CH_WAVES - 1) / CH_WAVES : 0;
+        if (cnt == 0) {
+            if (L + 1 < a.n_layers) __syncthreads();  // the one inside layer_pass()
+        } else if (split) {
+            float part[1] = {0.0f};
+            layer_pass<1, 1>(a, t, L, first, tile, part);
+            dot_part[0] = part[0];
+        } else if (cnt == 1) {
+            layer_pass<1, RT>(a, t, L, first, 0, dot_part);
+        } else if (cnt == 2) {
+            layer_pass<2, RT>(a, t, L, first, 0, dot_part);
+        } else if (cnt == 3) {
+            layer_pass<3, RT>(a, t, L, first, 0, dot_part);
+        } else {
+            layer_pass<4, RT>(a, t, L, first, 0, dot_part);
+        }
+        if (L + 1 < a.n_layers) __syncthreads();
+    }
+    if (a.out_mode != CHAIN_OUT_DOT) return;
+    // Per sample: the two half-waves, then the waves in order.
+#pragma unroll
+    for (int j = 0; j < RT; ++j) {
+        const float d = dot_part[j] + __shfl_xor(dot_part[j], 32, 64);
+        // a split layer leaves one tile's part in dot_part[0] and nothing for the other
+        if (lane < 32) red[wave * R + ((split ? tile ^ j : j) * 32) + lane] = d;
+    }
+    __syncthreads();
+    if (tid < R && (tid & 31) <= t.last_row && t.row0 + tid < a.M) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int w = 0; w < CH_WAVES; ++w) sum += red[w * R + tid];
+        a.dot_out[(long long)(t.row0 + tid) * a.dot_ld + t.g] = sum + a.dot_bias[t.g][0];
+    }
+}
+
+// Dynamic LDS of a block: the activations and the partial dots of its waves.
+template <int RT>
+constexpr size_t act_bytes(int ld) { return (size_t)rows_of<RT>() * ld * sizeof(__bf16); }
+template <int RT>
+constexpr size_t chain_lds_bytes(int ld) { return act_bytes<RT>(ld) + sizeof(float) * CH_WAVES * rows_of<RT>(); }
+
+// One block's share of the run: samples bx * rows ... of stack g.  The block is
+// number `mine` of the `share` that run this stack on one XCD.  `smem` is
+// chain_lds_bytes<RT>(a.ld_lds) of dynamic LDS; all CH_THREADS threads take part.
+template <bool A_F32, int RT>
+__device__ inline void mlp_chain_block(const ChainProblem &a, unsigned char *smem, int bx, int g, int mine, int share)
+{
+    __bf16 *X = reinterpret_cast<__bf16 *>(smem);
+    float *red = reinterpret_cast<float *>(smem + act_bytes<RT>(a.ld_lds));
+    const RunCtx t{X, nullptr, a.ld_lds, 0, g, bx * rows_of<RT>(), 31};
+    const Touched touched = touch_weights(a, g, mine, share);
+    stage_input<A_F32, RT == 2 ? 16 : 8>(a, g, t.row0, rows_of<RT>(), X, a.ld_lds);
+    touched.done();
+    __syncthreads();
+    run_layers<RT>(a, t, red);
+}
 
 }  // namespace chain
 }  // namespace rec

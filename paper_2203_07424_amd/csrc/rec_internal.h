@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "rec.h"
 
 namespace rec {
@@ -146,9 +148,12 @@ struct ChainProblem {
     const float *dot_w[MAX_GROUPS];
     const float *dot_bias[MAX_GROUPS];
     float *dot_out; int dot_ld;
+    int num_cus;
     int ld_lds, a_vec;  // filled in by chain_finalize()
 };
 bool chain_layer_fits(int Kpad, int Npad);
+// Do blocks of 64 samples (two row tiles) cover three quarters of the compute units?
+bool chain_two_tiles(int groups, int M, int num_cus);
 // Checks p and completes it (LDS row pitch, whether wide input loads apply) into a.
 hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a);
 hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s);

@@ -195,7 +195,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_tile_offsets(const int32_t 
 
 // The same with a stack of fully connected layers riding along: blocks of
 // chain::CH_THREADS threads; behind the scan's and the copy's blocks come
-// chain_grid_x blocks that each take chain::CH_ROWS samples through the stack.
+// chain_grid_x blocks that each take 32 samples through the stack.
 // A scan block uses its first SCAN_THREADS threads; the waves of the others end
 // at once (a barrier counts only the waves of a group that have not ended).
 __global__ __launch_bounds__(chain::CH_THREADS) void scan_offsets_ride_kernel(
@@ -210,7 +210,8 @@ __global__ __launch_bounds__(chain::CH_THREADS) void scan_offsets_ride_kernel(
     } else if (b < tiles + extra) {
         concat_dense_block(job, b - tiles, extra);
     } else {
-        chain::mlp_chain_block<true>(a, smem, b - tiles - extra, 0, chain_grid_x);
+        const int bx = b - tiles - extra, share = chain::touch_share(chain_grid_x);
+        chain::mlp_chain_block<true, 1>(a, smem, bx, 0, (bx >> 3) % share, share);
     }
 }
 
@@ -224,7 +225,7 @@ hipError_t launch_clear_err(ErrRecord *err, hipStream_t s)
 
 hipError_t scan_prepare()
 {
-    const int most = (int)chain::chain_lds_bytes(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
+    const int most = (int)chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
     return hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, most);
 }
@@ -257,9 +258,9 @@ hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *of
         ChainProblem a;
         const hipError_t e = chain_finalize(*rider, a);
         if (e != hipSuccess) return e;
-        const int chain_grid_x = (a.M + chain::CH_ROWS - 1) / chain::CH_ROWS;
+        const int chain_grid_x = (a.M + 31) / 32;
         hipLaunchKernelGGL(scan_offsets_ride_kernel, dim3(tiles + extra + chain_grid_x),
-                           dim3(chain::CH_THREADS), chain::chain_lds_bytes(a.ld_lds), s, lengths, n, nnz, sums,
+                           dim3(chain::CH_THREADS), chain::chain_lds_bytes<1>(a.ld_lds), s, lengths, n, nnz, sums,
                            offsets, err, tiles, job, extra, a, chain_grid_x);
         return hipGetLastError();
     }
