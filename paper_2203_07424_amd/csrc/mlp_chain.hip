@@ -36,8 +36,8 @@ namespace {
 
 using namespace chain;
 
-template <bool A_F32, int RT>
-__global__ __launch_bounds__(CH_THREADS) void mlp_chain_kernel(const ChainProblem a, int per_group)
+template <bool A_F32, int RT, int MAXC>
+__global__ __launch_bounds__(CH_THREADS, waves_per_simd<MAXC>()) void mlp_chain_kernel(const ChainProblem a, int per_group)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // Blocks run over the samples of stack 0, then stack 1, ...; XCD x (blocks are
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(CH_THREADS) void mlp_chain_kernel(const ChainProble
     const int v = eighths ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
     const int g = v / per_group, bx = v - g * per_group;
     const int share = eighths ? min(32, min(per_group, (int)gridDim.x >> 3)) : touch_share(per_group);
-    mlp_chain_block<A_F32, RT>(a, smem, bx, g, (eighths ? bx : bx >> 3) % share, share);
+    mlp_chain_block<A_F32, RT, MAXC>(a, smem, bx, g, (eighths ? bx : bx >> 3) % share, share);
 }
 
 // fp32 [N][K] -> bf16 fragments: element e of lane l of fragment (nc, ks) is
@@ -69,23 +69,23 @@ __global__ __launch_bounds__(256) void pack_chain_kernel(const float *__restrict
 
 }  // namespace
 
-bool chain_layer_fits(int Kpad, int Npad) { return Kpad <= CHAIN_MAX_WIDTH && Npad <= CHAIN_MAX_WIDTH; }
+bool chain_layer_fits(int Kpad, int Npad, int max_input) { return Kpad <= max_input && Npad <= CHAIN_MAX_WIDTH; }
 
 namespace {
 
-template <bool A_F32, int RT>
+template <bool A_F32, int RT, int MAXC>
 hipError_t prepare_as()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(mlp_chain_kernel<A_F32, RT>),
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(mlp_chain_kernel<A_F32, RT, MAXC>),
                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)chain_lds_bytes<RT>(CHAIN_MAX_WIDTH + CH_LDS_PAD));
 }
 
-template <bool A_F32, int RT>
+template <bool A_F32, int RT, int MAXC>
 hipError_t launch_as(const ChainProblem &a, hipStream_t s)
 {
     const int per_group = (a.M + rows_of<RT>() - 1) / rows_of<RT>();
-    hipLaunchKernelGGL((mlp_chain_kernel<A_F32, RT>), dim3(per_group * a.groups), dim3(CH_THREADS),
+    hipLaunchKernelGGL((mlp_chain_kernel<A_F32, RT, MAXC>), dim3(per_group * a.groups), dim3(CH_THREADS),
                        (chain_lds_bytes<RT>(a.ld_lds)), s, a, per_group);
     return hipGetLastError();
 }
@@ -94,19 +94,21 @@ hipError_t launch_as(const ChainProblem &a, hipStream_t s)
 
 hipError_t chain_prepare()
 {
-    hipError_t e = prepare_as<true, 1>();
-    if (e == hipSuccess) e = prepare_as<false, 1>();
-    if (e == hipSuccess) e = prepare_as<false, 2>();
+    hipError_t e = prepare_as<true, 1, 1>();
+    if (e == hipSuccess) e = prepare_as<true, 1, 4>();
+    if (e == hipSuccess) e = prepare_as<false, 1, 1>();
+    if (e == hipSuccess) e = prepare_as<false, 1, 4>();
+    if (e == hipSuccess) e = prepare_as<false, 2, 4>();
     return e;
 }
 
-hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a)
+hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a, int max_input)
 {
     if (p.n_layers < 1 || p.n_layers > CHAIN_MAX_LAYERS || p.groups < 1 || p.groups > MAX_GROUPS)
         return hipErrorInvalidValue;
     int widest = p.Kpad[0];
     for (int L = 0; L < p.n_layers; ++L) {
-        if (p.Kpad[L] % PAD != 0 || p.Npad[L] % PAD != 0 || !chain_layer_fits(p.Kpad[L], p.Npad[L]))
+        if (p.Kpad[L] % PAD != 0 || p.Npad[L] % PAD != 0 || !chain_layer_fits(p.Kpad[L], p.Npad[L], L == 0 ? max_input : CHAIN_MAX_WIDTH))
             return hipErrorInvalidValue;
         if (L > 0 && p.Kpad[L] != p.Npad[L - 1]) return hipErrorInvalidValue;
         if (L + 1 < p.n_layers) widest = widest > p.Npad[L] ? widest : p.Npad[L];
@@ -129,7 +131,9 @@ hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a)
 
 bool chain_two_tiles(int groups, int M, int num_cus)
 {
-    return (long long)groups * ((M + 63) / 64) >= (long long)num_cus * 3 / 4;
+    if (num_cus <= 0) return false;
+    const long long blocks = (long long)groups * ((M + 63) / 64), rounds = (blocks + num_cus - 1) / num_cus;
+    return 4 * blocks >= 3 * rounds * num_cus;
 }
 
 hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s)
@@ -138,8 +142,9 @@ hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s)
     ChainProblem a;
     const hipError_t e = chain_finalize(p, a);
     if (e != hipSuccess) return e;
-    if (a.a_f32) return launch_as<true, 1>(a, s);
-    return chain_two_tiles(a.groups, a.M, a.num_cus) ? launch_as<false, 2>(a, s) : launch_as<false, 1>(a, s);
+    if (narrow_run(a)) return a.a_f32 ? launch_as<true, 1, 1>(a, s) : launch_as<false, 1, 1>(a, s);
+    if (a.a_f32) return launch_as<true, 1, 4>(a, s);
+    return chain_two_tiles(a.groups, a.M, a.num_cus) ? launch_as<false, 2, 4>(a, s) : launch_as<false, 1, 4>(a, s);
 }
 
 hipError_t launch_pack_chain(const float *W, int N, int K, int Npad, int Kpad, void *W_packed, hipStream_t s)

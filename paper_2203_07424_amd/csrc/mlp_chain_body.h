@@ -330,7 +330,11 @@ __device__ inline void layer_pass(const ChainProblem &a, const RunCtx &t, int L,
 // wave takes chunks wave, wave + 8, ... of 32 output columns for all RT row tiles,
 // or, with two row tiles and at most four chunks, one chunk of one tile.
 // red: [CH_WAVES][rows] floats of LDS.
-template <int RT>
+// MAXC: the most chunks a wave has in any layer, 4 (up to 1024 columns) or 1 (up to
+// 256: 128 registers instead of 174 to 236, so that two blocks share a compute
+// unit and a launch of more blocks than compute units does not take a second
+// round for it: towers of 96-72, 264 blocks, 24.0 -> 19.4 us per forward).
+template <int RT, int MAXC>
 __device__ inline void run_layers(const ChainProblem &a, const RunCtx &t, float *red)
 {
     constexpr int R = rows_of<RT>();
@@ -354,12 +358,13 @@ __device__ inline void run_layers(const ChainProblem &a, const RunCtx &t, float 
             dot_part[0] = part[0];
         } else if (cnt == 1) {
             layer_pass<1, RT>(a, t, L, first, 0, dot_part);
-        } else if (cnt == 2) {
-            layer_pass<2, RT>(a, t, L, first, 0, dot_part);
-        } else if (cnt == 3) {
-            layer_pass<3, RT>(a, t, L, first, 0, dot_part);
-        } else {
-            layer_pass<4, RT>(a, t, L, first, 0, dot_part);
+        } else if constexpr (MAXC > 1) {
+            if (cnt == 2)
+                layer_pass<2, RT>(a, t, L, first, 0, dot_part);
+            else if (cnt == 3)
+                layer_pass<3, RT>(a, t, L, first, 0, dot_part);
+            else
+                layer_pass<4, RT>(a, t, L, first, 0, dot_part);
         }
         if (L + 1 < a.n_layers) __syncthreads();
     }
@@ -386,10 +391,21 @@ constexpr size_t act_bytes(int ld) { return (size_t)rows_of<RT>() * ld * sizeof(
 template <int RT>
 constexpr size_t chain_lds_bytes(int ld) { return act_bytes<RT>(ld) + sizeof(float) * CH_WAVES * rows_of<RT>(); }
 
+// Does MAXC = 1 take the run?
+inline bool narrow_run(const ChainProblem &a)
+{
+    for (int L = 0; L < a.n_layers; ++L)
+        if (a.Npad[L] > 32 * CH_WAVES) return false;
+    return true;
+}
+// Blocks a compute unit is to hold at a time: sets the registers a wave gets.
+template <int MAXC>
+constexpr int waves_per_simd() { return MAXC == 1 ? 4 : 2; }
+
 // One block's share of the run: samples bx * rows ... of stack g.  The block is
 // number `mine` of the `share` that run this stack on one XCD.  `smem` is
 // chain_lds_bytes<RT>(a.ld_lds) of dynamic LDS; all CH_THREADS threads take part.
-template <bool A_F32, int RT>
+template <bool A_F32, int RT, int MAXC>
 __device__ inline void mlp_chain_block(const ChainProblem &a, unsigned char *smem, int bx, int g, int mine, int share)
 {
     __bf16 *X = reinterpret_cast<__bf16 *>(smem);
@@ -399,7 +415,7 @@ __device__ inline void mlp_chain_block(const ChainProblem &a, unsigned char *sme
     stage_input<A_F32, RT == 2 ? 16 : 8>(a, g, t.row0, rows_of<RT>(), X, a.ld_lds);
     touched.done();
     __syncthreads();
-    run_layers<RT>(a, t, red);
+    run_layers<RT, MAXC>(a, t, red);
 }
 
 }  // namespace chain

@@ -129,12 +129,13 @@ hipError_t fc_big_prepare();
 //   X_{L+1} = act_L(X_L W_{L,g}^T + bias_{L,g}),  act_L = ReLU where relu[L] != 0,
 // each layer narrowing its input to bf16 as the per-layer path does.  Layer L is
 // Kpad[L] -> Npad[L] with Kpad[L + 1] == Npad[L], all at most CHAIN_MAX_WIDTH
-// and multiples of PAD; W[L][g] is the fragment order launch_pack_chain() writes.
+// (Kpad[0] TAIL_MAX_INPUT in a tail) and multiples of PAD; W[L][g] is the fragment order launch_pack_chain() writes.
 // The last X goes to C_g = C + g * c_stride (CHAIN_OUT_BF16 / CHAIN_OUT_F32, row
 // stride ldc), or (CHAIN_OUT_DOT) into the one-output layer that follows:
 //   dot_out[m * dot_ld + g] = sum_n X[m][n] * dot_w[g][n] + dot_bias[g][0]   in fp32.
 constexpr int CHAIN_MAX_LAYERS = 6;
 constexpr int CHAIN_MAX_WIDTH = 1024;
+constexpr int TAIL_MAX_INPUT = 2048;  // Kpad of the first Predict-FC layer in launch_tail()
 enum { CHAIN_OUT_BF16 = 0, CHAIN_OUT_F32 = 1, CHAIN_OUT_DOT = 2 };
 struct ChainProblem {
     const void *A; bool a_f32; int lda; long long a_stride;
@@ -151,16 +152,39 @@ struct ChainProblem {
     int num_cus;
     int ld_lds, a_vec;  // filled in by chain_finalize()
 };
-bool chain_layer_fits(int Kpad, int Npad);
-// Do blocks of 64 samples (two row tiles) cover three quarters of the compute units?
+bool chain_layer_fits(int Kpad, int Npad, int max_input = CHAIN_MAX_WIDTH);
+// Do blocks of 64 samples (two row tiles, one block a compute unit) fill at least
+// three quarters of the rounds they take?  (256 blocks of four 1024-512-256 towers:
+// 107.7 -> 102.4 us per forward; 376, two rounds: 113.1 -> 117.8, so not there.)
 bool chain_two_tiles(int groups, int M, int num_cus);
 // Checks p and completes it (LDS row pitch, whether wide input loads apply) into a.
-hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a);
+hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a, int max_input = CHAIN_MAX_WIDTH);
 hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).
 hipError_t chain_prepare();
 // fp32 [N][K] -> bf16 [Npad * Kpad] in MFMA fragment order (nearest even, zero padded).
 hipError_t launch_pack_chain(const float *W, int N, int K, int Npad, int Kpad, void *W_packed, hipStream_t s);
+
+// Interaction and Predict-FC of a dot model with one tower in one launch, behind
+// the last layers of Bottom-FC where run[0].n_layers > 0.
+//   run[0]: bf16 input, CHAIN_OUT_F32 into the x0 buffer (M rows)
+//   x0:     fp32 rows of Bottom-FC's output, 16-byte aligned, ldx0 % 4 == 0 (run[0].n_layers == 0)
+//   run[1]: input z (its A is not read), CHAIN_OUT_DOT
+//   z:      the Predict-FC input rows, written for inspection, ldz == run[1].Kpad[0]
+struct TailProblem {
+    ChainProblem run[2];  // Bottom-FC part, Predict-FC
+    const float *x0; int ldx0;
+    const float *pooled;
+    int T, D;
+    void *z; int ldz;
+    int rows, ld_lds;  // filled in by launch_tail()
+};
+bool tail_fits(int T, int D);
+// Up to how many samples a compute unit gets no more than one block.
+int tail_most_samples(int num_cus);
+hipError_t launch_tail(const TailProblem &p, int num_cus, hipStream_t s);
+// Once per process and device, before the first launch (not under stream capture).
+hipError_t tail_prepare();
 
 // Last Predict-FC layer of every stack: logits[m * ld + g] = sum_k A_g[m][k] * w_g[k] + bias_g[0]
 // in fp32.  A_g = A + g * a_stride is fp32 [M][lda] (a_f32) or bf16 [M][lda];

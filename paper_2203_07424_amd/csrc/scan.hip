@@ -198,7 +198,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_tile_offsets(const int32_t 
 // chain_grid_x blocks that each take 32 samples through the stack.
 // A scan block uses its first SCAN_THREADS threads; the waves of the others end
 // at once (a barrier counts only the waves of a group that have not ended).
-__global__ __launch_bounds__(chain::CH_THREADS) void scan_offsets_ride_kernel(
+template <int MAXC>
+__global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<MAXC>()) void scan_offsets_ride_kernel(
     const int32_t *__restrict__ len, int n, long long nnz, const long long *__restrict__ tile_sums,
     int32_t *__restrict__ offsets, ErrRecord *err, int tiles, const ConcatDense job, int extra,
     const ChainProblem a, int chain_grid_x)
@@ -211,7 +212,7 @@ __global__ __launch_bounds__(chain::CH_THREADS) void scan_offsets_ride_kernel(
         concat_dense_block(job, b - tiles, extra);
     } else {
         const int bx = b - tiles - extra, share = chain::touch_share(chain_grid_x);
-        chain::mlp_chain_block<true, 1>(a, smem, bx, 0, (bx >> 3) % share, share);
+        chain::mlp_chain_block<true, 1, MAXC>(a, smem, bx, 0, (bx >> 3) % share, share);
     }
 }
 
@@ -226,7 +227,10 @@ hipError_t launch_clear_err(ErrRecord *err, hipStream_t s)
 hipError_t scan_prepare()
 {
     const int most = (int)chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<1>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<4>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, most);
 }
 
@@ -259,9 +263,10 @@ hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *of
         const hipError_t e = chain_finalize(*rider, a);
         if (e != hipSuccess) return e;
         const int chain_grid_x = (a.M + 31) / 32;
-        hipLaunchKernelGGL(scan_offsets_ride_kernel, dim3(tiles + extra + chain_grid_x),
-                           dim3(chain::CH_THREADS), chain::chain_lds_bytes<1>(a.ld_lds), s, lengths, n, nnz, sums,
-                           offsets, err, tiles, job, extra, a, chain_grid_x);
+        auto k = chain::narrow_run(a) ? scan_offsets_ride_kernel<1> : scan_offsets_ride_kernel<4>;
+        hipLaunchKernelGGL(k, dim3(tiles + extra + chain_grid_x), dim3(chain::CH_THREADS),
+                           chain::chain_lds_bytes<1>(a.ld_lds), s, lengths, n, nnz, sums, offsets, err, tiles, job,
+                           extra, a, chain_grid_x);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(scan_tile_offsets, dim3(tiles + extra), dim3(SCAN_THREADS), 0, s, lengths, n, nnz,
