@@ -20,10 +20,12 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 template <int NBLK, int KST>
 struct RawRows {
     f32x4 v[NBLK][KST][2];
-    // Row 0 is x0, rows 1 .. T the pooled vectors (contiguous), the rest zero.
+    // Row 0 is x0 (loaded here, or null and left to load_x0()), rows 1 .. T the
+    // pooled vectors (contiguous), the rest zero.
     __device__ inline void load(const float *x0, const float *pooled, int T, int lane)
     {
         const int r16 = lane & 15, kq = lane >> 4;
+        const int first = x0 ? 0 : 1;
 #pragma unroll
         for (int I = 0; I < NBLK; ++I) {
             const int r = 16 * I + r16;
@@ -33,10 +35,20 @@ struct RawRows {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     v[I][ks][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                    if (r <= T) v[I][ks][h] = *reinterpret_cast<const f32x4 *>(p + 32 * ks + 4 * h);
+                    if (r >= first && r <= T) v[I][ks][h] = *reinterpret_cast<const f32x4 *>(p + 32 * ks + 4 * h);
                 }
             }
         }
+    }
+    // Row 0 from LDS.
+    __device__ inline void load_x0(const float *x0, int lane)
+    {
+        if ((lane & 15) != 0) return;
+#pragma unroll
+        for (int ks = 0; ks < KST; ++ks)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                v[0][ks][h] = *reinterpret_cast<const f32x4 *>(x0 + 32 * ks + 8 * (lane >> 4) + 4 * h);
     }
 };
 

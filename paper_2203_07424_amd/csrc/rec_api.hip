@@ -29,10 +29,11 @@ struct Layer {
     const float *bias = nullptr;  // fp32 [Npad]
     bool dot = false;             // last Predict-FC layer: fp32 dot product, not a GEMM
     bool chain = false;           // narrow enough for the kernel that runs several layers on chip
-    const void *Wc = nullptr;     // chain layers: the same weights in MFMA fragment order
+    bool packed = false;          // kept in MFMA fragment order too: chain layers, and a wider input of the tail kernel
+    const void *Wc = nullptr;     // the weights in that order
     bool loaded = false;
     size_t w_bytes() const { return dot ? sizeof(float) * Kpad : 2 * (size_t)Npad * Kpad; }
-    size_t chain_bytes() const { return chain ? 2 * (size_t)Npad * Kpad : 0; }
+    size_t chain_bytes() const { return packed ? 2 * (size_t)Npad * Kpad : 0; }
 };
 
 }  // namespace
@@ -134,6 +135,17 @@ Carve carve(const rec_model *m, int batch, int frames)
 }  // namespace
 
 namespace {
+
+// Can S3 + S4 run as the one launch of csrc/tail.hip?
+bool tail_possible(const rec_model *m)
+{
+    const int n = m->n_top - 1;  // layers ahead of the one-output layer
+    if (m->interaction != REC_INTERACT_DOT || m->towers != 1 || n < 1 || n > CHAIN_MAX_LAYERS || !tail_fits(m->T, m->D))
+        return false;
+    for (int i = 0; i < n; ++i)
+        if (!chain_layer_fits(m->top[i].Kpad, m->top[i].Npad, i == 0 ? TAIL_MAX_INPUT : CHAIN_MAX_WIDTH)) return false;
+    return true;
+}
 
 bool all_loaded(const rec_model *m)
 {
@@ -256,10 +268,13 @@ int chain_end(const rec_model *m, const Layer *layers, int i, int n, int G, int 
     return bytes > CHAIN_AUTO_BYTES ? i : j;
 }
 
-// S2: ReLU after every layer; the last one leaves fp32 for the interaction.
-hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev)
+// S2: ReLU after every layer; the last one leaves fp32 for the interaction.  Of
+// the layers only the first `upto_layer`, the tail kernel taking the others
+// (their input: *rest, row stride *rest_ld).
+hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev,
+                          int upto_layer, const void **rest, int *rest_ld)
 {
-    const int n = (int)m->bottom.size();
+    const int all = (int)m->bottom.size(), n = upto_layer;
     const Layer *layers = m->bottom.data();
     const void *A = c.dense;
     bool a_f32 = true;
@@ -267,13 +282,13 @@ hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipS
     for (int i = 0; i < n;) {
         const int j = chain_end(m, layers, i, n, 1, c.B, a_f32, false);
         const int upto = j > i ? j : i + 1;
-        const bool last = upto == n;
+        const bool last = upto == all;
         void *C = last ? static_cast<void *>(u.x0) : u.act[1 + (launches & 1)];
         const int ldc = last ? m->x0_ld : m->act_ld;
         if (j > i) {
             ChainProblem cp{};
             cp.A = A; cp.a_f32 = a_f32; cp.lda = lda; cp.a_stride = 0; cp.M = c.B;
-            chain_run(layers, n, 1, i, j, m->num_cus, cp);
+            chain_run(layers, all, 1, i, j, m->num_cus, cp);
             cp.out_mode = last ? CHAIN_OUT_F32 : CHAIN_OUT_BF16;
             cp.C = C; cp.ldc = ldc; cp.c_stride = 0;
             REC_TRY(launch_mlp_chain(cp, s));
@@ -292,17 +307,12 @@ hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipS
         i = upto;
     }
     if (launches == 0) REC_TRY(mark(ev, EV_BOTTOM_FIRST_END, s));
+    if (rest) { *rest = A; *rest_ld = lda; }
     return mark(ev, EV_BOTTOM_END, s);
 }
-
-// S0 and S1.  With hot lists registered (and use_hot), hot rows are served from
-// LDS.  In the concatenation model the sums go straight into the Predict-FC
-// input rows.
-// A concatenation model without Bottom-FC has the dense part of its Predict-FC
-// input rows written by spare blocks of the scan: one launch less in front of S4.
-bool concat_rides_on_scan(const rec_model *m)
+hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev)
 {
-    return m->interaction == REC_INTERACT_CONCAT && m->bottom.empty();
+    return enqueue_bottom(m, u, c, s, ev, (int)m->bottom.size(), nullptr, nullptr);
 }
 
 // Bottom-FC does not depend on the sparse side (Sec. III-A): when the whole
@@ -313,6 +323,55 @@ bool bottom_rides_on_scan(const rec_model *m)
 {
     const int n = (int)m->bottom.size();
     return n > 0 && !m->pipeline && !m->overlap_dense && chain_end(m, m->bottom.data(), 0, n, 1, 1, true, false) == n;
+}
+
+// The first layer of Bottom-FC that the tail kernel would take (none: the number of
+// layers): a run of narrow layers at its end, behind at least one layer that
+// narrows the input, when the stack does not ride on the scan as a whole.
+int tail_bottom_from(const rec_model *m)
+{
+    const int n = (int)m->bottom.size();
+    if (m->overlap_dense || m->pipeline || bottom_rides_on_scan(m)) return n;
+    int i = n;
+    while (i > 1 && m->bottom[i - 1].chain && n - i < CHAIN_MAX_LAYERS) --i;
+    return i;
+}
+
+// Do S3 and S4 of this call run as the one launch of csrc/tail.hip?  Measured on
+// the 40-table model (1.05 MB of weights, 2 launches saved) and the one with a
+// 2560-wide Bottom-FC (0.95 MB, 4 saved), us per forward as separate launches / as
+// one, uniform ids over small tables: a block streams all weights whatever its
+// samples, 10 us a MB, so at small batches it has to save a launch per 320 KB
+// (B = 256: 45.4 / 47.2, 57.8 / 48.7); from a dozen samples a compute unit the
+// separate layers are past their launch cost as well and it wins regardless
+// (4096: 267.7 / 264.8, 92.1 / 81.6); with more samples than compute units can
+// take in one round of blocks it loses (16384: 892 / 900, 251 / 260).
+bool tail_applies(const rec_model *m, const Call &c)
+{
+    if (m->fuse_mlp == 0 || !tail_possible(m)) return false;
+    if (m->bottom.empty() && (m->F % 4 != 0 || reinterpret_cast<uintptr_t>(c.dense) % 16 != 0)) return false;
+    if (m->fuse_mlp == 2) return true;
+    if (m->pipeline || c.B > tail_most_samples(m->num_cus)) return false;
+    const int n = m->n_top - 1, nb = (int)m->bottom.size();
+    size_t bytes = 0, launches = 0;
+    for (int i = 0; i < n;) {
+        const int j = chain_end(m, m->top.data(), i, n, 1, c.B, false, true);
+        for (int l = i; l < std::max(j, i + 1); ++l) bytes += m->top[l].chain_bytes();
+        i = std::max(j, i + 1);
+        ++launches;
+    }
+    for (int i = tail_bottom_from(m); i < nb; ++i, ++launches) bytes += m->bottom[i].chain_bytes();
+    return bytes <= launches * 320 * 1024 || c.B >= 12 * m->num_cus;
+}
+
+// S0 and S1.  With hot lists registered (and use_hot), hot rows are served from
+// LDS.  In the concatenation model the sums go straight into the Predict-FC
+// input rows.
+// A concatenation model without Bottom-FC has the dense part of its Predict-FC
+// input rows written by spare blocks of the scan: one launch less in front of S4.
+bool concat_rides_on_scan(const rec_model *m)
+{
+    return m->interaction == REC_INTERACT_CONCAT && m->bottom.empty();
 }
 
 hipError_t enqueue_scan(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, bool with_bottom)
@@ -368,9 +427,40 @@ hipError_t enqueue_sparse(const rec_model *m, const Bufs &u, const Call &c, bool
     return mark(ev, EV_POOL_END, s);
 }
 
+// S3 and S4 in one launch, behind the Bottom-FC layers [from, ...) on `rest`.
+hipError_t enqueue_fused_tail(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev,
+                              int from, const void *rest, int rest_ld)
+{
+    const int nb = (int)m->bottom.size(), n = m->n_top - 1;
+    TailProblem t{};
+    if (from < nb) {
+        ChainProblem &b = t.run[0];
+        b.A = rest; b.a_f32 = false; b.lda = rest_ld; b.M = c.B;
+        chain_run(m->bottom.data(), nb, 1, from, nb, m->num_cus, b);
+        b.out_mode = CHAIN_OUT_F32;
+        b.C = u.x0; b.ldc = m->x0_ld;
+    }
+    // Without a Bottom-FC the dense part of the Predict-FC input is the dense input.
+    t.x0 = nb ? u.x0 : c.dense;
+    t.ldx0 = nb ? m->x0_ld : m->F;
+    t.pooled = u.pooled; t.T = m->T; t.D = m->D;
+    t.z = u.act[0]; t.ldz = m->z_ld;
+    t.run[1].A = u.act[0]; t.run[1].lda = m->z_ld; t.run[1].M = c.B;
+    chain_run(m->top.data(), m->n_top, 1, 0, n, m->num_cus, t.run[1]);
+    t.run[1].out_mode = CHAIN_OUT_DOT;
+    t.run[1].dot_w[0] = static_cast<const float *>(m->top[n].W);
+    t.run[1].dot_bias[0] = m->top[n].bias;
+    t.run[1].dot_out = c.logits; t.run[1].dot_ld = 1;
+    REC_TRY(mark(ev, EV_INTERACT_END, s));
+    REC_TRY(launch_tail(t, m->num_cus, s));
+    REC_TRY(mark(ev, EV_TOP_FIRST_END, s));
+    return mark(ev, EV_END, s);
+}
+
 // S3 and S4.
 hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev)
 {
+    if (tail_applies(m, c)) return enqueue_fused_tail(m, u, c, s, ev, (int)m->bottom.size(), nullptr, 0);
     const int B = c.B, T = m->T, D = m->D;
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
     // Without a Bottom-FC the dense part of the Predict-FC input is the dense input.
@@ -462,6 +552,11 @@ hipError_t enqueue_in_order(const rec_model *m, const Bufs &u, const Call &c, bo
     if (ride) {  // S2 ran inside S0's second launch: its stages read zero
         REC_TRY(mark(ev, EV_BOTTOM_FIRST_END, s));
         REC_TRY(mark(ev, EV_BOTTOM_END, s));
+    } else if (const int from = tail_bottom_from(m); from < (int)m->bottom.size() && tail_applies(m, c)) {
+        const void *rest = nullptr;
+        int rest_ld = 0;
+        REC_TRY(enqueue_bottom(m, u, c, s, ev, from, &rest, &rest_ld));
+        return enqueue_fused_tail(m, u, c, s, ev, from, rest, rest_ld);
     } else {
         REC_TRY(enqueue_bottom(m, u, c, s, ev));
     }
@@ -482,7 +577,8 @@ rec_status static_scratch(char **out)
     if (!g_scratch_ptr[dev]) {
         void *p = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return REC_ERR_DEVICE;
-        if (fc_big_prepare() != hipSuccess || chain_prepare() != hipSuccess || scan_prepare() != hipSuccess)
+        if (fc_big_prepare() != hipSuccess || chain_prepare() != hipSuccess || scan_prepare() != hipSuccess ||
+            tail_prepare() != hipSuccess)
             return REC_ERR_DEVICE;
         g_scratch_ptr[dev] = static_cast<char *>(p);
     }
@@ -625,6 +721,7 @@ rec_status rec_create(const rec_config *cfg, rec_model **out)
             v[i].K = w[i]; v[i].N = w[i + 1];
             v[i].Kpad = pad_up(w[i]); v[i].Npad = pad_up(w[i + 1]);
             v[i].chain = chain_layer_fits(v[i].Kpad, v[i].Npad);
+            v[i].packed = v[i].chain;
             if (i + 1 < n || side_by_side == 1)  // the one-output layer leaves no activation row
                 m->act_ld = std::max(m->act_ld, side_by_side * v[i].Npad);
         }
@@ -636,7 +733,10 @@ rec_status rec_create(const rec_config *cfg, rec_model **out)
         fill(&m->top[(size_t)k * cfg->n_top], cfg->top_widths, cfg->n_top, towers);
         m->top[(size_t)k * cfg->n_top + cfg->n_top - 1].dot = true;
         m->top[(size_t)k * cfg->n_top + cfg->n_top - 1].chain = false;
+        m->top[(size_t)k * cfg->n_top + cfg->n_top - 1].packed = false;
     }
+    if (tail_possible(m))
+        m->top[0].packed = true;
     m->act_row_bytes = 2 * (size_t)m->act_ld;
     if (cfg->n_top > 1)  // the layer feeding the dot leaves fp32
         m->act_row_bytes = std::max(m->act_row_bytes, sizeof(float) * towers * m->top[cfg->n_top - 2].Npad);
@@ -687,9 +787,8 @@ rec_status rec_bind_workspace(rec_model *m, void *dev_ptr, size_t bytes, void *s
     for (bool &b : m->tail_pending) b = false;
     m->next_frame = m->last_frame = 0;
     m->pool_turn = 0;
-    if (fc_big_prepare() != hipSuccess || chain_prepare() != hipSuccess || scan_prepare() != hipSuccess)
-            return REC_ERR_DEVICE;
-    {   // set-up is also where the static scratch of this device is looked up
+    {   // set-up is also where the kernels are granted their LDS and the static scratch
+        // of this device is looked up, once per device
         char *unused = nullptr;
         if (static_scratch(&unused) != REC_OK) return REC_ERR_DEVICE;
     }
@@ -758,7 +857,7 @@ rec_status rec_load_mlp(rec_model *m, int32_t which, int32_t layer, const float 
     const hipError_t e = l->dot ? launch_pack_dot(dev_W, dev_b, l->K, l->Kpad, reinterpret_cast<float *>(p), bias, s)
                                 : launch_pack_fc(dev_W, dev_b, l->N, l->K, l->Npad, l->Kpad, p, bias, s);
     if (e != hipSuccess) return REC_ERR_DEVICE;
-    if (l->chain) {
+    if (l->packed) {
         char *pc = p + align_up(l->w_bytes()) + align_up(sizeof(float) * l->Npad);
         if (launch_pack_chain(dev_W, l->N, l->K, l->Npad, l->Kpad, pc, s) != hipSuccess) return REC_ERR_DEVICE;
         l->Wc = pc;
