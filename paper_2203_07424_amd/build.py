@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "librec_mi355x.so")
 
-SOURCES = ["scan.hip", "pool.hip", "pool_hot.hip", "gemm.hip", "gemm_big.hip", "mlp_chain.hip", "tail.hip", "interact.hip", "synth_fill.hip", "probe.hip", "rec_api.hip"]
+SOURCES = ["scan.hip", "pool.hip", "pool_hot.hip", "gemm.hip", "gemm_big.hip", "mlp_chain.hip", "tail.hip", "front.hip", "interact.hip", "synth_fill.hip", "probe.hip", "rec_api.hip"]
 
 # The packed-fp32 target feature is switched off for all device code.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
@@ -36,8 +36,7 @@ SAN_FLAGS = ["-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsaniti
 def _compile(src: str, force: bool, sanitize: bool = False) -> str:
     s = os.path.join(CSRC, src)
     o = os.path.join(OBJ_SAN if sanitize else OBJ, src + ".o")
-    deps = [s, os.path.join(CSRC, "rec_internal.h"), os.path.join(CSRC, "mlp_chain_body.h"),
-            os.path.join(CSRC, "interact_body.h"),
+    deps = [s, *(os.path.join(CSRC, h) for h in sorted(os.listdir(CSRC)) if h.endswith(".h")),
             os.path.join(ROOT, "include", "rec.h"),
             os.path.join(ROOT, "include", "rec_synth.h"), os.path.join(ROOT, "include", "rec_probe.h"),
             os.path.abspath(__file__)]

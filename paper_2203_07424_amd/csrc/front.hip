@@ -1,0 +1,246 @@
+// S0 and S1 in one launch, with Bottom-FC (S2) riding along: everything up to the
+// pooled vectors, for small batches.
+//
+// Pooling needs where its bags start, which is why the scan runs before it.  But a
+// block of pooling waves takes neighbouring bags, so it needs one sum, that of all
+// earlier lengths, and a few thousand lengths are added up by its threads with a
+// few loads each, all in flight together: about as long as reading the offsets
+// the scan would have left, and a launch (8 to 9 us with Bottom-FC inside, 9 to 11
+// for the two of a model without) less in front of it.  The offsets themselves
+// are still written, by the scan's own blocks, for inspection and for its checks.
+//
+// front_kernel (pooled dot model, Bottom-FC of narrow layers): blocks of 8 waves;
+// first those of the scan, then those of Bottom-FC, then pooling, one bag a wave.
+// front_short_kernel (concatenation model without Bottom-FC, bags of a few ids):
+// blocks of 4 waves; the scan's, those that narrow the dense part, then pooling.
+//
+// The pooling waves of front_kernel get the 106 registers Bottom-FC's need, so 16
+// of them share a compute unit instead of 32.  Up to LONG_BAGS that costs less
+// than the launch: 8 tables x 256 samples 18.1 -> 15.4 us per forward, one sample
+// 17.1 -> 13.8; 40 x 128 37.8 -> 33.5, 10 x 512 33.2 -> 29.9 (uniform ids); beyond
+// it loses (10 x 1024 34.3 -> 37.0, 8 x 2048 23.9 -> 34.7).  front_short_kernel:
+// 26 tables x 300 samples 47.4 -> 44.8 us, x 16 36.7 -> 34.0, even at 16380 bags,
+// where adding up the lengths takes as long as the launches it saves.
+#include <algorithm>
+
+#include "mlp_chain_body.h"
+#include "pool_body.h"
+#include "scan_body.h"
+
+namespace rec {
+
+namespace {
+
+using namespace scan;
+using namespace pool;
+
+constexpr int LONG_BAGS = 3 * SCAN_TILE, SHORT_FORM_BAGS = 6 * SCAN_TILE;
+
+// Sum over max(len, 0) of lengths [0, n) by all threads of the block; s_w: a word
+// per wave.
+template <int THREADS>
+__device__ inline long long sum_before(const int32_t *__restrict__ len, int n, long long *s_w)
+{
+    long long sum = 0;
+    for (int k0 = threadIdx.x; k0 < n; k0 += 4 * THREADS) {
+        int v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = k0 + i * THREADS < n ? len[k0 + i * THREADS] : 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum += v[i] > 0 ? v[i] : 0;
+    }
+    sum = wave_sum(sum);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    long long all = 0;
+#pragma unroll
+    for (int w = 0; w < THREADS / 64; ++w) all += s_w[w];
+    return all;
+}
+
+template <int LPR, bool HALF, bool STREAM>
+__global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void front_kernel(
+    const int32_t *__restrict__ len, int n, long long nnz, int32_t *__restrict__ offsets, ErrRecord *err, int tiles,
+    const ChainProblem a, int chain_blocks, const TableDesc *__restrict__ tables,
+    const int32_t *__restrict__ indices, const PoolOut out, int B, int T, float one)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    int b = blockIdx.x;
+    if (b < tiles) {
+        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, nullptr, offsets, err, b);
+        return;
+    }
+    b -= tiles;
+    if (b < chain_blocks) {
+        const int share = chain::touch_share(chain_blocks);
+        chain::mlp_chain_block<true, 1, 1>(a, smem, b, 0, (b >> 3) % share, share);
+        return;
+    }
+    b -= chain_blocks;
+    // XCD x takes an eighth of the table-major bag list (see pool_kernel).
+    const int per = (gridDim.x - tiles - chain_blocks) >> 3;
+    const int first = ((b & 7) * per + (b >> 3)) * chain::CH_WAVES;
+    if (first >= n) return;
+    __shared__ long long s_w[chain::CH_WAVES];
+    long long start = sum_before<chain::CH_THREADS>(len, first, s_w);
+    const int bag = __builtin_amdgcn_readfirstlane(first + (int)(threadIdx.x >> 6));
+    if (bag >= n) return;
+    for (int k = first; k < bag; ++k) start += max(len[k], 0);
+    const long long end = start + max(len[bag], 0);
+    const int t = bag / B;
+    pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, bag - t * B, t, (int)min(start, nnz),
+                                             (int)min(end, nnz), one, err);
+}
+
+// Bags of one block of front_short_kernel: consecutive, each group of LPR lanes
+// taking SHORT_BAGS of them a block's groups apart.
+template <int LPR>
+constexpr int short_groups() { return POOL_WAVES * (64 / LPR); }
+template <int LPR>
+constexpr int short_block_bags() { return short_groups<LPR>() * SHORT_BAGS; }
+
+template <int LPR, bool HALF>
+__global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
+    const int32_t *__restrict__ len, int n, long long nnz, int32_t *__restrict__ offsets, ErrRecord *err, int tiles,
+    const ConcatDense job, int extra, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
+    const PoolOut out, int vec_ok, int B, int T, float one)
+{
+    constexpr int THREADS = POOL_WAVES * 64, GROUPS = short_groups<LPR>(), BAGS = short_block_bags<LPR>();
+    static_assert(THREADS == SCAN_THREADS && BAGS <= THREADS, "a thread per bag of the block");
+    int b = blockIdx.x;
+    if (b < tiles) {
+        scan_offsets_tile(len, n, nnz, nullptr, offsets, err, b);
+        return;
+    }
+    b -= tiles;
+    if (b < extra) {
+        concat_dense_block(job, b, extra);
+        return;
+    }
+    b -= extra;
+    const int per = (gridDim.x - tiles - extra) >> 3;
+    const int first = ((b & 7) * per + (b >> 3)) * BAGS;
+    if (first >= n) return;
+    __shared__ long long s_w[POOL_WAVES], s_scan[POOL_WAVES];
+    __shared__ int s_off[BAGS + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int k = first + tid;
+    const long long mine = tid < BAGS && k < n ? max(len[k], 0) : 0;
+    long long incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const long long up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+    }
+    if (lane == 63) s_scan[wave] = incl;
+    long long run = sum_before<THREADS>(len, first, s_w);  // its barrier makes s_scan visible too
+    for (int w = 0; w < wave; ++w) run += s_scan[w];
+    if (tid < BAGS) {
+        s_off[tid] = (int)min(run + incl - mine, nnz);
+        if (tid == BAGS - 1) s_off[BAGS] = (int)min(run + incl, nnz);
+    }
+    __syncthreads();
+    const int group = wave * (64 / LPR) + lane / LPR;
+    bool live[SHORT_BAGS];
+    int bag[SHORT_BAGS], pos[SHORT_BAGS], end[SHORT_BAGS];
+#pragma unroll
+    for (int g = 0; g < SHORT_BAGS; ++g) {
+        const int at = group + g * GROUPS;
+        live[g] = first + at < n;
+        bag[g] = live[g] ? first + at : n - 1;
+        pos[g] = s_off[at];
+        end[g] = live[g] ? s_off[at + 1] : pos[g];
+    }
+    pool_short_bags<LPR, HALF, true>(tables, indices, out, vec_ok, B, T, live, bag, pos, end, one, err);
+}
+
+template <int LPR, bool HALF>
+hipError_t launch_long(const FrontProblem &f, const ChainProblem &a, hipStream_t s)
+{
+    const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE, chain_blocks = (a.M + 31) / 32;
+    const int pool_blocks = ((n + chain::CH_WAVES - 1) / chain::CH_WAVES + 7) / 8 * 8;
+    auto k = f.stream_rows ? front_kernel<LPR, HALF, true> : front_kernel<LPR, HALF, false>;
+    hipLaunchKernelGGL(k, dim3(tiles + chain_blocks + pool_blocks), dim3(chain::CH_THREADS),
+                       chain::chain_lds_bytes<1>(a.ld_lds), s, f.lengths, n, f.nnz, f.offsets, f.err, tiles, a,
+                       chain_blocks, f.tables, f.indices, f.out, f.B, f.T, 1.0f);
+    return hipGetLastError();
+}
+
+template <int LPR, bool HALF>
+hipError_t launch_short(const FrontProblem &f, hipStream_t s)
+{
+    constexpr int NACC = HALF ? 8 : 4;
+    const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
+    const int vec_ok = f.out.col0 % NACC == 0 && reinterpret_cast<uintptr_t>(f.out.z) % 16 == 0;
+    const long long total = (long long)f.dense.B * (f.dense.w0 + f.dense.ldz - f.dense.width);
+    const int extra = (int)std::min<long long>((total + 8 * SCAN_THREADS - 1) / (8 * SCAN_THREADS), 256);
+    constexpr int BAGS = short_block_bags<LPR>();
+    const int pool_blocks = ((n + BAGS - 1) / BAGS + 7) / 8 * 8;
+    hipLaunchKernelGGL((front_short_kernel<LPR, HALF>), dim3(tiles + extra + pool_blocks), dim3(POOL_WAVES * 64), 0, s,
+                       f.lengths, n, f.nnz, f.offsets, f.err, tiles, f.dense, extra, f.tables, f.indices, f.out, vec_ok,
+                       f.B, f.T, 1.0f);
+    return hipGetLastError();
+}
+
+template <int LPR, bool HALF>
+hipError_t prepare_long()
+{
+    const int most = (int)chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(front_kernel<LPR, HALF, false>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(front_kernel<LPR, HALF, true>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, most);
+}
+
+}  // namespace
+
+bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat)
+{
+    const long long n = (long long)T * B;
+    const int rowbytes = D * (dtype == REC_F16 ? 2 : 4);
+    if (n > (concat ? SHORT_FORM_BAGS : LONG_BAGS) || (rowbytes != 64 && rowbytes != 128 && rowbytes != 256)) return false;
+    const bool sh = pool_short_applies(rowbytes, nnz, n);
+    return concat ? sh : !sh && pool_narrow(max_rows, rowbytes);
+}
+
+hipError_t front_prepare()
+{
+    hipError_t e = prepare_long<4, true>();
+    if (e == hipSuccess) e = prepare_long<8, true>();
+    if (e == hipSuccess) e = prepare_long<16, true>();
+    if (e == hipSuccess) e = prepare_long<4, false>();
+    if (e == hipSuccess) e = prepare_long<8, false>();
+    if (e == hipSuccess) e = prepare_long<16, false>();
+    return e;
+}
+
+bool front_takes(const ChainProblem &rider) { return chain::narrow_run(rider); }
+
+hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStream_t s)
+{
+    if (f.T <= 0 || f.B <= 0) return hipSuccess;
+    const bool half = f.dtype == REC_F16;
+    const int lpr = f.D * (half ? 2 : 4) / 16;
+    if (rider) {
+        if (!rider->a_f32 || rider->groups != 1 || !front_takes(*rider) || f.out.z) return hipErrorInvalidValue;
+        ChainProblem a;
+        const hipError_t e = chain_finalize(*rider, a);
+        if (e != hipSuccess) return e;
+        switch (lpr) {
+        case 4: return half ? launch_long<4, true>(f, a, s) : launch_long<4, false>(f, a, s);
+        case 8: return half ? launch_long<8, true>(f, a, s) : launch_long<8, false>(f, a, s);
+        case 16: return half ? launch_long<16, true>(f, a, s) : launch_long<16, false>(f, a, s);
+        default: return hipErrorInvalidValue;
+        }
+    }
+    if (!f.out.z || !f.dense.x0) return hipErrorInvalidValue;
+    switch (lpr) {
+    case 4: return half ? launch_short<4, true>(f, s) : launch_short<4, false>(f, s);
+    case 8: return half ? launch_short<8, true>(f, s) : launch_short<8, false>(f, s);
+    case 16: return half ? launch_short<16, true>(f, s) : launch_short<16, false>(f, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace rec

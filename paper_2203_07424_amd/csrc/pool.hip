@@ -33,134 +33,13 @@
 // In the concatenation model the sums go, narrowed to bf16, straight into the
 // Predict-FC input row of their sample (concatenation and conversion fused,
 // Sec. IV-A) instead of the fp32 pooled buffer.
-#include <hip/hip_fp16.h>
-
-#include "rec_internal.h"
+#include "pool_body.h"
 
 namespace rec {
 
 namespace {
 
-// Both were swept on the RMC2-style workload (2..8 loads, 2..8 waves); these are the best.
-constexpr int POOL_WAVES = 4;   // bags per block
-constexpr int POOL_UNROLL = 4;  // row loads in flight per lane and step
-
-constexpr int SHORT_UNROLL = 4;  // row loads in flight per lane in the short-bag kernel
-constexpr int SHORT_BAGS = 2;    // bags a group of lanes works on at a time
-constexpr int SHORT_MEAN = 4;    // mean ids per bag up to which bags share a wave
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-template <bool HALF>
-struct Acc {
-    static constexpr int N = HALF ? 8 : 4;
-    float v[N];
-};
-
-// One more row into the sums.  `one` is 1.0f held in a register: the product
-// form lets each fp16 element be widened, and added, by a single mixed-precision
-// fused multiply-add (bit-identical to widening and adding, the product being exact).
-template <bool HALF>
-__device__ inline void accumulate(Acc<HALF> &a, const u32x4 raw, float one)
-{
-    if (HALF) {
-        const f16x8 h = __builtin_bit_cast(f16x8, raw);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) a.v[i] = __builtin_fmaf((float)h[i], one, a.v[i]);
-    } else {
-        const f32x4 f = __builtin_bit_cast(f32x4, raw);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a.v[i] += f[i];
-    }
-}
-
-// Rows of one table, 16 bytes per lane.  NARROW (table smaller than 4 GiB): a
-// buffer descriptor over the table and 32-bit byte offsets; an offset past the
-// table reads as zero, which is how ids marked invalid (key 0xFFFFFFFF..) add
-// nothing.  Otherwise 64-bit addresses, invalid keys masked by hand.
-template <int ROWBYTES, bool NARROW, bool STREAM>
-struct RowSource {
-    __amdgpu_buffer_rsrc_t rsrc;
-    const __attribute__((address_space(1))) char *lane_base;
-    unsigned lane_off;
-
-    __device__ inline RowSource(const void *base, long long rows, int chunk)
-    {
-        lane_off = chunk * 16;
-        if (NARROW)
-            rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0,
-                                                     (int)(unsigned)(rows * ROWBYTES), 0x00020000);
-        else
-            lane_base = (const __attribute__((address_space(1))) char *)base + chunk * 16;
-    }
-    // What a lane hands out for id (id < 0: invalid).
-    __device__ static inline unsigned key(int id) { return NARROW ? (unsigned)id * ROWBYTES : (unsigned)id; }
-    __device__ inline u32x4 fetch(unsigned k) const
-    {
-        if (NARROW) return __builtin_amdgcn_raw_buffer_load_b128(rsrc, k + lane_off, 0, STREAM ? 2 : 0);
-        const bool ok = (int)k >= 0;
-        typedef const __attribute__((address_space(1))) u32x4 *row_ptr;
-        const row_ptr src = (row_ptr)(lane_base + (unsigned long long)(ok ? k : 0u) * ROWBYTES);
-        u32x4 v = STREAM ? __builtin_nontemporal_load(src) : *src;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = ok ? v[i] : 0u;
-        return v;
-    }
-};
-
-// N sums a lane holds (columns col ... of bag (t, b)) to where they belong.
-template <int N, bool CONCAT>
-__device__ inline void store_sums(const float *v, const PoolOut &out, int vec_ok, int b, int t, int T,
-                                  int D, int col)
-{
-    typedef __bf16 bvec __attribute__((ext_vector_type(N)));
-    if (CONCAT) {
-        __bf16 *o = static_cast<__bf16 *>(out.z) + (long long)b * out.ldz + out.col0 + t * D + col;
-        if (vec_ok) {
-            bvec h;
-#pragma unroll
-            for (int i = 0; i < N; ++i) h[i] = (__bf16)v[i];
-            *reinterpret_cast<bvec *>(o) = h;
-        } else {
-#pragma unroll
-            for (int i = 0; i < N; ++i) o[i] = (__bf16)v[i];
-        }
-    } else {
-        constexpr int W = N < 4 ? N : 4;  // at most 16 bytes a store
-        typedef float wvec __attribute__((ext_vector_type(W)));
-        float *o = out.pooled + ((long long)b * T + t) * D + col;
-#pragma unroll
-        for (int i = 0; i < N; i += W) {
-            wvec w;
-#pragma unroll
-            for (int k = 0; k < W; ++k) w[k] = v[i + k];
-            *reinterpret_cast<wvec *>(o + i) = w;
-        }
-    }
-}
-
-// a <- a + (a of lane ^ M) in lanes that keep a, b + (b of lane ^ M) in the others
-// (lanes with bit M set), M = 32 or 16: one register swap and one add.
-template <int M>
-__device__ inline float fold_pair(float a, float b)
-{
-    const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
-    const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(ua, ub, false, false)
-                           : __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
-    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
-}
-
-// v + v of the lane R further on in its row of 16 lanes.
-template <int R>
-__device__ inline float add_ror(float v)
-{
-    const int x = __builtin_bit_cast(int, v);
-    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, x, 0x120 + R, 0xf, 0xf, false));
-}
+using namespace pool;
 
 template <int LPR, bool HALF, bool CONCAT, bool STREAM, bool NARROW>
 __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
@@ -168,13 +47,6 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
     const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, int B, int T, int nbags,
     float one, ErrRecord *err)
 {
-    constexpr int RPW = 64 / LPR;
-    constexpr int ROWBYTES = LPR * 16;
-    constexpr int NACC = HALF ? 8 : 4;
-    constexpr int D = ROWBYTES / (HALF ? 2 : 4);
-    typedef RowSource<ROWBYTES, NARROW, STREAM> Rows;
-
-    const int lane = threadIdx.x & 63;
     // Blocks are handed to the 8 XCDs round-robin; give XCD x the x-th eighth
     // of the (table-major) bag list so that each L2 sees few tables at a time.
     // The grid is a multiple of 8 blocks; surplus blocks fall past nbags.
@@ -184,171 +56,32 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
     if (bag >= nbags) return;
     bag = __builtin_amdgcn_readfirstlane(bag);
     const int t = bag / B;
-    const int b = bag - t * B;
-    const int start = offsets[bag];
-    const int end = offsets[bag + 1];
-    const long long rows = tables[t].rows;
-
-    const int sub = lane / LPR;  // which of the RPW rows of a wave-wide load
-    const int chunk = lane % LPR;
-    const Rows src(tables[t].base, rows, chunk);
-
-    Acc<HALF> acc;
-#pragma unroll
-    for (int i = 0; i < NACC; ++i) acc.v[i] = 0.0f;
-
-    int ids = -1;
-    if (start + lane < end) ids = indices[start + lane];
-    for (int k0 = start; k0 < end; k0 += 64) {
-        const int n = min(64, end - k0);
-        int cur = ids;  // -1 in the lanes past the end of the bag
-        // Ids outside the table contribute zero and leave a record.
-        if (lane < n && (unsigned long long)(long long)cur >= (unsigned long long)rows) {
-            atomicMin(&err->first_bad_idx, (unsigned long long)(k0 + lane));
-            atomicOr(&err->flags, ERR_INDEX_RANGE);
-            cur = -1;
-        }
-        const unsigned key = Rows::key(cur);
-        // Next 64 ids, requested before the row loads of this step.
-        ids = -1;
-        if (k0 + 64 + lane < end) ids = indices[k0 + 64 + lane];
-
-        const int steps = (n + RPW - 1) / RPW;  // wave-wide loads this chunk needs
-        // slot4: byte address of this lane's slot in the cross-lane permute (the
-        // hardware takes it modulo the wave).
-        int j = 0;
-        for (; j + POOL_UNROLL <= steps; j += POOL_UNROLL) {
-            const int slot4 = (j * RPW + sub) * 4;
-            u32x4 raw[POOL_UNROLL];
-#pragma unroll
-            for (int u = 0; u < POOL_UNROLL; ++u)
-                raw[u] = src.fetch(__builtin_amdgcn_ds_bpermute(slot4 + u * RPW * 4, key));
-#pragma unroll
-            for (int u = 0; u < POOL_UNROLL; ++u) accumulate<HALF>(acc, raw[u], one);
-        }
-        if (j < steps) {  // the last, partial group: loads it does not need are not issued
-            const int slot4 = (j * RPW + sub) * 4;
-            u32x4 raw[POOL_UNROLL - 1];
-#pragma unroll
-            for (int u = 0; u < POOL_UNROLL - 1; ++u)
-                if (j + u < steps) raw[u] = src.fetch(__builtin_amdgcn_ds_bpermute(slot4 + u * RPW * 4, key));
-#pragma unroll
-            for (int u = 0; u < POOL_UNROLL - 1; ++u)
-                if (j + u < steps) accumulate<HALF>(acc, raw[u], one);
-        }
-    }
-
-    // Fold the RPW partial sums, lanes l and l ^ m holding the same columns.  While
-    // m is 32 or 16 a lane passes half of its columns to l ^ m and keeps the sum of
-    // the other half; within a row of 16 lanes the rest are rotate-and-add.  None of
-    // it goes through the LDS: folding with __shfl_xor, 24 of the 34 permutes a
-    // bag of 80 fp16 rows of 64 needed, queued on it.
-    float *v = acc.v;
-    int col = chunk * NACC;
-    constexpr int N1 = LPR <= 32 ? NACC / 2 : NACC, N2 = LPR <= 16 ? N1 / 2 : N1;
-    if constexpr (LPR <= 32) {
-#pragma unroll
-        for (int i = 0; i < N1; ++i) v[i] = fold_pair<32>(v[i], v[i + N1]);
-        col += (lane >> 5) * N1;
-    }
-    if constexpr (LPR <= 16) {
-#pragma unroll
-        for (int i = 0; i < N2; ++i) v[i] = fold_pair<16>(v[i], v[i + N2]);
-        col += (lane >> 4 & 1) * N2;
-    }
-#pragma unroll
-    for (int i = 0; i < N2; ++i) {
-        if (LPR <= 8) v[i] = add_ror<8>(v[i]);
-        if (LPR <= 4) v[i] = add_ror<4>(v[i]);
-        if (LPR <= 2) v[i] = add_ror<2>(v[i]);
-        if (LPR <= 1) v[i] = add_ror<1>(v[i]);
-    }
-    if (LPR > 8 || (lane & 15) < LPR) store_sums<N2, CONCAT>(v, out, vec_ok, b, t, T, D, col);
+    pool_bag<LPR, HALF, CONCAT, STREAM, NARROW>(tables, indices, out, vec_ok, T, bag - t * B, t, offsets[bag],
+                                                offsets[bag + 1], one, err);
 }
 
-// SHORT_BAGS bags per group of LPR lanes, their load chains (offsets -> ids ->
-// rows) running side by side; group g of the launch takes bags g, g + groups,
-// ...  Slots past the last bag work on a copy of it and store nothing.
+// Group g of the launch takes bags g, g + groups, ...
 template <int LPR, bool HALF, bool CONCAT>
 __global__ __launch_bounds__(POOL_WAVES * 64) void pool_short_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, int B, int T, int nbags,
     int groups, float one, ErrRecord *err)
 {
-    typedef const __attribute__((address_space(1))) char *table_ptr;
-    typedef const __attribute__((address_space(1))) u32x4 *row_ptr;
     constexpr int RPW = 64 / LPR;
-    constexpr int ROWBYTES = LPR * 16;
-    constexpr int NACC = HALF ? 8 : 4;
-    constexpr int D = ROWBYTES / (HALF ? 2 : 4);
-    constexpr int PER_BAG = SHORT_UNROLL / SHORT_BAGS;  // row loads in flight per bag
-
-    const int lane = threadIdx.x & 63;
-    const int sub = lane / LPR, chunk = lane % LPR;
     const int per = gridDim.x >> 3;
     const int vblk = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    const long long group = ((long long)vblk * POOL_WAVES + (threadIdx.x >> 6)) * RPW + sub;
-
+    const long long group = ((long long)vblk * POOL_WAVES + (threadIdx.x >> 6)) * RPW + (threadIdx.x & 63) / LPR;
     bool live[SHORT_BAGS];
-    int t[SHORT_BAGS], b[SHORT_BAGS], pos[SHORT_BAGS], end[SHORT_BAGS];
-    table_ptr lane_base[SHORT_BAGS];
-    long long rows[SHORT_BAGS];
-    Acc<HALF> acc[SHORT_BAGS];
+    int bag[SHORT_BAGS], pos[SHORT_BAGS], end[SHORT_BAGS];
 #pragma unroll
     for (int g = 0; g < SHORT_BAGS; ++g) {
         const long long slot = group + (long long)g * groups;
         live[g] = slot < nbags;
-        const int bag = live[g] ? (int)slot : nbags - 1;
-        t[g] = bag / B;
-        b[g] = bag - t[g] * B;
-        pos[g] = offsets[bag];
-        end[g] = live[g] ? offsets[bag + 1] : pos[g];
-        lane_base[g] = (table_ptr)tables[t[g]].base + chunk * 16;
-        rows[g] = tables[t[g]].rows;
-#pragma unroll
-        for (int i = 0; i < NACC; ++i) acc[g].v[i] = 0.0f;
+        bag[g] = live[g] ? (int)slot : nbags - 1;
+        pos[g] = offsets[bag[g]];
+        end[g] = live[g] ? offsets[bag[g] + 1] : pos[g];
     }
-
-    bool more = false;
-#pragma unroll
-    for (int g = 0; g < SHORT_BAGS; ++g) more |= pos[g] < end[g];
-    while (more) {
-        u32x4 raw[SHORT_BAGS][PER_BAG];
-#pragma unroll
-        for (int g = 0; g < SHORT_BAGS; ++g) {
-#pragma unroll
-            for (int u = 0; u < PER_BAG; ++u) {
-                const int k = pos[g] + u;
-                bool ok = k < end[g];
-                // positions past the bag re-read its last id (or, for an empty bag, nothing: id 0)
-                const int kk = ok ? k : (end[g] > 0 ? end[g] - 1 : 0);
-                const int id = pos[g] < end[g] ? indices[kk] : 0;
-                if (ok && (unsigned long long)(long long)id >= (unsigned long long)rows[g]) {
-                    if (chunk == 0) {
-                        atomicMin(&err->first_bad_idx, (unsigned long long)k);
-                        atomicOr(&err->flags, ERR_INDEX_RANGE);
-                    }
-                    ok = false;
-                }
-                const long long row = ok ? id : 0;
-                u32x4 v = *(row_ptr)(lane_base[g] + row * ROWBYTES);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = ok ? v[i] : 0u;
-                raw[g][u] = v;
-            }
-        }
-        more = false;
-#pragma unroll
-        for (int g = 0; g < SHORT_BAGS; ++g) {
-#pragma unroll
-            for (int u = 0; u < PER_BAG; ++u) accumulate<HALF>(acc[g], raw[g][u], one);
-            pos[g] = min(pos[g] + PER_BAG, end[g]);
-            more |= pos[g] < end[g];
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < SHORT_BAGS; ++g)
-        if (live[g]) store_sums<NACC, CONCAT>(acc[g].v, out, vec_ok, b[g], t[g], T, D, chunk * NACC);
+    pool_short_bags<LPR, HALF, CONCAT>(tables, indices, out, vec_ok, B, T, live, bag, pos, end, one, err);
 }
 
 template <int LPR, bool HALF, bool CONCAT>
@@ -396,6 +129,15 @@ hipError_t launch_lpr(bool half, bool short_bags, bool stream_rows, bool narrow,
 
 }  // namespace
 
+bool pool_short_applies(int rowbytes, long long nnz, long long bags)
+{
+    return rowbytes < 1024 && nnz <= SHORT_MEAN * bags;
+}
+
+// 32-bit byte offsets reach every row, and leave room above the table for the
+// offsets that stand for "no row".
+bool pool_narrow(long long max_rows, int rowbytes) { return max_rows * rowbytes <= 0xFFFF0000ll; }
+
 hipError_t launch_pool(const TableDesc *tables, int dtype, int T, int D, int B,
                        const int32_t *indices, const int32_t *offsets, PoolOut out, long long nnz,
                        bool stream_rows, long long max_rows, ErrRecord *err, hipStream_t s)
@@ -403,10 +145,8 @@ hipError_t launch_pool(const TableDesc *tables, int dtype, int T, int D, int B,
     if (T <= 0 || B <= 0) return hipSuccess;
     const bool half = dtype == REC_F16;
     const int rowbytes = D * (half ? 2 : 4);
-    // 32-bit byte offsets reach every row, and leave room above the table for the
-    // offsets that stand for "no row".
-    const bool narrow = max_rows * rowbytes <= 0xFFFF0000ll;
-    const bool sh = rowbytes < 1024 && nnz <= (long long)SHORT_MEAN * T * B;
+    const bool narrow = pool_narrow(max_rows, rowbytes);
+    const bool sh = pool_short_applies(rowbytes, nnz, (long long)T * B);
     switch (rowbytes / 16) {
     case 1: return launch_lpr<1>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
     case 2: return launch_lpr<2>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);

@@ -374,32 +374,81 @@ bool concat_rides_on_scan(const rec_model *m)
     return m->interaction == REC_INTERACT_CONCAT && m->bottom.empty();
 }
 
+// Bottom-FC as a run that rides along with the sparse side.
+ChainProblem bottom_run(const rec_model *m, const Bufs &u, const Call &c)
+{
+    const int n = (int)m->bottom.size();
+    ChainProblem cp{};
+    cp.A = c.dense; cp.a_f32 = true; cp.lda = m->F; cp.a_stride = 0; cp.M = c.B;
+    chain_run(m->bottom.data(), n, 1, 0, n, m->num_cus, cp);
+    cp.out_mode = CHAIN_OUT_F32;
+    cp.C = u.x0; cp.ldc = m->x0_ld; cp.c_stride = 0;
+    return cp;
+}
+
+ConcatDense concat_job(const rec_model *m, const Bufs &u, const Call &c)
+{
+    ConcatDense job;
+    job.x0 = c.dense; job.ldx0 = m->F; job.w0 = m->w0; job.B = c.B;
+    job.z_bf16 = u.act[0]; job.width = m->z_width; job.ldz = m->z_ld;
+    return job;
+}
+
 hipError_t enqueue_scan(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, bool with_bottom)
 {
     ConcatDense job;
-    if (concat_rides_on_scan(m)) {
-        job.x0 = c.dense; job.ldx0 = m->F; job.w0 = m->w0; job.B = c.B;
-        job.z_bf16 = u.act[0]; job.width = m->z_width; job.ldz = m->z_ld;
-    }
+    if (concat_rides_on_scan(m)) job = concat_job(m, u, c);
     ChainProblem cp{};
-    if (with_bottom) {
-        const int n = (int)m->bottom.size();
-        cp.A = c.dense; cp.a_f32 = true; cp.lda = m->F; cp.a_stride = 0; cp.M = c.B;
-        chain_run(m->bottom.data(), n, 1, 0, n, m->num_cus, cp);
-        cp.out_mode = CHAIN_OUT_F32;
-        cp.C = u.x0; cp.ldc = m->x0_ld; cp.c_stride = 0;
-    }
+    if (with_bottom) cp = bottom_run(m, u, c);
     return launch_scan(c.lengths, m->T * c.B, c.nnz, u.offsets, u.tile_sums, u.err, job,
                        with_bottom ? &cp : nullptr, s);
+}
+
+int longest_hot_list(const rec_model *m, bool use_hot)
+{
+    int hmax = 0;
+    if (use_hot)
+        for (const TableDesc &d : m->desc) hmax = d.n_hot > hmax ? d.n_hot : hmax;
+    return hmax;
+}
+
+PoolOut pool_out(const rec_model *m, const Bufs &u)
+{
+    return m->interaction == REC_INTERACT_CONCAT ? PoolOut{nullptr, u.act[0], m->z_ld, m->w0}
+                                                 : PoolOut{u.pooled, nullptr, 0, 0};
+}
+
+// S0 and S1 (and Bottom-FC, with_bottom) of a small in-order batch as one launch,
+// where csrc/front.hip has one for it.
+bool front_runs(const rec_model *m, const Call &c, bool use_hot, bool with_bottom)
+{
+    const bool concat = m->interaction == REC_INTERACT_CONCAT;
+    if (m->pipeline || (concat ? with_bottom || !concat_rides_on_scan(m) : !with_bottom)) return false;
+    if (!concat && longest_hot_list(m, use_hot) > 0) return false;
+    for (const Layer &l : m->bottom)
+        if (l.Npad > 256) return false;
+    return front_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows, concat);
+}
+
+hipError_t enqueue_front(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, bool with_bottom)
+{
+    FrontProblem f{};
+    f.lengths = c.lengths; f.indices = c.indices; f.nnz = c.nnz;
+    f.offsets = u.offsets; f.tables = u.tables; f.err = u.err;
+    f.dtype = m->dtype; f.T = m->T; f.D = m->D; f.B = c.B;
+    f.stream_rows = m->stream_rows;
+    f.out = pool_out(m, u);
+    if (concat_rides_on_scan(m)) f.dense = concat_job(m, u, c);
+    ChainProblem cp{};
+    if (with_bottom) cp = bottom_run(m, u, c);
+    return launch_front(f, with_bottom ? &cp : nullptr, s);
 }
 
 hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, hipStream_t s)
 {
     const int B = c.B, T = m->T, D = m->D;
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
-    int hmax = 0;
-    if (use_hot)
-        for (const TableDesc &d : m->desc) hmax = d.n_hot > hmax ? d.n_hot : hmax;
+    const int hmax = longest_hot_list(m, use_hot);
     if (hmax > 0 && !concat) {
         // Capacity: at least the longest list; a sparse hash (128 slots of rows
         // or more, where LDS allows) keeps the per-wave probe chains short.
@@ -410,9 +459,7 @@ hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool u
         REC_TRY(launch_pool_hot(u.tables, m->dtype, T, D, B, c.indices, u.offsets, u.pooled, hcap,
                                 m->num_cus, u.err, s));
     } else {
-        const PoolOut out = concat ? PoolOut{nullptr, u.act[0], m->z_ld, m->w0}
-                                   : PoolOut{u.pooled, nullptr, 0, 0};
-        REC_TRY(launch_pool(u.tables, m->dtype, T, D, B, c.indices, u.offsets, out, c.nnz, m->stream_rows,
+        REC_TRY(launch_pool(u.tables, m->dtype, T, D, B, c.indices, u.offsets, pool_out(m, u), c.nnz, m->stream_rows,
                             m->max_rows, u.err, s));
     }
     return hipSuccess;
@@ -421,6 +468,11 @@ hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool u
 hipError_t enqueue_sparse(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, hipStream_t s,
                           hipEvent_t *ev, bool with_bottom = false)
 {
+    if (front_runs(m, c, use_hot, with_bottom)) {  // all of it in the pooling stage; the scan's reads an empty interval
+        REC_TRY(mark(ev, EV_SCAN_END, s));
+        REC_TRY(enqueue_front(m, u, c, s, with_bottom));
+        return mark(ev, EV_POOL_END, s);
+    }
     REC_TRY(enqueue_scan(m, u, c, s, with_bottom));
     REC_TRY(mark(ev, EV_SCAN_END, s));
     REC_TRY(enqueue_pool(m, u, c, use_hot, s));
@@ -578,7 +630,7 @@ rec_status static_scratch(char **out)
         void *p = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return REC_ERR_DEVICE;
         if (fc_big_prepare() != hipSuccess || chain_prepare() != hipSuccess || scan_prepare() != hipSuccess ||
-            tail_prepare() != hipSuccess)
+            tail_prepare() != hipSuccess || front_prepare() != hipSuccess)
             return REC_ERR_DEVICE;
         g_scratch_ptr[dev] = static_cast<char *>(p);
     }

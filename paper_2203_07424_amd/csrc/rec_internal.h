@@ -78,6 +78,11 @@ hipError_t launch_pool(const TableDesc *tables, int dtype, int T, int D, int B,
                        const int32_t *indices, const int32_t *offsets, PoolOut out, long long nnz,
                        bool stream_rows, long long max_rows, ErrRecord *err, hipStream_t s);
 
+// Which form launch_pool() takes: bags of a few ids side by side in a wave; 32-bit
+// byte offsets into the tables.
+bool pool_short_applies(int rowbytes, long long nnz, long long bags);
+bool pool_narrow(long long max_rows, int rowbytes);
+
 // S1 with the tables' hot rows served from an LDS copy (hcap: power of two >= the
 // longest hot list, pool_hot_fits(hcap, rowbytes) must hold).
 bool pool_hot_fits(int hcap, int rowbytes);
@@ -185,6 +190,26 @@ int tail_most_samples(int num_cus);
 hipError_t launch_tail(const TailProblem &p, int num_cus, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).
 hipError_t tail_prepare();
+
+// S0 and S1 of a small batch in one launch (front_applies()): with `rider`, a
+// Bottom-FC stack front_takes() (fp32 input, one stack), into out.pooled; without,
+// a concatenation model without Bottom-FC, into out.z, dense part included.
+struct FrontProblem {
+    const int32_t *lengths, *indices;
+    long long nnz;
+    int32_t *offsets;
+    const TableDesc *tables;
+    ErrRecord *err;
+    int dtype, T, D, B;
+    bool stream_rows;
+    PoolOut out;
+    ConcatDense dense;
+};
+bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat);
+bool front_takes(const ChainProblem &rider);
+hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStream_t s);
+// Once per process and device, before the first launch (not under stream capture).
+hipError_t front_prepare();
 
 // Last Predict-FC layer of every stack: logits[m * ld + g] = sum_k A_g[m][k] * w_g[k] + bias_g[0]
 // in fp32.  A_g = A + g * a_stride is fp32 [M][lda] (a_f32) or bf16 [M][lda];

@@ -10,31 +10,13 @@
 // a last-block-done ticket (its device-scope fences cost more than a launch).
 #include <algorithm>
 #include "mlp_chain_body.h"
+#include "scan_body.h"
 
 namespace rec {
 
 namespace {
 
-__device__ inline long long wave_sum(long long v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    return v;  // valid in lane 0
-}
-
-// Sum over the block, returned to every thread.
-__device__ inline long long block_sum(long long v, long long *s_w)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    v = wave_sum(v);
-    __syncthreads();
-    if (lane == 0) s_w[wave] = v;
-    __syncthreads();
-    long long r = 0;
-#pragma unroll
-    for (int w = 0; w < SCAN_THREADS / 64; ++w) r += s_w[w];
-    return r;
-}
+using namespace scan;
 
 __global__ __launch_bounds__(64) void clear_err_kernel(ErrRecord *err)
 {
@@ -61,121 +43,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_tile_sums(const int32_t *__
     }
     sum = block_sum(sum, s_w);
     if (threadIdx.x == 0) tile_sums[blockIdx.x] = sum;
-}
-
-// Dense part of the Predict-FC input rows of a concatenation model, narrowed,
-// and the zero padding behind each row: block `b` of `nb` blocks.
-__device__ inline void concat_dense_block(const ConcatDense &job, int b, int nb)
-{
-    __bf16 *z = static_cast<__bf16 *>(job.z_bf16);
-    const int per_row = job.w0 + (job.ldz - job.width);
-    const long long total = (long long)job.B * per_row;
-    const long long stride = (long long)nb * blockDim.x;
-    for (long long i = (long long)b * blockDim.x + threadIdx.x; i < total; i += stride) {
-        const long long r = i / per_row;
-        const int c = (int)(i - r * per_row);
-        if (c < job.w0)
-            z[r * job.ldz + c] = (__bf16)job.x0[r * job.ldx0 + c];
-        else
-            z[r * job.ldz + job.width + (c - job.w0)] = (__bf16)0.0f;
-    }
-}
-
-// Offsets of tile `tile`; the threads with threadIdx.x < SCAN_THREADS call it,
-// all of them.
-__device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n, long long nnz,
-                                         const long long *__restrict__ tile_sums,
-                                         int32_t *__restrict__ offsets, ErrRecord *err, int tile)
-{
-    // One extra word per 32 keeps the 8-per-thread strided reads off one bank.
-    __shared__ int s_tile[SCAN_TILE + SCAN_TILE / 32];
-    __shared__ long long s_w[SCAN_THREADS / 64];
-    __shared__ long long s_wave_excl[SCAN_THREADS / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long base = (long long)tile * SCAN_TILE;
-
-    // Sum of all earlier tiles: from their sums, or (no sums: a short input whose
-    // first launch was left out) from the lengths themselves.
-    long long before = 0;
-    if (tile_sums) {
-        for (int j = tid; j < tile; j += SCAN_THREADS) before += tile_sums[j];
-    } else {
-        // base is a multiple of SCAN_TILE: SCAN_ITEMS loads per thread and tile, all in flight together
-        for (long long k0 = 0; k0 < base; k0 += SCAN_TILE) {
-            int v[SCAN_ITEMS];
-#pragma unroll
-            for (int i = 0; i < SCAN_ITEMS; ++i) v[i] = len[k0 + i * SCAN_THREADS + tid];
-#pragma unroll
-            for (int i = 0; i < SCAN_ITEMS; ++i) before += v[i] > 0 ? v[i] : 0;
-        }
-    }
-    before = block_sum(before, s_w);
-
-    // Coalesced load of this tile; negative lengths count as 0.
-#pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; ++i) {
-        const int p = i * SCAN_THREADS + tid;
-        const long long k = base + p;
-        int v = 0;
-        if (k < n) v = len[k];
-        if (v < 0) {
-            atomicMin(&err->first_bad_len, (unsigned long long)k);
-            atomicOr(&err->flags, ERR_NEG_LENGTH);
-        }
-        s_tile[p + (p >> 5)] = v > 0 ? v : 0;
-    }
-    __syncthreads();
-
-    // Each thread owns SCAN_ITEMS consecutive entries.
-    int mine[SCAN_ITEMS];
-    long long tsum = 0;
-#pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; ++i) {
-        const int p = tid * SCAN_ITEMS + i;
-        mine[i] = s_tile[p + (p >> 5)];
-        tsum += mine[i];
-    }
-    // Inclusive scan of the thread sums inside the wave, then across waves.
-    long long incl = tsum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const long long up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
-    }
-    if (lane == 63) s_w[wave] = incl;
-    __syncthreads();
-    if (tid == 0) {
-        long long run = 0;
-#pragma unroll
-        for (int w = 0; w < SCAN_THREADS / 64; ++w) {
-            s_wave_excl[w] = run;
-            run += s_w[w];
-        }
-    }
-    __syncthreads();
-    long long run = before + s_wave_excl[wave] + (incl - tsum);
-#pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; ++i) {
-        const int p = tid * SCAN_ITEMS + i;
-        // Clamping to nnz keeps every bag inside the ids the caller passed.
-        s_tile[p + (p >> 5)] = (int)(run < nnz ? run : nnz);
-        run += mine[i];
-    }
-    // `run` of the thread owning the last valid entry is the grand total.
-    const long long last = (long long)n - 1 - base;
-    if (last >= 0 && last < SCAN_TILE && tid == (int)(last / SCAN_ITEMS)) {
-        long long total = before + s_wave_excl[wave] + (incl - tsum);
-        for (int i = 0; i <= (int)(last % SCAN_ITEMS); ++i) total += mine[i];
-        offsets[n] = (int)(total < nnz ? total : nnz);
-        if (total != nnz) atomicOr(&err->flags, ERR_TOTAL_MISMATCH);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; ++i) {
-        const int p = i * SCAN_THREADS + tid;
-        const long long k = base + p;
-        if (k < n) offsets[k] = s_tile[p + (p >> 5)];
-    }
 }
 
 // Second launch of the scan: blocks [0, tiles) write the offsets, the blocks
