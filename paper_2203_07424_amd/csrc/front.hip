@@ -5,9 +5,8 @@
 // block of pooling waves takes neighbouring bags, so it needs one sum, that of all
 // earlier lengths, and a few thousand lengths are added up by its threads with a
 // few loads each, all in flight together: about as long as reading the offsets
-// the scan would have left, and a launch (8 to 9 us with Bottom-FC inside, 9 to 11
-// for the two of a model without) less in front of it.  The offsets themselves
-// are still written, by the scan's own blocks, for inspection and for its checks.
+// the scan would have left, and a launch less in front of it.  The offsets
+// themselves are still written, by the scan's own blocks, for inspection and for its checks.
 //
 // front_kernel (pooled dot model, Bottom-FC of narrow layers): blocks of 8 waves;
 // first those of the scan, then those of Bottom-FC, then pooling, one bag a wave.
@@ -67,7 +66,7 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int b = blockIdx.x;
     if (b < tiles) {
-        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, nullptr, offsets, err, b);
+        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b);
         return;
     }
     b -= tiles;
@@ -109,7 +108,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
     static_assert(THREADS == SCAN_THREADS && BAGS <= THREADS, "a thread per bag of the block");
     int b = blockIdx.x;
     if (b < tiles) {
-        scan_offsets_tile(len, n, nnz, nullptr, offsets, err, b);
+        scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b);
         return;
     }
     b -= tiles;

@@ -43,8 +43,9 @@ struct Layer {
 // table descriptors exist once; what one batch passes through (a frame) once
 // up to four times.
 constexpr int MAX_FRAMES = 4;
+static_assert(sizeof(ErrRecord::tiles_done) / sizeof(unsigned) == MAX_FRAMES, "a counter per frame");
 struct Frame {
-    size_t off_offsets = 0, off_tile_sums = 0, off_pooled = 0, off_x0 = 0, off_act[3] = {0, 0, 0};
+    size_t off_offsets = 0, off_tile_words = 0, off_pooled = 0, off_x0 = 0, off_act[3] = {0, 0, 0};
 };
 struct Carve {
     size_t off_err = 0, off_tables = 0, bytes = 0;
@@ -118,7 +119,7 @@ Carve carve(const rec_model *m, int batch, int frames)
     for (int f = 0; f < frames; ++f) {
         Frame &fr = c.fr[f];
         fr.off_offsets = o;   o += align_up(sizeof(int32_t) * (nb + 1));
-        fr.off_tile_sums = o; o += align_up(sizeof(long long) * ((nb + SCAN_TILE - 1) / SCAN_TILE));
+        fr.off_tile_words = o; o += align_up(sizeof(long long) * ((nb + SCAN_TILE - 1) / SCAN_TILE));
         fr.off_pooled = o;    o += concat ? 0 : align_up(sizeof(float) * nb * m->D);
         fr.off_x0 = o;        o += !m->bottom.empty() ? align_up(sizeof(float) * (size_t)batch * m->x0_ld) : 0;
         // act[0] holds the Predict-FC input (kept for inspection); the hidden
@@ -178,7 +179,8 @@ struct Bufs {
     ErrRecord *err;
     const TableDesc *tables;
     int32_t *offsets;
-    long long *tile_sums;
+    unsigned long long *tile_words;
+    unsigned *tiles_done;
     float *pooled;
     float *x0;      // Bottom-FC output (unused without a Bottom-FC)
     void *act[3];
@@ -191,7 +193,8 @@ Bufs bufs_at(char *base, const Carve &c, int frame)
     b.err = reinterpret_cast<ErrRecord *>(base + c.off_err);
     b.tables = reinterpret_cast<const TableDesc *>(base + c.off_tables);
     b.offsets = reinterpret_cast<int32_t *>(base + f.off_offsets);
-    b.tile_sums = reinterpret_cast<long long *>(base + f.off_tile_sums);
+    b.tile_words = reinterpret_cast<unsigned long long *>(base + f.off_tile_words);
+    b.tiles_done = &b.err->tiles_done[frame];
     b.pooled = reinterpret_cast<float *>(base + f.off_pooled);
     b.x0 = reinterpret_cast<float *>(base + f.off_x0);
     for (int i = 0; i < 3; ++i) b.act[i] = base + f.off_act[i];
@@ -317,7 +320,7 @@ hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipS
 
 // Bottom-FC does not depend on the sparse side (Sec. III-A): when the whole
 // stack is one run of the on-chip kernel, an in-order forward lets it ride on
-// the scan's second launch instead of giving it a launch of its own (9-11 us on
+// the scan's launch instead of giving it a launch of its own (9-11 us on
 // every workload here, whatever its size).
 bool bottom_rides_on_scan(const rec_model *m)
 {
@@ -400,7 +403,7 @@ hipError_t enqueue_scan(const rec_model *m, const Bufs &u, const Call &c, hipStr
     if (concat_rides_on_scan(m)) job = concat_job(m, u, c);
     ChainProblem cp{};
     if (with_bottom) cp = bottom_run(m, u, c);
-    return launch_scan(c.lengths, m->T * c.B, c.nnz, u.offsets, u.tile_sums, u.err, job,
+    return launch_scan(c.lengths, m->T * c.B, c.nnz, u.offsets, u.tile_words, u.tiles_done, u.err, job,
                        with_bottom ? &cp : nullptr, s);
 }
 
@@ -601,7 +604,7 @@ hipError_t enqueue_in_order(const rec_model *m, const Bufs &u, const Call &c, bo
     REC_TRY(mark(ev, EV_BEGIN, s));
     const bool ride = bottom_rides_on_scan(m);
     REC_TRY(enqueue_sparse(m, u, c, use_hot, s, ev, ride));
-    if (ride) {  // S2 ran inside S0's second launch: its stages read zero
+    if (ride) {  // S2 ran inside S0's launch: its stages read zero
         REC_TRY(mark(ev, EV_BOTTOM_FIRST_END, s));
         REC_TRY(mark(ev, EV_BOTTOM_END, s));
     } else if (const int from = tail_bottom_from(m); from < (int)m->bottom.size() && tail_applies(m, c)) {
@@ -645,10 +648,11 @@ struct StaticTables {
     long long rows[REC_STATIC_MAX_TABLES];
 };
 
-__global__ __launch_bounds__(64) void static_begin_kernel(const StaticTables st, int T, TableDesc *dst,
-                                                          ErrRecord *err)
+__global__ __launch_bounds__(256) void static_begin_kernel(const StaticTables st, int T, TableDesc *dst,
+                                                           ErrRecord *err, unsigned long long *tile_words, int tiles)
 {
     const int t = threadIdx.x;
+    for (int i = t; i < tiles; i += 256) tile_words[i] = 0;
     if (t < T) {
         dst[t].base = st.base[t];
         dst[t].rows = st.rows[t];
@@ -660,6 +664,7 @@ __global__ __launch_bounds__(64) void static_begin_kernel(const StaticTables st,
         err->first_bad_len = ~0ull;
         err->first_bad_idx = ~0ull;
         err->flags = 0u;
+        err->tiles_done[0] = 0u;
     }
 }
 
@@ -854,6 +859,11 @@ rec_status rec_bind_workspace(rec_model *m, void *dev_ptr, size_t bytes, void *s
     for (TableDesc &d : m->desc) { d.base = nullptr; d.hot_ids = nullptr; d.n_hot = 0; }
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (launch_clear_err(m->at<ErrRecord>(m->lay.off_err), s) != hipSuccess) return REC_ERR_DEVICE;
+    const int most_tiles = (int)(((size_t)m->T * m->max_batch + SCAN_TILE - 1) / SCAN_TILE);
+    for (int f = 0; f < (m->pipeline ? MAX_FRAMES : 1); ++f) {
+        const Bufs u = bufs_at(m->ws, m->lay, f);
+        if (launch_clear_tile_words(u.tile_words, most_tiles, u.tiles_done, s) != hipSuccess) return REC_ERR_DEVICE;
+    }
     if (hipStreamSynchronize(s) != hipSuccess) return REC_ERR_DEVICE;
     return REC_OK;
 }
@@ -1027,8 +1037,8 @@ rec_status rec_forward_static(rec_model *m, const float *dev_dense, const int32_
         tabs.base[t] = m->desc[t].base;
         tabs.rows[t] = m->desc[t].rows;
     }
-    hipLaunchKernelGGL(static_begin_kernel, dim3(1), dim3(64), 0, s, tabs, m->T,
-                       const_cast<TableDesc *>(u.tables), u.err);
+    hipLaunchKernelGGL(static_begin_kernel, dim3(1), dim3(256), 0, s, tabs, m->T, const_cast<TableDesc *>(u.tables),
+                       u.err, u.tile_words, (int)(((size_t)m->T * batch + SCAN_TILE - 1) / SCAN_TILE));
     if (hipGetLastError() != hipSuccess) return REC_ERR_DEVICE;
     if (batch > 0) {
         const Call c{dev_dense, dev_indices, dev_lengths, batch, nnz, dev_logits};

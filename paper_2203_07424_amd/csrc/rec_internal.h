@@ -16,7 +16,8 @@ struct ErrRecord {
     unsigned long long first_bad_len;  // smallest position of a negative length
     unsigned long long first_bad_idx;  // smallest position of an id outside its table
     unsigned int flags;                // ERR_* bits
-    unsigned int pad[11];
+    unsigned int tiles_done[4];        // per frame: the scan's counter (launch_scan())
+    unsigned int pad[7];
 };
 enum : unsigned int { ERR_NEG_LENGTH = 1u, ERR_TOTAL_MISMATCH = 2u, ERR_INDEX_RANGE = 4u };
 
@@ -40,9 +41,10 @@ inline int pad_up(int x) { return (x + PAD - 1) / PAD * PAD; }
 
 hipError_t launch_clear_err(ErrRecord *err, hipStream_t s);
 
-// S0. offsets[k] = min(sum_{j<k} max(len[j], 0), nnz), k = 0..n; block_sums is
-// scratch of ceil(n / SCAN_TILE) int64 entries.
-// With a ConcatDense job (x0 != null) extra blocks of the second launch also do
+// S0. offsets[k] = min(sum_{j<k} max(len[j], 0), nnz), k = 0..n.  tile_words is
+// scratch of ceil(n / SCAN_TILE) words, tiles_done one counter; both are zero before
+// the first launch (launch_clear_tile_words()) and left zero by each.
+// With a ConcatDense job (x0 != null) extra blocks of the launch also do
 // the work of launch_concat_dense(), which a model without Bottom-FC can start
 // this early: its x0 is the dense input.
 struct ConcatDense {
@@ -52,13 +54,14 @@ struct ConcatDense {
     int width = 0, ldz = 0;
 };
 // With `rider` (a stack of fully connected layers that fits the on-chip kernel,
-// fp32 input, one stack) further blocks of the second launch run that stack:
+// fp32 input, one stack) further blocks of the launch run that stack:
 // Bottom-FC does not depend on the sparse side (Sec. III-A), so it can share a
 // launch with the scan instead of costing one of its own.
 struct ChainProblem;
 hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *offsets,
-                       long long *block_sums, ErrRecord *err, const ConcatDense &job,
+                       unsigned long long *tile_words, unsigned *tiles_done, ErrRecord *err, const ConcatDense &job,
                        const ChainProblem *rider, hipStream_t s);
+hipError_t launch_clear_tile_words(unsigned long long *words, int n, unsigned *done, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).
 hipError_t scan_prepare();
 

@@ -2,12 +2,16 @@
 //
 // The sparse input gives, per (table, sample), how many ids follow (the pooling
 // factor varies per lookup, Fig. 2(c)); the gather needs where each bag starts.
-// Two passes over at most a few hundred thousand int32: per-tile sums, then
-// per-tile scans in LDS that first reduce the sums of the tiles before them.
-// One-launch variants were measured and dropped: blocks re-reading the earlier
-// lengths themselves (5x slower, a single block pulls only tens of GB/s); tile
-// totals reduced by each pooling wave (+28 us of pooling for -3 us of scan);
-// a last-block-done ticket (its device-scope fences cost more than a launch).
+// One launch over at most a few hundred thousand int32: a block scans a tile of
+// 2048 in LDS, publishes its sum in a word of device memory that carries its own
+// "valid" bit (no fence: there is nothing else to order) and polls the words of
+// the tiles before it.  Bound by that hand-over, a round trip to memory: 80 tiles
+// with Bottom-FC riding along 11.2 us against 5.5 + 9.6 in two launches (40 tables x
+// 4096 170.9 -> 166.7 us per forward), 52 tiles alone 8.4 against 4.6 + 5.4 (103.8
+// -> 102.3), 480 tiles with Bottom-FC 26.6 against 6.3 + 20.
+// Measured and dropped: two launches, tile sums first (what this replaced); tile
+// totals reduced by each pooling wave (+28 us of pooling); a last-block-done
+// ticket in front of the offsets (its device-scope fences cost more than a launch).
 #include <algorithm>
 #include "mlp_chain_body.h"
 #include "scan_body.h"
@@ -27,35 +31,23 @@ __global__ __launch_bounds__(64) void clear_err_kernel(ErrRecord *err)
     }
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void scan_tile_sums(const int32_t *__restrict__ len,
-                                                               int n, long long *__restrict__ tile_sums)
+__global__ __launch_bounds__(256) void clear_tile_words_kernel(unsigned long long *words, int n, unsigned *done)
 {
-    __shared__ long long s_w[SCAN_THREADS / 64];
-    const long long base = (long long)blockIdx.x * SCAN_TILE;
-    long long sum = 0;
-#pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; ++i) {
-        const long long k = base + i * SCAN_THREADS + threadIdx.x;
-        if (k < n) {
-            const int v = len[k];
-            if (v > 0) sum += v;
-        }
-    }
-    sum = block_sum(sum, s_w);
-    if (threadIdx.x == 0) tile_sums[blockIdx.x] = sum;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) words[i] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0;
 }
 
-// Second launch of the scan: blocks [0, tiles) write the offsets, the blocks
+// The scan alone: blocks [0, tiles) write the offsets, the blocks
 // behind them do a concatenation model's dense copy.
 __global__ __launch_bounds__(SCAN_THREADS) void scan_tile_offsets(const int32_t *__restrict__ len,
                                                                   int n, long long nnz,
-                                                                  const long long *__restrict__ tile_sums,
+                                                                  const TileLink link,
                                                                   int32_t *__restrict__ offsets,
                                                                   ErrRecord *err, int tiles,
                                                                   const ConcatDense job)
 {
     if ((int)blockIdx.x < tiles)
-        scan_offsets_tile(len, n, nnz, tile_sums, offsets, err, blockIdx.x);
+        scan_offsets_tile(len, n, nnz, link, offsets, err, blockIdx.x);
     else
         concat_dense_block(job, blockIdx.x - tiles, gridDim.x - tiles);
 }
@@ -67,14 +59,14 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_tile_offsets(const int32_t 
 // at once (a barrier counts only the waves of a group that have not ended).
 template <int MAXC>
 __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<MAXC>()) void scan_offsets_ride_kernel(
-    const int32_t *__restrict__ len, int n, long long nnz, const long long *__restrict__ tile_sums,
+    const int32_t *__restrict__ len, int n, long long nnz, const TileLink link,
     int32_t *__restrict__ offsets, ErrRecord *err, int tiles, const ConcatDense job, int extra,
     const ChainProblem a, int chain_grid_x)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int b = blockIdx.x;
     if (b < tiles) {
-        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, tile_sums, offsets, err, b);
+        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, link, offsets, err, b);
     } else if (b < tiles + extra) {
         concat_dense_block(job, b - tiles, extra);
     } else {
@@ -91,6 +83,12 @@ hipError_t launch_clear_err(ErrRecord *err, hipStream_t s)
     return hipGetLastError();
 }
 
+hipError_t launch_clear_tile_words(unsigned long long *words, int n, unsigned *done, hipStream_t s)
+{
+    hipLaunchKernelGGL(clear_tile_words_kernel, dim3(std::min((n + 255) / 256, 256)), dim3(256), 0, s, words, n, done);
+    return hipGetLastError();
+}
+
 hipError_t scan_prepare()
 {
     const int most = (int)chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
@@ -102,7 +100,7 @@ hipError_t scan_prepare()
 }
 
 hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *offsets,
-                       long long *block_sums, ErrRecord *err, const ConcatDense &job,
+                       unsigned long long *tile_words, unsigned *tiles_done, ErrRecord *err, const ConcatDense &job,
                        const ChainProblem *rider, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
@@ -112,17 +110,14 @@ hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *of
         const long long total = (long long)job.B * (job.w0 + job.ldz - job.width);
         extra = (int)std::min<long long>((total + 8 * SCAN_THREADS - 1) / (8 * SCAN_THREADS), 256);
     }
-    // With a stack riding along the second launch lasts as long as the stack, so
-    // for a few tiles its scan blocks have the time to add up the earlier lengths
-    // themselves and the first launch can go (alone, that was measured no faster
-    // than two launches at 5 tiles and slower beyond).
+    // With a stack riding along the launch lasts as long as the stack, so for a few
+    // tiles its scan blocks have the time to add up the earlier lengths themselves.
     const bool has_rider = rider && rider->M > 0;
-    const long long *sums = has_rider && tiles <= 8 ? nullptr : block_sums;
-    if (tiles > 1 && sums) {
-        hipLaunchKernelGGL(scan_tile_sums, dim3(tiles), dim3(SCAN_THREADS), 0, s, lengths, n,
-                           block_sums);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    TileLink link;
+    if (tiles > (has_rider ? 8 : 1)) {
+        link.words = tile_words;
+        link.done = tiles_done;
+        link.tiles = tiles;
     }
     if (has_rider) {
         if (!rider->a_f32 || rider->groups != 1) return hipErrorInvalidValue;
@@ -132,12 +127,12 @@ hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *of
         const int chain_grid_x = (a.M + 31) / 32;
         auto k = chain::narrow_run(a) ? scan_offsets_ride_kernel<1> : scan_offsets_ride_kernel<4>;
         hipLaunchKernelGGL(k, dim3(tiles + extra + chain_grid_x), dim3(chain::CH_THREADS),
-                           chain::chain_lds_bytes<1>(a.ld_lds), s, lengths, n, nnz, sums, offsets, err, tiles, job,
+                           chain::chain_lds_bytes<1>(a.ld_lds), s, lengths, n, nnz, link, offsets, err, tiles, job,
                            extra, a, chain_grid_x);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(scan_tile_offsets, dim3(tiles + extra), dim3(SCAN_THREADS), 0, s, lengths, n, nnz,
-                       sums, offsets, err, tiles, job);
+                       link, offsets, err, tiles, job);
     return hipGetLastError();
 }
 

@@ -46,37 +46,51 @@ __device__ inline void concat_dense_block(const ConcatDense &job, int b, int nb)
     }
 }
 
+// How the blocks of a scan that is one launch learn what lies before their tile:
+// each publishes the sum of its own (value * 2 + 1, so that the word says by itself
+// that it is there) and adds up those of earlier tiles.  The last block to have
+// read them all clears words and counter for the next launch.
+struct TileLink {
+    unsigned long long *words = nullptr;  // one per tile, zero between launches
+    unsigned *done = nullptr;             // blocks that have read all they need, zero between launches
+    int tiles = 0;
+};
+// A block waits for words of blocks with smaller numbers only, which never wait
+// for it; past so many polls it adds up the lengths of that tile itself.
+constexpr int LINK_POLLS = 1 << 16;
+
+__device__ inline long long linked_sum(const TileLink &l, int tile, const int32_t *__restrict__ len)
+{
+    long long sum = 0;
+    for (int j = threadIdx.x; j < tile; j += SCAN_THREADS) {
+        unsigned long long w = 0;
+        for (int p = 0; p < LINK_POLLS && !(w & 1); ++p)
+            w = __hip_atomic_load(l.words + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (w & 1) {
+            sum += (long long)(w >> 1);
+        } else {  // tiles before `tile` are full
+            for (int k = 0; k < SCAN_TILE; ++k) sum += max(len[(long long)j * SCAN_TILE + k], 0);
+        }
+    }
+    return sum;
+}
+
 // Offsets of tile `tile`; the threads with threadIdx.x < SCAN_THREADS call it,
-// all of them.
-__device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n, long long nnz,
-                                         const long long *__restrict__ tile_sums,
+// all of them.  The sum of earlier tiles comes by `link`, or (no words: a few
+// tiles) from their lengths.
+__device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n, long long nnz, const TileLink &link,
                                          int32_t *__restrict__ offsets, ErrRecord *err, int tile)
 {
     // One extra word per 32 keeps the 8-per-thread strided reads off one bank.
     __shared__ int s_tile[SCAN_TILE + SCAN_TILE / 32];
     __shared__ long long s_w[SCAN_THREADS / 64];
     __shared__ long long s_wave_excl[SCAN_THREADS / 64];
+    __shared__ int s_last;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long base = (long long)tile * SCAN_TILE;
 
-    // Sum of all earlier tiles: from their sums, or (no sums: a short input whose
-    // first launch was left out) from the lengths themselves.
-    long long before = 0;
-    if (tile_sums) {
-        for (int j = tid; j < tile; j += SCAN_THREADS) before += tile_sums[j];
-    } else {
-        // base is a multiple of SCAN_TILE: SCAN_ITEMS loads per thread and tile, all in flight together
-        for (long long k0 = 0; k0 < base; k0 += SCAN_TILE) {
-            int v[SCAN_ITEMS];
-#pragma unroll
-            for (int i = 0; i < SCAN_ITEMS; ++i) v[i] = len[k0 + i * SCAN_THREADS + tid];
-#pragma unroll
-            for (int i = 0; i < SCAN_ITEMS; ++i) before += v[i] > 0 ? v[i] : 0;
-        }
-    }
-    before = block_sum(before, s_w);
-
     // Coalesced load of this tile; negative lengths count as 0.
+    long long own = 0;
 #pragma unroll
     for (int i = 0; i < SCAN_ITEMS; ++i) {
         const int p = i * SCAN_THREADS + tid;
@@ -87,8 +101,30 @@ __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n,
             atomicMin(&err->first_bad_len, (unsigned long long)k);
             atomicOr(&err->flags, ERR_NEG_LENGTH);
         }
-        s_tile[p + (p >> 5)] = v > 0 ? v : 0;
+        v = max(v, 0);
+        s_tile[p + (p >> 5)] = v;
+        own += v;
     }
+    long long before = 0;
+    unsigned seen = 0;
+    if (link.words) {
+        own = block_sum(own, s_w);
+        if (tid == 0)
+            __hip_atomic_store(link.words + tile, (unsigned long long)own * 2 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = linked_sum(link, tile, len);
+    } else {
+        // base is a multiple of SCAN_TILE: SCAN_ITEMS loads per thread and tile, all in flight together
+        for (long long k0 = 0; k0 < base; k0 += SCAN_TILE) {
+            int v[SCAN_ITEMS];
+#pragma unroll
+            for (int i = 0; i < SCAN_ITEMS; ++i) v[i] = len[k0 + i * SCAN_THREADS + tid];
+#pragma unroll
+            for (int i = 0; i < SCAN_ITEMS; ++i) before += v[i] > 0 ? v[i] : 0;
+        }
+    }
+    before = block_sum(before, s_w);  // every thread has read what it needs
+    if (link.words && tid == 0)
+        seen = __hip_atomic_fetch_add(link.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
 
     // Each thread owns SCAN_ITEMS consecutive entries.
@@ -134,12 +170,18 @@ __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n,
         offsets[n] = (int)(total < nnz ? total : nnz);
         if (total != nnz) atomicOr(&err->flags, ERR_TOTAL_MISMATCH);
     }
+    if (tid == 0) s_last = link.words && seen == (unsigned)link.tiles - 1;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < SCAN_ITEMS; ++i) {
         const int p = i * SCAN_THREADS + tid;
         const long long k = base + p;
         if (k < n) offsets[k] = s_tile[p + (p >> 5)];
+    }
+    if (s_last) {
+        for (int j = tid; j < link.tiles; j += SCAN_THREADS)
+            __hip_atomic_store(link.words + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(link.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
