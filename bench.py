@@ -323,23 +323,39 @@ def latency_profile(torch, np, model, stream, db, out, iters, warmup=10):
 SUSTAINED_RANDOM_TFLOPS = None   # set by main() once mfma_sustained() has run
 
 
+# A stage without a launch of its own reads one event record (4 to 5 us); the shortest
+# launch and a record take 7.
+EMPTY_BRACKET_MS = 6.5e-3
+
+
 def mlp_mfma(wl, avg):
     """Matrix-unit use of the FC stages: unpadded 2*M*N*K of the stage's layers over
     its HIP-event interval (which includes one event record and, for small
     layers, mostly launch latency) against the bf16 MFMA peak.  bottom_first and
-    top_first bracket a single launch each."""
+    top_first bracket a single launch each.  Where the whole Predict-FC runs in the
+    launch of the interaction, its stage holds that launch (top_with_interaction)
+    and the rest of the stack an empty bracket, which is left out, as is that of
+    Bottom-FC layers gone into the same launch."""
     def flops(widths):
         return sum(2.0 * wl.batch * widths[i] * widths[i + 1] for i in range(len(widths) - 1))
     out = {}
-    for stage, widths, mult in (("bottom_first", wl.bottom[:2], 1), ("bottom_rest", wl.bottom[1:], 1),
-                                ("top_first", wl.top[:2], wl.towers), ("top_rest", wl.top[1:], wl.towers)):
+    empty = lambda stage: 0 < avg.get(stage, 0) < EMPTY_BRACKET_MS
+    stages = [("bottom_first", "bottom_first", wl.bottom[:2], 1)]
+    if empty("interact") and wl.interaction == "dot":
+        stages.append(("top_with_interaction", "top_first", wl.top, wl.towers))
+        if not empty("bottom_rest"):
+            stages.append(("bottom_rest", "bottom_rest", wl.bottom[1:], 1))
+    else:
+        stages += [("bottom_rest", "bottom_rest", wl.bottom[1:], 1), ("top_first", "top_first", wl.top[:2], wl.towers),
+                   ("top_rest", "top_rest", wl.top[1:], wl.towers)]
+    for name, stage, widths, mult in stages:
         f = flops(widths) * mult
         if f > 0 and avg.get(stage, 0) > 0:
             tf = f / (avg[stage] * 1e-3) / 1e12
-            out[stage] = {"gflop": f / 1e9, "ms": avg[stage], "tflops": tf,
-                          "frac_of_bf16_peak": tf / MFMA_BF16_PEAK_TFLOPS}
+            out[name] = {"gflop": f / 1e9, "ms": avg[stage], "tflops": tf,
+                         "frac_of_bf16_peak": tf / MFMA_BF16_PEAK_TFLOPS}
             if SUSTAINED_RANDOM_TFLOPS:
-                out[stage]["frac_of_sustained_rate_on_random_operands"] = tf / SUSTAINED_RANDOM_TFLOPS
+                out[name]["frac_of_sustained_rate_on_random_operands"] = tf / SUSTAINED_RANDOM_TFLOPS
     return out
 
 

@@ -323,7 +323,11 @@ REC_API rec_status rec_drain(rec_model *m, void *stream);
  * caller's stream waited for Bottom-FC after pooling had finished, and the
  * second reads about zero.  An in-order forward whose Bottom-FC runs inside the
  * scan's launch (a stack that fits the on-chip kernel) reports it under
- * REC_STAGE_SCAN and gives 0 for both Bottom-FC stages.  With REC_OPT_PIPELINE every stage is bracketed on
+ * REC_STAGE_SCAN and gives 0 for both Bottom-FC stages.  Where several stages
+ * are one launch the last of them holds it and the others read an empty
+ * bracket (one event record): scan, Bottom-FC and pooling of a small batch
+ * under REC_STAGE_POOL; interaction, Predict-FC and the last Bottom-FC layers
+ * under REC_STAGE_TOP_FIRST.  With REC_OPT_PIPELINE every stage is bracketed on
  * the stream it runs on (a stage's time then includes whatever shared the
  * device with it). */
 REC_API rec_status rec_set_profiling(rec_model *m, int32_t slots, int32_t period);
