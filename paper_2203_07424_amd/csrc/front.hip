@@ -61,7 +61,7 @@ template <int LPR, bool HALF, bool STREAM>
 __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void front_kernel(
     const int32_t *__restrict__ len, int n, long long nnz, int32_t *__restrict__ offsets, ErrRecord *err, int tiles,
     const ChainProblem a, int chain_blocks, const TableDesc *__restrict__ tables,
-    const int32_t *__restrict__ indices, const PoolOut out, int B, int T, float one)
+    const int32_t *__restrict__ indices, const PoolOut out, const BagTable div, int T, float one)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int b = blockIdx.x;
@@ -86,8 +86,8 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
     if (bag >= n) return;
     for (int k = first; k < bag; ++k) start += max(len[k], 0);
     const long long end = start + max(len[bag], 0);
-    const int t = bag / B;
-    pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, bag - t * B, t, (int)min(start, nnz),
+    const int t = div.of(bag);
+    pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, bag - t * (int)div.B, t, (int)min(start, nnz),
                                              (int)min(end, nnz), one, err);
 }
 
@@ -102,7 +102,7 @@ template <int LPR, bool HALF>
 __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
     const int32_t *__restrict__ len, int n, long long nnz, int32_t *__restrict__ offsets, ErrRecord *err, int tiles,
     const ConcatDense job, int extra, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
-    const PoolOut out, int vec_ok, int B, int T, float one)
+    const PoolOut out, int vec_ok, const BagTable div, int T, float one)
 {
     constexpr int THREADS = POOL_WAVES * 64, GROUPS = short_groups<LPR>(), BAGS = short_block_bags<LPR>();
     static_assert(THREADS == SCAN_THREADS && BAGS <= THREADS, "a thread per bag of the block");
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
         pos[g] = s_off[at];
         end[g] = live[g] ? s_off[at + 1] : pos[g];
     }
-    pool_short_bags<LPR, HALF, true>(tables, indices, out, vec_ok, B, T, live, bag, pos, end, one, err);
+    pool_short_bags<LPR, HALF, true>(tables, indices, out, vec_ok, div, T, live, bag, pos, end, one, err);
 }
 
 template <int LPR, bool HALF>
@@ -161,7 +161,7 @@ hipError_t launch_long(const FrontProblem &f, const ChainProblem &a, hipStream_t
     auto k = f.stream_rows ? front_kernel<LPR, HALF, true> : front_kernel<LPR, HALF, false>;
     hipLaunchKernelGGL(k, dim3(tiles + chain_blocks + pool_blocks), dim3(chain::CH_THREADS),
                        chain::chain_lds_bytes<1>(a.ld_lds), s, f.lengths, n, f.nnz, f.offsets, f.err, tiles, a,
-                       chain_blocks, f.tables, f.indices, f.out, f.B, f.T, 1.0f);
+                       chain_blocks, f.tables, f.indices, f.out, BagTable(f.B), f.T, 1.0f);
     return hipGetLastError();
 }
 
@@ -177,7 +177,7 @@ hipError_t launch_short(const FrontProblem &f, hipStream_t s)
     const int pool_blocks = ((n + BAGS - 1) / BAGS + 7) / 8 * 8;
     hipLaunchKernelGGL((front_short_kernel<LPR, HALF>), dim3(tiles + extra + pool_blocks), dim3(POOL_WAVES * 64), 0, s,
                        f.lengths, n, f.nnz, f.offsets, f.err, tiles, f.dense, extra, f.tables, f.indices, f.out, vec_ok,
-                       f.B, f.T, 1.0f);
+                       BagTable(f.B), f.T, 1.0f);
     return hipGetLastError();
 }
 

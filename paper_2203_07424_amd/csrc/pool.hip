@@ -44,7 +44,7 @@ using namespace pool;
 template <int LPR, bool HALF, bool CONCAT, bool STREAM, bool NARROW>
 __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
-    const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, int B, int T, int nbags,
+    const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, const BagTable div, int T, int nbags,
     float one, ErrRecord *err)
 {
     // Blocks are handed to the 8 XCDs round-robin; give XCD x the x-th eighth
@@ -55,8 +55,9 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
     int bag = vblk * POOL_WAVES + (threadIdx.x >> 6);
     if (bag >= nbags) return;
     bag = __builtin_amdgcn_readfirstlane(bag);
-    const int t = bag / B;
-    pool_bag<LPR, HALF, CONCAT, STREAM, NARROW>(tables, indices, out, vec_ok, T, bag - t * B, t, offsets[bag],
+    const int t = div.of(bag);
+    pool_bag<LPR, HALF, CONCAT, STREAM, NARROW>(tables, indices, out, vec_ok, T, bag - t * (int)div.B, t,
+                                                offsets[bag],
                                                 offsets[bag + 1], one, err);
 }
 
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
 template <int LPR, bool HALF, bool CONCAT>
 __global__ __launch_bounds__(POOL_WAVES * 64) void pool_short_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
-    const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, int B, int T, int nbags,
+    const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, const BagTable div, int T, int nbags,
     int groups, float one, ErrRecord *err)
 {
     constexpr int RPW = 64 / LPR;
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_short_kernel(
         pos[g] = offsets[bag[g]];
         end[g] = live[g] ? offsets[bag[g] + 1] : pos[g];
     }
-    pool_short_bags<LPR, HALF, CONCAT>(tables, indices, out, vec_ok, B, T, live, bag, pos, end, one, err);
+    pool_short_bags<LPR, HALF, CONCAT>(tables, indices, out, vec_ok, div, T, live, bag, pos, end, one, err);
 }
 
 template <int LPR, bool HALF, bool CONCAT>
@@ -98,12 +99,12 @@ hipError_t launch_shape(bool short_bags, bool stream_rows, bool narrow, const Ta
         const dim3 grid(((nbags + per_block - 1) / per_block + 7) / 8 * 8);
         const int groups = (int)grid.x * groups_per_block;
         hipLaunchKernelGGL((pool_short_kernel<LPR, HALF, CONCAT>), grid, block, 0, s, tables, indices,
-                           offsets, out, vec_ok, B, T, nbags, groups, 1.0f, err);
+                           offsets, out, vec_ok, BagTable(B), T, nbags, groups, 1.0f, err);
     } else {
         const dim3 grid(((nbags + POOL_WAVES - 1) / POOL_WAVES + 7) / 8 * 8);
 #define REC_POOL_LAUNCH(STREAM, NARROW)                                                                  \
     hipLaunchKernelGGL((pool_kernel<LPR, HALF, CONCAT, STREAM, NARROW>), grid, block, 0, s, tables, indices, \
-                       offsets, out, vec_ok, B, T, nbags, 1.0f, err)
+                       offsets, out, vec_ok, BagTable(B), T, nbags, 1.0f, err)
         if (stream_rows) {
             if (narrow) REC_POOL_LAUNCH(true, true); else REC_POOL_LAUNCH(true, false);
         } else {

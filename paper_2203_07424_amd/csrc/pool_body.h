@@ -24,6 +24,21 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// bag -> table, bag / B, without a division on the way to a wave's first load (some 30
+// dependent instructions, v_rcp_f32 among them; a wave lives for one bag, and 60
+// tables x 16384 take about 1 % less per forward without it).  magic = floor((2^32 - 1) / B) is short of 2^32 / B by at most
+// 1, so for bag < 2^31 the high product is short by less than 1/2 and its floor by
+// at most one.
+struct BagTable {
+    unsigned B, magic;
+    explicit BagTable(int batch) : B((unsigned)batch), magic(0xFFFFFFFFu / (unsigned)batch) {}
+    __device__ inline int of(int bag) const
+    {
+        const unsigned t = __umulhi((unsigned)bag, magic);
+        return (int)((unsigned)bag - t * B >= B ? t + 1 : t);
+    }
+};
+
 template <bool HALF>
 struct Acc {
     static constexpr int N = HALF ? 8 : 4;
@@ -227,7 +242,7 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
 // copy of another (live[g] false) and store nothing.
 template <int LPR, bool HALF, bool CONCAT>
 __device__ inline void pool_short_bags(const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
-                                       const PoolOut &out, int vec_ok, int B, int T, const bool (&live)[SHORT_BAGS],
+                                       const PoolOut &out, int vec_ok, const BagTable &div, int T, const bool (&live)[SHORT_BAGS],
                                        const int (&bag)[SHORT_BAGS], int (&pos)[SHORT_BAGS],
                                        const int (&end)[SHORT_BAGS], float one, ErrRecord *err)
 {
@@ -244,8 +259,8 @@ __device__ inline void pool_short_bags(const TableDesc *__restrict__ tables, con
     Acc<HALF> acc[SHORT_BAGS];
 #pragma unroll
     for (int g = 0; g < SHORT_BAGS; ++g) {
-        t[g] = bag[g] / B;
-        b[g] = bag[g] - t[g] * B;
+        t[g] = div.of(bag[g]);
+        b[g] = bag[g] - t[g] * (int)div.B;
         lane_base[g] = (table_ptr)tables[t[g]].base + chunk * 16;
         rows[g] = tables[t[g]].rows;
 #pragma unroll
