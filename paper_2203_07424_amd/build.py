@@ -14,10 +14,13 @@ LIB = os.path.join(PKG, "librec_mi355x.so")
 
 SOURCES = ["scan.hip", "pool.hip", "pool_hot.hip", "gemm.hip", "gemm_big.hip", "mlp_chain.hip", "tail.hip", "front.hip", "interact.hip", "synth_fill.hip", "probe.hip", "rec_api.hip"]
 
-# The packed-fp32 target feature is switched off for all device code.
+# The packed-fp32 target feature is switched off for all device code.  A wave starts
+# with the first 16 words of its kernel's arguments in registers instead of loading
+# them before anything else: launches of a few microseconds get 1 to 2 % shorter
+# (8 tables x 256 15.44 -> 15.22 us per forward, 40 x 256 37.6 -> 37.3).
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         "-Wall", "-Wno-unused-command-line-argument",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall", "-Wno-unused-command-line-argument",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
