@@ -49,11 +49,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 matrix rate
 # 1.000), see profiles/pool_rmc2_counters.md; Zipf ids with cached row loads,
 # the uniform twin with non-temporal ones.  These are figures from a profile, not
 # of this run, and hold only for the kernel source the counters were taken with:
-# reported as null once csrc/pool.hip differs.
+# reported as null once csrc/pool.hip or csrc/pool_body.h differs.
 POOL_TRAFFIC = {
-    "sha256": "ab1846d96d7f5f0750d6a6ca9f670f1d5e0548b462a4c702c976c977754e84da",
-    ("rmc2", 4096): {"fetch_bytes": 553867622.0, "write_bytes": 41943056.0},
-    ("rmc2-uniform", 4096): {"fetch_bytes": 1721570714.0, "write_bytes": 41943100.0},
+    "sha256": "2210b2eaead4655f03d06024390b139b26de29ae506e8401fe8599e913436365",
+    ("rmc2", 4096): {"fetch_bytes": 553886384.1, "write_bytes": 41943040.0},
+    ("rmc2-uniform", 4096): {"fetch_bytes": 1721444358.1, "write_bytes": 41943040.0},
 }
 
 
@@ -61,13 +61,17 @@ def profiled_pool_traffic(w, streaming):
     import hashlib
     if streaming != (w.index_dist[0] == "uniform"):   # the counters were taken with the automatic choice
         return None
-    src = os.path.join(ROOT, "paper_2203_07424_amd", "csrc", "pool.hip")
+    csrc = os.path.join(ROOT, "paper_2203_07424_amd", "csrc")
+    src = [os.path.join(csrc, n) for n in ("pool.hip", "pool_body.h")]
     rec = POOL_TRAFFIC.get((w.name, w.batch))
-    if rec is None or not os.path.exists(src):
+    if rec is None or not all(os.path.exists(p) for p in src):
         return None
-    with open(src, "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != POOL_TRAFFIC["sha256"]:
-            return None
+    h = hashlib.sha256()
+    for p in src:
+        with open(p, "rb") as f:
+            h.update(f.read())
+    if h.hexdigest() != POOL_TRAFFIC["sha256"]:
+        return None
     return rec["fetch_bytes"] + rec["write_bytes"]
 
 
