@@ -160,7 +160,9 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
     const int lane = threadIdx.x & 63;
     const long long rows = tables[t].rows;
 
-    const int sub = lane / LPR;  // which of the RPW rows of a wave-wide load
+    // Which of the RPW rows of a wave-wide load: lane / LPR with its bits in reverse, so
+    // that neighbouring rows sit 32 lanes apart, the next pair 16, and so on.
+    const int sub = (int)(__builtin_bitreverse32((unsigned)lane) >> 26) & (RPW - 1);
     const int chunk = lane % LPR;
     const Rows src(tables[t].base, rows, chunk);
 
@@ -213,7 +215,8 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
     // m is 32 or 16 a lane passes half of its columns to l ^ m and keeps the sum of
     // the other half; within a row of 16 lanes the rest are rotate-and-add.  None of
     // it goes through the LDS: folding with __shfl_xor, 24 of the 34 permutes a
-    // bag of 80 fp16 rows of 64 needed, queued on it.
+    // bag of 80 fp16 rows of 64 needed, queued on it.  In terms of the rows of a
+    // load the order is r with r ^ 1, then r ^ 2, r ^ 4, ...: fp32 sums depend on it.
     float *v = acc.v;
     int col = chunk * NACC;
     constexpr int N1 = LPR <= 32 ? NACC / 2 : NACC, N2 = LPR <= 16 ? N1 / 2 : N1;
