@@ -1,6 +1,7 @@
 /*
- * rec_probe.h - measurement helper: what the matrix cores of this device sustain.
+ * rec_probe.h - helpers for measurements and tests.  Not part of the forward pass.
  *
+ * What the matrix cores of this device sustain:
  * The published bf16 matrix rate of the chip (the MLP roofline of this build)
  * assumes every compute unit issuing matrix instructions at the top clock.
  * Whether a device sustains that depends on the operand values: with all compute
@@ -8,7 +9,9 @@
  * multiplier array lower the rate it settles at.  rec_probe_mfma() runs nothing
  * but v_mfma_f32_32x32x16_bf16 on register operands, so that a benchmark can
  * put the rate the hardware reaches on constant and on random operands beside
- * the published peak and beside its own GEMMs.  Not part of the forward pass.
+ * the published peak and beside its own GEMMs.
+ *
+ * The offsets scan by itself, with the bound on its waits in the caller's hand.
  */
 #ifndef REC_PROBE_H
 #define REC_PROBE_H
@@ -30,6 +33,21 @@ extern "C" {
  * REC_ERR_ARG on null sink or non-positive counts (blocks <= 65536, iters <= 2^20). */
 REC_API rec_status rec_probe_mfma(int32_t random_operands, int32_t blocks, int32_t iters,
                           float *dev_sink, void *stream);
+
+/* Most polls rec_probe_scan() takes, and what rec_forward() uses. */
+#define REC_SCAN_POLLS 65536
+
+/* Enqueues the scan of one forward pass alone: dev_offsets (int32 [n + 1]) from
+ * dev_lengths (int32 [n]) as rec_forward() computes them.  A block of the scan
+ * covers 2048 lengths, publishes their sum in a word of dev_words (uint64
+ * [ceil(n / 2048)], zero on entry; the last word is not touched) and reads the
+ * words of earlier blocks, at most `polls` times each before it adds up those
+ * lengths itself.  The published words are left in place (in a forward pass the
+ * pooling launch clears them).  dev_err: 64 bytes, 8-byte aligned, of scratch.
+ * REC_ERR_ARG on a null pointer, n < 1, nnz < 0 or >= 2^31, polls outside
+ * [0, REC_SCAN_POLLS]. */
+REC_API rec_status rec_probe_scan(const int32_t *dev_lengths, int32_t n, int64_t nnz, int32_t *dev_offsets,
+                          uint64_t *dev_words, int32_t polls, void *dev_err, void *stream);
 
 #ifdef __cplusplus
 }

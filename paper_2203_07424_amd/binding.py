@@ -44,7 +44,7 @@ STAGE_NAMES = ("scan", "pool", "bottom_first", "bottom_rest", "interact", "top_f
 EXPORTS = ("rec_create", "rec_destroy", "rec_workspace_bytes", "rec_bind_workspace",
            "rec_load_tables", "rec_load_hot_rows", "rec_mlp_packed_bytes", "rec_load_mlp", "rec_forward", "rec_forward_static", "rec_check",
            "rec_debug_get", "rec_set_option", "rec_set_dense_stream", "rec_set_pool_streams", "rec_drain", "rec_set_profiling", "rec_stage_ms", "rec_status_string",
-           "rec_synth_fill_table", "rec_probe_mfma")
+           "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan")
 
 
 class rec_config(C.Structure):
@@ -101,6 +101,8 @@ _lib.rec_synth_fill_table.argtypes = [_vp, C.c_int32, C.c_uint64, C.c_int32, C.c
 
 _lib.rec_probe_mfma.restype = C.c_int
 _lib.rec_probe_mfma.argtypes = [C.c_int32, C.c_int32, C.c_int32, _vp, _vp]
+_lib.rec_probe_scan.restype = C.c_int
+_lib.rec_probe_scan.argtypes = [_vp, C.c_int32, C.c_int64, _vp, _vp, C.c_int32, _vp, _vp]
 
 
 class RecError(RuntimeError):
@@ -229,6 +231,13 @@ def rec_synth_fill_table(dev_rows: torch.Tensor, seed: int, table: int) -> int:
 def rec_probe_mfma(random_operands: bool, blocks: int, iters: int, dev_sink: Optional[torch.Tensor]) -> int:
     """One launch of nothing but bf16 matrix instructions (blocks * 8 * iters * 32 * 32768 flops)."""
     return _lib.rec_probe_mfma(int(bool(random_operands)), int(blocks), int(iters), _ptr(dev_sink), _stream())
+
+
+def rec_probe_scan(dev_lengths: torch.Tensor, nnz: int, dev_offsets: torch.Tensor, dev_words: torch.Tensor,
+                   polls: int, dev_err: torch.Tensor) -> int:
+    """The offsets scan alone; dev_words int64, one per 2048 lengths, zero on entry; dev_err 64 bytes."""
+    return _lib.rec_probe_scan(_ptr(dev_lengths), dev_lengths.numel(), int(nnz), _ptr(dev_offsets), _ptr(dev_words),
+                               int(polls), _ptr(dev_err), _stream())
 
 
 class RecModel:

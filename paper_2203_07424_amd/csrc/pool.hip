@@ -45,7 +45,7 @@ template <int LPR, bool HALF, bool CONCAT, bool STREAM, bool NARROW>
 __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, const BagTable div, int T, int nbags,
-    float one, ErrRecord *err)
+    float one, ErrRecord *err, const TileWords left)
 {
     // Blocks are handed to the 8 XCDs round-robin; give XCD x the x-th eighth
     // of the (table-major) bag list so that each L2 sees few tables at a time.
@@ -59,6 +59,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
     pool_bag<LPR, HALF, CONCAT, STREAM, NARROW>(tables, indices, out, vec_ok, T, bag - t * (int)div.B, t,
                                                 offsets[bag],
                                                 offsets[bag + 1], one, err);
+    if (bag == 0) clear_tile_words(left);  // last: its arguments are not waited for in front of the first id
 }
 
 // Group g of the launch takes bags g, g + groups, ...
@@ -66,7 +67,7 @@ template <int LPR, bool HALF, bool CONCAT>
 __global__ __launch_bounds__(POOL_WAVES * 64) void pool_short_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, const BagTable div, int T, int nbags,
-    int groups, float one, ErrRecord *err)
+    int groups, float one, ErrRecord *err, const TileWords left)
 {
     constexpr int RPW = 64 / LPR;
     const int per = gridDim.x >> 3;
@@ -83,11 +84,12 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_short_kernel(
         end[g] = live[g] ? offsets[bag[g] + 1] : pos[g];
     }
     pool_short_bags<LPR, HALF, CONCAT>(tables, indices, out, vec_ok, div, T, live, bag, pos, end, one, err);
+    if (blockIdx.x == 0 && threadIdx.x < 64) clear_tile_words(left);
 }
 
 template <int LPR, bool HALF, bool CONCAT>
 hipError_t launch_shape(bool short_bags, bool stream_rows, bool narrow, const TableDesc *tables, int T, int B, const int32_t *indices,
-                        const int32_t *offsets, const PoolOut &out, ErrRecord *err, hipStream_t s)
+                        const int32_t *offsets, const PoolOut &out, const TileWords &left, ErrRecord *err, hipStream_t s)
 {
     constexpr int NACC = HALF ? 8 : 4;
     const int nbags = T * B;
@@ -99,12 +101,12 @@ hipError_t launch_shape(bool short_bags, bool stream_rows, bool narrow, const Ta
         const dim3 grid(((nbags + per_block - 1) / per_block + 7) / 8 * 8);
         const int groups = (int)grid.x * groups_per_block;
         hipLaunchKernelGGL((pool_short_kernel<LPR, HALF, CONCAT>), grid, block, 0, s, tables, indices,
-                           offsets, out, vec_ok, BagTable(B), T, nbags, groups, 1.0f, err);
+                           offsets, out, vec_ok, BagTable(B), T, nbags, groups, 1.0f, err, left);
     } else {
         const dim3 grid(((nbags + POOL_WAVES - 1) / POOL_WAVES + 7) / 8 * 8);
 #define REC_POOL_LAUNCH(STREAM, NARROW)                                                                  \
     hipLaunchKernelGGL((pool_kernel<LPR, HALF, CONCAT, STREAM, NARROW>), grid, block, 0, s, tables, indices, \
-                       offsets, out, vec_ok, BagTable(B), T, nbags, 1.0f, err)
+                       offsets, out, vec_ok, BagTable(B), T, nbags, 1.0f, err, left)
         if (stream_rows) {
             if (narrow) REC_POOL_LAUNCH(true, true); else REC_POOL_LAUNCH(true, false);
         } else {
@@ -117,15 +119,15 @@ hipError_t launch_shape(bool short_bags, bool stream_rows, bool narrow, const Ta
 
 template <int LPR>
 hipError_t launch_lpr(bool half, bool short_bags, bool stream_rows, bool narrow, const TableDesc *tables, int T, int B,
-                      const int32_t *indices, const int32_t *offsets, const PoolOut &out, ErrRecord *err,
-                      hipStream_t s)
+                      const int32_t *indices, const int32_t *offsets, const PoolOut &out, const TileWords &left,
+                      ErrRecord *err, hipStream_t s)
 {
     if (out.z) {
-        if (half) return launch_shape<LPR, true, true>(short_bags, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
-        return launch_shape<LPR, false, true>(short_bags, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
+        if (half) return launch_shape<LPR, true, true>(short_bags, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
+        return launch_shape<LPR, false, true>(short_bags, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
     }
-    if (half) return launch_shape<LPR, true, false>(short_bags, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
-    return launch_shape<LPR, false, false>(short_bags, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
+    if (half) return launch_shape<LPR, true, false>(short_bags, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
+    return launch_shape<LPR, false, false>(short_bags, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
 }
 
 }  // namespace
@@ -141,7 +143,7 @@ bool pool_narrow(long long max_rows, int rowbytes) { return max_rows * rowbytes 
 
 hipError_t launch_pool(const TableDesc *tables, int dtype, int T, int D, int B,
                        const int32_t *indices, const int32_t *offsets, PoolOut out, long long nnz,
-                       bool stream_rows, long long max_rows, ErrRecord *err, hipStream_t s)
+                       bool stream_rows, long long max_rows, const TileWords &left, ErrRecord *err, hipStream_t s)
 {
     if (T <= 0 || B <= 0) return hipSuccess;
     const bool half = dtype == REC_F16;
@@ -149,13 +151,13 @@ hipError_t launch_pool(const TableDesc *tables, int dtype, int T, int D, int B,
     const bool narrow = pool_narrow(max_rows, rowbytes);
     const bool sh = pool_short_applies(rowbytes, nnz, (long long)T * B);
     switch (rowbytes / 16) {
-    case 1: return launch_lpr<1>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
-    case 2: return launch_lpr<2>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
-    case 4: return launch_lpr<4>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
-    case 8: return launch_lpr<8>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
-    case 16: return launch_lpr<16>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
-    case 32: return launch_lpr<32>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
-    case 64: return launch_lpr<64>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, err, s);
+    case 1: return launch_lpr<1>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
+    case 2: return launch_lpr<2>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
+    case 4: return launch_lpr<4>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
+    case 8: return launch_lpr<8>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
+    case 16: return launch_lpr<16>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
+    case 32: return launch_lpr<32>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
+    case 64: return launch_lpr<64>(half, sh, stream_rows, narrow, tables, T, B, indices, offsets, out, left, err, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -62,7 +62,7 @@ template <int LPR, bool HALF>
 __global__ __launch_bounds__(PH_THREADS) void pool_hot_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     const int32_t *__restrict__ offsets, float *__restrict__ pooled, int B, int T, int nbags,
-    int bags_per_block, int hcap, float one, ErrRecord *err)
+    int bags_per_block, int hcap, float one, ErrRecord *err, const TileWords left)
 {
     typedef const __attribute__((address_space(1))) char *table_ptr;
     typedef const __attribute__((address_space(1))) u32x4 *row_ptr;
@@ -219,6 +219,7 @@ __global__ __launch_bounds__(PH_THREADS) void pool_hot_kernel(
         }
         p0 = pend;
     }
+    if (blockIdx.x == 0 && tid < 64) clear_tile_words(left);
 }
 
 size_t hot_lds_bytes(int hcap, int rowbytes)
@@ -228,8 +229,8 @@ size_t hot_lds_bytes(int hcap, int rowbytes)
 
 template <int LPR>
 hipError_t launch_lpr(bool half, const TableDesc *tables, int T, int B, const int32_t *indices,
-                      const int32_t *offsets, float *pooled, int hcap, int num_cus, ErrRecord *err,
-                      hipStream_t s)
+                      const int32_t *offsets, float *pooled, int hcap, int num_cus, const TileWords &left,
+                      ErrRecord *err, hipStream_t s)
 {
     const int nbags = T * B;
     const size_t lds = hot_lds_bytes(hcap, LPR * 16);
@@ -248,10 +249,10 @@ hipError_t launch_lpr(bool half, const TableDesc *tables, int T, int B, const in
     const dim3 grid(blocks), block(PH_THREADS);
     if (half)
         hipLaunchKernelGGL((pool_hot_kernel<LPR, true>), grid, block, lds, s, tables, indices, offsets,
-                           pooled, B, T, nbags, bpb, hcap, 1.0f, err);
+                           pooled, B, T, nbags, bpb, hcap, 1.0f, err, left);
     else
         hipLaunchKernelGGL((pool_hot_kernel<LPR, false>), grid, block, lds, s, tables, indices, offsets,
-                           pooled, B, T, nbags, bpb, hcap, 1.0f, err);
+                           pooled, B, T, nbags, bpb, hcap, 1.0f, err, left);
     return hipGetLastError();
 }
 
@@ -261,20 +262,20 @@ bool pool_hot_fits(int hcap, int rowbytes) { return hot_lds_bytes(hcap, rowbytes
 
 hipError_t launch_pool_hot(const TableDesc *tables, int dtype, int T, int D, int B,
                            const int32_t *indices, const int32_t *offsets, float *pooled, int hcap,
-                           int num_cus, ErrRecord *err, hipStream_t s)
+                           int num_cus, const TileWords &left, ErrRecord *err, hipStream_t s)
 {
     if (T <= 0 || B <= 0) return hipSuccess;
     const bool half = dtype == REC_F16;
     const int rowbytes = D * (half ? 2 : 4);
     if (!pool_hot_fits(hcap, rowbytes) || (hcap & (hcap - 1)) != 0) return hipErrorInvalidValue;
     switch (rowbytes / 16) {
-    case 1: return launch_lpr<1>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, err, s);
-    case 2: return launch_lpr<2>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, err, s);
-    case 4: return launch_lpr<4>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, err, s);
-    case 8: return launch_lpr<8>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, err, s);
-    case 16: return launch_lpr<16>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, err, s);
-    case 32: return launch_lpr<32>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, err, s);
-    case 64: return launch_lpr<64>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, err, s);
+    case 1: return launch_lpr<1>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, left, err, s);
+    case 2: return launch_lpr<2>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, left, err, s);
+    case 4: return launch_lpr<4>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, left, err, s);
+    case 8: return launch_lpr<8>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, left, err, s);
+    case 16: return launch_lpr<16>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, left, err, s);
+    case 32: return launch_lpr<32>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, left, err, s);
+    case 64: return launch_lpr<64>(half, tables, T, B, indices, offsets, pooled, hcap, num_cus, left, err, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1,8 +1,9 @@
-// Measurement helper (not part of the forward pass): the rate at which the
-// matrix cores run v_mfma_f32_32x32x16_bf16 on register operands, on constant
-// or on pseudo-random values.  With every compute unit busy the chip is
-// power-limited and the rate depends on the operand bits; a benchmark puts it
-// beside the published peak.
+// Helpers for measurements and tests (not part of the forward pass).
+//
+// The rate at which the matrix cores run v_mfma_f32_32x32x16_bf16 on register
+// operands, on constant or on pseudo-random values.  With every compute unit
+// busy the chip is power-limited and the rate depends on the operand bits; a
+// benchmark puts it beside the published peak.
 #include "rec_internal.h"
 #include "rec_probe.h"
 
@@ -75,4 +76,18 @@ extern "C" rec_status rec_probe_mfma(int32_t random_operands, int32_t blocks, in
     hipLaunchKernelGGL(mfma_probe_kernel, dim3(blocks), dim3(64 * PROBE_WAVES), 0,
                        static_cast<hipStream_t>(stream), random_operands, iters, dev_sink);
     return hipGetLastError() == hipSuccess ? REC_OK : REC_ERR_DEVICE;
+}
+
+// The scan's launch as in a forward pass, for tests of the hand-over between its blocks.
+extern "C" rec_status rec_probe_scan(const int32_t *dev_lengths, int32_t n, int64_t nnz, int32_t *dev_offsets,
+                                     uint64_t *dev_words, int32_t polls, void *dev_err, void *stream)
+{
+    static_assert(REC_SCAN_POLLS == rec::SCAN_LINK_POLLS && sizeof(rec::ErrRecord) == 64, "as rec_probe.h says");
+    if (!dev_lengths || !dev_offsets || !dev_words || !dev_err || n < 1 || nnz < 0 || nnz >= (1ll << 31) || polls < 0 ||
+        polls > rec::SCAN_LINK_POLLS)
+        return REC_ERR_ARG;
+    const hipError_t e = rec::launch_scan(dev_lengths, n, nnz, dev_offsets, reinterpret_cast<unsigned long long *>(dev_words),
+                                          static_cast<rec::ErrRecord *>(dev_err), rec::ConcatDense{}, nullptr,
+                                          static_cast<hipStream_t>(stream), polls);
+    return e == hipSuccess ? REC_OK : REC_ERR_DEVICE;
 }

@@ -43,7 +43,6 @@ struct Layer {
 // table descriptors exist once; what one batch passes through (a frame) once
 // up to four times.
 constexpr int MAX_FRAMES = 4;
-static_assert(sizeof(ErrRecord::tiles_done) / sizeof(unsigned) == MAX_FRAMES, "a counter per frame");
 struct Frame {
     size_t off_offsets = 0, off_tile_words = 0, off_pooled = 0, off_x0 = 0, off_act[3] = {0, 0, 0};
 };
@@ -180,7 +179,6 @@ struct Bufs {
     const TableDesc *tables;
     int32_t *offsets;
     unsigned long long *tile_words;
-    unsigned *tiles_done;
     float *pooled;
     float *x0;      // Bottom-FC output (unused without a Bottom-FC)
     void *act[3];
@@ -194,7 +192,6 @@ Bufs bufs_at(char *base, const Carve &c, int frame)
     b.tables = reinterpret_cast<const TableDesc *>(base + c.off_tables);
     b.offsets = reinterpret_cast<int32_t *>(base + f.off_offsets);
     b.tile_words = reinterpret_cast<unsigned long long *>(base + f.off_tile_words);
-    b.tiles_done = &b.err->tiles_done[frame];
     b.pooled = reinterpret_cast<float *>(base + f.off_pooled);
     b.x0 = reinterpret_cast<float *>(base + f.off_x0);
     for (int i = 0; i < 3; ++i) b.act[i] = base + f.off_act[i];
@@ -403,7 +400,7 @@ hipError_t enqueue_scan(const rec_model *m, const Bufs &u, const Call &c, hipStr
     if (concat_rides_on_scan(m)) job = concat_job(m, u, c);
     ChainProblem cp{};
     if (with_bottom) cp = bottom_run(m, u, c);
-    return launch_scan(c.lengths, m->T * c.B, c.nnz, u.offsets, u.tile_words, u.tiles_done, u.err, job,
+    return launch_scan(c.lengths, m->T * c.B, c.nnz, u.offsets, u.tile_words, u.err, job,
                        with_bottom ? &cp : nullptr, s);
 }
 
@@ -447,8 +444,10 @@ hipError_t enqueue_front(const rec_model *m, const Bufs &u, const Call &c, hipSt
     return launch_front(f, with_bottom ? &cp : nullptr, s);
 }
 
-hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, hipStream_t s)
+// with_bottom: as in the enqueue_scan() before it.
+hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, hipStream_t s, bool with_bottom)
 {
+    const TileWords left{u.tile_words, scan_linked_words(m->T * c.B, with_bottom)};
     const int B = c.B, T = m->T, D = m->D;
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
     const int hmax = longest_hot_list(m, use_hot);
@@ -460,10 +459,10 @@ hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool u
         while (hcap < hmax) hcap *= 2;
         while (hcap < 128 && pool_hot_fits(hcap * 2, rowbytes)) hcap *= 2;
         REC_TRY(launch_pool_hot(u.tables, m->dtype, T, D, B, c.indices, u.offsets, u.pooled, hcap,
-                                m->num_cus, u.err, s));
+                                m->num_cus, left, u.err, s));
     } else {
         REC_TRY(launch_pool(u.tables, m->dtype, T, D, B, c.indices, u.offsets, pool_out(m, u), c.nnz, m->stream_rows,
-                            m->max_rows, u.err, s));
+                            m->max_rows, left, u.err, s));
     }
     return hipSuccess;
 }
@@ -478,7 +477,7 @@ hipError_t enqueue_sparse(const rec_model *m, const Bufs &u, const Call &c, bool
     }
     REC_TRY(enqueue_scan(m, u, c, s, with_bottom));
     REC_TRY(mark(ev, EV_SCAN_END, s));
-    REC_TRY(enqueue_pool(m, u, c, use_hot, s));
+    REC_TRY(enqueue_pool(m, u, c, use_hot, s, with_bottom));
     return mark(ev, EV_POOL_END, s);
 }
 
@@ -664,7 +663,6 @@ __global__ __launch_bounds__(256) void static_begin_kernel(const StaticTables st
         err->first_bad_len = ~0ull;
         err->first_bad_idx = ~0ull;
         err->flags = 0u;
-        err->tiles_done[0] = 0u;
     }
 }
 
@@ -862,7 +860,7 @@ rec_status rec_bind_workspace(rec_model *m, void *dev_ptr, size_t bytes, void *s
     const int most_tiles = (int)(((size_t)m->T * m->max_batch + SCAN_TILE - 1) / SCAN_TILE);
     for (int f = 0; f < (m->pipeline ? MAX_FRAMES : 1); ++f) {
         const Bufs u = bufs_at(m->ws, m->lay, f);
-        if (launch_clear_tile_words(u.tile_words, most_tiles, u.tiles_done, s) != hipSuccess) return REC_ERR_DEVICE;
+        if (launch_clear_tile_words(u.tile_words, most_tiles, s) != hipSuccess) return REC_ERR_DEVICE;
     }
     if (hipStreamSynchronize(s) != hipSuccess) return REC_ERR_DEVICE;
     return REC_OK;
@@ -970,7 +968,7 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
         REC_DEV(hipEventRecord(m->ev_scan[k], s));
         REC_DEV(hipStreamWaitEvent(p, m->ev_scan[k], 0));
         REC_DEV(mark(ev, EV_POOL_BEGIN, p));
-        REC_DEV(enqueue_pool(m, u, c, true, p));
+        REC_DEV(enqueue_pool(m, u, c, true, p, false));
         REC_DEV(mark(ev, EV_POOL_END, p));
         REC_DEV(hipEventRecord(m->ev_pool[k], p));
         if (!m->bottom.empty()) {

@@ -16,8 +16,7 @@ struct ErrRecord {
     unsigned long long first_bad_len;  // smallest position of a negative length
     unsigned long long first_bad_idx;  // smallest position of an id outside its table
     unsigned int flags;                // ERR_* bits
-    unsigned int tiles_done[4];        // per frame: the scan's counter (launch_scan())
-    unsigned int pad[7];
+    unsigned int pad[11];
 };
 enum : unsigned int { ERR_NEG_LENGTH = 1u, ERR_TOTAL_MISMATCH = 2u, ERR_INDEX_RANGE = 4u };
 
@@ -42,8 +41,10 @@ inline int pad_up(int x) { return (x + PAD - 1) / PAD * PAD; }
 hipError_t launch_clear_err(ErrRecord *err, hipStream_t s);
 
 // S0. offsets[k] = min(sum_{j<k} max(len[j], 0), nnz), k = 0..n.  tile_words is
-// scratch of ceil(n / SCAN_TILE) words, tiles_done one counter; both are zero before
-// the first launch (launch_clear_tile_words()) and left zero by each.
+// scratch of ceil(n / SCAN_TILE) words, zero before the launch, which leaves sums in
+// the first scan_linked_words() of them; the pooling launch behind it clears these
+// (clear_tile_words()), and whoever owns the words clears them before their first use
+// (launch_clear_tile_words()).
 // With a ConcatDense job (x0 != null) extra blocks of the launch also do
 // the work of launch_concat_dense(), which a model without Bottom-FC can start
 // this early: its x0 is the dense input.
@@ -58,10 +59,23 @@ struct ConcatDense {
 // Bottom-FC does not depend on the sparse side (Sec. III-A), so it can share a
 // launch with the scan instead of costing one of its own.
 struct ChainProblem;
+constexpr int SCAN_LINK_POLLS = 65536;  // of another tile's word before its lengths are added up instead
 hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *offsets,
-                       unsigned long long *tile_words, unsigned *tiles_done, ErrRecord *err, const ConcatDense &job,
-                       const ChainProblem *rider, hipStream_t s);
-hipError_t launch_clear_tile_words(unsigned long long *words, int n, unsigned *done, hipStream_t s);
+                       unsigned long long *tile_words, ErrRecord *err, const ConcatDense &job,
+                       const ChainProblem *rider, hipStream_t s, int polls = SCAN_LINK_POLLS);
+int scan_linked_words(int n, bool with_rider);
+hipError_t launch_clear_tile_words(unsigned long long *words, int n, hipStream_t s);
+// The words a scan has published, for the pooling launch behind it to clear.
+struct TileWords {
+    unsigned long long *words;
+    int n;
+};
+// One wave clears the words.
+__device__ inline void clear_tile_words(const TileWords &w)
+{
+    for (int i = threadIdx.x & 63; i < w.n; i += 64)
+        __hip_atomic_store(w.words + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // Once per process and device, before the first launch (not under stream capture).
 hipError_t scan_prepare();
 
@@ -74,12 +88,13 @@ struct PoolOut {
 };
 
 // S1. Sum of the rows of every bag, fp32 accumulation.  nnz (the batch's id
-// count) only picks the launch shape: bags of a few ids share a wavefront.
+// count) only picks the launch shape: bags of a few ids share a wavefront.  The
+// words in `left` are cleared on the way.
 // stream_rows: load rows with the non-temporal hint (id streams without reuse).
 // max_rows: row count of the largest table (tables under 4 GiB take 32-bit offsets).
 hipError_t launch_pool(const TableDesc *tables, int dtype, int T, int D, int B,
                        const int32_t *indices, const int32_t *offsets, PoolOut out, long long nnz,
-                       bool stream_rows, long long max_rows, ErrRecord *err, hipStream_t s);
+                       bool stream_rows, long long max_rows, const TileWords &left, ErrRecord *err, hipStream_t s);
 
 // Which form launch_pool() takes: bags of a few ids side by side in a wave; 32-bit
 // byte offsets into the tables.
@@ -91,7 +106,7 @@ bool pool_narrow(long long max_rows, int rowbytes);
 bool pool_hot_fits(int hcap, int rowbytes);
 hipError_t launch_pool_hot(const TableDesc *tables, int dtype, int T, int D, int B,
                            const int32_t *indices, const int32_t *offsets, float *pooled, int hcap,
-                           int num_cus, ErrRecord *err, hipStream_t s);
+                           int num_cus, const TileWords &left, ErrRecord *err, hipStream_t s);
 
 // S2 / S4. One layer of `groups` stacks that run side by side (the task towers
 // of the Predict-FC; 1 for a single stack), stack g being

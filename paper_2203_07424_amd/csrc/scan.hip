@@ -4,8 +4,8 @@
 // factor varies per lookup, Fig. 2(c)); the gather needs where each bag starts.
 // One launch over at most a few hundred thousand int32: a block scans a tile of
 // 2048 in LDS, publishes its sum in a word of device memory that carries its own
-// "valid" bit (no fence: there is nothing else to order) and polls the words of
-// the tiles before it.  Bound by that hand-over, a round trip to memory: 80 tiles
+// "valid" bit (no fence: the word is all that is handed on, and the pooling launch
+// clears it) and polls the words of the tiles before it.  Bound by that hand-over, a round trip to memory: 80 tiles
 // with Bottom-FC riding along 11.2 us against 5.5 + 9.6 in two launches (40 tables x
 // 4096 170.9 -> 166.7 us per forward), 52 tiles alone 8.4 against 4.6 + 5.4 (103.8
 // -> 102.3), 480 tiles with Bottom-FC 26.6 against 6.3 + 20.
@@ -31,10 +31,9 @@ __global__ __launch_bounds__(64) void clear_err_kernel(ErrRecord *err)
     }
 }
 
-__global__ __launch_bounds__(256) void clear_tile_words_kernel(unsigned long long *words, int n, unsigned *done)
+__global__ __launch_bounds__(256) void clear_tile_words_kernel(unsigned long long *words, int n)
 {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) words[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0;
 }
 
 // The scan alone: blocks [0, tiles) write the offsets, the blocks
@@ -83,9 +82,9 @@ hipError_t launch_clear_err(ErrRecord *err, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_clear_tile_words(unsigned long long *words, int n, unsigned *done, hipStream_t s)
+hipError_t launch_clear_tile_words(unsigned long long *words, int n, hipStream_t s)
 {
-    hipLaunchKernelGGL(clear_tile_words_kernel, dim3(std::min((n + 255) / 256, 256)), dim3(256), 0, s, words, n, done);
+    hipLaunchKernelGGL(clear_tile_words_kernel, dim3(std::min((n + 255) / 256, 256)), dim3(256), 0, s, words, n);
     return hipGetLastError();
 }
 
@@ -99,9 +98,17 @@ hipError_t scan_prepare()
                                hipFuncAttributeMaxDynamicSharedMemorySize, most);
 }
 
+// With a stack riding along the launch lasts as long as the stack, so for a few
+// tiles its scan blocks have the time to add up the earlier lengths themselves.
+int scan_linked_words(int n, bool with_rider)
+{
+    const int tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
+    return tiles > (with_rider ? 8 : 1) ? tiles - 1 : 0;
+}
+
 hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *offsets,
-                       unsigned long long *tile_words, unsigned *tiles_done, ErrRecord *err, const ConcatDense &job,
-                       const ChainProblem *rider, hipStream_t s)
+                       unsigned long long *tile_words, ErrRecord *err, const ConcatDense &job,
+                       const ChainProblem *rider, hipStream_t s, int polls)
 {
     if (n <= 0) return hipSuccess;
     const int tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
@@ -110,14 +117,12 @@ hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *of
         const long long total = (long long)job.B * (job.w0 + job.ldz - job.width);
         extra = (int)std::min<long long>((total + 8 * SCAN_THREADS - 1) / (8 * SCAN_THREADS), 256);
     }
-    // With a stack riding along the launch lasts as long as the stack, so for a few
-    // tiles its scan blocks have the time to add up the earlier lengths themselves.
     const bool has_rider = rider && rider->M > 0;
     TileLink link;
-    if (tiles > (has_rider ? 8 : 1)) {
+    if (scan_linked_words(n, has_rider) > 0) {
         link.words = tile_words;
-        link.done = tiles_done;
         link.tiles = tiles;
+        link.polls = polls;
     }
     if (has_rider) {
         if (!rider->a_f32 || rider->groups != 1) return hipErrorInvalidValue;

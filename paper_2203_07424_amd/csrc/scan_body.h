@@ -48,23 +48,24 @@ __device__ inline void concat_dense_block(const ConcatDense &job, int b, int nb)
 
 // How the blocks of a scan that is one launch learn what lies before their tile:
 // each publishes the sum of its own (value * 2 + 1, so that the word says by itself
-// that it is there) and adds up those of earlier tiles.  The last block to have
-// read them all clears words and counter for the next launch.
-struct TileLink {
-    unsigned long long *words = nullptr;  // one per tile, zero between launches
-    unsigned *done = nullptr;             // blocks that have read all they need, zero between launches
-    int tiles = 0;
-};
+// that it is there), except the last, whose sum nobody reads, and adds up those of
+// earlier tiles.  A word only ever goes from zero to its value within the launch;
+// the launch behind it on the stream clears it.  So there is no order between
+// accesses to different words to keep, and nothing that a call leaves behind
+// outlives its own pooling launch, whatever else ran beside it.
 // A block waits for words of blocks with smaller numbers only, which never wait
-// for it; past so many polls it adds up the lengths of that tile itself.
-constexpr int LINK_POLLS = 1 << 16;
+// for it; past `polls` polls it adds up the lengths of that tile itself.
+struct TileLink {
+    unsigned long long *words = nullptr;  // one per tile, zero before the launch
+    int tiles = 0, polls = 0;
+};
 
 __device__ inline long long linked_sum(const TileLink &l, int tile, const int32_t *__restrict__ len)
 {
     long long sum = 0;
     for (int j = threadIdx.x; j < tile; j += SCAN_THREADS) {
         unsigned long long w = 0;
-        for (int p = 0; p < LINK_POLLS && !(w & 1); ++p)
+        for (int p = 0; p < l.polls && !(w & 1); ++p)
             w = __hip_atomic_load(l.words + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (w & 1) {
             sum += (long long)(w >> 1);
@@ -85,7 +86,6 @@ __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n,
     __shared__ int s_tile[SCAN_TILE + SCAN_TILE / 32];
     __shared__ long long s_w[SCAN_THREADS / 64];
     __shared__ long long s_wave_excl[SCAN_THREADS / 64];
-    __shared__ int s_last;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long base = (long long)tile * SCAN_TILE;
 
@@ -106,10 +106,9 @@ __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n,
         own += v;
     }
     long long before = 0;
-    unsigned seen = 0;
     if (link.words) {
         own = block_sum(own, s_w);
-        if (tid == 0)
+        if (tid == 0 && tile + 1 < link.tiles)
             __hip_atomic_store(link.words + tile, (unsigned long long)own * 2 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         before = linked_sum(link, tile, len);
     } else {
@@ -122,9 +121,7 @@ __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n,
             for (int i = 0; i < SCAN_ITEMS; ++i) before += v[i] > 0 ? v[i] : 0;
         }
     }
-    before = block_sum(before, s_w);  // every thread has read what it needs
-    if (link.words && tid == 0)
-        seen = __hip_atomic_fetch_add(link.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    before = block_sum(before, s_w);
     __syncthreads();
 
     // Each thread owns SCAN_ITEMS consecutive entries.
@@ -170,18 +167,12 @@ __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n,
         offsets[n] = (int)(total < nnz ? total : nnz);
         if (total != nnz) atomicOr(&err->flags, ERR_TOTAL_MISMATCH);
     }
-    if (tid == 0) s_last = link.words && seen == (unsigned)link.tiles - 1;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < SCAN_ITEMS; ++i) {
         const int p = i * SCAN_THREADS + tid;
         const long long k = base + p;
         if (k < n) offsets[k] = s_tile[p + (p >> 5)];
-    }
-    if (s_last) {
-        for (int j = tid; j < link.tiles; j += SCAN_THREADS)
-            __hip_atomic_store(link.words + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (tid == 0) __hip_atomic_store(link.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

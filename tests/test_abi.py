@@ -137,3 +137,10 @@ def test_null_and_order_errors_without_device(binding):
     assert lib.rec_probe_mfma(1, 0, 100, 4096, None) == b.REC_ERR_ARG
     assert lib.rec_probe_mfma(1, 256, 0, 4096, None) == b.REC_ERR_ARG
     assert lib.rec_probe_mfma(1, 1 << 20, 1, 4096, None) == b.REC_ERR_ARG
+    lib.rec_probe_scan.restype = C.c_int
+    lib.rec_probe_scan.argtypes = [C.c_void_p, C.c_int32, C.c_int64, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]
+    good = [4096, 5000, 10, 4096, 4096, 0, 4096, None]
+    for at, bad in ((0, None), (1, 0), (2, -1), (2, 1 << 31), (3, None), (4, None), (5, -1), (5, 65537), (6, None)):
+        args = list(good)
+        args[at] = bad
+        assert lib.rec_probe_scan(*args) == b.REC_ERR_ARG, (at, bad)

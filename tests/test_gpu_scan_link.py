@@ -1,5 +1,5 @@
 """The scan in one launch: its blocks hand their tiles' sums to the later ones through
-words that each launch leaves as it found them.  Offsets exact for batches of one
+words that the pooling launch behind it clears.  Offsets exact for batches of one
 to 300 tiles, call after call on one model with other batch sizes in between, with
 Bottom-FC riding along, alone, and in a graph replayed over changing lengths."""
 import numpy as np
@@ -80,3 +80,85 @@ def test_offsets_of_graph_replays(binding):
         torch.cuda.synchronize()
         assert torch.equal(got, out)
     m.close()
+
+
+# ---------------------------------------------------------------- the words themselves
+def tile_words(m):
+    """The scan's words in the model's workspace: behind the offsets of the last call's frame."""
+    from paper_2203_07424_amd import binding as b
+    st, p, _ = b.rec_debug_get(m.handle, b.REC_DBG_OFFSETS)
+    assert st == b.REC_OK
+    at = p - m.ws.data_ptr() + (4 * (m.T * m.max_batch + 1) + 255) // 256 * 256
+    return m.ws[at:at + 8 * ((m.T * m.max_batch + 2047) // 2048)].view(torch.int64)
+
+
+def bags_model(binding, g, T, D, R, B, F, nnz, **kw):
+    tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(np.float32) for _ in range(T)]
+    width = D + T * (T + 1) // 2
+    m = binding.RecModel(T, D, [R] * T, "f32", F, [F, D], [width, 1], B, nnz, **kw)
+    for t, tab in enumerate(tabs):
+        m.load_table(t, torch.from_numpy(tab).cuda())
+    H.load_mlps(binding, m, layer(g, D, F), layer(g, 1, width))
+    m.max_batch = B
+    return m
+
+
+@pytest.mark.parametrize("pooling", ["bags", "short bags", "hot rows", "pipelined"])
+def test_words_are_clear_after_every_call(binding, pooling):
+    """Whatever a call finds in the words, the next one starts from zeros: a word left
+    behind would be taken for a tile's sum by a later, larger batch."""
+    print("tile words", pooling, flush=True)
+    g = np.random.default_rng(970)
+    T, D, R, F, most = 6, 4, 50, 5, 20_000
+    mean = 2 if pooling == "short bags" else 6
+    m = bags_model(binding, g, T, D, R, most, F, T * most * 2 * mean, pipeline=pooling == "pipelined")
+    if pooling == "hot rows":
+        for t in range(T):
+            m.load_hot_rows(t, np.arange(16, dtype=np.int32))
+
+    def call(B):
+        lens = g.integers(0, 2 * mean, T * B).astype(np.int32)
+        idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
+        m.forward(*(torch.from_numpy(a).cuda() for a in (g.standard_normal((B, F)).astype(np.float32), idx, lens)))
+        m.drain()
+        torch.cuda.synchronize()
+        assert not tile_words(m).any()
+        return np.array_equal(m.debug_offsets().cpu().numpy().astype(np.int64), orc.offsets(lens)[0])
+
+    for B in (most, 700, 12_345, most):
+        assert call(B)
+        assert m.check() == (binding.REC_OK, -1)
+    for fill in (1, 2 * 777 + 1):     # words of calls that raced, say: they spoil one call, not those behind it
+        frames = 4 if pooling == "pipelined" else 1
+        tile_words(m)[:-1].fill_(fill)    # the last tile's word is neither written nor read
+        torch.cuda.synchronize()
+        for _ in range(frames):           # the last of them in the spoilt frame
+            call(most)
+        m.check()
+        for B in (most,) * frames:
+            assert call(B)
+            assert m.check() == (binding.REC_OK, -1)
+    m.close()
+
+
+@pytest.mark.parametrize("n", [2049, 4096, 40_000, 1_000_000])
+def test_hand_over_between_blocks(binding, n):
+    """The scan alone: with its waits cut short (every block adds up the lengths before it
+    itself) and with the usual bound.  Each tile but the last publishes its sum."""
+    print("scan alone", n, flush=True)
+    g = np.random.default_rng(980 + n)
+    lens = g.integers(-1, 6, n).astype(np.int32)
+    want = orc.offsets(lens)[0]
+    tiles = (n + 2047) // 2048
+    sums = np.add.reduceat(np.maximum(lens, 0).astype(np.int64), np.arange(0, n, 2048))
+    dl, err = torch.from_numpy(lens).cuda(), torch.zeros(8, dtype=torch.int64, device="cuda")
+    for polls in (0, 65536):
+        out = torch.full((n + 1,), -9, dtype=torch.int32, device="cuda")
+        words = torch.zeros(tiles, dtype=torch.int64, device="cuda")
+        words[-1] = -12345                    # nobody's business
+        st = binding.rec_probe_scan(dl, int(want[-1]), out, words, polls, err)
+        assert st == binding.REC_OK
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().astype(np.int64), want), polls
+        left = words.cpu().numpy()
+        assert np.array_equal(left[:-1], 2 * sums[:-1] + 1) and left[-1] == -12345
