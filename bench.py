@@ -287,7 +287,8 @@ def run_steps(torch, model, stream, db, outs, steps, first=0):
 
 def stage_profile(torch, binding, np, model, stream, db, n):
     """n in-order forwards, every stage bracketed with HIP events on `stream`.
-    Returns (mean ms per stage, per-forward pool ms, index of the batch each used)."""
+    Returns (mean ms per stage, per-forward pool ms, index of the batch each used,
+    names of the stages that had no launch of their own)."""
     with torch.cuda.stream(stream):
         for i in range(5):
             model.forward(*db[i % len(db)])
@@ -300,9 +301,10 @@ def stage_profile(torch, binding, np, model, stream, db, n):
         model.drain()
     torch.cuda.synchronize()
     rows = np.array([list(model.stage_ms(j).values()) for j in range(n)])
+    shared = model.stage_shared(0)
     model.set_profiling(0)
     mean = dict(zip(binding.STAGE_NAMES, rows.mean(axis=0).tolist()))
-    return mean, rows[:, binding.STAGE_NAMES.index("pool")], [i % len(db) for i in range(n)]
+    return mean, rows[:, binding.STAGE_NAMES.index("pool")], [i % len(db) for i in range(n)], shared
 
 
 def latency_profile(torch, np, model, stream, db, out, iters, warmup=10):
@@ -327,34 +329,25 @@ def latency_profile(torch, np, model, stream, db, out, iters, warmup=10):
 SUSTAINED_RANDOM_TFLOPS = None   # set by main() once mfma_sustained() has run
 
 
-# A stage without a launch of its own reads one event record (4 to 5 us); the shortest
-# launch and a record take 7.
-EMPTY_BRACKET_MS = 6.5e-3
-
-
-def mlp_mfma(wl, avg):
+def mlp_mfma(wl, avg, shared=frozenset()):
     """Matrix-unit use of the FC stages: unpadded 2*M*N*K of the stage's layers over
     its HIP-event interval (which includes one event record and, for small
     layers, mostly launch latency) against the bf16 MFMA peak.  bottom_first and
-    top_first bracket a single launch each.  Where the whole Predict-FC runs in the
-    launch of the interaction, its stage holds that launch (top_with_interaction)
-    and the rest of the stack an empty bracket, which is left out, as is that of
-    Bottom-FC layers gone into the same launch."""
+    top_first bracket a single launch each.  Stages in `shared` (no launch of their
+    own, rec_stage_shared()) hold an empty bracket and are left out; where the whole
+    Predict-FC runs in the launch of the interaction that launch is
+    top_with_interaction."""
     def flops(widths):
         return sum(2.0 * wl.batch * widths[i] * widths[i + 1] for i in range(len(widths) - 1))
     out = {}
-    empty = lambda stage: 0 < avg.get(stage, 0) < EMPTY_BRACKET_MS
-    stages = [("bottom_first", "bottom_first", wl.bottom[:2], 1)]
-    if empty("interact") and wl.interaction == "dot":
+    stages = [("bottom_first", "bottom_first", wl.bottom[:2], 1), ("bottom_rest", "bottom_rest", wl.bottom[1:], 1)]
+    if "interact" in shared and wl.interaction == "dot":
         stages.append(("top_with_interaction", "top_first", wl.top, wl.towers))
-        if not empty("bottom_rest"):
-            stages.append(("bottom_rest", "bottom_rest", wl.bottom[1:], 1))
     else:
-        stages += [("bottom_rest", "bottom_rest", wl.bottom[1:], 1), ("top_first", "top_first", wl.top[:2], wl.towers),
-                   ("top_rest", "top_rest", wl.top[1:], wl.towers)]
+        stages += [("top_first", "top_first", wl.top[:2], wl.towers), ("top_rest", "top_rest", wl.top[1:], wl.towers)]
     for name, stage, widths, mult in stages:
         f = flops(widths) * mult
-        if f > 0 and avg.get(stage, 0) > 0:
+        if f > 0 and avg.get(stage, 0) > 0 and stage not in shared:
             tf = f / (avg[stage] * 1e-3) / 1e12
             out[name] = {"gflop": f / 1e9, "ms": avg[stage], "tflops": tf,
                          "frac_of_bf16_peak": tf / MFMA_BF16_PEAK_TFLOPS}
@@ -432,17 +425,22 @@ def widest_layer_yardstick(torch, wl, dev):
     return y
 
 
-def pool_roofline(np, wl, hb, used, pool_ms, streaming, kind="algorithmic"):
+def pool_roofline(np, wl, hb, used, pool_ms, streaming, shared=frozenset(), kind="algorithmic"):
     """The pooling kernel against the HBM peak: bytes per launch over the mean
-    launch time of the timed launches."""
+    launch time of the timed launches.  Where pooling shares its launch with the
+    scan (and Bottom-FC) that launch is named, and no rate of pooling alone given."""
     fn = algorithmic_pool_bytes if kind == "algorithmic" else compulsory_pool_bytes
     per_batch = [fn(wl, b) for b in hb]
     nbytes = float(np.mean([per_batch[i] for i in used]))
     ms = float(np.mean(pool_ms))
     gbps = nbytes / (ms * 1e-3) / 1e9
-    return {"kernel": "pool_kernel (embedding-bag gather-reduce)", "bound": "hbm", "achieved": gbps,
-            "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": gbps / HBM_PEAK_GBPS,
-            "traffic": profiled_pool_traffic(wl, streaming), "bytes_per_launch": nbytes,
+    if "scan" in shared:
+        what = {"kernel": "front_kernel (offsets, Bottom-FC or dense part, and pooling in one launch)", "traffic": None}
+    else:
+        what = {"kernel": "pool_kernel (embedding-bag gather-reduce)", "bound": "hbm", "achieved": gbps,
+                "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": gbps / HBM_PEAK_GBPS,
+                "traffic": profiled_pool_traffic(wl, streaming)}
+    return {**what, "bytes_per_launch": nbytes,
             "bytes_counted": "gathered rows + ids + offsets + pooled vectors written" if kind == "algorithmic"
                              else "distinct rows + ids + offsets + pooled vectors written",
             "avg_launch_ms": ms, "min_launch_ms": float(np.min(pool_ms)), "launches_timed": int(len(pool_ms)),
@@ -473,14 +471,15 @@ def short_leg(torch, binding, synth, np, name, args, dev, streams):
         assert model.check() == (binding.REC_OK, -1)
     res["value"] = max(res["in_order"]["value"], res["pipelined"]["value"])
     res["latency_ms"] = latency_profile(torch, np, m, streams[0], db, outs[0], 100)
-    avg, pool_ms, used = stage_profile(torch, binding, np, m, streams[0], db, 32)
+    avg, pool_ms, used, shared = stage_profile(torch, binding, np, m, streams[0], db, 32)
     res["stage_ms"] = avg
-    res["mlp_mfma"] = mlp_mfma(w, avg)
+    res["stages_in_another_launch"] = sorted(shared)
+    res["mlp_mfma"] = mlp_mfma(w, avg, shared)
     y = widest_layer_yardstick(torch, w, dev)
     if y:
         res["library_gemm_yardstick"] = y
-    res["pooling"] = pool_roofline(np, w, hb, used, pool_ms, streaming)
-    if w.index_dist[0] == "zipf":      # cache-served: an algorithmic rate, not a fraction of the HBM peak
+    res["pooling"] = pool_roofline(np, w, hb, used, pool_ms, streaming, shared)
+    if w.index_dist[0] == "zipf" and "achieved" in res["pooling"]:      # cache-served: an algorithmic rate, not a fraction of the HBM peak
         res["pooling"]["algorithmic_gbps"] = res["pooling"].pop("achieved")
         for k in ("frac", "bound"):
             res["pooling"].pop(k)
@@ -811,15 +810,16 @@ def main() -> int:
     extra["latency_ms"]["note"] = "in-order forward of one batch, closed loop, host launch and synchronisation included"
 
     # every stage of in-order forwards bracketed with HIP events
-    stage_avg, pool_ms, used = stage_profile(torch, binding, np, m, streams[0], dev_batches, args.timed_launches)
-    this_leg = pool_roofline(np, w, host_batches, used, pool_ms, wants_streaming(w))
-    comp = pool_roofline(np, w, host_batches, used, pool_ms, wants_streaming(w), kind="compulsory")
+    stage_avg, pool_ms, used, shared = stage_profile(torch, binding, np, m, streams[0], dev_batches, args.timed_launches)
+    extra["stages_in_another_launch"] = sorted(shared)
+    this_leg = pool_roofline(np, w, host_batches, used, pool_ms, wants_streaming(w), shared)
+    comp = pool_roofline(np, w, host_batches, used, pool_ms, wants_streaming(w), shared, kind="compulsory")
     traffic = this_leg["traffic"]
     pool_detail = dict(this_leg)
     pool_detail.update({
-        "algorithmic_gbps": this_leg["achieved"],
-        "compulsory_bytes_per_launch": comp["bytes_per_launch"], "compulsory_gbps": comp["achieved"],
-        "compulsory_frac_of_hbm_peak": comp["frac"],
+        "algorithmic_gbps": this_leg.get("achieved"),
+        "compulsory_bytes_per_launch": comp["bytes_per_launch"], "compulsory_gbps": comp.get("achieved"),
+        "compulsory_frac_of_hbm_peak": comp.get("frac"),
         "traffic_source": "rocprofv3 counters of an earlier run of the same kernel source (profiles/), not this run",
         "hbm_frac_by_profiled_traffic": (traffic / (this_leg["avg_launch_ms"] * 1e-3) / 1e9 / HBM_PEAK_GBPS)
         if traffic else None})
@@ -828,7 +828,7 @@ def main() -> int:
         pool_detail["note"] = ("skewed ids: the caches serve most rows, so the algorithmic rate may exceed the "
                                "HBM peak; the binding comparison is the uniform-id twin under `roofline`")
         for k in ("frac", "achieved", "bound"):
-            pool_detail.pop(k)
+            pool_detail.pop(k, None)
         if w.pooling[0] != "fixed" or w.pooling[1] > 1:
             pool_detail["id_repeats"] = repeats_within_chunks(w, host_batches[0])
         extra["roofline_zipf"] = pool_detail
@@ -839,11 +839,11 @@ def main() -> int:
         wu = w.with_uniform_indices()
         hbu, dbu = make_batches(torch, synth, wu, args.batches, 500, dev)
         m.set_option(binding.REC_OPT_STREAM_ROWS, int(wants_streaming(wu)))
-        _, pool_u, used_u = stage_profile(torch, binding, np, m, streams[0], dbu, args.timed_launches)
+        _, pool_u, used_u, shared_u = stage_profile(torch, binding, np, m, streams[0], dbu, args.timed_launches)
         st, pos = m.check()
         assert st == binding.REC_OK, (st, pos)
         m.set_option(binding.REC_OPT_STREAM_ROWS, int(wants_streaming(w)))
-        roofline = pool_roofline(np, wu, hbu, used_u, pool_u, wants_streaming(wu))
+        roofline = pool_roofline(np, wu, hbu, used_u, pool_u, wants_streaming(wu), shared_u)
         roofline["note"] = ("uniform-id twin of the headline workload (same shapes, ids uniform): nothing for the "
                             "caches to serve, so algorithmic bytes are HBM bytes")
         del dbu, hbu
@@ -948,7 +948,8 @@ def main() -> int:
                    "streams": 4 if args.mode == "pipelined" else 1,
                    "hot_rows_per_table": args.hot_rows,
                    "mean_nnz": float(np.mean([b.nnz for b in host_batches]))},
-        "roofline": roofline, "cpu_baseline": cpu, "stage_ms": stage_avg, "mlp_mfma": mlp_mfma(w, stage_avg),
+        "roofline": roofline, "cpu_baseline": cpu, "stage_ms": stage_avg,
+        "mlp_mfma": mlp_mfma(w, stage_avg, shared),
     }
     out.update(extra)
     print(json.dumps(out), flush=True)

@@ -333,6 +333,11 @@ REC_API rec_status rec_drain(rec_model *m, void *stream);
 REC_API rec_status rec_set_profiling(rec_model *m, int32_t slots, int32_t period);
 REC_API rec_status rec_stage_ms(rec_model *m, int32_t slot, float *ms);
 
+/* Which stages of the forward timed in `slot` had no launch of their own, their
+ * work (if any) being part of another stage's: bit REC_STAGE_* of *mask.  Host
+ * bookkeeping, no wait.  REC_ERR_STATE as rec_stage_ms(). */
+REC_API rec_status rec_stage_shared(const rec_model *m, int32_t slot, uint32_t *mask);
+
 /* Text for a status; any other number gives "unknown status". */
 REC_API const char *rec_status_string(int status);
 

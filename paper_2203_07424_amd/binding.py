@@ -43,7 +43,7 @@ STAGE_NAMES = ("scan", "pool", "bottom_first", "bottom_rest", "interact", "top_f
 
 EXPORTS = ("rec_create", "rec_destroy", "rec_workspace_bytes", "rec_bind_workspace",
            "rec_load_tables", "rec_load_hot_rows", "rec_mlp_packed_bytes", "rec_load_mlp", "rec_forward", "rec_forward_static", "rec_check",
-           "rec_debug_get", "rec_set_option", "rec_set_dense_stream", "rec_set_pool_streams", "rec_drain", "rec_set_profiling", "rec_stage_ms", "rec_status_string",
+           "rec_debug_get", "rec_set_option", "rec_set_dense_stream", "rec_set_pool_streams", "rec_drain", "rec_set_profiling", "rec_stage_ms", "rec_stage_shared", "rec_status_string",
            "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan")
 
 
@@ -93,6 +93,8 @@ _lib.rec_set_profiling.restype = C.c_int
 _lib.rec_set_profiling.argtypes = [_vp, C.c_int32, C.c_int32]
 _lib.rec_stage_ms.restype = C.c_int
 _lib.rec_stage_ms.argtypes = [_vp, C.c_int32, C.POINTER(C.c_float)]
+_lib.rec_stage_shared.restype = C.c_int
+_lib.rec_stage_shared.argtypes = [_vp, C.c_int32, C.POINTER(C.c_uint32)]
 _lib.rec_status_string.restype = C.c_char_p
 _lib.rec_status_string.argtypes = [C.c_int]
 _lib.rec_synth_fill_table.restype = C.c_int
@@ -220,6 +222,12 @@ def rec_stage_ms(m: int, slot: int = 0) -> Tuple[int, List[float]]:
     ms = (C.c_float * REC_NUM_STAGES)()
     st = _lib.rec_stage_ms(m, slot, ms)
     return st, [float(v) for v in ms]
+
+
+def rec_stage_shared(m: int, slot: int = 0) -> Tuple[int, int]:
+    mask = C.c_uint32(0)
+    st = _lib.rec_stage_shared(m, slot, C.byref(mask))
+    return st, int(mask.value)
 
 
 def rec_synth_fill_table(dev_rows: torch.Tensor, seed: int, table: int) -> int:
@@ -368,6 +376,12 @@ class RecModel:
         st, ms = rec_stage_ms(self.handle, slot)
         self._ok(st, "rec_stage_ms")
         return dict(zip(STAGE_NAMES, ms))
+
+    def stage_shared(self, slot: int = 0) -> set:
+        """Names of the stages that had no launch of their own in the forward timed in `slot`."""
+        st, mask = rec_stage_shared(self.handle, slot)
+        self._ok(st, "rec_stage_shared")
+        return {name for i, name in enumerate(STAGE_NAMES) if mask >> i & 1}
 
     def _view(self, what: int, nbytes: int) -> Tuple[torch.Tensor, int]:
         st, p, ld = rec_debug_get(self.handle, what)

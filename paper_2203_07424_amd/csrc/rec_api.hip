@@ -96,6 +96,7 @@ struct rec_model {
     // Stage timing: forward number i records into slot i % slots.
     std::vector<hipEvent_t> ev;  // slots * EV_PER_SLOT
     std::vector<char> slot_mode; // per slot: 1 recorded by a pipelined forward, 2 in order with Bottom-FC inside the scan's launch
+    std::vector<uint32_t> slot_shared;  // per slot: stages without a launch of their own (rec_stage_shared())
     int slots = 0, period = 1;
     long long forwards = 0;      // forwards seen since profiling was switched on
 
@@ -353,7 +354,7 @@ bool tail_applies(const rec_model *m, const Call &c)
     if (m->fuse_mlp == 2) return true;
     if (m->pipeline || c.B > tail_most_samples(m->num_cus)) return false;
     const int n = m->n_top - 1, nb = (int)m->bottom.size();
-    size_t bytes = 0, launches = 0;
+    size_t bytes = 0, launches = 0;  // of the layers the launch would take
     for (int i = 0; i < n;) {
         const int j = chain_end(m, m->top.data(), i, n, 1, c.B, false, true);
         for (int l = i; l < std::max(j, i + 1); ++l) bytes += m->top[l].chain_bytes();
@@ -364,9 +365,6 @@ bool tail_applies(const rec_model *m, const Call &c)
     return bytes <= launches * 320 * 1024 || c.B >= 12 * m->num_cus;
 }
 
-// S0 and S1.  With hot lists registered (and use_hot), hot rows are served from
-// LDS.  In the concatenation model the sums go straight into the Predict-FC
-// input rows.
 // A concatenation model without Bottom-FC has the dense part of its Predict-FC
 // input rows written by spare blocks of the scan: one launch less in front of S4.
 bool concat_rides_on_scan(const rec_model *m)
@@ -420,7 +418,7 @@ PoolOut pool_out(const rec_model *m, const Bufs &u)
 
 // S0 and S1 (and Bottom-FC, with_bottom) of a small in-order batch as one launch,
 // where csrc/front.hip has one for it.
-bool front_runs(const rec_model *m, const Call &c, bool use_hot, bool with_bottom)
+bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with_bottom)
 {
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
     if (m->pipeline || (concat ? with_bottom || !concat_rides_on_scan(m) : !with_bottom)) return false;
@@ -444,6 +442,57 @@ hipError_t enqueue_front(const rec_model *m, const Bufs &u, const Call &c, hipSt
     return launch_front(f, with_bottom ? &cp : nullptr, s);
 }
 
+// Which stages of a forward share a launch; decided once per call.
+struct Plan {
+    bool ride = false;   // Bottom-FC in the scan's launch
+    bool front = false;  // scan (and Bottom-FC, with ride) in the pooling launch
+    bool tail = false;   // interaction, Predict-FC and the Bottom-FC layers [tail_from, ...) in one launch
+    int tail_from = 0;
+};
+Plan plan_of(const rec_model *m, const Call &c, bool use_hot)
+{
+    Plan p;
+    p.ride = bottom_rides_on_scan(m);
+    p.front = front_applies_to(m, c, use_hot, p.ride);
+    p.tail = tail_applies(m, c);
+    p.tail_from = p.tail ? tail_bottom_from(m) : (int)m->bottom.size();
+    return p;
+}
+
+// Launches of layers [0, n) of G stacks side by side.
+int launches_of(const rec_model *m, const Layer *layers, int n, int G, int B, bool a_f32, bool dot_after)
+{
+    int launches = 0;
+    for (int i = 0; i < n; ++launches) i = std::max(chain_end(m, layers, i, n, G, B, a_f32 && i == 0, dot_after), i + 1);
+    return launches;
+}
+
+// The stages that have no launch of their own under plan p (bits REC_STAGE_*).
+uint32_t shared_stages(const rec_model *m, const Plan &p, int B)
+{
+    const int n = m->n_top - 1;
+    uint32_t s = 0;
+    const auto in_another = [&s](int stage) { s |= 1u << stage; };
+    if (p.front) in_another(REC_STAGE_SCAN);
+    const int bottom = p.ride ? 0 : launches_of(m, m->bottom.data(), p.tail_from, 1, B, true, false);
+    if (bottom < 1) in_another(REC_STAGE_BOTTOM_FIRST);
+    if (bottom < 2) in_another(REC_STAGE_BOTTOM_REST);
+    if (p.tail || concat_rides_on_scan(m)) in_another(REC_STAGE_INTERACT);
+    // Does the one-output layer fold into the launch of the layers in front of it?
+    int top = launches_of(m, m->top.data(), n, m->towers, B, false, true);
+    bool folded = n > 0 && fc_can_fuse_dot(m->top[n - 1].Npad);
+    for (int i = 0; i < n && !folded;) {
+        const int j = chain_end(m, m->top.data(), i, n, m->towers, B, false, true);
+        folded = j > i && j == n;
+        i = std::max(j, i + 1);
+    }
+    if (!folded) ++top;
+    if (p.tail || top < 2) in_another(REC_STAGE_TOP_REST);
+    return s;
+}
+
+// S1.  With hot lists registered (and use_hot), hot rows are served from LDS.  In the
+// concatenation model the sums go straight into the Predict-FC input rows.
 // with_bottom: as in the enqueue_scan() before it.
 hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, hipStream_t s, bool with_bottom)
 {
@@ -467,17 +516,17 @@ hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool u
     return hipSuccess;
 }
 
-hipError_t enqueue_sparse(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, hipStream_t s,
-                          hipEvent_t *ev, bool with_bottom = false)
+hipError_t enqueue_sparse(const rec_model *m, const Bufs &u, const Call &c, const Plan &plan, bool use_hot,
+                          hipStream_t s, hipEvent_t *ev)
 {
-    if (front_runs(m, c, use_hot, with_bottom)) {  // all of it in the pooling stage; the scan's reads an empty interval
+    if (plan.front) {  // all of it in the pooling stage; the scan's reads an empty interval
         REC_TRY(mark(ev, EV_SCAN_END, s));
-        REC_TRY(enqueue_front(m, u, c, s, with_bottom));
+        REC_TRY(enqueue_front(m, u, c, s, plan.ride));
         return mark(ev, EV_POOL_END, s);
     }
-    REC_TRY(enqueue_scan(m, u, c, s, with_bottom));
+    REC_TRY(enqueue_scan(m, u, c, s, plan.ride));
     REC_TRY(mark(ev, EV_SCAN_END, s));
-    REC_TRY(enqueue_pool(m, u, c, use_hot, s, with_bottom));
+    REC_TRY(enqueue_pool(m, u, c, use_hot, s, plan.ride));
     return mark(ev, EV_POOL_END, s);
 }
 
@@ -512,9 +561,10 @@ hipError_t enqueue_fused_tail(const rec_model *m, const Bufs &u, const Call &c, 
 }
 
 // S3 and S4.
-hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev)
+hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, const Plan &plan, hipStream_t s,
+                        hipEvent_t *ev)
 {
-    if (tail_applies(m, c)) return enqueue_fused_tail(m, u, c, s, ev, (int)m->bottom.size(), nullptr, 0);
+    if (plan.tail) return enqueue_fused_tail(m, u, c, s, ev, (int)m->bottom.size(), nullptr, 0);
     const int B = c.B, T = m->T, D = m->D;
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
     // Without a Bottom-FC the dense part of the Predict-FC input is the dense input.
@@ -597,24 +647,23 @@ hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, hipStr
 }
 
 // The whole pass in order on one stream: S0, S1, S2, S3, S4.
-hipError_t enqueue_in_order(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, hipStream_t s,
-                            hipEvent_t *ev)
+hipError_t enqueue_in_order(const rec_model *m, const Bufs &u, const Call &c, const Plan &plan, bool use_hot,
+                            hipStream_t s, hipEvent_t *ev)
 {
     REC_TRY(mark(ev, EV_BEGIN, s));
-    const bool ride = bottom_rides_on_scan(m);
-    REC_TRY(enqueue_sparse(m, u, c, use_hot, s, ev, ride));
-    if (ride) {  // S2 ran inside S0's launch: its stages read zero
+    REC_TRY(enqueue_sparse(m, u, c, plan, use_hot, s, ev));
+    if (plan.ride) {  // S2 ran inside S0's launch: its stages read zero
         REC_TRY(mark(ev, EV_BOTTOM_FIRST_END, s));
         REC_TRY(mark(ev, EV_BOTTOM_END, s));
-    } else if (const int from = tail_bottom_from(m); from < (int)m->bottom.size() && tail_applies(m, c)) {
+    } else if (plan.tail_from < (int)m->bottom.size()) {
         const void *rest = nullptr;
         int rest_ld = 0;
-        REC_TRY(enqueue_bottom(m, u, c, s, ev, from, &rest, &rest_ld));
-        return enqueue_fused_tail(m, u, c, s, ev, from, rest, rest_ld);
+        REC_TRY(enqueue_bottom(m, u, c, s, ev, plan.tail_from, &rest, &rest_ld));
+        return enqueue_fused_tail(m, u, c, s, ev, plan.tail_from, rest, rest_ld);
     } else {
         REC_TRY(enqueue_bottom(m, u, c, s, ev));
     }
-    return enqueue_tail(m, u, c, s, ev);
+    return enqueue_tail(m, u, c, plan, s, ev);
 }
 
 // Device address of `scratch` on each GPU, looked up once per device with that
@@ -942,6 +991,7 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
     const bool prof = m->slots > 0 && m->forwards % m->period == 0;
     const size_t slot = prof ? (size_t)((m->forwards / m->period) % m->slots) : 0;
     hipEvent_t *ev = prof ? &m->ev[slot * EV_PER_SLOT] : nullptr;
+    const Plan plan = plan_of(m, c, true);
 #define REC_DEV(call)                                  \
     do {                                               \
         if ((call) != hipSuccess) return REC_ERR_DEVICE; \
@@ -979,7 +1029,7 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
         REC_DEV(hipStreamWaitEvent(d, m->ev_bottom[k], 0));
         REC_DEV(hipStreamWaitEvent(d, m->ev_pool[k], 0));
         REC_DEV(mark(ev, EV_INTERACT_BEGIN, d));
-        REC_DEV(enqueue_tail(m, u, c, d, ev));
+        REC_DEV(enqueue_tail(m, u, c, plan, d, ev));
         REC_DEV(hipEventRecord(m->ev_tail[k], d));
         m->tail_pending[k] = true;
         m->last_frame = k;
@@ -997,18 +1047,19 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
             REC_DEV(hipStreamWaitEvent(m->side, m->ev_fork, 0));
             REC_DEV(enqueue_bottom(m, u, c, m->side, nullptr));
             REC_DEV(hipEventRecord(m->ev_join, m->side));
-            REC_DEV(enqueue_sparse(m, u, c, true, s, ev));
+            REC_DEV(enqueue_sparse(m, u, c, plan, true, s, ev));
             // the "bottom" stage then times only what pooling did not hide
             REC_DEV(hipStreamWaitEvent(s, m->ev_join, 0));
             REC_DEV(mark(ev, EV_BOTTOM_FIRST_END, s));
             REC_DEV(mark(ev, EV_BOTTOM_END, s));
-            REC_DEV(enqueue_tail(m, u, c, s, ev));
+            REC_DEV(enqueue_tail(m, u, c, plan, s, ev));
         } else {
-            REC_DEV(enqueue_in_order(m, u, c, true, s, ev));
+            REC_DEV(enqueue_in_order(m, u, c, plan, true, s, ev));
         }
-        if (prof) m->slot_mode[slot] = !m->overlap_dense && bottom_rides_on_scan(m) ? 2 : 0;
+        if (prof) m->slot_mode[slot] = plan.ride ? 2 : 0;
     }
 #undef REC_DEV
+    if (prof) m->slot_shared[slot] = shared_stages(m, plan, batch);
     if (m->slots > 0) ++m->forwards;
     return REC_OK;
 }
@@ -1040,7 +1091,7 @@ rec_status rec_forward_static(rec_model *m, const float *dev_dense, const int32_
     if (hipGetLastError() != hipSuccess) return REC_ERR_DEVICE;
     if (batch > 0) {
         const Call c{dev_dense, dev_indices, dev_lengths, batch, nnz, dev_logits};
-        if (enqueue_in_order(m, u, c, false, s, nullptr) != hipSuccess) return REC_ERR_DEVICE;
+        if (enqueue_in_order(m, u, c, plan_of(m, c, false), false, s, nullptr) != hipSuccess) return REC_ERR_DEVICE;
     }
     if (dev_fault) {
         hipLaunchKernelGGL(static_end_kernel, dim3(1), dim3(64), 0, s, u.err,
@@ -1152,6 +1203,7 @@ rec_status rec_set_profiling(rec_model *m, int32_t slots, int32_t period)
         if (e) (void)hipEventDestroy(e);
     m->ev.assign((size_t)slots * EV_PER_SLOT, nullptr);
     m->slot_mode.assign((size_t)slots, 0);
+    m->slot_shared.assign((size_t)slots, 0);
     m->slots = 0;
     m->forwards = 0;
     for (hipEvent_t &e : m->ev)
@@ -1185,6 +1237,15 @@ rec_status rec_stage_ms(rec_model *m, int32_t slot, float *ms)
             continue;  // no launch of its own: nothing to time
         if (hipEventElapsedTime(&ms[i], ev[begin[i]], ev[end[i]]) != hipSuccess) return REC_ERR_DEVICE;
     }
+    return REC_OK;
+}
+
+rec_status rec_stage_shared(const rec_model *m, int32_t slot, uint32_t *mask)
+{
+    if (!m || !mask) return REC_ERR_ARG;
+    const long long timed = (m->forwards + m->period - 1) / m->period;
+    if (m->slots <= 0 || slot < 0 || slot >= m->slots || slot >= timed) return REC_ERR_STATE;
+    *mask = m->slot_shared[slot];
     return REC_OK;
 }
 

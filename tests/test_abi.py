@@ -119,6 +119,7 @@ def test_null_and_order_errors_without_device(binding):
     assert b.rec_check(h)[0] == b.REC_ERR_STATE
     assert b.rec_debug_get(h, b.REC_DBG_POOLED)[0] == b.REC_ERR_STATE
     assert b.rec_stage_ms(h)[0] == b.REC_ERR_STATE
+    assert b.rec_stage_shared(h)[0] == b.REC_ERR_STATE
     assert b.rec_set_profiling(h, 4, 0) == b.REC_ERR_ARG
     assert b.rec_set_option(h, 99, 1) == b.REC_ERR_ARG
     assert b.rec_set_option(h, b.REC_OPT_FUSE_MLP, 3) == b.REC_ERR_ARG

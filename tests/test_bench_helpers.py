@@ -73,3 +73,34 @@ def test_strings_name_the_workload_and_the_arithmetic():
     assert "4 towers" in bench.workload_string(w) and "concatenation" in bench.workload_string(w)
     assert "interaction" not in bench.dtype_string(w)
     assert "two bf16 planes" in bench.dtype_string(synth.WORKLOADS["rmc2"])
+
+
+def test_stages_in_another_launch_are_not_reported_as_their_own():
+    """Which stages shared a launch is what the library says of the timed forward, not
+    what a stage's time looks like."""
+    w = synth.WORKLOADS["rmc3"]
+    whole = 2.0 * w.batch * sum(a * b for a, b in zip(w.top[:-1], w.top[1:]))
+    # an interaction launch of its own, as short as an empty bracket is long
+    avg = {"bottom_first": 0.030, "bottom_rest": 0.012, "interact": 0.006, "top_first": 0.009, "top_rest": 0.008}
+    out = bench.mlp_mfma(w, avg)
+    assert set(out) == {"bottom_first", "bottom_rest", "top_first", "top_rest"}
+    assert np.isclose(out["top_first"]["gflop"], 2.0 * w.batch * w.top[0] * w.top[1] / 1e9)
+    # interaction, Predict-FC and the end of Bottom-FC in one launch
+    out = bench.mlp_mfma(w, avg, {"interact", "top_rest", "bottom_rest"})
+    assert set(out) == {"bottom_first", "top_with_interaction"}
+    assert np.isclose(out["top_with_interaction"]["gflop"], whole / 1e9)
+    assert np.isclose(out["top_with_interaction"]["ms"], 0.009)
+    # Bottom-FC inside the scan's launch
+    out = bench.mlp_mfma(w, avg, {"bottom_first", "bottom_rest"})
+    assert set(out) == {"top_first", "top_rest"}
+
+
+def test_pooling_inside_another_launch_has_no_rate_of_its_own():
+    w = hand_workload()
+    b = synth.Batch(np.zeros((2, 4), np.float32), np.array([5, 5, 7, 9, 5, 5, 1, 2], np.int32),
+                    np.array([3, 1, 2, 2], np.int32))
+    own = bench.pool_roofline(np, w, [b], [0, 0], [0.01, 0.03], False)
+    assert np.isclose(own["achieved"], bench.algorithmic_pool_bytes(w, b) / 0.02e-3 / 1e9) and "pool_kernel" in own["kernel"]
+    shared = bench.pool_roofline(np, w, [b], [0, 0], [0.01, 0.03], False, {"scan", "bottom_first"})
+    assert not {"achieved", "frac", "bound", "peak"} & set(shared) and "front_kernel" in shared["kernel"]
+    assert np.isclose(shared["avg_launch_ms"], 0.02) and shared["traffic"] is None

@@ -6,6 +6,8 @@ order of the fp32 sums, so each is held to the oracle's bars (2e-2 relative on
 the batch against the exact forward, 5e-3 per sample against the bf16 mirror)
 and the two are held to each other more tightly (1e-3).
 """
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -251,6 +253,36 @@ def test_stage_timing_says_where_bottom_fc_ran(binding):
                 else:
                     assert v > 0.0, ms
         m.set_profiling(0)
+    m.close()
+
+
+@pytest.mark.parametrize("name,B,fuse,pipelined,shared", [
+    ("tiny", 256, 1, False, {"scan", "bottom_first", "bottom_rest", "interact", "top_rest"}),   # two launches
+    ("tiny", 2000, 1, False, {"bottom_first", "bottom_rest", "interact", "top_rest"}),          # too many bags for the first
+    ("tiny", 256, 0, False, {"top_rest"}),                                                      # one hidden layer, dot folded in
+    ("tiny", 256, 2, True, {"bottom_rest", "interact", "top_rest"}),
+    ("mtwnd-tiny", 200, 1, False, {"bottom_rest", "top_rest"}),
+    ("mtwnd", 64, 1, False, {"scan", "bottom_first", "bottom_rest", "interact"}),               # no Bottom-FC
+    ("rmc2", 256, 1, False, {"bottom_first", "bottom_rest"}),
+    ("rmc2", 4096, 1, False, {"bottom_first", "bottom_rest", "interact", "top_rest"}),
+])
+def test_stages_that_share_a_launch_are_named(binding, name, B, fuse, pipelined, shared):
+    w = synth.WORKLOADS[name].with_batch(B)
+    if w.rows > 100_000:
+        w = dataclasses.replace(w, rows=100_000)
+    say("stages sharing a launch", name, B, fuse, pipelined)
+    m, _, _ = H.make_workload_model(binding, w, pipeline=pipelined)
+    m.set_option(binding.REC_OPT_FUSE_MLP, fuse)
+    b = synth.draw_batch(w, 9)
+    d = [torch.from_numpy(a).cuda() for a in (b.dense, b.indices, b.lengths)]
+    assert binding.rec_stage_shared(m.handle)[0] == binding.REC_ERR_STATE
+    m.set_profiling(2, 1)
+    m.forward(*d)
+    m.drain()
+    torch.cuda.synchronize()
+    assert m.stage_shared(0) == shared
+    assert binding.rec_stage_shared(m.handle, 1)[0] == binding.REC_ERR_STATE
+    m.set_profiling(0)
     m.close()
 
 
