@@ -338,15 +338,24 @@ int tail_bottom_from(const rec_model *m)
     return i;
 }
 
-// Do S3 and S4 of this call run as the one launch of csrc/tail.hip?  Measured on
-// the 40-table model (1.05 MB of weights, 2 launches saved) and the one with a
-// 2560-wide Bottom-FC (0.95 MB, 4 saved), us per forward as separate launches / as
-// one, uniform ids over small tables: a block streams all weights whatever its
-// samples, 10 us a MB, so at small batches it has to save a launch per 320 KB
-// (B = 256: 45.4 / 47.2, 57.8 / 48.7); from a dozen samples a compute unit the
-// separate layers are past their launch cost as well and it wins regardless
-// (4096: 267.7 / 264.8, 92.1 / 81.6); with more samples than compute units can
-// take in one round of blocks it loses (16384: 892 / 900, 251 / 260).
+// Do S3 and S4 of this call run as the one launch of csrc/tail.hip?  A block streams
+// all weights whatever its samples, 10 us a MB, so it is a question of the weights
+// for each launch it takes the place of.  us per forward as separate launches / as
+// one; at small batches (B = 256) 1 MiB for 2: 45.4 / 47.2, 0.9 for 4: 57.8 / 48.7,
+// so 320 KiB a launch.  From a dozen samples a compute unit the separate layers are
+// past their launch cost as well, but blocks of 16 samples leave half of each
+// matrix instruction idle: at 12 and 16 samples a compute unit (40 tables of 64,
+// Predict-FC of two or more layers; 10 tables of 32, 2560-wide Bottom-FC)
+//   1 MiB for 2     72.6 / 72.5    86.3 / 85.7     2.5 for 4   88.0 / 83.5   101.1 / 98.9
+//   1.5 for 2       78.2 / 77.3    88.3 / 90.7     2.8 for 4   91.6 / 90.6   103.8 / 106.5
+//   2 for 2         75.9 / 83.2    90.7 / 96.8     4.4 for 4  102.2 / 104.7  113.9 / 121.6
+//   9.8 for 5      126.1 / 168.0  147.7 / 194.4    6.4 for 5  115.9 / 133.3  127.7 / 150.3
+// so 640 KiB a launch; in blocks of 32 (20 and 32 samples a compute unit)
+//   1.5 for 2      101.5 / 105.3  152.6 / 147.4    2.5 for 4  126.4 / 116.6  151.0 / 146.4
+//   3.8 for 2      130.8 / 129.8  183.6 / 173.7    6.4 for 5  168.8 / 162.9  197.3 / 194.9
+//   5 for 2        180.6 / 181.6  256.2 / 250.9    9.8 for 5  191.7 / 199.9  249.3 / 270.6
+// 1920.  With more samples than compute units can take in one round of blocks it
+// loses (64 a unit, 1 MiB for 2: 892 / 900, 0.9 for 4: 251 / 260).
 bool tail_applies(const rec_model *m, const Call &c)
 {
     if (m->fuse_mlp == 0 || !tail_possible(m)) return false;
@@ -362,7 +371,8 @@ bool tail_applies(const rec_model *m, const Call &c)
         ++launches;
     }
     for (int i = tail_bottom_from(m); i < nb; ++i, ++launches) bytes += m->bottom[i].chain_bytes();
-    return bytes <= launches * 320 * 1024 || c.B >= 12 * m->num_cus;
+    const size_t kib = c.B < 12 * m->num_cus ? 320 : tail_rows(c.B, m->num_cus) < 32 ? 640 : 1920;
+    return bytes <= launches * kib * 1024;
 }
 
 // A concatenation model without Bottom-FC has the dense part of its Predict-FC

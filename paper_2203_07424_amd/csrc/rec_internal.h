@@ -203,7 +203,9 @@ struct TailProblem {
     int rows, ld_lds;  // filled in by launch_tail()
 };
 bool tail_fits(int T, int D);
-// Up to how many samples a compute unit gets no more than one block.
+// Samples a block takes (8, 16 or 32), and up to how many samples a compute unit
+// gets no more than one block.
+int tail_rows(int M, int num_cus);
 int tail_most_samples(int num_cus);
 hipError_t launch_tail(const TailProblem &p, int num_cus, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).

@@ -109,6 +109,13 @@ hipError_t prepare_as()
 
 bool tail_fits(int T, int D) { return inter::fits_wave(T, D); }
 
+int tail_rows(int M, int num_cus)
+{
+    int rows = 8;
+    while (rows < 32 && (M + rows - 1) / rows > num_cus) rows *= 2;
+    return rows;
+}
+
 int tail_most_samples(int num_cus) { return 32 * num_cus; }
 
 hipError_t tail_prepare()
@@ -144,8 +151,7 @@ hipError_t launch_tail(const TailProblem &q, int num_cus, hipStream_t s)
     } else if (q.ldx0 % 4 != 0 || reinterpret_cast<uintptr_t>(q.x0) % 16 != 0) {
         return hipErrorInvalidValue;
     }
-    p.rows = 8;
-    while (p.rows < 32 && (p.run[1].M + p.rows - 1) / p.rows > num_cus) p.rows *= 2;
+    p.rows = tail_rows(p.run[1].M, num_cus);
     if (tail_lds_bytes(p) > TAIL_LDS) return hipErrorInvalidValue;
     switch ((p.T + 16) / 16 * 2 + p.D / 32 - 1) {
     case 2: return launch_as<1, 1>(p, num_cus, s);

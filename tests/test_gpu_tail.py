@@ -73,3 +73,27 @@ def test_tail_in_one_launch(binding, T, D, B, F, hb, ht):
     close(fused, plain, np.maximum(np.abs(exact), np.sqrt((exact ** 2).mean())))
     assert np.array_equal(fused, H.run(m, batch))
     m.close()
+
+
+@pytest.mark.parametrize("hidden,per_cu,one", [
+    ((512, 128), 1, False), ((512, 128), 12, True), ((1024, 128), 12, False), ((1024,) * 5, 12, False),
+    ((1024,) * 5, 16, False), ((1024, 1024), 17, True), ((1024,) * 5, 32, False), ((512, 128), 33, False)])
+def test_the_joint_launch_is_taken_by_weights_and_batch(binding, hidden, per_cu, one):
+    """Left to itself the library takes the one launch where it is the faster: every
+    block streams all weights, so heavy stacks stay layer by layer."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T, D, B, F, R = 40, 64, per_cu * cus, 20, 50
+    print("tail rule", hidden, B, flush=True)
+    g = np.random.default_rng(850)
+    tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(np.float16) for _ in range(T)]
+    bottom, top = stack(g, (F, 64, D)), stack(g, (D + T * (T + 1) // 2,) + hidden + (1,))
+    m = H.make_model(binding, tabs, bottom, top, B, T * B, F)
+    idx = g.integers(0, R, T * B).astype(np.int32)
+    d = [torch.from_numpy(a).cuda() for a in (g.standard_normal((B, F)).astype(np.float32), idx, np.ones(T * B, np.int32))]
+    m.set_profiling(1, 1)
+    m.forward(*d)
+    torch.cuda.synchronize()
+    assert m.check() == (binding.REC_OK, -1)
+    assert ("interact" in m.stage_shared(0)) == one
+    m.set_profiling(0)
+    m.close()
