@@ -13,6 +13,7 @@ namespace chain {
 constexpr int CH_WAVES = 8;
 constexpr int CH_THREADS = CH_WAVES * 64;
 static_assert(CHAIN_MAX_WIDTH <= 4 * 32 * CH_WAVES, "a wave takes at most four chunks of 32 output columns");
+static_assert(CHAIN_NARROW_WIDTH <= 32 * CH_WAVES, "and one in the narrow form");
 constexpr int CH_LDS_PAD = 8; // elements added to an LDS row: consecutive rows start 4 banks apart
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -331,7 +332,7 @@ __device__ inline void layer_pass(const ChainProblem &a, const RunCtx &t, int L,
 // or, with two row tiles and at most four chunks, one chunk of one tile.
 // red: [CH_WAVES][rows] floats of LDS.
 // MAXC: the most chunks a wave has in any layer, 4 (up to 1024 columns) or 1 (up to
-// 256: 128 registers instead of 174 to 236, so that two blocks share a compute
+// 256: 106 registers instead of 174 to 236, so that two blocks share a compute
 // unit and a launch of more blocks than compute units does not take a second
 // round for it: towers of 96-72, 264 blocks, 24.0 -> 19.4 us per forward).
 template <int RT, int MAXC>
@@ -395,7 +396,7 @@ constexpr size_t chain_lds_bytes(int ld) { return act_bytes<RT>(ld) + sizeof(flo
 inline bool narrow_run(const ChainProblem &a)
 {
     for (int L = 0; L < a.n_layers; ++L)
-        if (a.Npad[L] > 32 * CH_WAVES) return false;
+        if (a.Npad[L] > CHAIN_NARROW_WIDTH) return false;
     return true;
 }
 // Blocks a compute unit is to hold at a time: sets the registers a wave gets.

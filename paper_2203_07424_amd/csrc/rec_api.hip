@@ -254,6 +254,11 @@ void chain_run(const Layer *layers, int per_stack, int G, int i, int j, int num_
 // a launch (dot_after: the one-output layer follows layer n - 1).  Where blocks of
 // 64 samples fill the chip each sample asks for half of that and runs of any size
 // win (four towers of 1024-512-256, 4096 samples: 107.7 -> 102.4 us per forward).
+// Runs of narrow layers keep blocks of 32, two a compute unit, so for them it is that
+// many bytes for each launch saved (us per forward of four towers in separate launches /
+// chained; 192 KiB a launch: 256-256-256 behind a wide layer, 4096 samples 53.7 / 50.8,
+// 512-256-256-256-256-256 84.4 / 73.3; 384: 1024-256-256-256 95.0 / 94.8, 12288 samples
+// 252.1 / 255.3; 640: 1024-256-256 89.3 / 90.6, 8192 samples 159.6 / 167.7).
 // G stacks side by side, B samples; a_f32: the run starts from the dense input.
 int chain_end(const rec_model *m, const Layer *layers, int i, int n, int G, int B, bool a_f32, bool dot_after)
 {
@@ -261,11 +266,15 @@ int chain_end(const rec_model *m, const Layer *layers, int i, int n, int G, int 
     if (m->fuse_mlp == 0 || (m->pipeline && m->fuse_mlp == 1)) return i;
     int j = i;
     size_t bytes = 0;
-    while (j < n && layers[j].chain && j - i < CHAIN_MAX_LAYERS) bytes += layers[j++].chain_bytes();
+    bool narrow = true;
+    for (; j < n && layers[j].chain && j - i < CHAIN_MAX_LAYERS; ++j) {
+        bytes += layers[j].chain_bytes();
+        narrow = narrow && layers[j].Npad <= CHAIN_NARROW_WIDTH;
+    }
     if (m->fuse_mlp == 2 || j == i) return j;
     const int saved = (j - i - 1) + (dot_after && j == n && !fc_can_fuse_dot(layers[j - 1].Npad) ? 1 : 0);
     if (saved < 1) return i;
-    if (!a_f32 && chain_two_tiles(G, B, m->num_cus)) return j;
+    if (!a_f32 && chain_two_tiles(G, B, m->num_cus)) return narrow && bytes > saved * CHAIN_AUTO_BYTES ? i : j;
     return bytes > CHAIN_AUTO_BYTES ? i : j;
 }
 
@@ -434,7 +443,7 @@ bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with
     if (m->pipeline || (concat ? with_bottom || !concat_rides_on_scan(m) : !with_bottom)) return false;
     if (!concat && longest_hot_list(m, use_hot) > 0) return false;
     for (const Layer &l : m->bottom)
-        if (l.Npad > 256) return false;
+        if (l.Npad > CHAIN_NARROW_WIDTH) return false;
     return front_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows, concat);
 }
 

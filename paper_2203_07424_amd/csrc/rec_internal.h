@@ -158,6 +158,7 @@ hipError_t fc_big_prepare();
 //   dot_out[m * dot_ld + g] = sum_n X[m][n] * dot_w[g][n] + dot_bias[g][0]   in fp32.
 constexpr int CHAIN_MAX_LAYERS = 6;
 constexpr int CHAIN_MAX_WIDTH = 1024;
+constexpr int CHAIN_NARROW_WIDTH = 256;  // up to this many outputs in every layer: the narrow form, two blocks a compute unit
 constexpr int TAIL_MAX_INPUT = 2048;  // Kpad of the first Predict-FC layer in launch_tail()
 enum { CHAIN_OUT_BF16 = 0, CHAIN_OUT_F32 = 1, CHAIN_OUT_DOT = 2 };
 struct ChainProblem {

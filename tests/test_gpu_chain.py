@@ -286,6 +286,30 @@ def test_stages_that_share_a_launch_are_named(binding, name, B, fuse, pipelined,
     m.close()
 
 
+@pytest.mark.parametrize("hidden,chained", [((256, 256), False), ((256, 128), False), ((256,) * 5, True),
+                                            ((512, 256), True), ((64, 64), True)])
+def test_heavy_runs_of_narrow_layers_are_chained_where_that_saves_launches(binding, hidden, chained):
+    """1024 inputs, four towers, blocks of 64 samples for every compute unit: runs with a
+    wide layer are chained whatever their weights, narrow ones (blocks of 32) up to
+    256 KiB a launch saved."""
+    say("narrow runs", hidden)
+    g = np.random.default_rng(990)
+    T, R, D, F, nt = 15, 40, 64, 64, 4
+    B = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(np.float16) for _ in range(T)]
+    towers = [stack(g, (F + T * D,) + hidden + (1,)) for _ in range(nt)]
+    m = H.make_model(binding, tabs, [], towers, B, T * B, F, interaction="concat")
+    idx = g.integers(0, R, T * B).astype(np.int32)
+    d = [torch.from_numpy(a).cuda() for a in (g.standard_normal((B, F)).astype(np.float32), idx, np.ones(T * B, np.int32))]
+    m.set_profiling(1, 1)
+    m.forward(*d)
+    torch.cuda.synchronize()
+    assert m.check() == (binding.REC_OK, -1)
+    assert ("top_rest" in m.stage_shared(0)) == chained
+    m.set_profiling(0)
+    m.close()
+
+
 @pytest.mark.parametrize("B", [300, 1000, 1024, 1100])
 def test_short_scan_in_one_launch_with_faults(binding, B):
     """Up to 8 scan tiles with a Bottom-FC riding along: the scan is one launch
