@@ -129,11 +129,11 @@ hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a, int max_input)
     return hipSuccess;
 }
 
-bool chain_two_tiles(int groups, int M, int num_cus)
+int chain_two_tile_rounds(int groups, int M, int num_cus)
 {
-    if (num_cus <= 0) return false;
+    if (num_cus <= 0) return 0;
     const long long blocks = (long long)groups * ((M + 63) / 64), rounds = (blocks + num_cus - 1) / num_cus;
-    return 4 * blocks >= 3 * rounds * num_cus;
+    return 4 * blocks >= 3 * rounds * num_cus ? (int)rounds : 0;
 }
 
 hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s)
@@ -144,7 +144,7 @@ hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s)
     if (e != hipSuccess) return e;
     if (narrow_run(a)) return a.a_f32 ? launch_as<true, 1, 1>(a, s) : launch_as<false, 1, 1>(a, s);
     if (a.a_f32) return launch_as<true, 1, 4>(a, s);
-    return chain_two_tiles(a.groups, a.M, a.num_cus) ? launch_as<false, 2, 4>(a, s) : launch_as<false, 1, 4>(a, s);
+    return chain_two_tile_rounds(a.groups, a.M, a.num_cus) > 0 ? launch_as<false, 2, 4>(a, s) : launch_as<false, 1, 4>(a, s);
 }
 
 hipError_t launch_pack_chain(const float *W, int N, int K, int Npad, int Kpad, void *W_packed, hipStream_t s)

@@ -254,6 +254,11 @@ void chain_run(const Layer *layers, int per_stack, int G, int i, int j, int num_
 // a launch (dot_after: the one-output layer follows layer n - 1).  Where blocks of
 // 64 samples fill the chip each sample asks for half of that and runs of any size
 // win (four towers of 1024-512-256, 4096 samples: 107.7 -> 102.4 us per forward).
+// In more than one round of blocks a launch saved no longer counts, and what is left
+// is the activations that stay on chip: not enough for several towers that save one
+// launch and up to 512 columns (two rounds, separate / chained: four of 1024-512-256
+// 183.0 / 192.0, eight of 512-256 59.9 / 67.5; but eight of 1024-256 101.0 / 97.5, two
+// of 512-256 110.3 / 107.2, four of 512-512-512 141.6 / 126.9).
 // Runs of narrow layers keep blocks of 32, two a compute unit, so for them it is that
 // many bytes for each launch saved (us per forward of four towers in separate launches /
 // chained; 192 KiB a launch: 256-256-256 behind a wide layer, 4096 samples 53.7 / 50.8,
@@ -274,7 +279,10 @@ int chain_end(const rec_model *m, const Layer *layers, int i, int n, int G, int 
     if (m->fuse_mlp == 2 || j == i) return j;
     const int saved = (j - i - 1) + (dot_after && j == n && !fc_can_fuse_dot(layers[j - 1].Npad) ? 1 : 0);
     if (saved < 1) return i;
-    if (!a_f32 && chain_two_tiles(G, B, m->num_cus)) return narrow && bytes > saved * CHAIN_AUTO_BYTES ? i : j;
+    if (const int rounds = a_f32 ? 0 : chain_two_tile_rounds(G, B, m->num_cus); rounds > 0) {
+        if (narrow) return bytes > saved * CHAIN_AUTO_BYTES ? i : j;
+        if (saved > 1 || rounds == 1 || G < 4 || layers[i].Npad > 512) return j;
+    }
     return bytes > CHAIN_AUTO_BYTES ? i : j;
 }
 

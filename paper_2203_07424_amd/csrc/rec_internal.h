@@ -177,10 +177,10 @@ struct ChainProblem {
     int ld_lds, a_vec;  // filled in by chain_finalize()
 };
 bool chain_layer_fits(int Kpad, int Npad, int max_input = CHAIN_MAX_WIDTH);
-// Do blocks of 64 samples (two row tiles, one block a compute unit) fill at least
-// three quarters of the rounds they take?  (256 blocks of four 1024-512-256 towers:
+// The rounds that blocks of 64 samples (two row tiles, one block a compute unit) take,
+// 0 where they fill less than three quarters of these.  (256 blocks of four 1024-512-256 towers:
 // 107.7 -> 102.4 us per forward; 376, two rounds: 113.1 -> 117.8, so not there.)
-bool chain_two_tiles(int groups, int M, int num_cus);
+int chain_two_tile_rounds(int groups, int M, int num_cus);
 // Checks p and completes it (LDS row pitch, whether wide input loads apply) into a.
 hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a, int max_input = CHAIN_MAX_WIDTH);
 hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s);

@@ -286,16 +286,18 @@ def test_stages_that_share_a_launch_are_named(binding, name, B, fuse, pipelined,
     m.close()
 
 
-@pytest.mark.parametrize("hidden,chained", [((256, 256), False), ((256, 128), False), ((256,) * 5, True),
-                                            ((512, 256), True), ((64, 64), True)])
-def test_heavy_runs_of_narrow_layers_are_chained_where_that_saves_launches(binding, hidden, chained):
-    """1024 inputs, four towers, blocks of 64 samples for every compute unit: runs with a
-    wide layer are chained whatever their weights, narrow ones (blocks of 32) up to
-    256 KiB a launch saved."""
-    say("narrow runs", hidden)
+@pytest.mark.parametrize("hidden,rounds,chained", [
+    ((256, 256), 1, False), ((256, 128), 1, False), ((256,) * 5, 1, True), ((512, 256), 1, True), ((64, 64), 1, True),
+    ((512, 256), 2, False), ((512, 512), 2, True), ((1024, 256), 2, True), ((256,) * 5, 2, True)])
+def test_heavy_runs_are_chained_where_that_saves_launches(binding, hidden, rounds, chained):
+    """1024 inputs, four towers, blocks of 64 samples for every compute unit once or
+    twice: runs with a wide layer are chained whatever their weights (twice: if that
+    saves two launches or more than 512 columns of activations), narrow ones (blocks
+    of 32) up to 256 KiB a launch saved."""
+    say("heavy runs", hidden, rounds)
     g = np.random.default_rng(990)
     T, R, D, F, nt = 15, 40, 64, 64, 4
-    B = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    B = 16 * rounds * torch.cuda.get_device_properties(0).multi_processor_count
     tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(np.float16) for _ in range(T)]
     towers = [stack(g, (F + T * D,) + hidden + (1,)) for _ in range(nt)]
     m = H.make_model(binding, tabs, [], towers, B, T * B, F, interaction="concat")
