@@ -31,7 +31,8 @@ def stack(g, ws):
 
 @pytest.mark.parametrize("T,D,dtype,B", [(1, 32, np.float16, 1), (7, 64, np.float16, 1), (3, 32, np.float32, 3),
                                          (23, 64, np.float32, 89), (16, 64, np.float16, 128), (3, 32, np.float16, 683),
-                                         (8, 64, np.float16, 768), (5, 32, np.float32, 1229), (29, 64, np.float16, 565)])
+                                         (8, 64, np.float16, 768), (5, 32, np.float32, 1229), (29, 64, np.float16, 565),
+                                         (6, 16, np.float32, 130), (9, 128, np.float16, 75)])
 def test_front_of_pooled_models(binding, T, D, dtype, B):
     print("front case", T, D, np.dtype(dtype).name, B, flush=True)
     g = np.random.default_rng(900 + T + B)
@@ -82,7 +83,8 @@ def test_front_of_pooled_models(binding, T, D, dtype, B):
 
 @pytest.mark.parametrize("T,D,dtype,B,F", [(1, 32, np.float16, 1, 8), (3, 64, np.float16, 43, 24), (5, 32, np.float16, 77, 5),
                                            (7, 64, np.float32, 293, 20), (26, 64, np.float16, 300, 64),
-                                           (4, 32, np.float32, 3072, 16), (1, 64, np.float16, 12289, 7)])
+                                           (4, 32, np.float32, 3072, 16), (1, 64, np.float16, 12289, 7),
+                                           (6, 16, np.float32, 55, 12), (5, 128, np.float16, 31, 16)])
 def test_front_of_concatenation_models(binding, T, D, dtype, B, F):
     print("front concat case", T, D, np.dtype(dtype).name, B, F, flush=True)
     g = np.random.default_rng(930 + T + B)

@@ -4,6 +4,8 @@ Predict-FC on a fourth, four batches in flight.  Same kernels as the in-order
 pass, so the logits must be bit-equal to it, and they are held to the oracle's
 bars as well.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -303,3 +305,32 @@ def test_full_size_pipelined_other_workloads_equal_in_order(binding, name):
     pm.close()
     ref.close()
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("name", ["tiny", "rmc3", "mtwnd-tiny"])
+def test_pipelined_with_all_stacks_on_chip_equals_in_order(binding, name):
+    """REC_OPT_FUSE_MLP = 2 in a pipelined model: chains beside pooling, interaction and
+    Predict-FC as one launch on the dense stream.  Bit-equal to the in-order model
+    with the same option, batch after batch."""
+    w = synth.WORKLOADS[name].with_batch(200)
+    if w.rows > 100_000:
+        w = dataclasses.replace(w, rows=100_000)
+    say("pipeline: stacks on chip", name)
+    ref, _, _ = H.make_workload_model(binding, w)
+    pm, _, _ = H.make_workload_model(binding, w, share_tables=ref, pipeline=True)
+    for mm in (ref, pm):
+        mm.set_option(binding.REC_OPT_FUSE_MLP, 2)
+    data = [dev(synth.draw_batch(w, 60 + i)) for i in range(3)]
+    want = [ref.forward(*d).cpu().numpy() for d in data]
+    shape = (w.batch,) if w.towers == 1 else (w.batch, w.towers)
+    outs = [torch.full(shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(6)]
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        pm.forward(*data[i % 3], o)
+    pm.drain()
+    torch.cuda.synchronize()
+    assert pm.check() == (binding.REC_OK, -1) and ref.check() == (binding.REC_OK, -1)
+    for i, o in enumerate(outs):
+        assert np.array_equal(o.cpu().numpy(), want[i % 3]), i
+    pm.close()
+    ref.close()

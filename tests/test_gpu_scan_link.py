@@ -1,7 +1,9 @@
 """The scan in one launch: its blocks hand their tiles' sums to the later ones through
 words that the pooling launch behind it clears.  Offsets exact for batches of one
-to 300 tiles, call after call on one model with other batch sizes in between, with
-Bottom-FC riding along, alone, and in a graph replayed over changing lengths."""
+to 300 tiles, call after call on one model with other batch sizes in between, alone,
+with Bottom-FC riding along (in its narrow and its wide form), with a concatenation
+model's dense copy, in graphs replayed over changing lengths, and from the static
+scratch behind a call that left something else where the words are."""
 import numpy as np
 import pytest
 import torch
@@ -24,19 +26,25 @@ def layer(g, n, k):
     return [((g.standard_normal((n, k)) * k ** -0.5).astype(np.float32), np.zeros(n, np.float32))]
 
 
-def model(binding, g, interaction, T, D, R, B, F, nnz):
+def model(binding, g, kind, T, D, R, B, F, nnz):
+    """dot: one Bottom-FC layer, which is a launch of its own; ride, ride-wide: two, which
+    go into the scan's launch; concat: none, the dense copy goes there."""
     tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(np.float32) for _ in range(T)]
-    dot = interaction == "dot"
+    dot = kind != "concat"
     width = D + T * (T + 1) // 2 if dot else F + T * D
-    return H.make_model(binding, tabs, layer(g, D, F) if dot else [], layer(g, 1, width), B, nnz, F,
-                        interaction=interaction)
+    hidden = {"ride": 40, "ride-wide": 300}.get(kind)
+    bottom = (layer(g, hidden, F) + layer(g, D, hidden)) if hidden else layer(g, D, F) if dot else []
+    m = H.make_model(binding, tabs, bottom, layer(g, 1, width), B, nnz, F, interaction="dot" if dot else "concat")
+    m.bottom = bottom
+    return m
 
 
-@pytest.mark.parametrize("interaction", ["dot", "concat"])
+@pytest.mark.parametrize("interaction", ["dot", "concat", "ride", "ride-wide"])
 def test_offsets_call_after_call(binding, interaction):
     g = np.random.default_rng(960)
     T, D, R, F, most = 6, 4, 50, 5, 102_400
     m = model(binding, g, interaction, T, D, R, most, F, T * most * 3)
+    m.set_profiling(1, 1)
     for B in (102_400, 342, 683, 102_399, 1, 3000, 102_400, 50_000):   # 300, 2 (just past), 3, ..., 147 tiles
         print("linked scan", interaction, B, flush=True)
         lens = g.integers(0, 3, T * B).astype(np.int32)
@@ -45,6 +53,19 @@ def test_offsets_call_after_call(binding, interaction):
         H.run(m, synth.Batch(dense, idx, lens))
         assert m.check() == (binding.REC_OK, -1)
         assert np.array_equal(m.debug_offsets().cpu().numpy().astype(np.int64), orc.offsets(lens)[0])
+        assert ("bottom_first" in m.stage_shared(0)) == (interaction != "dot")
+        if interaction.startswith("ride"):   # the stack beside the scan, on every 997th sample
+            W1, W2 = (l[0].T.astype(np.float64) for l in m.bottom)
+            x = dense[::997].astype(np.float64)
+            # both operands of a layer are narrowed to bf16, 2^-9 of their value each, and ReLU
+            # does not widen an error: 2^-8 of the sum of absolute products a layer (and a
+            # tenth for second-order terms and the fp32 sums), the first layer's carried on
+            err = 1.1 * 2.0 ** -8 * (np.abs(x) @ np.abs(W1))
+            h = np.maximum(x @ W1, 0.0)
+            err = err @ np.abs(W2) + 1.1 * 2.0 ** -8 * ((h + err) @ np.abs(W2))
+            got = m.debug_bottom_out()[::997].cpu().numpy()
+            assert (np.abs(got - np.maximum(h @ W2, 0.0)) <= err + 1e-30).all()
+    m.set_profiling(0)
     neg = lens.copy()
     neg[[-5000, -3]] = (-7, -1)
     keep = int(np.maximum(neg, 0).sum())
@@ -54,11 +75,13 @@ def test_offsets_call_after_call(binding, interaction):
     m.close()
 
 
-def test_offsets_of_graph_replays(binding):
-    print("linked scan, graph", flush=True)
+@pytest.mark.parametrize("kind", ["concat", "ride", "pipelined"])
+def test_offsets_of_graph_replays(binding, kind):
+    print("linked scan, graph", kind, flush=True)
     g = np.random.default_rng(961)
     T, D, R, F, B, nnz = 9, 4, 50, 5, 20_000, 180_000      # 88 tiles
-    m = model(binding, g, "concat", T, D, R, B, F, nnz)
+    m = bags_model(binding, g, T, D, R, B, F, nnz, pipeline=True) if kind == "pipelined" else \
+        model(binding, g, kind, T, D, R, B, F, nnz)
     dense = torch.from_numpy(g.standard_normal((B, F)).astype(np.float32)).cuda()
     idx = torch.from_numpy(g.integers(0, R, nnz).astype(np.int32)).cuda()
 
@@ -67,6 +90,7 @@ def test_offsets_of_graph_replays(binding):
     lens = torch.from_numpy(lengths()).cuda()
     out = torch.empty(B, dtype=torch.float32, device="cuda")
     m.forward(dense, idx, lens, out)
+    m.drain()
     cap = binding.CapturedForward(m, [(dense, idx, lens)], [out])
     for _ in range(4):
         now = lengths()
@@ -74,10 +98,13 @@ def test_offsets_of_graph_replays(binding):
         cap.replay()
         torch.cuda.synchronize()
         assert m.check() == (binding.REC_OK, -1)
-        assert np.array_equal(m.debug_offsets().cpu().numpy().astype(np.int64), orc.offsets(now)[0])
+        if kind != "pipelined":                      # there the last eager call's frame is shown
+            assert np.array_equal(m.debug_offsets().cpu().numpy().astype(np.int64), orc.offsets(now)[0])
         got = out.clone()
         m.forward(dense, idx, lens, out)             # eager work between the replays
+        m.drain()
         torch.cuda.synchronize()
+        assert np.array_equal(m.debug_offsets().cpu().numpy().astype(np.int64), orc.offsets(now)[0])
         assert torch.equal(got, out)
     m.close()
 
@@ -162,3 +189,28 @@ def test_hand_over_between_blocks(binding, n):
         assert np.array_equal(out.cpu().numpy().astype(np.int64), want), polls
         left = words.cpu().numpy()
         assert np.array_equal(left[:-1], 2 * sums[:-1] + 1) and left[-1] == -12345
+
+
+def test_static_scratch_behind_another_layout(binding):
+    """Linked scans from the static array: its layout moves with model and batch, so the
+    words of one call lie where another left lengths' offsets or activations.  Logits
+    equal to the workspace path bit for bit, call after call."""
+    print("linked scan, static scratch", flush=True)
+    g = np.random.default_rng(963)
+    T, D, R, F, most = 8, 32, 50, 13, 6000
+    models = [model(binding, g, k, T, D, R, most, F, T * most * 3) for k in ("ride", "concat", "dot", "ride-wide")]
+    fault = torch.full((2,), 7, dtype=torch.int64, device="cuda")
+    for B, k in ((6000, 0), (3000, 1), (6000, 1), (2100, 0), (5000, 2), (2500, 3), (400, 2), (6000, 3), (2100, 1)):
+        m = models[k]
+        lens = g.integers(0, 3, T * B).astype(np.int32)
+        idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
+        d = [torch.from_numpy(a).cuda() for a in (g.standard_normal((B, F)).astype(np.float32), idx, lens)]
+        got = torch.full((B,), float("nan"), device="cuda")
+        m.forward_static(*d, got, fault)
+        want = m.forward(*d)
+        torch.cuda.synchronize()
+        assert fault.tolist() == [binding.REC_OK, -1] and m.check() == (binding.REC_OK, -1)
+        assert np.array_equal(m.debug_offsets().cpu().numpy().astype(np.int64), orc.offsets(lens)[0])
+        assert torch.equal(got, want), (B, k)
+    for m in models:
+        m.close()

@@ -45,6 +45,12 @@ def close(a, b, scale):
     (62, 64, 33, 16, (64,), (1024,)),             # V = 63, 2017 wide input, four chunks a wave
     (3, 32, 4097, 1500, (1100, 200), (700, 64)),  # Bottom-FC's last layers in the launch; 32 samples a block
     (4, 64, 300, 2000, (1100, 1000, 70), (96,)),
+    (20, 64, 17, 30, (96,), (200, 72)),           # V = 21
+    (31, 64, 300, 30, (), (512, 128)),            # V = 32
+    (33, 32, 33, 30, (96,), (100, 50)),           # V = 34
+    (47, 32, 2100, 30, (300,), (640, 64)),        # V = 48
+    (49, 32, 25, 30, (96,), (256, 40)),           # V = 50
+    (62, 32, 130, 30, (), (800, 300)),            # V = 63, 1985 wide input
 ])
 def test_tail_in_one_launch(binding, T, D, B, F, hb, ht):
     print("tail case", T, D, B, F, hb, ht, flush=True)
