@@ -90,6 +90,7 @@ struct rec_model {
     hipStream_t own_stream[2] = {nullptr, nullptr};
     hipEvent_t ev_scan[MAX_FRAMES] = {}, ev_bottom[MAX_FRAMES] = {}, ev_pool[MAX_FRAMES] = {}, ev_tail[MAX_FRAMES] = {};
     bool tail_pending[MAX_FRAMES] = {};  // Predict-FC of that frame's batch enqueued, not yet waited for
+    bool words_left[MAX_FRAMES] = {};    // a call failed with its scan perhaps enqueued and its pooling not: tile words to be cleared
     int next_frame = 0, last_frame = 0;
     int pool_turn = 0;                   // which pooling stream takes the next batch
 
@@ -198,6 +199,9 @@ Bufs bufs_at(char *base, const Carve &c, int frame)
     for (int i = 0; i < 3; ++i) b.act[i] = base + f.off_act[i];
     return b;
 }
+
+// Scan tiles of the largest batch.
+int most_tiles(const rec_model *m) { return (int)(((size_t)m->T * m->max_batch + SCAN_TILE - 1) / SCAN_TILE); }
 
 // Arguments of one forward.
 struct Call {
@@ -933,10 +937,10 @@ rec_status rec_bind_workspace(rec_model *m, void *dev_ptr, size_t bytes, void *s
     for (TableDesc &d : m->desc) { d.base = nullptr; d.hot_ids = nullptr; d.n_hot = 0; }
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (launch_clear_err(m->at<ErrRecord>(m->lay.off_err), s) != hipSuccess) return REC_ERR_DEVICE;
-    const int most_tiles = (int)(((size_t)m->T * m->max_batch + SCAN_TILE - 1) / SCAN_TILE);
     for (int f = 0; f < (m->pipeline ? MAX_FRAMES : 1); ++f) {
         const Bufs u = bufs_at(m->ws, m->lay, f);
-        if (launch_clear_tile_words(u.tile_words, most_tiles, s) != hipSuccess) return REC_ERR_DEVICE;
+        if (launch_clear_tile_words(u.tile_words, most_tiles(m), s) != hipSuccess) return REC_ERR_DEVICE;
+        m->words_left[f] = false;
     }
     if (hipStreamSynchronize(s) != hipSuccess) return REC_ERR_DEVICE;
     return REC_OK;
@@ -1018,6 +1022,7 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
     const bool prof = m->slots > 0 && m->forwards % m->period == 0;
     const size_t slot = prof ? (size_t)((m->forwards / m->period) % m->slots) : 0;
     hipEvent_t *ev = prof ? &m->ev[slot * EV_PER_SLOT] : nullptr;
+    const int frame = m->pipeline ? m->next_frame : 0;
     const Plan plan = plan_of(m, c, true);
 #define REC_DEV(call)                                  \
     do {                                               \
@@ -1031,7 +1036,7 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
         // pooling launches are in flight at any time, so neither the packets between
         // launches nor the ramps of a launch leave the memory system idle; a batch
         // owns one of four frames until its logits are written.
-        const int k = m->next_frame;
+        const int k = frame;
         const Bufs u = bufs_at(m->ws, m->lay, k);
         hipStream_t p = m->pool_stream[m->pool_turn] ? m->pool_stream[m->pool_turn] : m->own_stream[m->pool_turn];
         hipStream_t d = m->dense_stream ? m->dense_stream : m->side;
@@ -1039,6 +1044,8 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
             REC_DEV(hipStreamWaitEvent(s, m->ev_tail[k], 0));
             m->tail_pending[k] = false;
         }
+        if (m->words_left[k]) REC_DEV(launch_clear_tile_words(u.tile_words, most_tiles(m), s));
+        m->words_left[k] = true;
         REC_DEV(mark(ev, EV_BEGIN, s));
         REC_DEV(enqueue_scan(m, u, c, s, false));
         REC_DEV(mark(ev, EV_SCAN_END, s));
@@ -1066,6 +1073,8 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
     } else {
         const Bufs u = bufs_at(m->ws, m->lay, 0);
         m->last_frame = 0;
+        if (m->words_left[0]) REC_DEV(launch_clear_tile_words(u.tile_words, most_tiles(m), s));
+        m->words_left[0] = true;
         // S2 does not depend on S0/S1: with overlap it is enqueued on the side
         // stream, forked from and joined back into the caller's stream.
         if (m->overlap_dense && !m->bottom.empty()) {
@@ -1086,6 +1095,7 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
         if (prof) m->slot_mode[slot] = plan.ride ? 2 : 0;
     }
 #undef REC_DEV
+    m->words_left[frame] = false;
     if (prof) m->slot_shared[slot] = shared_stages(m, plan, batch);
     if (m->slots > 0) ++m->forwards;
     return REC_OK;
