@@ -34,7 +34,8 @@
  *     stream).  rec_forward() only enqueues work on that stream.
  *   - Every call returns a rec_status; nothing aborts or throws.
  *   - A model is not thread-safe; forwards of one model that overlap on the
- *     device race on its workspace.
+ *     device race on its workspace and their results are lost (later calls are
+ *     not affected).
  */
 #ifndef REC_H
 #define REC_H
@@ -144,9 +145,9 @@ REC_API size_t rec_workspace_bytes(const rec_model *m);
 /* Hands the model its workspace: dev_ptr is 256-byte aligned device memory of
  * at least rec_workspace_bytes().  Clears the device error record on `stream`
  * and waits for it; the first call also creates the library's side stream and
- * its two ordering events on the current device, and every call sets the
- * kernels' LDS limits there (so: not under stream capture).  REC_ERR_ARG if too small or
- * misaligned. */
+ * its two ordering events on the current device, and the first call on a device
+ * in a process sets the kernels' LDS limits there (so: not under stream capture).
+ * REC_ERR_ARG if too small or misaligned. */
 REC_API rec_status rec_bind_workspace(rec_model *m, void *dev_ptr, size_t bytes, void *stream);
 
 /* Registers table `table`: dev_rows is [rows[table]][emb_dim], row-major, of
@@ -204,7 +205,7 @@ REC_API rec_status rec_forward(rec_model *m, const float *dev_dense, const int32
  * rec_forward() for callers that cannot allocate device memory or hand over a
  * workspace of their own at call time: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same pass, same kernels,
- * same results, but every intermediate (offsets, tile sums, pooled vectors,
+ * same results, but every intermediate (offsets, tile words, pooled vectors,
  * activations, table descriptors, error record) lives in a static device
  * array of REC_STATIC_SCRATCH_BYTES that the library holds on each GPU it runs
  * on until the process ends, laid out for `batch` (not max_batch) samples.
@@ -257,14 +258,22 @@ enum {
      * pooled sums are the same either way. */
     REC_OPT_STREAM_ROWS = 1,
     /* Consecutive FC layers of at most 1024 (padded) inputs and outputs can run
-     * as one kernel per stack, their activations held on chip between layers.
-     * 2: always; 0: never, every layer is a kernel of its own; 1 (default):
-     * where it was measured to pay, runs that save at least one launch and
-     * whose weights total at most 256 KiB (every block of such a kernel
-     * streams all weights of its run; never in a pipelined model, where its
-     * 8-wave blocks would find no room beside the pooling launch).  Same
-     * arithmetic either way: bf16 operands, fp32 accumulation, the one-output
-     * layer in fp32; sums are taken in a different order. */
+     * as one kernel per stack (a chain), their activations held on chip between
+     * layers; a Bottom-FC that is one chain rides on the launch of the scan, and
+     * with it scan and pooling of small batches become one launch.  The
+     * interaction and Predict-FC of a model with pairwise dots and one tower
+     * (emb_dim 32 or 64, up to 63 tables, Predict-FC input up to 2048) can run as
+     * one launch too, the last narrow Bottom-FC layers in front.
+     * 2: both wherever the shapes allow; 0: neither, every layer is a kernel of
+     * its own; 1 (default): where it was measured to pay.  Every block of such a
+     * kernel streams all weights of its run, so that is: chains that save a
+     * launch and total at most 256 KiB of weights, and heavier ones where blocks of
+     * 64 samples fill the chip; the joint launch up to 32 samples a compute unit,
+     * as far as its weights are few for the launches it takes the place of.
+     * Neither in a pipelined model, where their 8-wave blocks would find no room
+     * beside the pooling launch.  Same arithmetic either way: bf16 operands, fp32
+     * accumulation, the one-output layer in fp32; sums are taken in a different
+     * order. */
     REC_OPT_FUSE_MLP = 2,
     /* 1: sparse-dense pipeline across batches (Sec. IV-A, "S-D pipeline": the
      * SparseNet of one query runs beside the DenseNet of others; Predict-FC
@@ -327,7 +336,7 @@ REC_API rec_status rec_drain(rec_model *m, void *stream);
  * are one launch the last of them holds it and the others read an empty
  * bracket (one event record): scan, Bottom-FC and pooling of a small batch
  * under REC_STAGE_POOL; interaction, Predict-FC and the last Bottom-FC layers
- * under REC_STAGE_TOP_FIRST.  With REC_OPT_PIPELINE every stage is bracketed on
+ * under REC_STAGE_TOP_FIRST (rec_stage_shared() says which).  With REC_OPT_PIPELINE every stage is bracketed on
  * the stream it runs on (a stage's time then includes whatever shared the
  * device with it). */
 REC_API rec_status rec_set_profiling(rec_model *m, int32_t slots, int32_t period);
