@@ -51,9 +51,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 matrix rate
 # of this run, and hold only for the kernel source the counters were taken with:
 # reported as null once csrc/pool.hip or csrc/pool_body.h differs.
 POOL_TRAFFIC = {
-    "sha256": "2210b2eaead4655f03d06024390b139b26de29ae506e8401fe8599e913436365",
-    ("rmc2", 4096): {"fetch_bytes": 553886384.1, "write_bytes": 41943040.0},
-    ("rmc2-uniform", 4096): {"fetch_bytes": 1721444358.1, "write_bytes": 41943040.0},
+    "sha256": "285c7f940111602c4608e88779e111ae1131e1c77cd717c2579d87a8bfd0146f",
+    ("rmc2", 4096): {"fetch_bytes": 553864462.4, "write_bytes": 41943680.0},
+    ("rmc2-uniform", 4096): {"fetch_bytes": 1721396654.3, "write_bytes": 41943680.0},
 }
 
 
