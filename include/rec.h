@@ -170,8 +170,8 @@ REC_API rec_status rec_load_tables(rec_model *m, int32_t table, const void *dev_
  * budget (about 384 rows of 128 bytes); REC_ERR_STATE without a workspace. */
 REC_API rec_status rec_load_hot_rows(rec_model *m, int32_t table, const int32_t *dev_ids, int32_t n);
 
-/* Bytes of the packed form of one layer (bf16 weights padded to the tile grid
- * followed by fp32 bias); 0 on a bad layer id. */
+/* Bytes of the packed form of one layer (bf16 weights padded to the tile grid, in
+ * rows and in matrix-operand order, and fp32 bias); 0 on a bad layer id. */
 REC_API size_t rec_mlp_packed_bytes(const rec_model *m, int32_t which, int32_t layer);
 
 /* Packs layer `layer` of stack `which` (REC_BOTTOM, or REC_TOP + tower):
@@ -269,8 +269,9 @@ enum {
      * kernel streams all weights of its run, so that is: chains that save a
      * launch and total at most 256 KiB of weights, and heavier ones where blocks of
      * 64 samples fill the chip; the joint launch up to 32 samples a compute unit,
-     * as far as its weights are few for the launches it takes the place of.
-     * Neither in a pipelined model, where their 8-wave blocks would find no room
+     * as far as its weights are few for the launches it takes the place of; short
+     * launches of single layers deal the k of a tile to the waves of a block.
+     * None of it in a pipelined model, where their 8-wave blocks would find no room
      * beside the pooling launch.  Same arithmetic either way: bf16 operands, fp32
      * accumulation, the one-output layer in fp32; sums are taken in a different
      * order. */

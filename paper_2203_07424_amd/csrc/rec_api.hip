@@ -29,11 +29,10 @@ struct Layer {
     const float *bias = nullptr;  // fp32 [Npad]
     bool dot = false;             // last Predict-FC layer: fp32 dot product, not a GEMM
     bool chain = false;           // narrow enough for the kernel that runs several layers on chip
-    bool packed = false;          // kept in MFMA fragment order too: chain layers, and a wider input of the tail kernel
-    const void *Wc = nullptr;     // the weights in that order
+    const void *Wc = nullptr;     // the weights in MFMA fragment order
     bool loaded = false;
     size_t w_bytes() const { return dot ? sizeof(float) * Kpad : 2 * (size_t)Npad * Kpad; }
-    size_t chain_bytes() const { return packed ? 2 * (size_t)Npad * Kpad : 0; }
+    size_t chain_bytes() const { return dot ? 0 : 2 * (size_t)Npad * Kpad; }
 };
 
 }  // namespace
@@ -290,6 +289,11 @@ int chain_end(const rec_model *m, const Layer *layers, int i, int n, int G, int 
     return bytes > CHAIN_AUTO_BYTES ? i : j;
 }
 
+// May a layer's launch deal the k of a tile to the waves of a block?  With the forms
+// prescribed (fuse_mlp 0 or 2) and beside pooling sums run over k in order, so that
+// a layer's result is the same bits in a pipelined model as in an in-order one.
+bool splits(const rec_model *m) { return m->fuse_mlp == 1 && !m->pipeline; }
+
 // S2: ReLU after every layer; the last one leaves fp32 for the interaction.  Of
 // the layers only the first `upto_layer`, the tail kernel taking the others
 // (their input: *rest, row stride *rest_ld).
@@ -321,6 +325,7 @@ hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipS
             p.M = c.B; p.relu = true; p.groups = 1; p.num_cus = m->num_cus; p.corun = m->pipeline;
             p.K = l.K; p.Kpad = l.Kpad; p.Npad = l.Npad;
             p.g.W[0] = l.W; p.g.bias[0] = l.bias;
+            if (splits(m)) p.frag[0] = l.Wc;
             p.C = C; p.out_f32 = last; p.ldc = ldc;
             REC_TRY(launch_fc(p, s));
         }
@@ -649,6 +654,7 @@ hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, const 
             for (int k = 0; k < G; ++k) {
                 p.g.W[k] = m->top[(size_t)k * n_top + i].W;
                 p.g.bias[k] = m->top[(size_t)k * n_top + i].bias;
+                p.frag[k] = splits(m) ? m->top[(size_t)k * n_top + i].Wc : nullptr;
             }
             p.K = l.K; p.Kpad = l.Kpad; p.Npad = l.Npad;
             const bool feeds_dot = i + 1 == n;
@@ -711,7 +717,7 @@ rec_status static_scratch(char **out)
     if (!g_scratch_ptr[dev]) {
         void *p = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return REC_ERR_DEVICE;
-        if (fc_big_prepare() != hipSuccess || chain_prepare() != hipSuccess || scan_prepare() != hipSuccess ||
+        if (fc_big_prepare() != hipSuccess || fc_split_prepare() != hipSuccess || chain_prepare() != hipSuccess || scan_prepare() != hipSuccess ||
             tail_prepare() != hipSuccess || front_prepare() != hipSuccess)
             return REC_ERR_DEVICE;
         g_scratch_ptr[dev] = static_cast<char *>(p);
@@ -856,7 +862,6 @@ rec_status rec_create(const rec_config *cfg, rec_model **out)
             v[i].K = w[i]; v[i].N = w[i + 1];
             v[i].Kpad = pad_up(w[i]); v[i].Npad = pad_up(w[i + 1]);
             v[i].chain = chain_layer_fits(v[i].Kpad, v[i].Npad);
-            v[i].packed = v[i].chain;
             if (i + 1 < n || side_by_side == 1)  // the one-output layer leaves no activation row
                 m->act_ld = std::max(m->act_ld, side_by_side * v[i].Npad);
         }
@@ -868,10 +873,7 @@ rec_status rec_create(const rec_config *cfg, rec_model **out)
         fill(&m->top[(size_t)k * cfg->n_top], cfg->top_widths, cfg->n_top, towers);
         m->top[(size_t)k * cfg->n_top + cfg->n_top - 1].dot = true;
         m->top[(size_t)k * cfg->n_top + cfg->n_top - 1].chain = false;
-        m->top[(size_t)k * cfg->n_top + cfg->n_top - 1].packed = false;
     }
-    if (tail_possible(m))
-        m->top[0].packed = true;
     m->act_row_bytes = 2 * (size_t)m->act_ld;
     if (cfg->n_top > 1)  // the layer feeding the dot leaves fp32
         m->act_row_bytes = std::max(m->act_row_bytes, sizeof(float) * towers * m->top[cfg->n_top - 2].Npad);
@@ -997,7 +999,7 @@ rec_status rec_load_mlp(rec_model *m, int32_t which, int32_t layer, const float 
     const hipError_t e = l->dot ? launch_pack_dot(dev_W, dev_b, l->K, l->Kpad, reinterpret_cast<float *>(p), bias, s)
                                 : launch_pack_fc(dev_W, dev_b, l->N, l->K, l->Npad, l->Kpad, p, bias, s);
     if (e != hipSuccess) return REC_ERR_DEVICE;
-    if (l->packed) {
+    if (!l->dot) {
         char *pc = p + align_up(l->w_bytes()) + align_up(sizeof(float) * l->Npad);
         if (launch_pack_chain(dev_W, l->N, l->K, l->Npad, l->Kpad, pc, s) != hipSuccess) return REC_ERR_DEVICE;
         l->Wc = pc;

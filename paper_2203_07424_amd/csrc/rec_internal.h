@@ -134,9 +134,19 @@ struct FcProblem {
     float *dot_out; int dot_ld;
     int num_cus;  // compute units of the device; 0 = unknown (never picks the wide-tile kernels)
     bool corun;   // the launch will share the device with a pooling launch: keep register use low
+    // Each stack's weights in the order of launch_pack_chain(), for the kernels that deal
+    // a tile's k to the waves of a block (sums in another order); null: not these.
+    const void *frag[MAX_GROUPS];
 };
 bool fc_can_fuse_dot(int Npad);
 hipError_t launch_fc(const FcProblem &p, hipStream_t s);
+
+// The same layer with the k of a tile dealt to the waves of a block, for launches
+// too short to fill the chip; launch_fc() takes this path by itself.
+bool fc_split_applies(const FcProblem &p);
+hipError_t launch_fc_split(const FcProblem &p, hipStream_t s);
+// Once per process and device, before the first launch (not under stream capture).
+hipError_t fc_split_prepare();
 
 // The same product with 256-row block tiles (bf16 input, C stored), for layers
 // wide and batches large enough that such tiles still cover the chip;
