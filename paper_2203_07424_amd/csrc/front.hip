@@ -59,9 +59,9 @@ __device__ inline long long sum_before(const int32_t *__restrict__ len, int n, l
 
 template <int LPR, bool HALF, bool STREAM>
 __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void front_kernel(
-    const int32_t *__restrict__ len, int n, long long nnz, int32_t *__restrict__ offsets, ErrRecord *err, int tiles,
-    const ChainProblem a, int chain_blocks, const TableDesc *__restrict__ tables,
-    const int32_t *__restrict__ indices, const PoolOut out, const BagTable div, int T, float one)
+    const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
+    long long nnz, int n, int tiles, int chain_blocks, int per, unsigned B, unsigned magic, int T, float one,
+    int32_t *__restrict__ offsets, ErrRecord *err, const PoolOut out, const ChainArgs<1> a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int b = blockIdx.x;
@@ -71,13 +71,14 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
     }
     b -= tiles;
     if (b < chain_blocks) {
+        chain::touch_args<72 + sizeof(out) + sizeof(a)>();
         const int share = chain::touch_share(chain_blocks);
         chain::mlp_chain_block<true, 1, 1>(a, smem, b, 0, (b >> 3) % share, share);
         return;
     }
     b -= chain_blocks;
     // XCD x takes an eighth of the table-major bag list (see pool_kernel).
-    const int per = (gridDim.x - tiles - chain_blocks) >> 3;
+    const BagTable div{B, magic};
     const int first = ((b & 7) * per + (b >> 3)) * chain::CH_WAVES;
     if (first >= n) return;
     __shared__ long long s_w[chain::CH_WAVES];
@@ -100,9 +101,9 @@ constexpr int short_block_bags() { return short_groups<LPR>() * SHORT_BAGS; }
 
 template <int LPR, bool HALF>
 __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
-    const int32_t *__restrict__ len, int n, long long nnz, int32_t *__restrict__ offsets, ErrRecord *err, int tiles,
-    const ConcatDense job, int extra, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
-    const PoolOut out, int vec_ok, const BagTable div, int T, float one)
+    const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
+    long long nnz, int n, int tiles, int extra, int per, unsigned B, unsigned magic, int T, float one, int vec_ok,
+    int32_t *__restrict__ offsets, ErrRecord *err, const PoolOut out, const ConcatDense job)
 {
     constexpr int THREADS = POOL_WAVES * 64, GROUPS = short_groups<LPR>(), BAGS = short_block_bags<LPR>();
     static_assert(THREADS == SCAN_THREADS && BAGS <= THREADS, "a thread per bag of the block");
@@ -113,11 +114,11 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
     }
     b -= tiles;
     if (b < extra) {
-        concat_dense_block(job, b, extra);
+        concat_dense_block<THREADS>(job, b, extra);
         return;
     }
     b -= extra;
-    const int per = (gridDim.x - tiles - extra) >> 3;
+    const BagTable div{B, magic};
     const int first = ((b & 7) * per + (b >> 3)) * BAGS;
     if (first >= n) return;
     __shared__ long long s_w[POOL_WAVES], s_scan[POOL_WAVES];
@@ -158,10 +159,11 @@ hipError_t launch_long(const FrontProblem &f, const ChainProblem &a, hipStream_t
 {
     const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE, chain_blocks = (a.M + 31) / 32;
     const int pool_blocks = ((n + chain::CH_WAVES - 1) / chain::CH_WAVES + 7) / 8 * 8;
+    const BagTable div = BagTable::of_batch(f.B);
     auto k = f.stream_rows ? front_kernel<LPR, HALF, true> : front_kernel<LPR, HALF, false>;
     hipLaunchKernelGGL(k, dim3(tiles + chain_blocks + pool_blocks), dim3(chain::CH_THREADS),
-                       chain::chain_lds_bytes<1>(a.ld_lds), s, f.lengths, n, f.nnz, f.offsets, f.err, tiles, a,
-                       chain_blocks, f.tables, f.indices, f.out, BagTable(f.B), f.T, 1.0f);
+                       chain::chain_lds_bytes<1>(a.ld_lds), s, f.lengths, f.tables, f.indices, f.nnz, n, tiles, chain_blocks,
+                       pool_blocks / 8, div.B, div.magic, f.T, 1.0f, f.offsets, f.err, f.out, one_stack(a));
     return hipGetLastError();
 }
 
@@ -174,10 +176,11 @@ hipError_t launch_short(const FrontProblem &f, hipStream_t s)
     const long long total = (long long)f.dense.B * (f.dense.w0 + f.dense.ldz - f.dense.width);
     const int extra = (int)std::min<long long>((total + 8 * SCAN_THREADS - 1) / (8 * SCAN_THREADS), 256);
     constexpr int BAGS = short_block_bags<LPR>();
+    const BagTable div = BagTable::of_batch(f.B);
     const int pool_blocks = ((n + BAGS - 1) / BAGS + 7) / 8 * 8;
     hipLaunchKernelGGL((front_short_kernel<LPR, HALF>), dim3(tiles + extra + pool_blocks), dim3(POOL_WAVES * 64), 0, s,
-                       f.lengths, n, f.nnz, f.offsets, f.err, tiles, f.dense, extra, f.tables, f.indices, f.out, vec_ok,
-                       BagTable(f.B), f.T, 1.0f);
+                       f.lengths, f.tables, f.indices, f.nnz, n, tiles, extra, pool_blocks / 8, div.B, div.magic, f.T, 1.0f,
+                       vec_ok, f.offsets, f.err, f.out, f.dense);
     return hipGetLastError();
 }
 

@@ -91,13 +91,10 @@ __device__ inline void load_a_chunk(AChunk<false> &c, const void *A, long long r
 // held to 128 registers, the part of a SIMD's register file that eight pooling
 // waves leave free, so that a wave of theirs needs nothing but a wave slot.
 template <int BM, int BN, int WAVES_M, int P, bool A_F32, bool OUT_F32, bool FUSE_DOT>
-__global__ __launch_bounds__(FC_THREADS, ((P == 2 && BM * BN <= 4096) || P == 1) ? 4 : 1) void fc_kernel(const void *__restrict__ A0, int lda,
-                                                        long long a_stride, int M, int K, int Kpad,
-                                                        const FcGroups groups, int relu,
-                                                        void *__restrict__ C0, int ldc,
-                                                        long long c_stride, int vec_ok,
-                                                        float *__restrict__ dot_out, int dot_ld,
-                                                        int grid_n, int tiles_per_group)
+__global__ __launch_bounds__(FC_THREADS, ((P == 2 && BM * BN <= 4096) || P == 1) ? 4 : 1) void fc_kernel(
+    const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_n,
+    int tiles_per_group, int per_xcd, int vec_ok, long long a_stride, int relu, void *__restrict__ C0, int ldc,
+    long long c_stride, float *__restrict__ dot_out, int dot_ld, const FcGroups groups)
 {
     constexpr int WAVES_N = 4 / WAVES_M;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // per-wave tile
@@ -115,14 +112,14 @@ __global__ __launch_bounds__(FC_THREADS, ((P == 2 && BM * BN <= 4096) || P == 1)
     // that share a slab of activations then share an L2 and the slab comes from
     // HBM once instead of once per XCD.
     int v = blockIdx.x;
-    if ((gridDim.x & 7) == 0) v = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (per_xcd > 0) v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     const int grp = v / tiles_per_group;
     v -= grp * tiles_per_group;
     const int bm = v / grid_n, bn = v - bm * grid_n;
     const int m0 = bm * BM, n0 = bn * BN;
     const void *A = static_cast<const char *>(A0) + grp * a_stride * (A_F32 ? 4 : 2);
     void *C = static_cast<char *>(C0) + grp * c_stride * (OUT_F32 ? 4 : 2);
-    const __bf16 *__restrict__ W = static_cast<const __bf16 *>(groups.W[grp]);
+    const __bf16 *__restrict__ W = static_cast<const __bf16 *>(grp == 0 ? W0 : groups.W[grp]);
     const float *__restrict__ bias = groups.bias[grp];
     const float *__restrict__ dot_w = groups.dot_w[grp];
     const float *__restrict__ dot_bias = groups.dot_bias[grp];
@@ -264,11 +261,11 @@ hipError_t launch_tile(const FcProblem &a, hipStream_t s)
     // 16-byte loads of fp32 rows need lda and the stack stride % 4 == 0 and an aligned base.
     const int vec_ok = a.a_f32 && (a.lda % 4 == 0) && (a.a_stride % 4 == 0) &&
                        (reinterpret_cast<uintptr_t>(a.A) % 16 == 0);
-    const int r = a.relu ? 1 : 0;
+    const int r = a.relu ? 1 : 0, per_xcd = grid.x % 8 == 0 ? grid.x / 8 : 0;
 #define REC_FC_LAUNCH(AF, OF, FD)                                                                  \
-    hipLaunchKernelGGL((fc_kernel<BM, BN, WAVES_M, P, AF, OF, FD>), grid, block, 0, s, a.A, a.lda, \
-                       a.a_stride, a.M, a.K, a.Kpad, a.g, r, a.C, a.ldc, a.c_stride, vec_ok,       \
-                       a.dot_out, a.dot_ld, grid_n, tiles)
+    hipLaunchKernelGGL((fc_kernel<BM, BN, WAVES_M, P, AF, OF, FD>), grid, block, 0, s, a.A, a.g.W[0], \
+                       a.lda, a.M, a.K, a.Kpad, grid_n, tiles, per_xcd, vec_ok, a.a_stride, r, a.C, a.ldc,   \
+                       a.c_stride, a.dot_out, a.dot_ld, a.g)
     if (a.dot_out) {
         if (a.a_f32) REC_FC_LAUNCH(true, false, true);
         else REC_FC_LAUNCH(false, false, true);

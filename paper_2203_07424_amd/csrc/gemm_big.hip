@@ -67,9 +67,9 @@ struct AReg<true> {
 // k >= K are fetched from the row's last valid chunk and zeroed.
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_F32, bool OUT_F32>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
-    const void *__restrict__ A0, int lda, long long a_stride, int M, int K, int Kpad,
-    const FcGroups groups, int relu, void *__restrict__ C0, int ldc, long long c_stride, int grid_m,
-    int grid_n, int tiles_per_group)
+    const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
+    int tiles_per_group, int per_xcd, long long a_stride, int relu, void *__restrict__ C0, int ldc, long long c_stride,
+    const FcGroups groups)
 {
     constexpr int THREADS = 64 * WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // per-wave tile
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
     // tiles resident on one XCD form a compact patch that shares its slabs of A
     // and W in that XCD's L2.
     int v = blockIdx.x;
-    if ((gridDim.x & 7) == 0) v = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (per_xcd > 0) v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     const int grp = v / tiles_per_group;
     v -= grp * tiles_per_group;
     int bm, bn;
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
     const int m0 = bm * BM, n0 = bn * BN;
     constexpr int A_ELT = A_F32 ? 4 : 2;
     const char *__restrict__ A = static_cast<const char *>(A0) + grp * a_stride * A_ELT;
-    const __bf16 *__restrict__ W = static_cast<const __bf16 *>(groups.W[grp]);
+    const __bf16 *__restrict__ W = static_cast<const __bf16 *>(grp == 0 ? W0 : groups.W[grp]);
     const float *__restrict__ bias = groups.bias[grp];
 
     const int ld_row = tid >> 3, ld_chunk = tid & 7;
@@ -260,8 +260,8 @@ hipError_t launch_big_as(const FcProblem &a, hipStream_t s)
     const dim3 grid(tiles * a.groups), block(64 * WAVES_M * WAVES_N);
     constexpr size_t lds = big_lds_bytes<BM, BN>();
     auto k = fc_big_kernel<BM, BN, WAVES_M, WAVES_N, A_F32, OUT_F32>;
-    hipLaunchKernelGGL(k, grid, block, lds, s, a.A, a.lda, a.a_stride, a.M, a.K, a.Kpad, a.g,
-                       a.relu ? 1 : 0, a.C, a.ldc, a.c_stride, grid_m, grid_n, tiles);
+    hipLaunchKernelGGL(k, grid, block, lds, s, a.A, a.g.W[0], a.lda, a.M, a.K, a.Kpad, grid_m, grid_n, tiles,
+                       (int)(grid.x % 8 == 0 ? grid.x / 8 : 0), a.a_stride, a.relu ? 1 : 0, a.C, a.ldc, a.c_stride, a.g);
     return hipGetLastError();
 }
 

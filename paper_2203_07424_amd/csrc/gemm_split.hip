@@ -41,6 +41,8 @@ struct SplitStack {
     const void *W;  // fragment order
     const float *bias, *dot_w, *dot_bias;
 };
+// Of the arguments the leading scalars, up to 14 words, are in registers when a wave
+// starts; the rest is a trip to cold memory that loads need not wait for.
 struct SplitGroups {
     SplitStack s[MAX_GROUPS];
 };
@@ -101,9 +103,9 @@ constexpr size_t split_lds_bytes()
 // CHAIN_OUT_* value; CHAIN_OUT_DOT needs all columns of the layer in the block.
 template <int TM, int TN, int WN, int WK, int IN, int OUT>
 __global__ __launch_bounds__(64 * WN * WK, TM * TN >= 16 || (IN != IN_BF16 && TM * TN >= 8) ? 2 : 4) void fc_split_kernel(
-    const void *__restrict__ A0, const SplitStack first, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
-    int m_fast, int relu, long long a_stride, void *__restrict__ C0, int ldc, long long c_stride,
-    float *__restrict__ dot_out, int dot_ld, int n_groups, const SplitGroups groups)
+    const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
+    int m_fast, int per_xcd, int n_groups, int relu, long long a_stride, void *__restrict__ C0, int ldc,
+    long long c_stride, float *__restrict__ dot_out, int dot_ld, const SplitGroups groups)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int THREADS = 64 * WN * WK, BM = 16 * TM, BN = 16 * TN * WN;
@@ -114,13 +116,11 @@ __global__ __launch_bounds__(64 * WN * WK, TM * TN >= 16 || (IN != IN_BF16 && TM
     // Blocks are dealt to the 8 XCDs round-robin: XCD x takes the x-th eighth of the
     // tile list, rows or columns fastest, whichever operand is then read by few L2s.
     const int per_group = grid_m * grid_n;
-    int v = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     const int g = v / per_group;
-    if (g >= n_groups) return;  // the grid is a multiple of 8 blocks
+    if (g >= n_groups) return;  // the grid is 8 per_xcd blocks
     v -= g * per_group;
     const int bm = m_fast ? v % grid_m : v / grid_n, bn = m_fast ? v / grid_m : v - bm * grid_n;
-    SplitStack st = first;
-    if (g > 0) st = groups.s[g];
     const int m0 = bm * BM, n0 = bn * BN;
     constexpr int ELT = IN == IN_BF16 ? 2 : 4;
     typedef RowUnit<TM, IN> Rows;
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64 * WN * WK, TM * TN >= 16 || (IN != IN_BF16 && TM
         row[i] = (unsigned)min(lane / Rows::LANES + i * (64 / Rows::LANES), M - 1 - m0) * (unsigned)lda * ELT;
     // Fragment (nc, ks) of 32 columns x 16 k is the KiB at (nc * Kpad / 16 + ks) * 1024:
     // 16 bytes for the lower 8 k of each column, then for the upper 8.
-    const char *W = static_cast<const char *>(st.W);
+    const char *W = static_cast<const char *>(g == 0 ? W0 : groups.s[g].W);
     unsigned wofs[TN];
 #pragma unroll
     for (int t = 0; t < TN; ++t) {
@@ -141,13 +141,14 @@ __global__ __launch_bounds__(64 * WN * WK, TM * TN >= 16 || (IN != IN_BF16 && TM
     }
     // Quad i: lane i % 64 of tile (wn, row tile, column tile) = i / 64, the last fastest.
     const auto quad_n = [&](int i) { return n0 + i / (64 * TM * TN) * 16 * TN + i / 64 % TN * 16 + 4 * (lane >> 4); };
+    const float *bias = groups.s[g].bias, *dot_w = groups.s[g].dot_w;
     f32x4 bv[MINE], dw[MINE];
 #pragma unroll
     for (int j = 0; j < MINE; ++j) {
         const int i = tid + j * THREADS;
         if (i < QUADS) {
-            bv[j] = *reinterpret_cast<const f32x4 *>(st.bias + quad_n(i));
-            if (OUT == CHAIN_OUT_DOT) dw[j] = *reinterpret_cast<const f32x4 *>(st.dot_w + quad_n(i));
+            bv[j] = *reinterpret_cast<const f32x4 *>(bias + quad_n(i));
+            if (OUT == CHAIN_OUT_DOT) dw[j] = *reinterpret_cast<const f32x4 *>(dot_w + quad_n(i));
         }
     }
 
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(64 * WN * WK, TM * TN >= 16 || (IN != IN_BF16 && TM
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     x += parts[((t / TN * TM + tid / 16) * TN + t % TN) * 64 + q * 16 + tid % 16];
-            dot_out[(long long)(m0 + tid) * dot_ld + g] = x + st.dot_bias[0];
+            dot_out[(long long)(m0 + tid) * dot_ld + g] = x + groups.s[g].dot_bias[0];
         }
     }
 }
@@ -247,10 +248,11 @@ hipError_t launch_as(const FcProblem &a, hipStream_t s)
     SplitGroups g{};
     for (int i = 0; i < a.groups; ++i) g.s[i] = SplitStack{a.frag[i], a.g.bias[i], a.g.dot_w[i], a.g.dot_bias[i]};
     const int m_fast = (long long)a.M * (IN == IN_BF16 ? 1 : 2) < a.Npad;
-    hipLaunchKernelGGL((fc_split_kernel<TM, TN, WN, WK, IN, OUT>), dim3((grid_m * grid_n * a.groups + 7) / 8 * 8),
-                       dim3(64 * WN * WK), (split_lds_bytes<TM, TN, WN, WK>()), s, a.A, g.s[0], a.lda, a.M, a.K, a.Kpad,
-                       grid_m, grid_n, m_fast, a.relu ? 1 : 0, a.a_stride, a.C, a.ldc, a.c_stride, a.dot_out, a.dot_ld,
-                       a.groups, g);
+    const int per_xcd = (grid_m * grid_n * a.groups + 7) / 8;
+    hipLaunchKernelGGL((fc_split_kernel<TM, TN, WN, WK, IN, OUT>), dim3(8 * per_xcd), dim3(64 * WN * WK),
+                       (split_lds_bytes<TM, TN, WN, WK>()), s, a.A, a.frag[0], a.lda, a.M, a.K, a.Kpad, grid_m, grid_n,
+                       m_fast, per_xcd, a.groups, a.relu ? 1 : 0, a.a_stride, a.C, a.ldc, a.c_stride, a.dot_out,
+                       a.dot_ld, g);
     return hipGetLastError();
 }
 

@@ -37,16 +37,17 @@ namespace {
 using namespace chain;
 
 template <bool A_F32, int RT, int MAXC>
-__global__ __launch_bounds__(CH_THREADS, waves_per_simd<MAXC>()) void mlp_chain_kernel(const ChainProblem a, int per_group)
+__global__ __launch_bounds__(CH_THREADS, waves_per_simd<MAXC>()) void mlp_chain_kernel(int blocks, int per_group, const ChainProblem a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    touch_args<8 + sizeof(a)>();
     // Blocks run over the samples of stack 0, then stack 1, ...; XCD x (blocks are
     // dealt round-robin) takes the x-th eighth of that list, so that its L2 holds
     // the weights of one stack or two instead of all of them.
-    const bool eighths = (gridDim.x & 7) == 0;
-    const int v = eighths ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const bool eighths = (blocks & 7) == 0;
+    const int v = eighths ? (blockIdx.x & 7) * (blocks >> 3) + (blockIdx.x >> 3) : blockIdx.x;
     const int g = v / per_group, bx = v - g * per_group;
-    const int share = eighths ? min(32, min(per_group, (int)gridDim.x >> 3)) : touch_share(per_group);
+    const int share = eighths ? min(32, min(per_group, blocks >> 3)) : touch_share(per_group);
     mlp_chain_block<A_F32, RT, MAXC>(a, smem, bx, g, (eighths ? bx : bx >> 3) % share, share);
 }
 
@@ -86,7 +87,7 @@ hipError_t launch_as(const ChainProblem &a, hipStream_t s)
 {
     const int per_group = (a.M + rows_of<RT>() - 1) / rows_of<RT>();
     hipLaunchKernelGGL((mlp_chain_kernel<A_F32, RT, MAXC>), dim3(per_group * a.groups), dim3(CH_THREADS),
-                       (chain_lds_bytes<RT>(a.ld_lds)), s, a, per_group);
+                       (chain_lds_bytes<RT>(a.ld_lds)), s, per_group * a.groups, per_group, a);
     return hipGetLastError();
 }
 

@@ -67,8 +67,8 @@ struct InVec<false> {
 // Input rows -> LDS as bf16, zero for rows >= M and columns >= K.  Each of the
 // `rows` (a power of two) has CH_THREADS / rows threads of its own; up to BATCH
 // loads of a thread are in flight.
-template <bool A_F32, int BATCH>
-__device__ inline void stage_input(const ChainProblem &a, int g, int row0, int rows, __bf16 *dst, int ld)
+template <bool A_F32, int BATCH, class Run>
+__device__ inline void stage_input(const Run &a, int g, int row0, int rows, __bf16 *dst, int ld)
 {
     typedef typename std::conditional<A_F32, float, __bf16>::type elem;
     const int TPR = CH_THREADS / rows;
@@ -129,6 +129,7 @@ struct WeightStream {
     {
         return *reinterpret_cast<const u32x4 *>(w + (c * wstep + (unsigned)k * 1024u) + lane16);
     }
+    WeightStream() = default;
     __device__ inline WeightStream(const char *w_, unsigned wstep_, int KS_) : w(w_), wstep(wstep_), KS(KS_)
     {
         lane16 = (threadIdx.x & 63) * 16;
@@ -216,7 +217,8 @@ struct Touched {
     }
 };
 // Slice `mine` of `share` of the run's weights.
-__device__ inline Touched touch_weights(const ChainProblem &a, int g, int mine, int share)
+template <class Run>
+__device__ inline Touched touch_weights(const Run &a, int g, int mine, int share)
 {
     int total = 0;
     for (int L = 0; L < a.n_layers; ++L) total += a.Kpad[L] * a.Npad[L] / 64;  // bf16: 64 elements per line
@@ -226,7 +228,7 @@ __device__ inline Touched touch_weights(const ChainProblem &a, int g, int mine, 
     for (int u = 0; u < TOUCH; ++u) t.v[u] = 0;
     int base = 0;
     for (int L = 0; L < a.n_layers; ++L) {
-        const unsigned *w = static_cast<const unsigned *>(a.W[L][g]);
+        const unsigned *w = static_cast<const unsigned *>(a.W[g][L]);
         const int lines = a.Kpad[L] * a.Npad[L] / 64;
 #pragma unroll
         for (int u = 0; u < TOUCH; ++u) {
@@ -241,6 +243,22 @@ __device__ inline Touched touch_weights(const ChainProblem &a, int g, int mine, 
 // share an XCD's touching; beyond 32 a slice is down to a few lines a wave.
 __device__ inline int touch_share(int n) { return min(32, max(1, n >> 3)); }
 
+// A launch's arguments are cold memory to every compute unit, and the layers of a run
+// read them line by line, each a trip in front of a layer: all lines of the kernel's
+// BYTES of arguments at once, first (8 tables x 150 samples, launches of three and two
+// layers: 16.0 -> 14.4 us).
+template <int BYTES>
+__device__ inline void touch_args()
+{
+    typedef const __attribute__((address_space(4))) unsigned *arg_ptr;
+    const arg_ptr args = (arg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    unsigned v[(BYTES + 63) / 64];
+#pragma unroll
+    for (int i = 0; i < (BYTES + 63) / 64; ++i) v[i] = args[i * 16];
+#pragma unroll
+    for (int i = 0; i < (BYTES + 63) / 64; ++i) asm volatile("" ::"s"(v[i]));
+}
+
 // What the layers of a run share.
 struct RunCtx {
     __bf16 *X;     // activations, bf16 [rows][ld]
@@ -250,12 +268,34 @@ struct RunCtx {
     int last_row;  // rows - 1: lanes past it work on copies and leave nothing behind
 };
 
+__device__ inline bf16x4 narrowed(const f32x4 &v)
+{
+    bf16x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
+    return o;
+}
+
+// Columns n .. n + 3 of the run's last activations of row `row`, to where they go.
+template <class Run>
+__device__ inline void store_last(const Run &a, const RunCtx &t, int row, int n, const f32x4 &v)
+{
+    if ((row & 31) > t.last_row) return;
+    if (t.x0s && n < t.x0_ld) *reinterpret_cast<f32x4 *>(t.x0s + row * t.x0_ld + n) = v;
+    if (t.row0 + row >= a.M) return;
+    const long long at = (long long)(t.row0 + row) * a.ldc + (long long)t.g * a.c_stride + n;
+    if (a.out_mode == CHAIN_OUT_F32)
+        *reinterpret_cast<f32x4 *>(static_cast<float *>(a.C) + at) = v;
+    else
+        *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.C) + at) = narrowed(v);
+}
+
 // One layer for a wave that has CNT chunks (first, first + 8, ...) of row tiles
 // tile .. tile + RT - 1: product, the block's barrier if the output goes back to
 // X, epilogue.  Adds the wave's part of the one-output layer behind the run to
 // dot_part.
-template <int CNT, int RT>
-__device__ inline void layer_pass(const ChainProblem &a, const RunCtx &t, int L, int first, int tile, float (&dot_part)[RT])
+template <int CNT, int RT, class Run>
+__device__ inline void layer_pass(const Run &a, const RunCtx &t, int L, int first, int tile, float (&dot_part)[RT])
 {
     int lane = threadIdx.x & 63;
     asm volatile("" : "+v"(lane));  // else every address below is kept in registers across all layers
@@ -267,7 +307,7 @@ __device__ inline void layer_pass(const ChainProblem &a, const RunCtx &t, int L,
     f32x16 acc[CNT][RT];
     f32x4 bv[CNT][4];
     const auto load_bias = [&]() {
-        const float *bias = a.bias[L][t.g] + first * 32 + 4 * half;
+        const float *bias = a.bias[t.g][L] + first * 32 + 4 * half;
 #pragma unroll
         for (int c = 0; c < CNT; ++c)
 #pragma unroll
@@ -281,7 +321,7 @@ __device__ inline void layer_pass(const ChainProblem &a, const RunCtx &t, int L,
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[c][j][r] = 0.0f;
     // fragment (nc, ks) is the KiB at W + (nc * KS + ks) * 1024
-    WeightStream<CNT> ws(static_cast<const char *>(a.W[L][t.g]) + (size_t)first * KS * 1024,
+    WeightStream<CNT> ws(static_cast<const char *>(a.W[t.g][L]) + (size_t)first * KS * 1024,
                          (unsigned)(CH_WAVES * KS * 1024), KS);
     chunk_product<CNT, RT>(ws, t.X + (tile * 32 + (m & t.last_row)) * t.ld + half * 8, 32 * t.ld, KS, acc);
     if (CNT > 2) load_bias();
@@ -301,27 +341,95 @@ __device__ inline void layer_pass(const ChainProblem &a, const RunCtx &t, int L,
                     const float s = acc[c][j][4 * q + e] + bv[c][q][e];
                     v[e] = relu && s < 0.0f ? 0.0f : s;
                 }
-                bf16x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
                 if (!last) {
-                    if (m <= t.last_row) *reinterpret_cast<bf16x4 *>(t.X + row * t.ld + n) = o;
+                    if (m <= t.last_row) *reinterpret_cast<bf16x4 *>(t.X + row * t.ld + n) = narrowed(v);
                 } else if (a.out_mode == CHAIN_OUT_DOT) {
                     const f32x4 wq = *reinterpret_cast<const f32x4 *>(a.dot_w[t.g] + n);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) dot_part[j] += v[e] * wq[e];
-                } else if (m <= t.last_row) {
-                    if (t.x0s && n < t.x0_ld) *reinterpret_cast<f32x4 *>(t.x0s + row * t.x0_ld + n) = v;
-                    if (t.row0 + row < a.M) {
-                        const long long at = (long long)(t.row0 + row) * a.ldc + (long long)t.g * a.c_stride + n;
-                        if (a.out_mode == CHAIN_OUT_F32)
-                            *reinterpret_cast<f32x4 *>(static_cast<float *>(a.C) + at) = v;
-                        else
-                            *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.C) + at) = o;
-                    }
+                } else {
+                    store_last(a, t, row, n, v);
                 }
             }
         }
+    }
+}
+
+// The first weights of a layer, requested before its input is complete.
+// Narrow runs only: a wave has one chunk of 32 columns or none.
+template <int MAXC>
+struct Ahead {
+    template <class Run>
+    __device__ inline void request(const Run &, int, int) {}
+};
+template <>
+struct Ahead<1> {
+    WeightStream<1> ws;
+    f32x4 bias[4];
+    template <class Run>
+    __device__ inline void request(const Run &a, int g, int L)
+    {
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), KS = a.Kpad[L] / 16;
+        if (wave >= a.Npad[L] / 32) return;
+        ws = WeightStream<1>(static_cast<const char *>(a.W[g][L]) + (size_t)wave * KS * 1024, 0, KS);
+        const float *b = a.bias[g][L] + wave * 32 + 4 * ((threadIdx.x & 63) >> 5);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bias[i] = *reinterpret_cast<const f32x4 *>(b + 8 * i);
+    }
+};
+
+// The layers of a narrow run.  A layer is a trip to L2 for its weights and little
+// else, so the next one's are requested as soon as this one's products have let go of
+// the registers, in front of the two barriers and the epilogue.
+template <class Run>
+__device__ inline void narrow_layers(const Run &a, const RunCtx &t, Ahead<1> &ahead, float &dot_part)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    for (int L = 0; L < a.n_layers; ++L) {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));  // else every address below is kept in registers across all layers
+        const int m = lane & 31, half = lane >> 5;
+        const bool last = L + 1 == a.n_layers, has = wave < a.Npad[L] / 32, dot = last && a.out_mode == CHAIN_OUT_DOT;
+        const int n0 = wave * 32 + 4 * half;
+        f32x16 acc[1][1];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.0f;
+        f32x4 bv[4], dw[4];
+        if (has) {
+            if (dot) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) dw[q] = *reinterpret_cast<const f32x4 *>(a.dot_w[t.g] + n0 + 8 * q);
+            }
+            chunk_product<1, 1>(ahead.ws, t.X + (m & t.last_row) * t.ld + half * 8, 0, a.Kpad[L] / 16, acc);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bv[q] = ahead.bias[q];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (!last) {
+            ahead.request(a, t.g, L + 1);
+            __syncthreads();  // every wave has read the input: the output may replace it
+        }
+        if (has) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = n0 + 8 * q;
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float s = acc[0][0][4 * q + e] + bv[q][e];
+                    v[e] = a.relu[L] != 0 && s < 0.0f ? 0.0f : s;
+                }
+                if (dot) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dot_part += v[e] * dw[q][e];
+                } else if (last) {
+                    store_last(a, t, m, n, v);
+                } else if (m <= t.last_row) {
+                    *reinterpret_cast<bf16x4 *>(t.X + m * t.ld + n) = narrowed(v);
+                }
+            }
+        }
+        if (!last) __syncthreads();
     }
 }
 
@@ -335,8 +443,9 @@ __device__ inline void layer_pass(const ChainProblem &a, const RunCtx &t, int L,
 // 256: 106 registers instead of 174 to 236, so that two blocks share a compute
 // unit and a launch of more blocks than compute units does not take a second
 // round for it: towers of 96-72, 264 blocks, 24.0 -> 19.4 us per forward).
-template <int RT, int MAXC>
-__device__ inline void run_layers(const ChainProblem &a, const RunCtx &t, float *red)
+// `ahead` holds the first layer's request.
+template <int RT, int MAXC, class Run>
+__device__ inline void run_layers(const Run &a, const RunCtx &t, Ahead<MAXC> &ahead, float *red)
 {
     constexpr int R = rows_of<RT>();
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -345,7 +454,11 @@ __device__ inline void run_layers(const ChainProblem &a, const RunCtx &t, float 
     for (int j = 0; j < RT; ++j) dot_part[j] = 0.0f;
     int tile = 0;
     bool split = false;  // row tiles dealt to the waves too: a wave's sums belong to row tile `tile`
-    for (int L = 0; L < a.n_layers; ++L) {
+    if constexpr (MAXC == 1) {
+        static_assert(RT == 1, "narrow runs are on one row tile");
+        narrow_layers(a, t, ahead, dot_part[0]);
+    }
+    for (int L = 0; MAXC > 1 && L < a.n_layers; ++L) {
         const int NC = a.Npad[L] / 32;
         split = RT == 2 && NC <= CH_WAVES / 2;
         const int first = split ? wave & (CH_WAVES / 2 - 1) : wave;
@@ -359,13 +472,12 @@ __device__ inline void run_layers(const ChainProblem &a, const RunCtx &t, float 
             dot_part[0] = part[0];
         } else if (cnt == 1) {
             layer_pass<1, RT>(a, t, L, first, 0, dot_part);
-        } else if constexpr (MAXC > 1) {
-            if (cnt == 2)
-                layer_pass<2, RT>(a, t, L, first, 0, dot_part);
-            else if (cnt == 3)
-                layer_pass<3, RT>(a, t, L, first, 0, dot_part);
-            else
-                layer_pass<4, RT>(a, t, L, first, 0, dot_part);
+        } else if (cnt == 2) {
+            layer_pass<2, RT>(a, t, L, first, 0, dot_part);
+        } else if (cnt == 3) {
+            layer_pass<3, RT>(a, t, L, first, 0, dot_part);
+        } else {
+            layer_pass<4, RT>(a, t, L, first, 0, dot_part);
         }
         if (L + 1 < a.n_layers) __syncthreads();
     }
@@ -406,17 +518,19 @@ constexpr int waves_per_simd() { return MAXC == 1 ? 4 : 2; }
 // One block's share of the run: samples bx * rows ... of stack g.  The block is
 // number `mine` of the `share` that run this stack on one XCD.  `smem` is
 // chain_lds_bytes<RT>(a.ld_lds) of dynamic LDS; all CH_THREADS threads take part.
-template <bool A_F32, int RT, int MAXC>
-__device__ inline void mlp_chain_block(const ChainProblem &a, unsigned char *smem, int bx, int g, int mine, int share)
+template <bool A_F32, int RT, int MAXC, class Run>
+__device__ inline void mlp_chain_block(const Run &a, unsigned char *smem, int bx, int g, int mine, int share)
 {
     __bf16 *X = reinterpret_cast<__bf16 *>(smem);
     float *red = reinterpret_cast<float *>(smem + act_bytes<RT>(a.ld_lds));
     const RunCtx t{X, nullptr, a.ld_lds, 0, g, bx * rows_of<RT>(), 31};
     const Touched touched = touch_weights(a, g, mine, share);
+    Ahead<MAXC> ahead;
+    ahead.request(a, g, 0);
     stage_input<A_F32, RT == 2 ? 16 : 8>(a, g, t.row0, rows_of<RT>(), X, a.ld_lds);
     touched.done();
     __syncthreads();
-    run_layers<RT, MAXC>(a, t, red);
+    run_layers<RT, MAXC>(a, t, ahead, red);
 }
 
 }  // namespace chain

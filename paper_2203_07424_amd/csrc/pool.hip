@@ -41,16 +41,20 @@ namespace {
 
 using namespace pool;
 
+// Arguments: a wave starts with the leading 14 words of them in registers, as far as they
+// are scalars; the rest, and the launch's own sizes (gridDim), are a trip to cold memory.
+// So what stands between a wave and its first loads comes first, structs last.
+
 template <int LPR, bool HALF, bool CONCAT, bool STREAM, bool NARROW>
 __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
-    const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, const BagTable div, int T, int nbags,
-    float one, ErrRecord *err, const TileWords left)
+    const int32_t *__restrict__ offsets, int per, int nbags, unsigned B, unsigned magic, int T, float one,
+    int vec_ok, ErrRecord *err, const PoolOut out, const TileWords left)
 {
     // Blocks are handed to the 8 XCDs round-robin; give XCD x the x-th eighth
     // of the (table-major) bag list so that each L2 sees few tables at a time.
-    // The grid is a multiple of 8 blocks; surplus blocks fall past nbags.
-    const int per = gridDim.x >> 3;
+    // The grid is 8 per blocks; surplus blocks fall past nbags.
+    const BagTable div{B, magic};
     const int vblk = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     int bag = vblk * POOL_WAVES + (threadIdx.x >> 6);
     if (bag >= nbags) return;
@@ -66,11 +70,11 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
 template <int LPR, bool HALF, bool CONCAT>
 __global__ __launch_bounds__(POOL_WAVES * 64) void pool_short_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
-    const int32_t *__restrict__ offsets, const PoolOut out, int vec_ok, const BagTable div, int T, int nbags,
-    int groups, float one, ErrRecord *err, const TileWords left)
+    const int32_t *__restrict__ offsets, int per, int nbags, unsigned B, unsigned magic, int T, float one,
+    int groups, int vec_ok, ErrRecord *err, const PoolOut out, const TileWords left)
 {
     constexpr int RPW = 64 / LPR;
-    const int per = gridDim.x >> 3;
+    const BagTable div{B, magic};
     const int vblk = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     const long long group = ((long long)vblk * POOL_WAVES + (threadIdx.x >> 6)) * RPW + (threadIdx.x & 63) / LPR;
     bool live[SHORT_BAGS];
@@ -95,18 +99,19 @@ hipError_t launch_shape(bool short_bags, bool stream_rows, bool narrow, const Ta
     const int nbags = T * B;
     const int vec_ok = CONCAT && out.col0 % NACC == 0 && reinterpret_cast<uintptr_t>(out.z) % 16 == 0;
     const dim3 block(POOL_WAVES * 64);
+    const BagTable div = BagTable::of_batch(B);
     if (short_bags) {
         const int groups_per_block = POOL_WAVES * (64 / LPR);
         const int per_block = groups_per_block * SHORT_BAGS;
         const dim3 grid(((nbags + per_block - 1) / per_block + 7) / 8 * 8);
         const int groups = (int)grid.x * groups_per_block;
         hipLaunchKernelGGL((pool_short_kernel<LPR, HALF, CONCAT>), grid, block, 0, s, tables, indices,
-                           offsets, out, vec_ok, BagTable(B), T, nbags, groups, 1.0f, err, left);
+                           offsets, (int)grid.x / 8, nbags, div.B, div.magic, T, 1.0f, groups, vec_ok, err, out, left);
     } else {
         const dim3 grid(((nbags + POOL_WAVES - 1) / POOL_WAVES + 7) / 8 * 8);
 #define REC_POOL_LAUNCH(STREAM, NARROW)                                                                  \
     hipLaunchKernelGGL((pool_kernel<LPR, HALF, CONCAT, STREAM, NARROW>), grid, block, 0, s, tables, indices, \
-                       offsets, out, vec_ok, BagTable(B), T, nbags, 1.0f, err, left)
+                       offsets, (int)grid.x / 8, nbags, div.B, div.magic, T, 1.0f, vec_ok, err, out, left)
         if (stream_rows) {
             if (narrow) REC_POOL_LAUNCH(true, true); else REC_POOL_LAUNCH(true, false);
         } else {

@@ -31,7 +31,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // at most one.
 struct BagTable {
     unsigned B, magic;
-    explicit BagTable(int batch) : B((unsigned)batch), magic(0xFFFFFFFFu / (unsigned)batch) {}
+    static BagTable of_batch(int batch) { return {(unsigned)batch, 0xFFFFFFFFu / (unsigned)batch}; }
     __device__ inline int of(int bag) const
     {
         const unsigned t = __umulhi((unsigned)bag, magic);

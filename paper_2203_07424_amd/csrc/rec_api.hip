@@ -243,8 +243,8 @@ void chain_run(const Layer *layers, int per_stack, int G, int i, int j, int num_
         c.Npad[l - i] = layers[l].Npad;
         c.relu[l - i] = 1;
         for (int k = 0; k < G; ++k) {
-            c.W[l - i][k] = layers[(size_t)k * per_stack + l].Wc;
-            c.bias[l - i][k] = layers[(size_t)k * per_stack + l].bias;
+            c.W[k][l - i] = layers[(size_t)k * per_stack + l].Wc;
+            c.bias[k][l - i] = layers[(size_t)k * per_stack + l].bias;
         }
     }
 }

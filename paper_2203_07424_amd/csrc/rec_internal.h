@@ -58,7 +58,9 @@ struct ConcatDense {
 // fp32 input, one stack) further blocks of the launch run that stack:
 // Bottom-FC does not depend on the sparse side (Sec. III-A), so it can share a
 // launch with the scan instead of costing one of its own.
-struct ChainProblem;
+template <int G>
+struct ChainArgs;
+using ChainProblem = ChainArgs<REC_MAX_TOWERS>;
 constexpr int SCAN_LINK_POLLS = 65536;  // of another tile's word before its lengths are added up instead
 hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *offsets,
                        unsigned long long *tile_words, ErrRecord *err, const ConcatDense &job,
@@ -162,7 +164,7 @@ hipError_t fc_big_prepare();
 //   X_{L+1} = act_L(X_L W_{L,g}^T + bias_{L,g}),  act_L = ReLU where relu[L] != 0,
 // each layer narrowing its input to bf16 as the per-layer path does.  Layer L is
 // Kpad[L] -> Npad[L] with Kpad[L + 1] == Npad[L], all at most CHAIN_MAX_WIDTH
-// (Kpad[0] TAIL_MAX_INPUT in a tail) and multiples of PAD; W[L][g] is the fragment order launch_pack_chain() writes.
+// (Kpad[0] TAIL_MAX_INPUT in a tail) and multiples of PAD; W[g][L] is the fragment order launch_pack_chain() writes.
 // The last X goes to C_g = C + g * c_stride (CHAIN_OUT_BF16 / CHAIN_OUT_F32, row
 // stride ldc), or (CHAIN_OUT_DOT) into the one-output layer that follows:
 //   dot_out[m * dot_ld + g] = sum_n X[m][n] * dot_w[g][n] + dot_bias[g][0]   in fp32.
@@ -171,21 +173,36 @@ constexpr int CHAIN_MAX_WIDTH = 1024;
 constexpr int CHAIN_NARROW_WIDTH = 256;  // up to this many outputs in every layer: the narrow form, two blocks a compute unit
 constexpr int TAIL_MAX_INPUT = 2048;  // Kpad of the first Predict-FC layer in launch_tail()
 enum { CHAIN_OUT_BF16 = 0, CHAIN_OUT_F32 = 1, CHAIN_OUT_DOT = 2 };
-struct ChainProblem {
+template <int G>  // stacks there is room for: what a launch of one stack passes is a quarter of the size
+struct ChainArgs {
     const void *A; bool a_f32; int lda; long long a_stride;
     int M, K;
     int n_layers, groups;
     int Kpad[CHAIN_MAX_LAYERS], Npad[CHAIN_MAX_LAYERS], relu[CHAIN_MAX_LAYERS];
-    const void *W[CHAIN_MAX_LAYERS][MAX_GROUPS];
-    const float *bias[CHAIN_MAX_LAYERS][MAX_GROUPS];
+    const void *W[G][CHAIN_MAX_LAYERS];
+    const float *bias[G][CHAIN_MAX_LAYERS];
     int out_mode;
     void *C; int ldc; long long c_stride;
-    const float *dot_w[MAX_GROUPS];
-    const float *dot_bias[MAX_GROUPS];
+    const float *dot_w[G];
+    const float *dot_bias[G];
     float *dot_out; int dot_ld;
     int num_cus;
     int ld_lds, a_vec;  // filled in by chain_finalize()
 };
+inline ChainArgs<1> one_stack(const ChainProblem &p)
+{
+    ChainArgs<1> a;
+    a.A = p.A; a.a_f32 = p.a_f32; a.lda = p.lda; a.a_stride = p.a_stride;
+    a.M = p.M; a.K = p.K; a.n_layers = p.n_layers; a.groups = 1;
+    for (int L = 0; L < CHAIN_MAX_LAYERS; ++L) {
+        a.Kpad[L] = p.Kpad[L]; a.Npad[L] = p.Npad[L]; a.relu[L] = p.relu[L];
+        a.W[0][L] = p.W[0][L]; a.bias[0][L] = p.bias[0][L];
+    }
+    a.out_mode = p.out_mode; a.C = p.C; a.ldc = p.ldc; a.c_stride = p.c_stride;
+    a.dot_w[0] = p.dot_w[0]; a.dot_bias[0] = p.dot_bias[0]; a.dot_out = p.dot_out; a.dot_ld = p.dot_ld;
+    a.num_cus = p.num_cus; a.ld_lds = p.ld_lds; a.a_vec = p.a_vec;
+    return a;
+}
 bool chain_layer_fits(int Kpad, int Npad, int max_input = CHAIN_MAX_WIDTH);
 // The rounds that blocks of 64 samples (two row tiles, one block a compute unit) take,
 // 0 where they fill less than three quarters of these.  (256 blocks of four 1024-512-256 towers:

@@ -38,17 +38,14 @@ __global__ __launch_bounds__(256) void clear_tile_words_kernel(unsigned long lon
 
 // The scan alone: blocks [0, tiles) write the offsets, the blocks
 // behind them do a concatenation model's dense copy.
-__global__ __launch_bounds__(SCAN_THREADS) void scan_tile_offsets(const int32_t *__restrict__ len,
-                                                                  int n, long long nnz,
-                                                                  const TileLink link,
-                                                                  int32_t *__restrict__ offsets,
-                                                                  ErrRecord *err, int tiles,
-                                                                  const ConcatDense job)
+__global__ __launch_bounds__(SCAN_THREADS) void scan_tile_offsets(
+    const int32_t *__restrict__ len, int32_t *__restrict__ offsets, unsigned long long *words, long long nnz, int n,
+    int tiles, int polls, int extra, ErrRecord *err, const ConcatDense job)
 {
     if ((int)blockIdx.x < tiles)
-        scan_offsets_tile(len, n, nnz, link, offsets, err, blockIdx.x);
+        scan_offsets_tile(len, n, nnz, TileLink{words, tiles, polls}, offsets, err, blockIdx.x);
     else
-        concat_dense_block(job, blockIdx.x - tiles, gridDim.x - tiles);
+        concat_dense_block<SCAN_THREADS>(job, blockIdx.x - tiles, extra);
 }
 
 // The same with a stack of fully connected layers riding along: blocks of
@@ -58,17 +55,17 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_tile_offsets(const int32_t 
 // at once (a barrier counts only the waves of a group that have not ended).
 template <int MAXC>
 __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<MAXC>()) void scan_offsets_ride_kernel(
-    const int32_t *__restrict__ len, int n, long long nnz, const TileLink link,
-    int32_t *__restrict__ offsets, ErrRecord *err, int tiles, const ConcatDense job, int extra,
-    const ChainProblem a, int chain_grid_x)
+    const int32_t *__restrict__ len, int32_t *__restrict__ offsets, unsigned long long *words, long long nnz, int n,
+    int tiles, int polls, int extra, int chain_grid_x, ErrRecord *err, const ConcatDense job, const ChainArgs<1> a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int b = blockIdx.x;
     if (b < tiles) {
-        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, link, offsets, err, b);
+        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, TileLink{words, tiles, polls}, offsets, err, b);
     } else if (b < tiles + extra) {
-        concat_dense_block(job, b - tiles, extra);
+        concat_dense_block<chain::CH_THREADS>(job, b - tiles, extra);
     } else {
+        chain::touch_args<64 + sizeof(job) + sizeof(a)>();
         const int bx = b - tiles - extra, share = chain::touch_share(chain_grid_x);
         chain::mlp_chain_block<true, 1, MAXC>(a, smem, bx, 0, (bx >> 3) % share, share);
     }
@@ -118,12 +115,7 @@ hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *of
         extra = (int)std::min<long long>((total + 8 * SCAN_THREADS - 1) / (8 * SCAN_THREADS), 256);
     }
     const bool has_rider = rider && rider->M > 0;
-    TileLink link;
-    if (scan_linked_words(n, has_rider) > 0) {
-        link.words = tile_words;
-        link.tiles = tiles;
-        link.polls = polls;
-    }
+    unsigned long long *words = scan_linked_words(n, has_rider) > 0 ? tile_words : nullptr;
     if (has_rider) {
         if (!rider->a_f32 || rider->groups != 1) return hipErrorInvalidValue;
         ChainProblem a;
@@ -132,12 +124,12 @@ hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *of
         const int chain_grid_x = (a.M + 31) / 32;
         auto k = chain::narrow_run(a) ? scan_offsets_ride_kernel<1> : scan_offsets_ride_kernel<4>;
         hipLaunchKernelGGL(k, dim3(tiles + extra + chain_grid_x), dim3(chain::CH_THREADS),
-                           chain::chain_lds_bytes<1>(a.ld_lds), s, lengths, n, nnz, link, offsets, err, tiles, job,
-                           extra, a, chain_grid_x);
+                           chain::chain_lds_bytes<1>(a.ld_lds), s, lengths, offsets, words, nnz, n, tiles, polls, extra,
+                           chain_grid_x, err, job, one_stack(a));
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(scan_tile_offsets, dim3(tiles + extra), dim3(SCAN_THREADS), 0, s, lengths, n, nnz,
-                       link, offsets, err, tiles, job);
+    hipLaunchKernelGGL(scan_tile_offsets, dim3(tiles + extra), dim3(SCAN_THREADS), 0, s, lengths, offsets, words, nnz, n,
+                       tiles, polls, extra, err, job);
     return hipGetLastError();
 }
 

@@ -29,14 +29,15 @@ __device__ inline long long block_sum(long long v, long long *s_w)
 }
 
 // Dense part of the Predict-FC input rows of a concatenation model, narrowed,
-// and the zero padding behind each row: block `b` of `nb` blocks.
+// and the zero padding behind each row: block `b` of `nb` blocks of THREADS threads.
+template <int THREADS>
 __device__ inline void concat_dense_block(const ConcatDense &job, int b, int nb)
 {
     __bf16 *z = static_cast<__bf16 *>(job.z_bf16);
     const int per_row = job.w0 + (job.ldz - job.width);
     const long long total = (long long)job.B * per_row;
-    const long long stride = (long long)nb * blockDim.x;
-    for (long long i = (long long)b * blockDim.x + threadIdx.x; i < total; i += stride) {
+    const long long stride = (long long)nb * THREADS;
+    for (long long i = (long long)b * THREADS + threadIdx.x; i < total; i += stride) {
         const long long r = i / per_row;
         const int c = (int)(i - r * per_row);
         if (c < job.w0)

@@ -30,11 +30,21 @@ namespace {
 
 using namespace chain;
 
+// What the kernel gets of a TailProblem.
+struct TailArgs {
+    ChainArgs<1> run[2];
+    const float *x0;
+    const float *pooled;
+    void *z;
+    int ldx0, T, ldz, rows, ld_lds, blocks;
+};
+
 template <int NBLK, int KST, int MAXC>
-__global__ __launch_bounds__(CH_THREADS) void tail_kernel(const TailProblem p)
+__global__ __launch_bounds__(CH_THREADS) void tail_kernel(const TailArgs p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int D = 32 * KST;
+    touch_args<sizeof(TailArgs)>();
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = p.rows, row0 = blockIdx.x * rows;
     const int ld = p.ld_lds;
@@ -44,7 +54,7 @@ __global__ __launch_bounds__(CH_THREADS) void tail_kernel(const TailProblem p)
 
     // Blocks behind those that have samples are there for this alone: cold weights
     // come in as fast as all compute units can ask for them.
-    const int share = touch_share(gridDim.x), mine = (blockIdx.x >> 3) % share;
+    const int share = touch_share(p.blocks), mine = (blockIdx.x >> 3) % share;
     const Touched touched = touch_weights(p.run[1], 0, mine, share);
     if (row0 >= p.run[1].M) {
         touch_weights(p.run[0], 0, mine, share).done();
@@ -72,8 +82,10 @@ __global__ __launch_bounds__(CH_THREADS) void tail_kernel(const TailProblem p)
             }
             touched.done();
         }
+        Ahead<MAXC> ahead;
+        ahead.request(p.run[part], 0, 0);
         __syncthreads();
-        run_layers<1, MAXC>(p.run[part], RunCtx{X, part == 0 ? x0s : nullptr, ld, D, 0, row0, rows - 1}, red);
+        run_layers<1, MAXC>(p.run[part], RunCtx{X, part == 0 ? x0s : nullptr, ld, D, 0, row0, rows - 1}, ahead, red);
         __syncthreads();
     }
 }
@@ -89,9 +101,10 @@ constexpr size_t TAIL_LDS = 32 * (TAIL_MAX_INPUT + CH_LDS_PAD) * sizeof(__bf16) 
 template <int NBLK, int KST>
 hipError_t launch_as(const TailProblem &p, int num_cus, hipStream_t s)
 {
-    const int blocks = (p.run[1].M + p.rows - 1) / p.rows;
+    const int blocks = (p.run[1].M + p.rows - 1) / p.rows, grid = blocks < num_cus ? num_cus : blocks;
     auto k = narrow_run(p.run[0]) && narrow_run(p.run[1]) ? tail_kernel<NBLK, KST, 1> : tail_kernel<NBLK, KST, 4>;
-    hipLaunchKernelGGL(k, dim3(blocks < num_cus ? num_cus : blocks), dim3(CH_THREADS), tail_lds_bytes(p), s, p);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(CH_THREADS), tail_lds_bytes(p), s,
+                       TailArgs{{one_stack(p.run[0]), one_stack(p.run[1])}, p.x0, p.pooled, p.z, p.ldx0, p.T, p.ldz, p.rows, p.ld_lds, grid});
     return hipGetLastError();
 }
 
