@@ -40,15 +40,7 @@ constexpr int LONG_BAGS = 3 * SCAN_TILE, SHORT_FORM_BAGS = 6 * SCAN_TILE;
 template <int THREADS>
 __device__ inline long long sum_before(const int32_t *__restrict__ len, int n, long long *s_w)
 {
-    long long sum = 0;
-    for (int k0 = threadIdx.x; k0 < n; k0 += 4 * THREADS) {
-        int v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = k0 + i * THREADS < n ? len[k0 + i * THREADS] : 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sum += v[i] > 0 ? v[i] : 0;
-    }
-    sum = wave_sum(sum);
+    const long long sum = wave_sum(part_of_sum<THREADS>(len, n));
     if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = sum;
     __syncthreads();
     long long all = 0;
@@ -82,11 +74,18 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
     const int first = ((b & 7) * per + (b >> 3)) * chain::CH_WAVES;
     if (first >= n) return;
     __shared__ long long s_w[chain::CH_WAVES];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), bag = first + wave;
+    int own[chain::CH_WAVES];  // the block's lengths, requested with the others
+#pragma unroll
+    for (int i = 0; i < chain::CH_WAVES; ++i) own[i] = max(len[min(first + i, n - 1)], 0);
     long long start = sum_before<chain::CH_THREADS>(len, first, s_w);
-    const int bag = __builtin_amdgcn_readfirstlane(first + (int)(threadIdx.x >> 6));
     if (bag >= n) return;
-    for (int k = first; k < bag; ++k) start += max(len[k], 0);
-    const long long end = start + max(len[bag], 0);
+    long long end = start;
+#pragma unroll
+    for (int i = 0; i < chain::CH_WAVES; ++i) {
+        start += i < wave ? own[i] : 0;
+        end += i <= wave ? own[i] : 0;
+    }
     const int t = div.of(bag);
     pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, bag - t * (int)div.B, t, (int)min(start, nnz),
                                              (int)min(end, nnz), one, err);

@@ -28,6 +28,35 @@ __device__ inline long long block_sum(long long v, long long *s_w)
     return r;
 }
 
+// This thread's part of the sum over max(len, 0) of lengths [0, n), n a multiple of 4
+// and a few thousand; threads [0, THREADS) of the block.  Up to six 16-byte loads a
+// thread in flight: with four single ones 7800 lengths were eight trips in a row
+// (26 tables x 300 samples 37.9 -> 33.5 us per forward).
+template <int THREADS>
+__device__ inline long long part_of_sum(const int32_t *__restrict__ len, int n)
+{
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    constexpr int U = 6;
+    const bool wide = (reinterpret_cast<uintptr_t>(len) & 15) == 0;
+    long long sum = 0;
+    for (int k0 = 4 * (int)threadIdx.x; k0 < n; k0 += 4 * THREADS * U) {
+        i32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t *p = len + min(k0 + u * 4 * THREADS, n - 4);
+            if (wide)
+                v[u] = *reinterpret_cast<const i32x4 *>(p);
+            else
+                v[u] = i32x4{p[0], p[1], p[2], p[3]};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum += k0 + u * 4 * THREADS < n && v[u][e] > 0 ? v[u][e] : 0;
+    }
+    return sum;
+}
+
 // Dense part of the Predict-FC input rows of a concatenation model, narrowed,
 // and the zero padding behind each row: block `b` of `nb` blocks of THREADS threads.
 template <int THREADS>
@@ -113,14 +142,7 @@ __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n,
             __hip_atomic_store(link.words + tile, (unsigned long long)own * 2 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         before = linked_sum(link, tile, len);
     } else {
-        // base is a multiple of SCAN_TILE: SCAN_ITEMS loads per thread and tile, all in flight together
-        for (long long k0 = 0; k0 < base; k0 += SCAN_TILE) {
-            int v[SCAN_ITEMS];
-#pragma unroll
-            for (int i = 0; i < SCAN_ITEMS; ++i) v[i] = len[k0 + i * SCAN_THREADS + tid];
-#pragma unroll
-            for (int i = 0; i < SCAN_ITEMS; ++i) before += v[i] > 0 ? v[i] : 0;
-        }
+        before = part_of_sum<SCAN_THREADS>(len, (int)base);
     }
     before = block_sum(before, s_w);
     __syncthreads();
