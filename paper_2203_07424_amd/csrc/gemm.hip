@@ -336,12 +336,15 @@ __global__ __launch_bounds__(256) void pack_fc_kernel(const float *__restrict__ 
                                                       int Npad, int Kpad, __bf16 *__restrict__ Wp,
                                                       float *__restrict__ bp)
 {
-    const long long total = (long long)Npad * Kpad;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
+    const long long chunks = (long long)Npad * Kpad / 8;  // of eight elements, one a thread
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < chunks;
          i += (long long)gridDim.x * blockDim.x) {
-        const int n = (int)(i / Kpad), k = (int)(i % Kpad);
-        Wp[i] = (__bf16)((n < N && k < K) ? W[(long long)n * K + k] : 0.0f);
-        if (k == 0) bp[n] = n < N ? b[n] : 0.0f;
+        const int n = (int)(i / (Kpad / 8)), k0 = (int)(i % (Kpad / 8)) * 8;
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((n < N && k0 + e < K) ? W[(long long)n * K + k0 + e] : 0.0f);
+        *reinterpret_cast<bf16x8 *>(Wp + 8 * i) = o;
+        if (k0 == 0) bp[n] = n < N ? b[n] : 0.0f;
     }
 }
 
@@ -418,8 +421,8 @@ hipError_t launch_pack_dot(const float *W, const float *b, int K, int Kpad, floa
 hipError_t launch_pack_fc(const float *W, const float *b, int N, int K, int Npad, int Kpad,
                           void *W_packed, float *bias_packed, hipStream_t s)
 {
-    const long long total = (long long)Npad * Kpad;
-    const int blocks = (int)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
+    const long long chunks = (long long)Npad * Kpad / 8;
+    const int blocks = (int)((chunks + 255) / 256 < 4096 ? (chunks + 255) / 256 : 4096);
     hipLaunchKernelGGL(pack_fc_kernel, dim3(blocks), dim3(256), 0, s, W, b, N, K, Npad, Kpad,
                        static_cast<__bf16 *>(W_packed), bias_packed);
     return hipGetLastError();

@@ -56,15 +56,18 @@ __global__ __launch_bounds__(CH_THREADS, waves_per_simd<MAXC>()) void mlp_chain_
 __global__ __launch_bounds__(256) void pack_chain_kernel(const float *__restrict__ W, int N, int K, int Npad,
                                                          int Kpad, __bf16 *__restrict__ Wp)
 {
-    const long long total = (long long)Npad * Kpad;
+    const long long lanes = (long long)Npad * Kpad / 8;  // a thread writes a lane's eight elements
     const int KS = Kpad / 16;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < lanes;
          i += (long long)gridDim.x * blockDim.x) {
-        const long long frag = i >> 9;
-        const int within = (int)(i & 511), lane = within >> 3, e = within & 7;
-        const int nc = (int)(frag / KS), ks = (int)(frag % KS);
-        const int n = nc * 32 + (lane & 31), k = ks * 16 + (lane >> 5) * 8 + e;
-        Wp[i] = (__bf16)((n < N && k < K) ? W[(long long)n * K + k] : 0.0f);
+        const long long frag = i >> 6;
+        const int lane = (int)(i & 63);
+        const long long nc = frag / KS;
+        const int n = (int)nc * 32 + (lane & 31), k0 = (int)(frag - nc * KS) * 16 + (lane >> 5) * 8;
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((n < N && k0 + e < K) ? W[(long long)n * K + k0 + e] : 0.0f);
+        *reinterpret_cast<bf16x8 *>(Wp + 8 * i) = o;
     }
 }
 
@@ -150,8 +153,8 @@ hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s)
 
 hipError_t launch_pack_chain(const float *W, int N, int K, int Npad, int Kpad, void *W_packed, hipStream_t s)
 {
-    const long long total = (long long)Npad * Kpad;
-    const int blocks = (int)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
+    const long long lanes = (long long)Npad * Kpad / 8;
+    const int blocks = (int)((lanes + 255) / 256 < 4096 ? (lanes + 255) / 256 : 4096);
     hipLaunchKernelGGL(pack_chain_kernel, dim3(blocks), dim3(256), 0, s, W, N, K, Npad, Kpad,
                        static_cast<__bf16 *>(W_packed));
     return hipGetLastError();
