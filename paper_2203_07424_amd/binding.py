@@ -23,6 +23,7 @@ if not os.path.exists(LIB_PATH):
         "or __graft_entry__.build()); there is no CPU fallback")
 
 _lib = C.CDLL(LIB_PATH)
+_F32, _I32 = torch.float32, torch.int32
 
 REC_OK = 0
 REC_ERR_ARG, REC_ERR_SHAPE, REC_ERR_STATE, REC_ERR_LENGTHS = 1, 2, 3, 4
@@ -118,6 +119,11 @@ def status_string(status: int) -> str:
 
 
 def _stream() -> Optional[int]:
+    # Behind the first use of the device its current stream is one cheap lookup; asking
+    # whether there is a device and building a stream object took a third of a
+    # forward's host time.
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     # Without a device only the host-side argument checks of the library can
     # run, and those never touch the stream.
     if not torch.cuda.is_available():
@@ -325,37 +331,44 @@ class RecModel:
     def forward(self, dense: torch.Tensor, indices: torch.Tensor, lengths: torch.Tensor,
                 logits: Optional[torch.Tensor] = None) -> torch.Tensor:
         """Returns fp32 logits: [batch] for one Predict-FC stack, [batch, towers] for several."""
-        batch = dense.shape[0]
+        batch = dense.size(0)
         if logits is None:
             shape = (batch,) if self.towers == 1 else (batch, self.towers)
             logits = torch.empty(shape, dtype=torch.float32, device=self.device)
-        # The library sees pointers only: check here that every buffer is as large
-        # as the call says, of the right type, contiguous and on the device.
-        for name, t, dt, n in (("dense", dense, torch.float32, batch * self.F),
-                               ("indices", indices, torch.int32, indices.numel()),
-                               ("lengths", lengths, torch.int32, self.T * batch),
-                               ("logits", logits, torch.float32, batch * self.towers)):
-            if not (t.is_cuda and t.is_contiguous() and t.dtype == dt and t.numel() >= n):
-                raise ValueError(f"rec_forward: {name} must be a contiguous {dt} device tensor of at least {n} elements")
-        self._ok(rec_forward(self.handle, dense, indices, lengths, batch, indices.numel(), logits),
-                 "rec_forward")
+        nnz = self._check_buffers("rec_forward", dense, indices, lengths, logits, batch)
+        st = _lib.rec_forward(self.handle, dense.data_ptr(), indices.data_ptr(), lengths.data_ptr(), batch, nnz,
+                              logits.data_ptr(), _stream())
+        if st:
+            self._ok(st, "rec_forward")
         self.last_batch = batch
         return logits
+
+    def _check_buffers(self, call: str, dense: torch.Tensor, indices: torch.Tensor, lengths: torch.Tensor,
+                       logits: torch.Tensor, batch: int) -> int:
+        """The library sees pointers only: check here that every buffer is as large as
+        the call says, of the right type, contiguous and on the device.  Returns the
+        id count."""
+        nnz = indices.numel()
+        if (dense.is_cuda and dense.dtype is _F32 and dense.numel() >= batch * self.F and dense.is_contiguous() and
+                indices.is_cuda and indices.dtype is _I32 and indices.is_contiguous() and
+                lengths.is_cuda and lengths.dtype is _I32 and lengths.numel() >= self.T * batch and lengths.is_contiguous() and
+                logits.is_cuda and logits.dtype is _F32 and logits.numel() >= batch * self.towers and logits.is_contiguous()):
+            return nnz
+        for name, t, dt, n in (("dense", dense, _F32, batch * self.F), ("indices", indices, _I32, nnz),
+                               ("lengths", lengths, _I32, self.T * batch), ("logits", logits, _F32, batch * self.towers)):
+            if not (t.is_cuda and t.is_contiguous() and t.dtype == dt and t.numel() >= n):
+                raise ValueError(f"{call}: {name} must be a contiguous {dt} device tensor of at least {n} elements")
+        return nnz
 
     def forward_static(self, dense: torch.Tensor, indices: torch.Tensor, lengths: torch.Tensor,
                        logits: torch.Tensor, fault: Optional[torch.Tensor] = None) -> torch.Tensor:
         """rec_forward_static(): the same pass with the library's static scratch; the
         caller brings every buffer (logits fp32, fault int64 [2] or None)."""
-        batch = dense.shape[0]
-        for name, t, dt, n in (("dense", dense, torch.float32, batch * self.F),
-                               ("indices", indices, torch.int32, indices.numel()),
-                               ("lengths", lengths, torch.int32, self.T * batch),
-                               ("logits", logits, torch.float32, batch * self.towers)):
-            if not (t.is_cuda and t.is_contiguous() and t.dtype == dt and t.numel() >= n):
-                raise ValueError(f"rec_forward_static: {name} must be a contiguous {dt} device tensor of at least {n} elements")
+        batch = dense.size(0)
+        nnz = self._check_buffers("rec_forward_static", dense, indices, lengths, logits, batch)
         if fault is not None and not (fault.is_cuda and fault.dtype == torch.int64 and fault.numel() >= 2):
             raise ValueError("rec_forward_static: fault must be an int64 device tensor of 2 elements")
-        self._ok(rec_forward_static(self.handle, dense, indices, lengths, batch, indices.numel(), logits, fault),
+        self._ok(rec_forward_static(self.handle, dense, indices, lengths, batch, nnz, logits, fault),
                  "rec_forward_static")
         return logits
 
