@@ -354,13 +354,25 @@ bool bottom_rides_on_scan(const rec_model *m)
 
 // The first layer of Bottom-FC that the tail kernel would take (none: the number of
 // layers): a run of narrow layers at its end, behind at least one layer that
-// narrows the input, when the stack does not ride on the scan as a whole.
-int tail_bottom_from(const rec_model *m)
+// narrows the input, when the stack does not ride on the scan as a whole.  A layer
+// with more weights than a launch is worth stays one of its own, all compute units
+// fetching them: 320, 960, 1920 KiB in blocks of 8, 16, 32 samples (us per forward with
+// the layer in the joint launch / on its own; 512 KiB: 1 sample 27.3 / 25.2, 300 39.7 / 38.0, 2048
+// 63.6 / 62.9, 3000 67.4 / 70.2; 800 KiB: 300 36.2 / 32.5, 4096 65.3 / 69.5; 1 MiB: 300 44.9 / 39.7,
+// 3000 67.3 / 61.3, 4096 68.0 / 68.0; 2 MiB: 4096 77.4 / 67.9).
+size_t tail_layer_bytes(const rec_model *m, int B)
+{
+    const int rows = tail_rows(B, m->num_cus);
+    return (rows == 8 ? 320 : rows == 16 ? 960 : 1920) * 1024;
+}
+int tail_bottom_from(const rec_model *m, int B)
 {
     const int n = (int)m->bottom.size();
     if (m->overlap_dense || m->pipeline || bottom_rides_on_scan(m)) return n;
     int i = n;
-    while (i > 1 && m->bottom[i - 1].chain && n - i < CHAIN_MAX_LAYERS) --i;
+    while (i > 1 && m->bottom[i - 1].chain && n - i < CHAIN_MAX_LAYERS &&
+           m->bottom[i - 1].chain_bytes() <= tail_layer_bytes(m, B))
+        --i;
     return i;
 }
 
@@ -396,7 +408,7 @@ bool tail_applies(const rec_model *m, const Call &c)
         i = std::max(j, i + 1);
         ++launches;
     }
-    for (int i = tail_bottom_from(m); i < nb; ++i, ++launches) bytes += m->bottom[i].chain_bytes();
+    for (int i = tail_bottom_from(m, c.B); i < nb; ++i, ++launches) bytes += m->bottom[i].chain_bytes();
     const size_t kib = c.B < 12 * m->num_cus ? 320 : tail_rows(c.B, m->num_cus) < 32 ? 640 : 1920;
     return bytes <= launches * kib * 1024;
 }
@@ -491,7 +503,7 @@ Plan plan_of(const rec_model *m, const Call &c, bool use_hot)
     p.ride = bottom_rides_on_scan(m);
     p.front = front_applies_to(m, c, use_hot, p.ride);
     p.tail = tail_applies(m, c);
-    p.tail_from = p.tail ? tail_bottom_from(m) : (int)m->bottom.size();
+    p.tail_from = p.tail ? tail_bottom_from(m, c.B) : (int)m->bottom.size();
     return p;
 }
 
