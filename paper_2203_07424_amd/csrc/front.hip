@@ -13,13 +13,12 @@
 // front_short_kernel (concatenation model without Bottom-FC, bags of a few ids):
 // blocks of 4 waves; the scan's, those that narrow the dense part, then pooling.
 //
-// The pooling waves of front_kernel get the 106 registers Bottom-FC's need, so 16
+// The pooling waves of front_kernel get the 122 registers Bottom-FC's need, so 16
 // of them share a compute unit instead of 32.  Up to LONG_BAGS that costs less
-// than the launch: 8 tables x 256 samples 18.1 -> 15.4 us per forward, one sample
-// 17.1 -> 13.8; 40 x 128 37.8 -> 33.5, 10 x 512 33.2 -> 29.9 (uniform ids); beyond
-// it loses (10 x 1024 34.3 -> 37.0, 8 x 2048 23.9 -> 34.7).  front_short_kernel:
-// 26 tables x 300 samples 47.4 -> 44.8 us, x 16 36.7 -> 34.0, even at 16380 bags,
-// where adding up the lengths takes as long as the launches it saves.
+// than the launch (us per forward, two launches / one: 8 tables x 800 samples 15.7 / 12.8, 40 x 160
+// 26.9 / 23.2, 10 x 700 22.2 / 20.2); beyond it some shapes lose (10 x 800 22.9 / 23.2, with 20 fp16
+// rows a bag 10 x 1000 17.8 / 18.2).  front_short_kernel: 26 tables x 300 samples 47.4 -> 44.8 us, x 16
+// 36.7 -> 34.0, even at 16380 bags, where adding up the lengths takes as long as the launches it saves.
 #include <algorithm>
 
 #include "mlp_chain_body.h"
@@ -33,7 +32,7 @@ namespace {
 using namespace scan;
 using namespace pool;
 
-constexpr int LONG_BAGS = 3 * SCAN_TILE, SHORT_FORM_BAGS = 6 * SCAN_TILE;
+constexpr int LONG_BAGS = 7 * SCAN_TILE / 2, SHORT_FORM_BAGS = 6 * SCAN_TILE;
 
 // Sum over max(len, 0) of lengths [0, n) by all threads of the block; s_w: a word
 // per wave.
