@@ -337,7 +337,9 @@ REC_API rec_status rec_drain(rec_model *m, void *stream);
  * are one launch the last of them holds it and the others read an empty
  * bracket (one event record): scan, Bottom-FC and pooling of a small batch
  * under REC_STAGE_POOL; interaction, Predict-FC and the last Bottom-FC layers
- * under REC_STAGE_TOP_FIRST (rec_stage_shared() says which).  With REC_OPT_PIPELINE every stage is bracketed on
+ * under REC_STAGE_TOP_FIRST (rec_stage_shared() says which).  A first Bottom-FC layer
+ * that forwards otherwise run beside the scan, and a scan they run beside pooling for
+ * its sake, have launches of their own in a timed one.  With REC_OPT_PIPELINE every stage is bracketed on
  * the stream it runs on (a stage's time then includes whatever shared the
  * device with it). */
 REC_API rec_status rec_set_profiling(rec_model *m, int32_t slots, int32_t period);

@@ -10,17 +10,27 @@
 //
 // front_kernel (pooled dot model, Bottom-FC of narrow layers): blocks of 8 waves;
 // first those of the scan, then those of Bottom-FC, then pooling, one bag a wave.
-// front_short_kernel (concatenation model without Bottom-FC, bags of a few ids):
-// blocks of 4 waves; the scan's, those that narrow the dense part, then pooling.
+// front_fc_kernel (pooled dot model, any other Bottom-FC or none): instead of the stack
+// its first layer alone, which needs nothing but the input, in the blocks its own
+// launch would have (csrc/gemm_split.hip): 2560-1024-256-32 beside 10 tables, 1 sample
+// 25.0 -> 20.3 us per forward, 64 26.9 -> 21.4, 300 37.2 -> 28.7, 700 46.3 -> 38.4;
+// 500-256-64, 400 samples 24.6 -> 18.1.
+// front_short_kernel (concatenation model, bags of a few ids, Bottom-FC none or one
+// layer): blocks of 4 waves; the scan's, those that narrow the dense part (or that
+// layer's, which write its columns of the Predict-FC input rows too), then pooling.
+// 64-64 in front of four towers, 26 tables x 300 42.6 -> 32.5 us, x 1 28.3 -> 17.3.
 //
 // The pooling waves of front_kernel get the 122 registers Bottom-FC's need, so 16
 // of them share a compute unit instead of 32.  Up to LONG_BAGS that costs less
 // than the launch (us per forward, two launches / one: 8 tables x 800 samples 15.7 / 12.8, 40 x 160
 // 26.9 / 23.2, 10 x 700 22.2 / 20.2); beyond it some shapes lose (10 x 800 22.9 / 23.2, with 20 fp16
-// rows a bag 10 x 1000 17.8 / 18.2).  front_short_kernel: 26 tables x 300 samples 47.4 -> 44.8 us, x 16
+// rows a bag 10 x 1000 17.8 / 18.2).  front_fc_kernel has no such waves, but beyond that
+// the layer beside the scan alone (csrc/scan.hip) wins as often (12 000 bags: 50.5 / 49.7, 57.9
+// as three launches; 14 000 and more 59.8 / 52.2, 41.6 / 24.8).  front_short_kernel: 26 tables x 300 samples 47.4 -> 44.8 us, x 16
 // 36.7 -> 34.0, even at 16380 bags, where adding up the lengths takes as long as the launches it saves.
 #include <algorithm>
 
+#include "gemm_split_body.h"
 #include "mlp_chain_body.h"
 #include "pool_body.h"
 #include "scan_body.h"
@@ -31,6 +41,7 @@ namespace {
 
 using namespace scan;
 using namespace pool;
+using split::Rider;
 
 constexpr int LONG_BAGS = 7 * SCAN_TILE / 2, SHORT_FORM_BAGS = 6 * SCAN_TILE;
 
@@ -48,6 +59,33 @@ __device__ inline long long sum_before(const int32_t *__restrict__ len, int n, l
     return all;
 }
 
+// Block `b` of the pooling blocks, WAVES bags a block, one a wave.
+template <int WAVES, int LPR, bool HALF, bool STREAM>
+__device__ inline void pool_from_lengths(const int32_t *__restrict__ len, const TableDesc *__restrict__ tables,
+                                         const int32_t *__restrict__ indices, long long nnz, int n, int b, int per,
+                                         const BagTable &div, int T, float one, ErrRecord *err, const PoolOut &out)
+{
+    // XCD x takes an eighth of the table-major bag list (see pool_kernel).
+    const int first = ((b & 7) * per + (b >> 3)) * WAVES;
+    if (first >= n) return;
+    __shared__ long long s_w[WAVES];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), bag = first + wave;
+    int own[WAVES];  // the block's lengths, requested with the others
+#pragma unroll
+    for (int i = 0; i < WAVES; ++i) own[i] = max(len[min(first + i, n - 1)], 0);
+    long long start = sum_before<WAVES * 64>(len, first, s_w);
+    if (bag >= n) return;
+    long long end = start;
+#pragma unroll
+    for (int i = 0; i < WAVES; ++i) {
+        start += i < wave ? own[i] : 0;
+        end += i <= wave ? own[i] : 0;
+    }
+    const int t = div.of(bag);
+    pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, bag - t * (int)div.B, t, (int)min(start, nnz),
+                                             (int)min(end, nnz), one, err);
+}
+
 template <int LPR, bool HALF, bool STREAM>
 __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void front_kernel(
     const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
@@ -57,7 +95,8 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int b = blockIdx.x;
     if (b < tiles) {
-        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b);
+        __shared__ ScanShared sh;
+        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b, sh);
         return;
     }
     b -= tiles;
@@ -67,27 +106,36 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
         chain::mlp_chain_block<true, 1, 1>(a, smem, b, 0, (b >> 3) % share, share);
         return;
     }
-    b -= chain_blocks;
-    // XCD x takes an eighth of the table-major bag list (see pool_kernel).
-    const BagTable div{B, magic};
-    const int first = ((b & 7) * per + (b >> 3)) * chain::CH_WAVES;
-    if (first >= n) return;
-    __shared__ long long s_w[chain::CH_WAVES];
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), bag = first + wave;
-    int own[chain::CH_WAVES];  // the block's lengths, requested with the others
-#pragma unroll
-    for (int i = 0; i < chain::CH_WAVES; ++i) own[i] = max(len[min(first + i, n - 1)], 0);
-    long long start = sum_before<chain::CH_THREADS>(len, first, s_w);
-    if (bag >= n) return;
-    long long end = start;
-#pragma unroll
-    for (int i = 0; i < chain::CH_WAVES; ++i) {
-        start += i < wave ? own[i] : 0;
-        end += i <= wave ? own[i] : 0;
+    pool_from_lengths<chain::CH_WAVES, LPR, HALF, STREAM>(len, tables, indices, nnz, n, b - chain_blocks, per,
+                                                          BagTable{B, magic}, T, one, err, out);
+}
+
+constexpr int fc_waves_per_simd(int tm, int tn) { return tm < 2 ? 6 : tm * tn < 8 ? 4 : 2; }
+
+// TM = 0: no layer.
+template <int LPR, bool HALF, bool STREAM, int TM, int TN>
+__global__ __launch_bounds__(64 * split::rider_waves(TM), fc_waves_per_simd(TM, TN)) void front_fc_kernel(
+    const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
+    long long nnz, int n, int tiles, int fc_blocks, int per, unsigned B, unsigned magic, int T, float one,
+    int32_t *__restrict__ offsets, ErrRecord *err, const PoolOut out, const Rider a)
+{
+    int b = blockIdx.x;
+    if (b < tiles) {
+        __shared__ ScanShared sh;
+        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b, sh);
+        return;
     }
-    const int t = div.of(bag);
-    pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, bag - t * (int)div.B, t, (int)min(start, nnz),
-                                             (int)min(end, nnz), one, err);
+    b -= tiles;
+    if constexpr (TM > 0) {
+        extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+        if (b < fc_blocks) {
+            split::split_block<TM, TN, 1, split::rider_waves(TM), split::IN_F32, split::OUT_EITHER>(a.p, a.g, smem, b);
+            return;
+        }
+        b -= fc_blocks;
+    }
+    pool_from_lengths<split::rider_waves(TM), LPR, HALF, STREAM>(len, tables, indices, nnz, n, b, per, BagTable{B, magic}, T, one,
+                                                         err, out);
 }
 
 // Bags of one block of front_short_kernel: consecutive, each group of LPR lanes
@@ -97,17 +145,20 @@ constexpr int short_groups() { return POOL_WAVES * (64 / LPR); }
 template <int LPR>
 constexpr int short_block_bags() { return short_groups<LPR>() * SHORT_BAGS; }
 
-template <int LPR, bool HALF>
+// FC: with a layer, in tiles of 16 x 32 (a dense part of at most a few units of k).
+template <int LPR, bool HALF, bool FC>
 __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
     const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     long long nnz, int n, int tiles, int extra, int per, unsigned B, unsigned magic, int T, float one, int vec_ok,
-    int32_t *__restrict__ offsets, ErrRecord *err, const PoolOut out, const ConcatDense job)
+    int fc_blocks, int32_t *__restrict__ offsets, ErrRecord *err, const PoolOut out, const ConcatDense job,
+    const typename std::conditional<FC, Rider, char>::type a)
 {
     constexpr int THREADS = POOL_WAVES * 64, GROUPS = short_groups<LPR>(), BAGS = short_block_bags<LPR>();
     static_assert(THREADS == SCAN_THREADS && BAGS <= THREADS, "a thread per bag of the block");
     int b = blockIdx.x;
     if (b < tiles) {
-        scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b);
+        __shared__ ScanShared sh;
+        scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b, sh);
         return;
     }
     b -= tiles;
@@ -116,6 +167,14 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
         return;
     }
     b -= extra;
+    if constexpr (FC) {
+        extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+        if (b < fc_blocks) {
+            split::split_block<1, 2, 1, POOL_WAVES, split::IN_F32, split::OUT_EITHER>(a.p, a.g, smem, b);
+            return;
+        }
+        b -= fc_blocks;
+    }
     const BagTable div{B, magic};
     const int first = ((b & 7) * per + (b >> 3)) * BAGS;
     if (first >= n) return;
@@ -165,6 +224,36 @@ hipError_t launch_long(const FrontProblem &f, const ChainProblem &a, hipStream_t
     return hipGetLastError();
 }
 
+template <int LPR, bool HALF, int TM, int TN>
+hipError_t launch_fc_beside(const FrontProblem &f, hipStream_t s)
+{
+    constexpr int WAVES = split::rider_waves(TM);
+    const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
+    const int pool_blocks = ((n + WAVES - 1) / WAVES + 7) / 8 * 8;
+    const BagTable div = BagTable::of_batch(f.B);
+    Rider a{};
+    size_t lds = 0;
+    if constexpr (TM > 0) {
+        a = split::rider_of(*f.layer, TM, TN, f.out.z, f.out.ldz, f.z_cols);
+        lds = split::split_lds_bytes<TM, TN, 1, WAVES>();
+    }
+    const int fc_blocks = 8 * a.p.per_xcd;
+    auto k = f.stream_rows ? front_fc_kernel<LPR, HALF, true, TM, TN> : front_fc_kernel<LPR, HALF, false, TM, TN>;
+    hipLaunchKernelGGL(k, dim3(tiles + fc_blocks + pool_blocks), dim3(WAVES * 64), lds, s, f.lengths, f.tables, f.indices,
+                       f.nnz, n, tiles, fc_blocks, pool_blocks / 8, div.B, div.magic, f.T, 1.0f, f.offsets, f.err, f.out, a);
+    return hipGetLastError();
+}
+
+template <int LPR, bool HALF>
+hipError_t launch_fc_front(const FrontProblem &f, hipStream_t s)
+{
+    if (!f.layer) return launch_fc_beside<LPR, HALF, 0, 0>(f, s);
+    const FcTile t = fc_split_tile(*f.layer);
+    if (t.tm == 1) return t.tn == 1 ? launch_fc_beside<LPR, HALF, 1, 1>(f, s) : launch_fc_beside<LPR, HALF, 1, 2>(f, s);
+    if (t.tm == 2) return t.tn == 2 ? launch_fc_beside<LPR, HALF, 2, 2>(f, s) : launch_fc_beside<LPR, HALF, 2, 4>(f, s);
+    return launch_fc_beside<LPR, HALF, 4, 4>(f, s);
+}
+
 template <int LPR, bool HALF>
 hipError_t launch_short(const FrontProblem &f, hipStream_t s)
 {
@@ -176,9 +265,18 @@ hipError_t launch_short(const FrontProblem &f, hipStream_t s)
     constexpr int BAGS = short_block_bags<LPR>();
     const BagTable div = BagTable::of_batch(f.B);
     const int pool_blocks = ((n + BAGS - 1) / BAGS + 7) / 8 * 8;
-    hipLaunchKernelGGL((front_short_kernel<LPR, HALF>), dim3(tiles + extra + pool_blocks), dim3(POOL_WAVES * 64), 0, s,
-                       f.lengths, f.tables, f.indices, f.nnz, n, tiles, extra, pool_blocks / 8, div.B, div.magic, f.T, 1.0f,
-                       vec_ok, f.offsets, f.err, f.out, f.dense);
+    if (f.layer) {
+        const Rider a = split::rider_of(*f.layer, 1, 2, f.out.z, f.out.ldz, f.z_cols);
+        const int fc_blocks = 8 * a.p.per_xcd;
+        hipLaunchKernelGGL((front_short_kernel<LPR, HALF, true>), dim3(tiles + extra + fc_blocks + pool_blocks),
+                           dim3(POOL_WAVES * 64), (split::split_lds_bytes<1, 2, 1, POOL_WAVES>()), s, f.lengths, f.tables,
+                           f.indices, f.nnz, n, tiles, extra, pool_blocks / 8, div.B, div.magic, f.T, 1.0f, vec_ok, fc_blocks,
+                           f.offsets, f.err, f.out, f.dense, a);
+    } else {
+        hipLaunchKernelGGL((front_short_kernel<LPR, HALF, false>), dim3(tiles + extra + pool_blocks), dim3(POOL_WAVES * 64), 0,
+                           s, f.lengths, f.tables, f.indices, f.nnz, n, tiles, extra, pool_blocks / 8, div.B, div.magic, f.T,
+                           1.0f, vec_ok, 0, f.offsets, f.err, f.out, f.dense, (char)0);
+    }
     return hipGetLastError();
 }
 
@@ -215,6 +313,12 @@ hipError_t front_prepare()
     return e;
 }
 
+// Beside short bags a layer rides along in tiles of 16 x 32, where these are few.
+bool front_layer_rides(const FcProblem &a, bool concat)
+{
+    return fc_split_rides(a) && (!concat || (long long)((a.M + 15) / 16) * (a.Npad / 32) <= 512);
+}
+
 bool front_takes(const ChainProblem &rider) { return chain::narrow_run(rider); }
 
 hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStream_t s)
@@ -234,13 +338,19 @@ hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStr
         default: return hipErrorInvalidValue;
         }
     }
-    if (!f.out.z || !f.dense.x0) return hipErrorInvalidValue;
-    switch (lpr) {
-    case 4: return half ? launch_short<4, true>(f, s) : launch_short<4, false>(f, s);
-    case 8: return half ? launch_short<8, true>(f, s) : launch_short<8, false>(f, s);
-    case 16: return half ? launch_short<16, true>(f, s) : launch_short<16, false>(f, s);
-    default: return hipErrorInvalidValue;
+    if (f.layer && (!front_layer_rides(*f.layer, f.out.z != nullptr) || (f.out.z && f.out.ldz % 4 != 0)))
+        return hipErrorInvalidValue;
+#define REC_FRONT_BY_ROW(LAUNCH)                                          \
+    switch (lpr) {                                                        \
+    case 4: return half ? LAUNCH<4, true>(f, s) : LAUNCH<4, false>(f, s);   \
+    case 8: return half ? LAUNCH<8, true>(f, s) : LAUNCH<8, false>(f, s);   \
+    case 16: return half ? LAUNCH<16, true>(f, s) : LAUNCH<16, false>(f, s); \
+    default: return hipErrorInvalidValue;                                 \
     }
+    if (!f.out.z) REC_FRONT_BY_ROW(launch_fc_front)
+    if (!f.dense.x0) return hipErrorInvalidValue;
+    REC_FRONT_BY_ROW(launch_short)
+#undef REC_FRONT_BY_ROW
 }
 
 }  // namespace rec

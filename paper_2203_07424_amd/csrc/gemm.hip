@@ -350,6 +350,21 @@ __global__ __launch_bounds__(256) void pack_fc_kernel(const float *__restrict__ 
 
 }  // namespace
 
+// Launches that do not fill the chip with 128 x 128 tiles deal the k of smaller tiles to
+// the waves of a block, and so does, at any size, a layer with the one-output layer behind
+// it (16384 samples, 512 -> 128 -> 1 10.7 / 7.6 us, 4096 x four of 512 -> 256 -> 1
+// 13 / 10.7).  Where the 128 x 128 tiles do fill it they win: 1000 samples, four of
+// 1728 -> 1024 26.8 / 28.1, 4096 samples 53 / 96.
+bool fc_takes_split(const FcProblem &a)
+{
+    if (!fc_split_applies(a)) return false;
+    if (a.dot_out) return fc_can_fuse_dot(a.Npad);
+    if (a.num_cus > 0 && fc_big_applies(a, a.num_cus)) return false;
+    const long long big_blocks = (long long)a.groups * (a.Npad / 128) * ((a.M + 127) / 128);
+    if (a.corun && !a.a_f32 && a.Npad % 128 == 0 && big_blocks >= 64) return false;
+    return a.Npad % 128 != 0 || big_blocks < 256;
+}
+
 bool fc_can_fuse_dot(int Npad) { return Npad == 64 || Npad == 128 || Npad == 256; }
 
 hipError_t launch_fc(const FcProblem &a, hipStream_t s)
@@ -364,15 +379,9 @@ hipError_t launch_fc(const FcProblem &a, hipStream_t s)
     // registers free.  With four k-tiles in flight these kernels need 184-214 and
     // would wait for a second slot on the same SIMD, which pooling refills first
     // (measured: 123 instead of 14 us); with three they need 130-150.
-    // Launches that do not fill the chip with 128 x 128 tiles deal the k of smaller tiles to
-    // the waves of a block, and so does, at any size, a layer with the one-output layer behind
-    // it (16384 samples, 512 -> 128 -> 1 10.7 / 7.6 us, 4096 x four of 512 -> 256 -> 1
-    // 13 / 10.7).  Where the 128 x 128 tiles do fill it they win: 1000 samples, four of
-    // 1728 -> 1024 26.8 / 28.1, 4096 samples 53 / 96.
-    const bool split = fc_split_applies(a);
+    if (fc_takes_split(a)) return launch_fc_split(a, s);
     if (a.dot_out) {
         // The block must own whole rows.
-        if (split && fc_can_fuse_dot(Npad)) return launch_fc_split(a, s);
         if (Npad == 256) return launch_tile<64, 256, 1, 2>(a, s);
         if (Npad == 128) return a.corun ? launch_tile<32, 128, 1, 2>(a, s) : launch_tile<32, 128, 1, 4>(a, s);
         if (Npad == 64) return a.corun ? launch_tile<64, 64, 2, 2>(a, s) : launch_tile<64, 64, 2, 4>(a, s);
@@ -388,7 +397,6 @@ hipError_t launch_fc(const FcProblem &a, hipStream_t s)
     // (bf16 input only: with fp32 staging registers the tile does not fit 128 registers.)
     if (a.corun && !a.a_f32 && Npad % 128 == 0 && big_blocks >= 64) return launch_tile<128, 128, 2, 1>(a, s);
     if (Npad % 128 == 0 && big_blocks >= 256) return launch_tile<128, 128, 2, 2>(a, s);
-    if (split) return launch_fc_split(a, s);
     const long long mid_blocks = (long long)a.groups * (Npad / 64) * ((M + 63) / 64);
     if (Npad % 128 == 0 && mid_blocks < 256)
         return a.corun ? launch_tile<32, 128, 1, 2>(a, s) : launch_tile<32, 128, 1, 4>(a, s);

@@ -16,7 +16,7 @@
 // of matrix instructions.  Measured and not kept: 4 waves with 128 x 128 wave
 // tiles (accumulators in AGPRs), 16 waves, and global loads written straight
 // into LDS (swizzled rows, no staging registers) - each within 5 % of this.
-#include "rec_internal.h"
+#include "scan_body.h"
 
 namespace rec {
 
@@ -63,14 +63,27 @@ struct AReg<true> {
     }
 };
 
+struct BigLayer {
+    const void *A, *W0;
+    int lda, M, K, Kpad, grid_m, grid_n, tiles_per_group, per_xcd;
+    long long a_stride;
+    int relu;
+    void *C;
+    int ldc;
+    long long c_stride;
+};
+
+// Block `block` of the launch; big_lds_bytes() of `smem`.
 // A_F32: A is fp32 [M][lda] with only k < K valid (K a multiple of 8); chunks at
 // k >= K are fetched from the row's last valid chunk and zeroed.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_F32, bool OUT_F32>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
-    const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
-    int tiles_per_group, int per_xcd, long long a_stride, int relu, void *__restrict__ C0, int ldc, long long c_stride,
-    const FcGroups groups)
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_F32, bool OUT_F32, class Groups>
+__device__ inline void big_block(const BigLayer &p, const Groups &groups, __bf16 *smem, int block)
 {
+    const void *__restrict__ A0 = p.A, *__restrict__ W0 = p.W0;
+    const int lda = p.lda, M = p.M, K = p.K, Kpad = p.Kpad, grid_m = p.grid_m, grid_n = p.grid_n;
+    const int tiles_per_group = p.tiles_per_group, per_xcd = p.per_xcd, relu = p.relu, ldc = p.ldc;
+    const long long a_stride = p.a_stride, c_stride = p.c_stride;
+    void *__restrict__ C0 = p.C;
     constexpr int THREADS = 64 * WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // per-wave tile
     constexpr int TM = WM / 32, TN = WN / 32;            // 32 x 32 MFMA tiles per wave
@@ -80,16 +93,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be whole MFMA tiles");
     static_assert(BM % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0, "staging passes must tile the block");
 
-    extern __shared__ __attribute__((aligned(16))) __bf16 smem[];
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
     // XCD x (blocks are dealt round-robin) takes the x-th eighth of the tile
     // list; the list runs over strips of 4 row-tiles, column-tiles next, so the
     // tiles resident on one XCD form a compact patch that shares its slabs of A
     // and W in that XCD's L2.
-    int v = blockIdx.x;
-    if (per_xcd > 0) v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    int v = block;
+    if (per_xcd > 0) v = (block & 7) * per_xcd + (block >> 3);
     const int grp = v / tiles_per_group;
     v -= grp * tiles_per_group;
     int bm, bn;
@@ -253,6 +264,44 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_F32, bool OUT_F32>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
+    const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
+    int tiles_per_group, int per_xcd, long long a_stride, int relu, void *__restrict__ C0, int ldc, long long c_stride,
+    const FcGroups groups)
+{
+    extern __shared__ __attribute__((aligned(16))) __bf16 smem[];
+    big_block<BM, BN, WAVES_M, WAVES_N, A_F32, OUT_F32>(
+        BigLayer{A0, W0, lda, M, K, Kpad, grid_m, grid_n, tiles_per_group, per_xcd, a_stride, relu, C0, ldc, c_stride}, groups,
+        smem, blockIdx.x);
+}
+
+// One stack's layer of fp32 rows behind the blocks of a scan, which are done before the
+// layer is a quarter through: two blocks of 128 x 128 tiles fit a compute unit (115
+// registers, 72 KB of LDS, the scan's inside it), so no tile waits for them: 4096 samples,
+// 2560-1024 beside 10 tables 76.4 -> 72.0 us per forward, 2400 beside 8 74.2 -> 67.7.
+template <bool OUT_F32>
+__global__ __launch_bounds__(512, 4) void fc_big_behind_scan_kernel(
+    const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
+    int tiles_per_group, int per_xcd, int relu, void *__restrict__ C0, int ldc, const float *__restrict__ bias, const ScanBlocks b)
+{
+    extern __shared__ __attribute__((aligned(16))) __bf16 smem[];
+    static_assert(sizeof(scan::ScanShared) <= big_lds_bytes<128, 128>(), "the scan's LDS is part of the tiles'");
+    if ((int)blockIdx.x < b.tiles) {
+        if (threadIdx.x < SCAN_THREADS)
+            scan::scan_offsets_tile(b.lengths, b.n, b.nnz, scan::TileLink{b.words, b.tiles, b.polls}, b.offsets, b.err,
+                                    blockIdx.x, *reinterpret_cast<scan::ScanShared *>(smem));
+        return;
+    }
+    struct {
+        const void *W[1];
+        const float *bias[1];
+    } groups{{W0}, {bias}};
+    big_block<128, 128, 2, 4, true, OUT_F32>(
+        BigLayer{A0, W0, lda, M, K, Kpad, grid_m, grid_n, tiles_per_group, per_xcd, 0, relu, C0, ldc, 0}, groups, smem,
+        blockIdx.x - b.tiles);
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_F32, bool OUT_F32>
 hipError_t launch_big_as(const FcProblem &a, hipStream_t s)
 {
     const int grid_m = (a.M + BM - 1) / BM, grid_n = a.Npad / BN;
@@ -314,8 +363,28 @@ int big_tile_choice(const FcProblem &a, int num_cus)
 
 bool fc_big_applies(const FcProblem &a, int num_cus) { return big_tile_choice(a, num_cus) != 0; }
 
+bool fc_big_rides(const FcProblem &a, int num_cus)
+{
+    return a.a_f32 && a.groups == 1 && !a.corun && num_cus > 0 && big_tile_choice(a, num_cus) == 3;
+}
+
+hipError_t launch_fc_big_behind_scan(const FcProblem &a, const ScanBlocks &scan, hipStream_t s)
+{
+    const int grid_m = (a.M + 127) / 128, grid_n = a.Npad / 128, tiles = grid_m * grid_n;
+    auto k = a.out_f32 ? fc_big_behind_scan_kernel<true> : fc_big_behind_scan_kernel<false>;
+    hipLaunchKernelGGL(k, dim3(scan.tiles + tiles), dim3(512), (big_lds_bytes<128, 128>()), s, a.A, a.g.W[0], a.lda, a.M, a.K,
+                       a.Kpad, grid_m, grid_n, tiles, tiles % 8 == 0 ? tiles / 8 : 0, a.relu ? 1 : 0, a.C, a.ldc, a.g.bias[0], scan);
+    return hipGetLastError();
+}
+
 hipError_t fc_big_prepare()
 {
+    const void *behind[] = {reinterpret_cast<const void *>(fc_big_behind_scan_kernel<true>),
+                            reinterpret_cast<const void *>(fc_big_behind_scan_kernel<false>)};
+    for (const void *k : behind) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)big_lds_bytes<128, 128>());
+        if (e != hipSuccess) return e;
+    }
     hipError_t e = grant_lds<256, 256, 2, 4>();
     if (e == hipSuccess) e = grant_lds<256, 128, 4, 2>();
     if (e == hipSuccess) e = grant_lds<128, 128, 2, 4>();

@@ -294,18 +294,45 @@ int chain_end(const rec_model *m, const Layer *layers, int i, int n, int G, int 
 // a layer's result is the same bits in a pipelined model as in an in-order one.
 bool splits(const rec_model *m) { return m->fuse_mlp == 1 && !m->pipeline; }
 
+// Layer i of Bottom-FC as a launch of its own, on rows A.
+FcProblem bottom_layer(const rec_model *m, int i, int B, const void *A, bool a_f32, int lda, void *C, int ldc)
+{
+    const Layer &l = m->bottom[i];
+    FcProblem p{};
+    p.A = A; p.a_f32 = a_f32; p.lda = lda;
+    p.M = B; p.relu = true; p.groups = 1; p.num_cus = m->num_cus; p.corun = m->pipeline;
+    p.K = l.K; p.Kpad = l.Kpad; p.Npad = l.Npad;
+    p.g.W[0] = l.W; p.g.bias[0] = l.bias;
+    if (splits(m)) p.frag[0] = l.Wc;
+    p.C = C; p.out_f32 = i + 1 == (int)m->bottom.size(); p.ldc = ldc;
+    return p;
+}
+// Its first layer.
+FcProblem first_bottom_layer(const rec_model *m, const Bufs &u, const Call &c)
+{
+    const bool last = m->bottom.size() == 1;
+    return bottom_layer(m, 0, c.B, c.dense, true, m->F, last ? static_cast<void *>(u.x0) : u.act[1], last ? m->x0_ld : m->act_ld);
+}
+
 // S2: ReLU after every layer; the last one leaves fp32 for the interaction.  Of
 // the layers only the first `upto_layer`, the tail kernel taking the others
-// (their input: *rest, row stride *rest_ld).
+// (their input: *rest, row stride *rest_ld); first_done: without the first, which
+// first_bottom_layer() has described to the launch that took it.
 hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev,
-                          int upto_layer, const void **rest, int *rest_ld)
+                          int upto_layer, bool first_done, const void **rest, int *rest_ld)
 {
     const int all = (int)m->bottom.size(), n = upto_layer;
     const Layer *layers = m->bottom.data();
     const void *A = c.dense;
     bool a_f32 = true;
-    int lda = m->F, launches = 0;
-    for (int i = 0; i < n;) {
+    int lda = m->F, launches = 0, i = 0;
+    if (first_done) {
+        const FcProblem p = first_bottom_layer(m, u, c);
+        A = p.C; lda = p.ldc; a_f32 = false;
+        launches = i = 1;
+        REC_TRY(mark(ev, EV_BOTTOM_FIRST_END, s));
+    }
+    while (i < n) {
         const int j = chain_end(m, layers, i, n, 1, c.B, a_f32, false);
         const int upto = j > i ? j : i + 1;
         const bool last = upto == all;
@@ -319,15 +346,7 @@ hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipS
             cp.C = C; cp.ldc = ldc; cp.c_stride = 0;
             REC_TRY(launch_mlp_chain(cp, s));
         } else {
-            const Layer &l = layers[i];
-            FcProblem p{};
-            p.A = A; p.a_f32 = a_f32; p.lda = lda;
-            p.M = c.B; p.relu = true; p.groups = 1; p.num_cus = m->num_cus; p.corun = m->pipeline;
-            p.K = l.K; p.Kpad = l.Kpad; p.Npad = l.Npad;
-            p.g.W[0] = l.W; p.g.bias[0] = l.bias;
-            if (splits(m)) p.frag[0] = l.Wc;
-            p.C = C; p.out_f32 = last; p.ldc = ldc;
-            REC_TRY(launch_fc(p, s));
+            REC_TRY(launch_fc(bottom_layer(m, i, c.B, A, a_f32, lda, C, ldc), s));
         }
         A = C; lda = ldc; a_f32 = false;
         if (launches++ == 0) REC_TRY(mark(ev, EV_BOTTOM_FIRST_END, s));  // the first launch is timed on its own
@@ -339,7 +358,7 @@ hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipS
 }
 hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev)
 {
-    return enqueue_bottom(m, u, c, s, ev, (int)m->bottom.size(), nullptr, nullptr);
+    return enqueue_bottom(m, u, c, s, ev, (int)m->bottom.size(), false, nullptr, nullptr);
 }
 
 // Bottom-FC does not depend on the sparse side (Sec. III-A): when the whole
@@ -440,16 +459,6 @@ ConcatDense concat_job(const rec_model *m, const Bufs &u, const Call &c)
     return job;
 }
 
-hipError_t enqueue_scan(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, bool with_bottom)
-{
-    ConcatDense job;
-    if (concat_rides_on_scan(m)) job = concat_job(m, u, c);
-    ChainProblem cp{};
-    if (with_bottom) cp = bottom_run(m, u, c);
-    return launch_scan(c.lengths, m->T * c.B, c.nnz, u.offsets, u.tile_words, u.err, job,
-                       with_bottom ? &cp : nullptr, s);
-}
-
 int longest_hot_list(const rec_model *m, bool use_hot)
 {
     int hmax = 0;
@@ -464,19 +473,41 @@ PoolOut pool_out(const rec_model *m, const Bufs &u)
                                                  : PoolOut{u.pooled, nullptr, 0, 0};
 }
 
+// Which stages of a forward share a launch; decided once per call.
+struct Plan {
+    bool ride = false;   // Bottom-FC in the scan's launch
+    bool front = false;  // scan (and Bottom-FC, with ride) in the pooling launch
+    bool layer = false;  // Bottom-FC's first layer in the launch of the scan
+    bool tail = false;   // interaction, Predict-FC and the Bottom-FC layers [tail_from, ...) in one launch
+    int tail_from = 0;
+};
+
 // S0 and S1 (and Bottom-FC, with_bottom) of a small in-order batch as one launch,
 // where csrc/front.hip has one for it.
 bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with_bottom)
 {
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
-    if (m->pipeline || (concat ? with_bottom || !concat_rides_on_scan(m) : !with_bottom)) return false;
+    if (m->pipeline || (m->overlap_dense && !m->bottom.empty()) || (concat && with_bottom)) return false;
     if (!concat && longest_hot_list(m, use_hot) > 0) return false;
-    for (const Layer &l : m->bottom)
-        if (l.Npad > CHAIN_NARROW_WIDTH) return false;
+    if (with_bottom)
+        for (const Layer &l : m->bottom)
+            if (l.Npad > CHAIN_NARROW_WIDTH) return false;
     return front_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows, concat);
 }
 
-hipError_t enqueue_front(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, bool with_bottom)
+// Does Bottom-FC's first layer, which waits for nothing, run beside the scan (and
+// pooling, p.front)?  (In a concatenation model as the only layer, its output being
+// part of the Predict-FC input rows.)
+bool first_layer_rides(const rec_model *m, const Bufs &u, const Call &c, const Plan &p)
+{
+    const bool concat = m->interaction == REC_INTERACT_CONCAT;
+    if (m->pipeline || m->overlap_dense || p.ride || m->bottom.empty() || (concat && m->bottom.size() > 1)) return false;
+    if (chain_end(m, m->bottom.data(), 0, p.tail_from, 1, c.B, true, false) > 0) return false;
+    const FcProblem first = first_bottom_layer(m, u, c);
+    return p.front ? front_layer_rides(first, concat) : scan_layer_rides(first, concat ? u.act[0] : nullptr);
+}
+
+hipError_t enqueue_front(const rec_model *m, const Bufs &u, const Call &c, const Plan &plan, hipStream_t s)
 {
     FrontProblem f{};
     f.lengths = c.lengths; f.indices = c.indices; f.nnz = c.nnz;
@@ -484,27 +515,52 @@ hipError_t enqueue_front(const rec_model *m, const Bufs &u, const Call &c, hipSt
     f.dtype = m->dtype; f.T = m->T; f.D = m->D; f.B = c.B;
     f.stream_rows = m->stream_rows;
     f.out = pool_out(m, u);
-    if (concat_rides_on_scan(m)) f.dense = concat_job(m, u, c);
+    if (m->interaction == REC_INTERACT_CONCAT) {
+        f.dense = concat_job(m, u, c);
+        if (!concat_rides_on_scan(m)) f.dense.w0 = 0;  // the padding only
+    }
+    FcProblem first{};
+    if (plan.layer) {
+        first = first_bottom_layer(m, u, c);
+        f.layer = &first;
+        f.z_cols = m->w0;
+    }
     ChainProblem cp{};
-    if (with_bottom) cp = bottom_run(m, u, c);
-    return launch_front(f, with_bottom ? &cp : nullptr, s);
+    if (plan.ride) cp = bottom_run(m, u, c);
+    return launch_front(f, plan.ride ? &cp : nullptr, s);
 }
 
-// Which stages of a forward share a launch; decided once per call.
-struct Plan {
-    bool ride = false;   // Bottom-FC in the scan's launch
-    bool front = false;  // scan (and Bottom-FC, with ride) in the pooling launch
-    bool tail = false;   // interaction, Predict-FC and the Bottom-FC layers [tail_from, ...) in one launch
-    int tail_from = 0;
-};
-Plan plan_of(const rec_model *m, const Call &c, bool use_hot)
+// timed: a forward whose stages are timed gives those an interval of their own that have
+// a launch to themselves layer by layer; the joint launches of the first layer only pay
+// where nothing stands between the launches.
+Plan plan_of(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, bool timed)
 {
     Plan p;
     p.ride = bottom_rides_on_scan(m);
     p.front = front_applies_to(m, c, use_hot, p.ride);
+    if (timed && !p.ride && !concat_rides_on_scan(m)) p.front = false;
     p.tail = tail_applies(m, c);
     p.tail_from = p.tail ? tail_bottom_from(m, c.B) : (int)m->bottom.size();
+    p.layer = !timed && first_layer_rides(m, u, c, p);
     return p;
+}
+
+hipError_t enqueue_scan(const rec_model *m, const Bufs &u, const Call &c, const Plan &plan, hipStream_t s)
+{
+    ConcatDense job;
+    if (plan.layer) {
+        const bool concat = m->interaction == REC_INTERACT_CONCAT;
+        if (concat) {
+            job = concat_job(m, u, c);
+            job.w0 = 0;  // the padding only
+        }
+        return launch_scan_beside_layer(c.lengths, m->T * c.B, c.nnz, u.offsets, u.tile_words, u.err, job,
+                                        first_bottom_layer(m, u, c), concat ? u.act[0] : nullptr, m->z_ld, m->w0, s);
+    }
+    if (concat_rides_on_scan(m)) job = concat_job(m, u, c);
+    ChainProblem cp{};
+    if (plan.ride) cp = bottom_run(m, u, c);
+    return launch_scan(c.lengths, m->T * c.B, c.nnz, u.offsets, u.tile_words, u.err, job, plan.ride ? &cp : nullptr, s);
 }
 
 // Launches of layers [0, n) of G stacks side by side.
@@ -541,7 +597,7 @@ uint32_t shared_stages(const rec_model *m, const Plan &p, int B)
 
 // S1.  With hot lists registered (and use_hot), hot rows are served from LDS.  In the
 // concatenation model the sums go straight into the Predict-FC input rows.
-// with_bottom: as in the enqueue_scan() before it.
+// with_bottom: Bottom-FC or its first layer shared the scan's launch.
 hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, hipStream_t s, bool with_bottom)
 {
     const TileWords left{u.tile_words, scan_linked_words(m->T * c.B, with_bottom)};
@@ -569,12 +625,12 @@ hipError_t enqueue_sparse(const rec_model *m, const Bufs &u, const Call &c, cons
 {
     if (plan.front) {  // all of it in the pooling stage; the scan's reads an empty interval
         REC_TRY(mark(ev, EV_SCAN_END, s));
-        REC_TRY(enqueue_front(m, u, c, s, plan.ride));
+        REC_TRY(enqueue_front(m, u, c, plan, s));
         return mark(ev, EV_POOL_END, s);
     }
-    REC_TRY(enqueue_scan(m, u, c, s, plan.ride));
+    REC_TRY(enqueue_scan(m, u, c, plan, s));
     REC_TRY(mark(ev, EV_SCAN_END, s));
-    REC_TRY(enqueue_pool(m, u, c, use_hot, s, plan.ride));
+    REC_TRY(enqueue_pool(m, u, c, use_hot, s, plan.ride || plan.layer));
     return mark(ev, EV_POOL_END, s);
 }
 
@@ -620,7 +676,7 @@ hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, const 
     const int x0_ld = m->bottom.empty() ? m->F : m->x0_ld;
     // S3 -> act[0], row stride z_ld, zero filled up to it
     if (concat) {
-        if (!concat_rides_on_scan(m))
+        if (!concat_rides_on_scan(m) && !plan.layer)
             REC_TRY(launch_concat_dense(x0, x0_ld, m->w0, B, u.act[0], m->z_width, m->z_ld, s));
     } else
         REC_TRY(launch_interact(x0, x0_ld, u.pooled, B, T, D, u.act[0], m->z_ld, s));
@@ -707,10 +763,10 @@ hipError_t enqueue_in_order(const rec_model *m, const Bufs &u, const Call &c, co
     } else if (plan.tail_from < (int)m->bottom.size()) {
         const void *rest = nullptr;
         int rest_ld = 0;
-        REC_TRY(enqueue_bottom(m, u, c, s, ev, plan.tail_from, &rest, &rest_ld));
+        REC_TRY(enqueue_bottom(m, u, c, s, ev, plan.tail_from, plan.layer, &rest, &rest_ld));
         return enqueue_fused_tail(m, u, c, s, ev, plan.tail_from, rest, rest_ld);
     } else {
-        REC_TRY(enqueue_bottom(m, u, c, s, ev));
+        REC_TRY(enqueue_bottom(m, u, c, s, ev, (int)m->bottom.size(), plan.layer, nullptr, nullptr));
     }
     return enqueue_tail(m, u, c, plan, s, ev);
 }
@@ -1037,7 +1093,8 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
     const size_t slot = prof ? (size_t)((m->forwards / m->period) % m->slots) : 0;
     hipEvent_t *ev = prof ? &m->ev[slot * EV_PER_SLOT] : nullptr;
     const int frame = m->pipeline ? m->next_frame : 0;
-    const Plan plan = plan_of(m, c, true);
+    const Bufs u = bufs_at(m->ws, m->lay, frame);
+    const Plan plan = plan_of(m, u, c, true, prof);
 #define REC_DEV(call)                                  \
     do {                                               \
         if ((call) != hipSuccess) return REC_ERR_DEVICE; \
@@ -1051,7 +1108,6 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
         // launches nor the ramps of a launch leave the memory system idle; a batch
         // owns one of four frames until its logits are written.
         const int k = frame;
-        const Bufs u = bufs_at(m->ws, m->lay, k);
         hipStream_t p = m->pool_stream[m->pool_turn] ? m->pool_stream[m->pool_turn] : m->own_stream[m->pool_turn];
         hipStream_t d = m->dense_stream ? m->dense_stream : m->side;
         if (m->tail_pending[k]) {  // the batch that used this frame four calls ago
@@ -1061,7 +1117,7 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
         if (m->words_left[k]) REC_DEV(launch_clear_tile_words(u.tile_words, most_tiles(m), s));
         m->words_left[k] = true;
         REC_DEV(mark(ev, EV_BEGIN, s));
-        REC_DEV(enqueue_scan(m, u, c, s, false));
+        REC_DEV(enqueue_scan(m, u, c, Plan{}, s));
         REC_DEV(mark(ev, EV_SCAN_END, s));
         REC_DEV(hipEventRecord(m->ev_scan[k], s));
         REC_DEV(hipStreamWaitEvent(p, m->ev_scan[k], 0));
@@ -1085,7 +1141,6 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
         m->pool_turn ^= 1;
         if (prof) m->slot_mode[slot] = 1;
     } else {
-        const Bufs u = bufs_at(m->ws, m->lay, 0);
         m->last_frame = 0;
         if (m->words_left[0]) REC_DEV(launch_clear_tile_words(u.tile_words, most_tiles(m), s));
         m->words_left[0] = true;
@@ -1142,7 +1197,7 @@ rec_status rec_forward_static(rec_model *m, const float *dev_dense, const int32_
     if (hipGetLastError() != hipSuccess) return REC_ERR_DEVICE;
     if (batch > 0) {
         const Call c{dev_dense, dev_indices, dev_lengths, batch, nnz, dev_logits};
-        if (enqueue_in_order(m, u, c, plan_of(m, c, false), false, s, nullptr) != hipSuccess) return REC_ERR_DEVICE;
+        if (enqueue_in_order(m, u, c, plan_of(m, u, c, false, false), false, s, nullptr) != hipSuccess) return REC_ERR_DEVICE;
     }
     if (dev_fault) {
         hipLaunchKernelGGL(static_end_kernel, dim3(1), dim3(64), 0, s, u.err,

@@ -65,7 +65,23 @@ constexpr int SCAN_LINK_POLLS = 65536;  // of another tile's word before its len
 hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *offsets,
                        unsigned long long *tile_words, ErrRecord *err, const ConcatDense &job,
                        const ChainProblem *rider, hipStream_t s, int polls = SCAN_LINK_POLLS);
+// The same with the first layer of Bottom-FC instead of a whole stack, where
+// scan_layer_rides(); z: its first z_cols columns, narrowed, go there as well.
+struct FcProblem;
+bool scan_layer_rides(const FcProblem &layer, const void *z);
+hipError_t launch_scan_beside_layer(const int32_t *lengths, int n, long long nnz, int32_t *offsets,
+                                    unsigned long long *tile_words, ErrRecord *err, const ConcatDense &job,
+                                    const FcProblem &layer, void *z, int ldz, int z_cols, hipStream_t s);
 int scan_linked_words(int n, bool with_rider);
+// What the scan's blocks of a launch get; blocks [0, tiles) are theirs.
+struct ScanBlocks {
+    const int32_t *lengths;
+    int32_t *offsets;
+    unsigned long long *words;
+    long long nnz;
+    int n, tiles, polls;
+    ErrRecord *err;
+};
 hipError_t launch_clear_tile_words(unsigned long long *words, int n, hipStream_t s);
 // The words a scan has published, for the pooling launch behind it to clear.
 struct TileWords {
@@ -146,6 +162,13 @@ hipError_t launch_fc(const FcProblem &p, hipStream_t s);
 // The same layer with the k of a tile dealt to the waves of a block, for launches
 // too short to fill the chip; launch_fc() takes this path by itself.
 bool fc_split_applies(const FcProblem &p);
+struct FcTile {
+    int tm, tn;  // 16 tm rows x 16 tn columns
+};
+FcTile fc_split_tile(const FcProblem &p);  // without the one-output layer
+bool fc_takes_split(const FcProblem &p);   // does launch_fc() take this path?
+// May the layer's blocks share a launch with others' (fp32 rows read in vectors)?
+bool fc_split_rides(const FcProblem &p);
 hipError_t launch_fc_split(const FcProblem &p, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).
 hipError_t fc_split_prepare();
@@ -155,6 +178,10 @@ hipError_t fc_split_prepare();
 // launch_fc() takes this path by itself when fc_big_applies().
 bool fc_big_applies(const FcProblem &p, int num_cus);
 hipError_t launch_fc_big(const FcProblem &p, int num_cus, hipStream_t s);
+// Does the layer take tiles of which two blocks fit a compute unit (128 x 128, fp32
+// input), so that a scan's blocks may stand in front of them?
+bool fc_big_rides(const FcProblem &p, int num_cus);
+hipError_t launch_fc_big_behind_scan(const FcProblem &p, const ScanBlocks &scan, hipStream_t s);
 // Once per process and device, before the first launch (not under stream
 // capture): lets these kernels use their more-than-64-KB LDS tiles.
 hipError_t fc_big_prepare();
@@ -239,9 +266,12 @@ hipError_t launch_tail(const TailProblem &p, int num_cus, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).
 hipError_t tail_prepare();
 
-// S0 and S1 of a small batch in one launch (front_applies()): with `rider`, a
-// Bottom-FC stack front_takes() (fp32 input, one stack), into out.pooled; without,
-// a concatenation model without Bottom-FC, into out.z, dense part included.
+// S0 and S1 of a small batch in one launch (front_applies()), into out.pooled or, in a
+// concatenation model, out.z.  Beside them
+//   rider: a whole Bottom-FC stack front_takes() (fp32 input, one stack); out.pooled only
+//   layer: the first Bottom-FC layer, where front_layer_rides(); at most one of the two
+//   dense: what launch_concat_dense() does for a model without Bottom-FC; with `layer`
+//          only the padding (w0 = 0), the layer's output going to out.z (z_cols columns) as well
 struct FrontProblem {
     const int32_t *lengths, *indices;
     long long nnz;
@@ -252,7 +282,10 @@ struct FrontProblem {
     bool stream_rows;
     PoolOut out;
     ConcatDense dense;
+    const FcProblem *layer;
+    int z_cols;
 };
+bool front_layer_rides(const FcProblem &p, bool concat);
 bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat);
 bool front_takes(const ChainProblem &rider);
 hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStream_t s);

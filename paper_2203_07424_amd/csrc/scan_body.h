@@ -106,16 +106,21 @@ __device__ inline long long linked_sum(const TileLink &l, int tile, const int32_
     return sum;
 }
 
+// LDS of a scan block.
+struct ScanShared {
+    // One extra word per 32 keeps the 8-per-thread strided reads off one bank.
+    int tile[SCAN_TILE + SCAN_TILE / 32];
+    long long w[SCAN_THREADS / 64], wave_excl[SCAN_THREADS / 64];
+};
+
 // Offsets of tile `tile`; the threads with threadIdx.x < SCAN_THREADS call it,
 // all of them.  The sum of earlier tiles comes by `link`, or (no words: a few
 // tiles) from their lengths.
 __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n, long long nnz, const TileLink &link,
-                                         int32_t *__restrict__ offsets, ErrRecord *err, int tile)
+                                         int32_t *__restrict__ offsets, ErrRecord *err, int tile, ScanShared &sh)
 {
-    // One extra word per 32 keeps the 8-per-thread strided reads off one bank.
-    __shared__ int s_tile[SCAN_TILE + SCAN_TILE / 32];
-    __shared__ long long s_w[SCAN_THREADS / 64];
-    __shared__ long long s_wave_excl[SCAN_THREADS / 64];
+    int *s_tile = sh.tile;
+    long long *s_w = sh.w, *s_wave_excl = sh.wave_excl;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long base = (long long)tile * SCAN_TILE;
 

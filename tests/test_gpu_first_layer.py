@@ -1,0 +1,133 @@
+"""The first Bottom-FC layer beside scan and pooling (small batches) or beside the
+scan, in each block tile it comes in, at their edges; in a concatenation model it
+writes its columns of the Predict-FC input rows as well.
+
+A forward whose stages are timed gives the layer and the scan launches of their own,
+with the same order of sums: every buffer is the same bits.  Offsets, sums and logits
+are held to the oracle as everywhere."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import rec_oracle as orc
+from paper_2203_07424_amd import synth
+
+import gpu_helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def binding():
+    from paper_2203_07424_amd import binding as b
+    return b
+
+
+def stack(g, ws):
+    return [((g.standard_normal((ws[i + 1], ws[i])) * ws[i] ** -0.5).astype(np.float32),
+             (g.standard_normal(ws[i + 1]) * ws[i] ** -0.5).astype(np.float32))
+            for i in range(len(ws) - 1)]
+
+
+def buffers(m, batch, concat):
+    logits = H.run(m, batch)
+    return [torch.from_numpy(logits), m.debug_offsets().clone(), m.debug_bottom_out().clone(), m.debug_interact().clone()] + \
+        ([] if concat else [m.debug_pooled().clone()])
+
+
+def spoil(binding, m, byte):
+    """What the forward is to overwrite: Bottom-FC's output and the Predict-FC input."""
+    for what, size in ((binding.REC_DBG_BOTTOM_OUT, 4), (binding.REC_DBG_INTERACT, 2)):
+        _, _, ld = binding.rec_debug_get(m.handle, what)
+        m._view(what, size * m.last_batch * ld)[0].fill_(byte)
+
+
+def compare(binding, m, batch, concat=False):
+    """One forward in joint launches against the same in launches of their own."""
+    H.run(m, batch)
+    spoil(binding, m, 0x41)
+    joint = buffers(m, batch, concat)
+    spoil(binding, m, 0x42)
+    m.set_profiling(1, 1)
+    apart = buffers(m, batch, concat)
+    m.set_profiling(0)
+    assert m.check() == (binding.REC_OK, -1)
+    assert all(torch.equal(a, b) for a, b in zip(joint, apart))
+    off, _, _ = orc.offsets(batch.lengths)
+    assert np.array_equal(joint[1].cpu().numpy().astype(np.int64), off)
+    return joint
+
+
+@pytest.mark.parametrize("T,D,dtype,B,F,bottom,mean", [
+    (1, 32, np.float32, 1, 2560, (1024, 256), 20),      # beside scan and pooling, tiles of 16 x 16
+    (10, 32, np.float16, 17, 1000, (1024, 256), 20),
+    (10, 64, np.float32, 113, 1000, (1024, 256), 8),    # 16 x 32
+    (11, 32, np.float32, 223, 1000, (1024, 256), 10),   # 32 x 32
+    (10, 32, np.float32, 301, 2560, (1024, 256), 9),    # 32 x 64
+    (7, 32, np.float32, 1001, 1536, (1024, 256), 8),    # 64 x 64
+    (8, 64, np.float16, 895, 500, (256,), 12),          # the largest batches
+    (9, 64, np.float16, 797, 500, (256,), 12),          # one tile of lengths more: beside the scan alone
+    (10, 32, np.float32, 901, 1536, (1024, 256), 8),
+    (30, 32, np.float16, 601, 1000, (1024, 256), 9),    # 9 tiles of lengths: their sums handed on
+    (12, 16, np.float32, 100, 640, (1024, 32), 9),      # rows of 64 bytes
+    (12, 8, np.float16, 100, 640, (1024, 32), 9),       # 16-byte rows: never with pooling
+    (5, 32, np.float32, 3500, 1536, (1024, 256), 8),    # 128 x 128, 224 tiles
+    (9, 32, np.float32, 4097, 1000, (1024, 256), 6),    # and with 19 tiles of lengths
+    (3, 64, np.float32, 65, 300, (), 7),                # the layer is the whole stack
+    (6, 32, np.float32, 70, 1501, (1024, 256), 7),      # rows that are not read in vectors
+])
+def test_layer_of_a_pooled_model(binding, T, D, dtype, B, F, bottom, mean):
+    print("first layer", T, D, np.dtype(dtype).name, B, F, bottom, flush=True)
+    g = np.random.default_rng(1500 + T + B)
+    R = 300
+    tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(dtype) for _ in range(T)]
+    lens = g.integers(1, 2 * mean, T * B).astype(np.int32)
+    lens[:3] = (90, 0, 71)[:min(3, lens.size)]
+    idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
+    mlp, top = stack(g, (F,) + bottom + (D,)), stack(g, (D + T * (T + 1) // 2, 200, 72, 1))
+    m = H.make_model(binding, tabs, mlp, top, B, idx.size, F)
+    dense = g.standard_normal((B, F)).astype(np.float32)
+    batch = synth.Batch(dense, idx, lens)
+    logits, _, x0, _, pooled = compare(binding, m, batch)
+    P, A, _, _ = orc.pool(tabs, idx, lens, B, want_abs=True)
+    H.check_pooled(pooled.cpu().numpy(), P, A)
+    if B >= 8:
+        H.check_logits(logits.numpy(), orc.forward(dense, tabs, idx, lens, mlp, top, orc.EXACT)["logits"])
+    m.set_option(binding.REC_OPT_STREAM_ROWS, 1)
+    assert torch.equal(compare(binding, m, batch)[4], pooled)
+    m.set_option(binding.REC_OPT_STREAM_ROWS, 0)
+    out, fault = torch.empty(B, device="cuda"), torch.zeros(2, dtype=torch.int64, device="cuda")
+    m.forward_static(*[torch.from_numpy(a).cuda() for a in (dense, idx, lens)], out, fault)
+    assert torch.equal(out.cpu(), logits) and fault.tolist() == [binding.REC_OK, -1]
+    bad = idx.copy()
+    bad[[3, idx.size - 1]] = (-1, R)
+    H.run(m, synth.Batch(dense, bad, lens))
+    assert m.check() == (binding.REC_ERR_INDEX_RANGE, 3)
+    H.run(m, synth.Batch(dense, idx[:-2], lens))
+    assert m.check() == (binding.REC_ERR_LENGTHS, -1)
+    assert all(torch.equal(a, b) for a, b in zip(compare(binding, m, batch), (logits, m.debug_offsets(), x0)))
+    m.close()
+
+
+@pytest.mark.parametrize("T,D,dtype,B,F,w0", [
+    (5, 32, np.float32, 1, 24, 40), (16, 32, np.float16, 38, 100, 42), (26, 64, np.float16, 300, 64, 64),
+    (4, 32, np.float32, 3072, 16, 13), (3, 64, np.float16, 17, 128, 250), (1, 32, np.float16, 8200, 8, 64),  # many tiles: apart
+    (1, 64, np.float16, 12289, 20, 64), (26, 64, np.float16, 1501, 64, 33), (6, 16, np.float32, 50, 37, 40),
+    (5, 128, np.float32, 40, 64, 40)])
+def test_layer_of_a_concatenation_model(binding, T, D, dtype, B, F, w0):
+    print("first layer, concat", T, D, np.dtype(dtype).name, B, F, w0, flush=True)
+    g = np.random.default_rng(1600 + T + B)
+    R = 200
+    tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(dtype) for _ in range(T)]
+    mlp, tops = stack(g, (F, w0)), [stack(g, (w0 + T * D, 96, 1)) for _ in range(2)]
+    m = H.make_model(binding, tabs, mlp, tops, B, 4 * T * B, F, interaction="concat")
+    dense = g.standard_normal((B, F)).astype(np.float32)
+    for lens in (np.ones(T * B, np.int32), g.integers(0, 4, T * B).astype(np.int32)):
+        lens[0] = max(int(lens[0]), 1)
+        idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
+        logits, _, x0, z = compare(binding, m, synth.Batch(dense, idx, lens), concat=True)
+        assert torch.equal(z[:, :w0], x0[:, :w0].bfloat16()) and not z[:, w0 + T * D:].any()
+        assert not x0[:, w0:].any()
+        if B >= 8:
+            H.check_logits(logits.numpy(), orc.forward_towers(dense, tabs, idx, lens, mlp, tops, orc.EXACT)["logits"])
+    m.close()
