@@ -33,9 +33,13 @@ template <int TM, int TN, int WN, int WK, int IN, int OUT>
 __global__ __launch_bounds__(64 * WN * WK, TM * TN >= 16 || (IN != IN_BF16 && TM * TN >= 8) ? 2 : 4) void fc_split_kernel(
     const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
     int m_fast, int per_xcd, int n_groups, int relu, long long a_stride, void *__restrict__ C0, int ldc,
-    long long c_stride, float *__restrict__ dot_out, int dot_ld, const SplitGroups<MAX_GROUPS> groups)
+    long long c_stride, float *__restrict__ dot_out, int dot_ld, const SplitGroups<MAX_GROUPS> groups, const FaultReport report)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    if (OUT == CHAIN_OUT_DOT && (int)blockIdx.x == 8 * per_xcd) {
+        report_fault(report.err, report.fault);
+        return;
+    }
     split_block<TM, TN, WN, WK, IN, OUT>(SplitLayer{A0, W0, lda, M, K, Kpad, grid_m, grid_n, m_fast, per_xcd, n_groups, relu,
                                                     a_stride, C0, ldc, c_stride, dot_out, dot_ld, 0, nullptr, 0, 0},
                                          groups, smem, blockIdx.x);
@@ -47,9 +51,9 @@ hipError_t launch_as(const FcProblem &a, hipStream_t s)
     SplitGroups<MAX_GROUPS> g{};
     for (int i = 0; i < a.groups; ++i) g.s[i] = SplitStack{a.frag[i], a.g.bias[i], a.g.dot_w[i], a.g.dot_bias[i]};
     const SplitLayer p = layer_in_tiles(a, TM, TN, WN);
-    hipLaunchKernelGGL((fc_split_kernel<TM, TN, WN, WK, IN, OUT>), dim3(8 * p.per_xcd), dim3(64 * WN * WK),
+    hipLaunchKernelGGL((fc_split_kernel<TM, TN, WN, WK, IN, OUT>), dim3(8 * p.per_xcd + report_blocks(a.report)), dim3(64 * WN * WK),
                        (split_lds_bytes<TM, TN, WN, WK>()), s, p.A, p.W0, p.lda, p.M, p.K, p.Kpad, p.grid_m, p.grid_n,
-                       p.m_fast, p.per_xcd, p.n_groups, p.relu, p.a_stride, p.C, p.ldc, p.c_stride, p.dot_out, p.dot_ld, g);
+                       p.m_fast, p.per_xcd, p.n_groups, p.relu, p.a_stride, p.C, p.ldc, p.c_stride, p.dot_out, p.dot_ld, g, a.report);
     return hipGetLastError();
 }
 

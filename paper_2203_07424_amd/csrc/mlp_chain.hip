@@ -37,10 +37,14 @@ namespace {
 using namespace chain;
 
 template <bool A_F32, int RT, int MAXC>
-__global__ __launch_bounds__(CH_THREADS, waves_per_simd<MAXC>()) void mlp_chain_kernel(int blocks, int per_group, const ChainProblem a)
+__global__ __launch_bounds__(CH_THREADS, waves_per_simd<MAXC>()) void mlp_chain_kernel(int blocks, int per_group, const ChainProblem a, const FaultReport report)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    touch_args<8 + sizeof(a)>();
+    touch_args<8 + sizeof(a) + sizeof(report)>();
+    if ((int)blockIdx.x == blocks) {
+        report_fault(report.err, report.fault);
+        return;
+    }
     // Blocks run over the samples of stack 0, then stack 1, ...; XCD x (blocks are
     // dealt round-robin) takes the x-th eighth of that list, so that its L2 holds
     // the weights of one stack or two instead of all of them.
@@ -86,11 +90,11 @@ hipError_t prepare_as()
 }
 
 template <bool A_F32, int RT, int MAXC>
-hipError_t launch_as(const ChainProblem &a, hipStream_t s)
+hipError_t launch_as(const ChainProblem &a, const FaultReport &report, hipStream_t s)
 {
     const int per_group = (a.M + rows_of<RT>() - 1) / rows_of<RT>();
-    hipLaunchKernelGGL((mlp_chain_kernel<A_F32, RT, MAXC>), dim3(per_group * a.groups), dim3(CH_THREADS),
-                       (chain_lds_bytes<RT>(a.ld_lds)), s, per_group * a.groups, per_group, a);
+    hipLaunchKernelGGL((mlp_chain_kernel<A_F32, RT, MAXC>), dim3(per_group * a.groups + report_blocks(report)), dim3(CH_THREADS),
+                       (chain_lds_bytes<RT>(a.ld_lds)), s, per_group * a.groups, per_group, a, report);
     return hipGetLastError();
 }
 
@@ -140,15 +144,15 @@ int chain_two_tile_rounds(int groups, int M, int num_cus)
     return 4 * blocks >= 3 * rounds * num_cus ? (int)rounds : 0;
 }
 
-hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s)
+hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s, const FaultReport &report)
 {
     if (p.M <= 0) return hipSuccess;
     ChainProblem a;
     const hipError_t e = chain_finalize(p, a);
     if (e != hipSuccess) return e;
-    if (narrow_run(a)) return a.a_f32 ? launch_as<true, 1, 1>(a, s) : launch_as<false, 1, 1>(a, s);
-    if (a.a_f32) return launch_as<true, 1, 4>(a, s);
-    return chain_two_tile_rounds(a.groups, a.M, a.num_cus) > 0 ? launch_as<false, 2, 4>(a, s) : launch_as<false, 1, 4>(a, s);
+    if (narrow_run(a)) return a.a_f32 ? launch_as<true, 1, 1>(a, report, s) : launch_as<false, 1, 1>(a, report, s);
+    if (a.a_f32) return launch_as<true, 1, 4>(a, report, s);
+    return chain_two_tile_rounds(a.groups, a.M, a.num_cus) > 0 ? launch_as<false, 2, 4>(a, report, s) : launch_as<false, 1, 4>(a, report, s);
 }
 
 hipError_t launch_pack_chain(const float *W, int N, int K, int Npad, int Kpad, void *W_packed, hipStream_t s)

@@ -210,6 +210,7 @@ struct Call {
     int B;
     long long nnz;
     float *logits;
+    FaultReport *report;  // rec_forward_static(): where the call's faults go; handed (fault nulled) to the launch that reports them
 };
 
 // Stage events of one timed forward (null: not timed).  Slot i of the array is
@@ -634,6 +635,15 @@ hipError_t enqueue_sparse(const rec_model *m, const Bufs &u, const Call &c, cons
     return mark(ev, EV_POOL_END, s);
 }
 
+// The report of call c, for the launch that is to make it.
+FaultReport take_report(const Call &c)
+{
+    if (!c.report) return FaultReport{};
+    const FaultReport r = *c.report;
+    c.report->fault = nullptr;
+    return r;
+}
+
 // S3 and S4 in one launch, behind the Bottom-FC layers [from, ...) on `rest`.
 hipError_t enqueue_fused_tail(const rec_model *m, const Bufs &u, const Call &c, hipStream_t s, hipEvent_t *ev,
                               int from, const void *rest, int rest_ld)
@@ -652,6 +662,7 @@ hipError_t enqueue_fused_tail(const rec_model *m, const Bufs &u, const Call &c, 
     t.ldx0 = nb ? m->x0_ld : m->F;
     t.pooled = u.pooled; t.T = m->T; t.D = m->D;
     t.z = u.act[0]; t.ldz = m->z_ld;
+    t.report = take_report(c);
     t.run[1].A = u.act[0]; t.run[1].lda = m->z_ld; t.run[1].M = c.B;
     chain_run(m->top.data(), m->n_top, 1, 0, n, m->num_cus, t.run[1]);
     t.run[1].out_mode = CHAIN_OUT_DOT;
@@ -716,7 +727,7 @@ hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, const 
                 cp.C = u.act[1 + (launches & 1)]; cp.ldc = G * layers[j - 1].Npad; cp.c_stride = layers[j - 1].Npad;
                 p.A = cp.C; p.lda = cp.ldc; p.a_stride = cp.c_stride; p.a_f32 = false;
             }
-            REC_TRY(launch_mlp_chain(cp, s));
+            REC_TRY(launch_mlp_chain(cp, s, done ? take_report(c) : FaultReport{}));
             i = j;
         } else {
             for (int k = 0; k < G; ++k) {
@@ -729,6 +740,7 @@ hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, const 
             if (feeds_dot && fc_can_fuse_dot(l.Npad)) {
                 p.C = nullptr; p.out_f32 = false; p.ldc = 0; p.c_stride = 0;
                 p.dot_out = c.logits; p.dot_ld = G;
+                if (fc_takes_split(p)) p.report = take_report(c);
                 REC_TRY(launch_fc(p, s));
                 done = true;
             } else {
@@ -820,21 +832,9 @@ __global__ __launch_bounds__(256) void static_begin_kernel(const StaticTables st
     }
 }
 
-// fault[0] = the status rec_check() would give for this call, fault[1] = its position.
 __global__ __launch_bounds__(64) void static_end_kernel(const ErrRecord *err, long long *fault)
 {
-    if (threadIdx.x != 0) return;
-    const unsigned flags = err->flags;
-    long long st = REC_OK, pos = -1;
-    if (flags & (ERR_NEG_LENGTH | ERR_TOTAL_MISMATCH)) {
-        st = REC_ERR_LENGTHS;
-        if (flags & ERR_NEG_LENGTH) pos = (long long)err->first_bad_len;
-    } else if (flags & ERR_INDEX_RANGE) {
-        st = REC_ERR_INDEX_RANGE;
-        pos = (long long)err->first_bad_idx;
-    }
-    fault[0] = st;
-    fault[1] = pos;
+    report_fault(err, fault);
 }
 
 // Host-checkable faults of a forward call.
@@ -1086,7 +1086,7 @@ rec_status rec_forward(rec_model *m, const float *dev_dense, const int32_t *dev_
     if (st != REC_OK || batch == 0) return st;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const Call c{dev_dense, dev_indices, dev_lengths, batch, nnz, dev_logits};
+    const Call c{dev_dense, dev_indices, dev_lengths, batch, nnz, dev_logits, nullptr};
     // Forward number i is timed when i is a multiple of the period; it is the
     // (i / period)-th timed one.
     const bool prof = m->slots > 0 && m->forwards % m->period == 0;
@@ -1195,13 +1195,13 @@ rec_status rec_forward_static(rec_model *m, const float *dev_dense, const int32_
     hipLaunchKernelGGL(static_begin_kernel, dim3(1), dim3(256), 0, s, tabs, m->T, const_cast<TableDesc *>(u.tables),
                        u.err, u.tile_words, (int)(((size_t)m->T * batch + SCAN_TILE - 1) / SCAN_TILE));
     if (hipGetLastError() != hipSuccess) return REC_ERR_DEVICE;
+    FaultReport report{u.err, reinterpret_cast<long long *>(dev_fault)};
     if (batch > 0) {
-        const Call c{dev_dense, dev_indices, dev_lengths, batch, nnz, dev_logits};
+        const Call c{dev_dense, dev_indices, dev_lengths, batch, nnz, dev_logits, &report};
         if (enqueue_in_order(m, u, c, plan_of(m, u, c, false, false), false, s, nullptr) != hipSuccess) return REC_ERR_DEVICE;
     }
-    if (dev_fault) {
-        hipLaunchKernelGGL(static_end_kernel, dim3(1), dim3(64), 0, s, u.err,
-                           reinterpret_cast<long long *>(dev_fault));
+    if (report.fault) {  // no launch took it
+        hipLaunchKernelGGL(static_end_kernel, dim3(1), dim3(64), 0, s, report.err, report.fault);
         if (hipGetLastError() != hipSuccess) return REC_ERR_DEVICE;
     }
     return REC_OK;

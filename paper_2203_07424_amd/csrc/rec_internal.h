@@ -20,6 +20,31 @@ struct ErrRecord {
 };
 enum : unsigned int { ERR_NEG_LENGTH = 1u, ERR_TOTAL_MISMATCH = 2u, ERR_INDEX_RANGE = 4u };
 
+// What the launch that ends a forward may do besides (fault not null): fault[0] = the
+// status rec_check() would give, fault[1] = its position.  A launch of one thread for it
+// took 2.5 us behind the last one.
+struct FaultReport {
+    const ErrRecord *err = nullptr;
+    long long *fault = nullptr;
+};
+// In a launch behind pooling's: a block of its own, so that nothing else waits for the record.
+inline int report_blocks(const FaultReport &r) { return r.fault ? 1 : 0; }
+__device__ inline void report_fault(const ErrRecord *err, long long *fault)
+{
+    if (threadIdx.x != 0) return;
+    const unsigned flags = err->flags;
+    long long st = REC_OK, pos = -1;
+    if (flags & (ERR_NEG_LENGTH | ERR_TOTAL_MISMATCH)) {
+        st = REC_ERR_LENGTHS;
+        if (flags & ERR_NEG_LENGTH) pos = (long long)err->first_bad_len;
+    } else if (flags & ERR_INDEX_RANGE) {
+        st = REC_ERR_INDEX_RANGE;
+        pos = (long long)err->first_bad_idx;
+    }
+    fault[0] = st;
+    fault[1] = pos;
+}
+
 struct TableDesc {
     const void *base;
     long long rows;
@@ -152,6 +177,7 @@ struct FcProblem {
     float *dot_out; int dot_ld;
     int num_cus;  // compute units of the device; 0 = unknown (never picks the wide-tile kernels)
     bool corun;   // the launch will share the device with a pooling launch: keep register use low
+    FaultReport report;  // with dot_out and fc_takes_split(): made on the way
     // Each stack's weights in the order of launch_pack_chain(), for the kernels that deal
     // a tile's k to the waves of a block (sums in another order); null: not these.
     const void *frag[MAX_GROUPS];
@@ -237,7 +263,7 @@ bool chain_layer_fits(int Kpad, int Npad, int max_input = CHAIN_MAX_WIDTH);
 int chain_two_tile_rounds(int groups, int M, int num_cus);
 // Checks p and completes it (LDS row pitch, whether wide input loads apply) into a.
 hipError_t chain_finalize(const ChainProblem &p, ChainProblem &a, int max_input = CHAIN_MAX_WIDTH);
-hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s);
+hipError_t launch_mlp_chain(const ChainProblem &p, hipStream_t s, const FaultReport &report = FaultReport{});
 // Once per process and device, before the first launch (not under stream capture).
 hipError_t chain_prepare();
 // fp32 [N][K] -> bf16 [Npad * Kpad] in MFMA fragment order (nearest even, zero padded).
@@ -255,6 +281,7 @@ struct TailProblem {
     const float *pooled;
     int T, D;
     void *z; int ldz;
+    FaultReport report;  // made on the way
     int rows, ld_lds;  // filled in by launch_tail()
 };
 bool tail_fits(int T, int D);

@@ -37,6 +37,7 @@ struct TailArgs {
     const float *pooled;
     void *z;
     int ldx0, T, ldz, rows, ld_lds, blocks;
+    FaultReport report;
 };
 
 template <int NBLK, int KST, int MAXC>
@@ -47,6 +48,10 @@ __global__ __launch_bounds__(CH_THREADS) void tail_kernel(const TailArgs p)
     touch_args<sizeof(TailArgs)>();
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = p.rows, row0 = blockIdx.x * rows;
+    if ((int)blockIdx.x == p.blocks) {
+        report_fault(p.report.err, p.report.fault);
+        return;
+    }
     const int ld = p.ld_lds;
     __bf16 *X = reinterpret_cast<__bf16 *>(smem);                        // [rows][ld]
     float *x0s = reinterpret_cast<float *>(X + (size_t)rows * ld);      // [rows][D], with a Bottom-FC part
@@ -103,8 +108,8 @@ hipError_t launch_as(const TailProblem &p, int num_cus, hipStream_t s)
 {
     const int blocks = (p.run[1].M + p.rows - 1) / p.rows, grid = blocks < num_cus ? num_cus : blocks;
     auto k = narrow_run(p.run[0]) && narrow_run(p.run[1]) ? tail_kernel<NBLK, KST, 1> : tail_kernel<NBLK, KST, 4>;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(CH_THREADS), tail_lds_bytes(p), s,
-                       TailArgs{{one_stack(p.run[0]), one_stack(p.run[1])}, p.x0, p.pooled, p.z, p.ldx0, p.T, p.ldz, p.rows, p.ld_lds, grid});
+    hipLaunchKernelGGL(k, dim3(grid + report_blocks(p.report)), dim3(CH_THREADS), tail_lds_bytes(p), s,
+                       TailArgs{{one_stack(p.run[0]), one_stack(p.run[1])}, p.x0, p.pooled, p.z, p.ldx0, p.T, p.ldz, p.rows, p.ld_lds, grid, p.report});
     return hipGetLastError();
 }
 
