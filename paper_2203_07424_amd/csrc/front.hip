@@ -110,11 +110,9 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
                                                           BagTable{B, magic}, T, one, err, out);
 }
 
-constexpr int fc_waves_per_simd(int tm, int tn) { return tm < 2 ? 6 : tm * tn < 8 ? 4 : 2; }
-
-// TM = 0: no layer.
-template <int LPR, bool HALF, bool STREAM, int TM, int TN>
-__global__ __launch_bounds__(64 * split::rider_waves(TM), fc_waves_per_simd(TM, TN)) void front_fc_kernel(
+// A block has the WK waves of the layer's tile.  TM = 0: no layer.
+template <int LPR, bool HALF, bool STREAM, int TM, int TN, int WK>
+__global__ __launch_bounds__(64 * WK, TM < 2 ? 6 : TN < 4 ? 4 : WK == 8 ? 4 : 2) void front_fc_kernel(
     const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     long long nnz, int n, int tiles, int fc_blocks, int per, unsigned B, unsigned magic, int T, float one,
     int32_t *__restrict__ offsets, ErrRecord *err, const PoolOut out, const Rider a)
@@ -129,12 +127,12 @@ __global__ __launch_bounds__(64 * split::rider_waves(TM), fc_waves_per_simd(TM, 
     if constexpr (TM > 0) {
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         if (b < fc_blocks) {
-            split::split_block<TM, TN, 1, split::rider_waves(TM), split::IN_F32, split::OUT_EITHER>(a.p, a.g, smem, b);
+            split::split_block<TM, TN, 1, WK, split::IN_F32, split::OUT_EITHER>(a.p, a.g, smem, b);
             return;
         }
         b -= fc_blocks;
     }
-    pool_from_lengths<split::rider_waves(TM), LPR, HALF, STREAM>(len, tables, indices, nnz, n, b, per, BagTable{B, magic}, T, one,
+    pool_from_lengths<WK, LPR, HALF, STREAM>(len, tables, indices, nnz, n, b, per, BagTable{B, magic}, T, one,
                                                          err, out);
 }
 
@@ -224,10 +222,9 @@ hipError_t launch_long(const FrontProblem &f, const ChainProblem &a, hipStream_t
     return hipGetLastError();
 }
 
-template <int LPR, bool HALF, int TM, int TN>
+template <int LPR, bool HALF, int TM, int TN, int WAVES>
 hipError_t launch_fc_beside(const FrontProblem &f, hipStream_t s)
 {
-    constexpr int WAVES = split::rider_waves(TM);
     const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
     const int pool_blocks = ((n + WAVES - 1) / WAVES + 7) / 8 * 8;
     const BagTable div = BagTable::of_batch(f.B);
@@ -238,7 +235,7 @@ hipError_t launch_fc_beside(const FrontProblem &f, hipStream_t s)
         lds = split::split_lds_bytes<TM, TN, 1, WAVES>();
     }
     const int fc_blocks = 8 * a.p.per_xcd;
-    auto k = f.stream_rows ? front_fc_kernel<LPR, HALF, true, TM, TN> : front_fc_kernel<LPR, HALF, false, TM, TN>;
+    auto k = f.stream_rows ? front_fc_kernel<LPR, HALF, true, TM, TN, WAVES> : front_fc_kernel<LPR, HALF, false, TM, TN, WAVES>;
     hipLaunchKernelGGL(k, dim3(tiles + fc_blocks + pool_blocks), dim3(WAVES * 64), lds, s, f.lengths, f.tables, f.indices,
                        f.nnz, n, tiles, fc_blocks, pool_blocks / 8, div.B, div.magic, f.T, 1.0f, f.offsets, f.err, f.out, a);
     return hipGetLastError();
@@ -247,11 +244,18 @@ hipError_t launch_fc_beside(const FrontProblem &f, hipStream_t s)
 template <int LPR, bool HALF>
 hipError_t launch_fc_front(const FrontProblem &f, hipStream_t s)
 {
-    if (!f.layer) return launch_fc_beside<LPR, HALF, 0, 0>(f, s);
+    if (!f.layer) return launch_fc_beside<LPR, HALF, 0, 0, 8>(f, s);
     const FcTile t = fc_split_tile(*f.layer);
-    if (t.tm == 1) return t.tn == 1 ? launch_fc_beside<LPR, HALF, 1, 1>(f, s) : launch_fc_beside<LPR, HALF, 1, 2>(f, s);
-    if (t.tm == 2) return t.tn == 2 ? launch_fc_beside<LPR, HALF, 2, 2>(f, s) : launch_fc_beside<LPR, HALF, 2, 4>(f, s);
-    return launch_fc_beside<LPR, HALF, 4, 4>(f, s);
+    switch (t.tm * 100 + t.tn * 10 + t.wk) {
+    case 118: return launch_fc_beside<LPR, HALF, 1, 1, 8>(f, s);
+    case 128: return launch_fc_beside<LPR, HALF, 1, 2, 8>(f, s);
+    case 224: return launch_fc_beside<LPR, HALF, 2, 2, 4>(f, s);
+    case 228: return launch_fc_beside<LPR, HALF, 2, 2, 8>(f, s);
+    case 248: return launch_fc_beside<LPR, HALF, 2, 4, 8>(f, s);
+    case 244: return launch_fc_beside<LPR, HALF, 2, 4, 4>(f, s);
+    case 444: return launch_fc_beside<LPR, HALF, 4, 4, 4>(f, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int LPR, bool HALF>
@@ -313,10 +317,15 @@ hipError_t front_prepare()
     return e;
 }
 
-// Beside short bags a layer rides along in tiles of 16 x 32, where these are few.
+// Beside short bags a layer rides along in tiles of 16 x 32, where these are few; else
+// in the tiles whose LDS, which every block of a launch gets, leaves pooling more than
+// a block a compute unit.
 bool front_layer_rides(const FcProblem &a, bool concat)
 {
-    return fc_split_rides(a) && (!concat || (long long)((a.M + 15) / 16) * (a.Npad / 32) <= 512);
+    if (!fc_split_rides(a)) return false;
+    if (concat) return (long long)((a.M + 15) / 16) * (a.Npad / 32) <= 512;
+    const FcTile t = fc_split_tile(a);
+    return t.tm == 1 || t.tm == 2 || (t.tm == 4 && t.wk == 4);
 }
 
 bool front_takes(const ChainProblem &rider) { return chain::narrow_run(rider); }

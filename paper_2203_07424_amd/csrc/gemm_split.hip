@@ -61,9 +61,19 @@ template <int IN, int OUT>
 hipError_t launch_tiles(const FcProblem &a, hipStream_t s)
 {
     const FcTile t = fc_split_tile(a);
-    if (t.tm == 1) return t.tn == 1 ? launch_as<1, 1, 1, 8, IN, OUT>(a, s) : launch_as<1, 2, 1, 8, IN, OUT>(a, s);
-    if (t.tm == 2) return t.tn == 2 ? launch_as<2, 2, 1, 4, IN, OUT>(a, s) : launch_as<2, 4, 1, 4, IN, OUT>(a, s);
-    return launch_as<4, 4, 1, 4, IN, OUT>(a, s);
+    switch (t.tm * 100 + t.tn * 10 + t.wk) {
+    case 118: return launch_as<1, 1, 1, 8, IN, OUT>(a, s);
+    case 128: return launch_as<1, 2, 1, 8, IN, OUT>(a, s);
+    case 224: return launch_as<2, 2, 1, 4, IN, OUT>(a, s);
+    case 228: return launch_as<2, 2, 1, 8, IN, OUT>(a, s);
+    case 244: return launch_as<2, 4, 1, 4, IN, OUT>(a, s);
+    case 248: return launch_as<2, 4, 1, 8, IN, OUT>(a, s);
+    case 348: return launch_as<3, 4, 1, 8, IN, OUT>(a, s);
+    case 444: return launch_as<4, 4, 1, 4, IN, OUT>(a, s);
+    case 448: return launch_as<4, 4, 1, 8, IN, OUT>(a, s);
+    case 548: return launch_as<5, 4, 1, 8, IN, OUT>(a, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 // With the one-output layer: a block has all columns, and as many rows as still give
@@ -86,44 +96,75 @@ hipError_t launch_in(const FcProblem &a, hipStream_t s)
     return a.out_f32 ? launch_tiles<IN, CHAIN_OUT_F32>(a, s) : launch_tiles<IN, CHAIN_OUT_BF16>(a, s);
 }
 
-template <int TM>
-hipError_t prepare_dot()
+template <int TM, int TN, int WN, int WK, int IN, int OUT>
+hipError_t grant_lds()
 {
-    constexpr size_t lds = split_lds_bytes<TM, 4, 4, 2>();
-    const void *kernels[] = {reinterpret_cast<const void *>(fc_split_kernel<TM, 4, 4, 2, IN_BF16, CHAIN_OUT_DOT>),
-                             reinterpret_cast<const void *>(fc_split_kernel<TM, 4, 4, 2, IN_F32, CHAIN_OUT_DOT>),
-                             reinterpret_cast<const void *>(fc_split_kernel<TM, 4, 4, 2, IN_F32_ANY, CHAIN_OUT_DOT>)};
-    for (const void *k : kernels) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    constexpr size_t lds = split_lds_bytes<TM, TN, WN, WK>();
+    if (lds <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(fc_split_kernel<TM, TN, WN, WK, IN, OUT>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+template <int TM, int IN>
+hipError_t prepare_tiles()
+{
+    const hipError_t e = grant_lds<TM, 4, 1, 8, IN, CHAIN_OUT_BF16>();
+    return e == hipSuccess ? grant_lds<TM, 4, 1, 8, IN, CHAIN_OUT_F32>() : e;
+}
+
+template <int IN>
+hipError_t prepare_in()
+{
+    hipError_t e = grant_lds<4, 4, 4, 2, IN, CHAIN_OUT_DOT>();
+    if (e == hipSuccess) e = prepare_tiles<3, IN>();
+    if (e == hipSuccess) e = prepare_tiles<4, IN>();
+    if (e == hipSuccess) e = prepare_tiles<5, IN>();
+    return e;
 }
 
 }  // namespace
 
-// The tile whose blocks bring the least through the busiest compute unit's L1: rounds
-// of blocks times bytes of both operands per k.  Tiles of 64 x 64 count a fifth more
-// (300 samples, four towers of 1728 -> 1024: 12.5 in 32 x 64, 13.6 in 64 x 64).
+// A compute unit spends its time bringing both operands of its blocks through its L1
+// (about 40 bytes a clock) and, once, on the trips of a first block that nothing covers: rounds
+// of blocks plus about one, times the rows and columns of a tile.  With one block a
+// compute unit eight waves share its k, else four, and two blocks cover one another's trips;
+// tiles of 48 and 80 rows, one block a compute unit at a time, pay that once more in every
+// round.  us per launch (64 x 64 or 32 x 64 with four waves, the choice without these two /
+// now): 300 samples, four of 1728 -> 1024 14.8 / 11.2 (80 rows, 256 blocks), 1024 -> 512
+// 7.4 / 6.3 (48 rows, 224), two of 1728 -> 1024 10.7 / 8.4; 2560 fp32 -> 1024, 300 samples 11.8 / 10.2,
+// 700 17.7 / 14.6, 1200 24.2 / 20.8.  Blocks of 96 rows never won.
 FcTile fc_split_tile(const FcProblem &a)
 {
+    struct Form {
+        int tm, tn, wk1, wk, once1, once;  // waves and uncovered part (tenths of a round), in one round and in several
+    };
+    static const Form forms[] = {{1, 1, 8, 8, 10, 11}, {1, 2, 8, 8, 10, 11}, {2, 2, 8, 4, 10, 11}, {2, 4, 8, 4, 10, 11},
+                                 {3, 4, 8, 8, 11, 14}, {4, 4, 8, 4, 11, 11}, {5, 4, 8, 8, 11, 18}};
     const int cus = a.num_cus > 0 ? a.num_cus : 256;
-    static const FcTile tiles[] = {{1, 1}, {1, 2}, {2, 2}, {2, 4}, {4, 4}};
-    FcTile best{0, 0};
+    FcTile best{0, 0, 0};
     long long least = 0;
-    for (const FcTile &t : tiles) {
-        const long long blocks = (long long)((a.M + 16 * t.tm - 1) / (16 * t.tm)) * (a.Npad / (16 * t.tn)) * a.groups;
-        long long cost = (blocks + cus - 1) / cus * (t.tm * (a.a_f32 ? 2 : 1) + t.tn) * 5;
-        if (t.tm == 4) cost = cost * 6 / 5;
+    for (const Form &f : forms) {
+        const long long blocks = (long long)((a.M + 16 * f.tm - 1) / (16 * f.tm)) * (a.Npad / (16 * f.tn)) * a.groups;
+        const long long rounds = (blocks + cus - 1) / cus;
+        const long long cost = (f.tm * (a.a_f32 ? 2 : 1) + f.tn) * (10 * rounds + (rounds == 1 ? f.once1 : f.once));
         if (best.tm == 0 || cost < least) {
-            best = t;
+            // Eight waves with a unit each gain nothing, and most fp32 layers run beside pooling,
+            // whose waves four leave more room (500 samples, 256 blocks 32.8 / 30.8 us per forward).
+            const bool four = a.Kpad <= 8 * UNIT || (a.a_f32 && f.tn == 4 && 4 * blocks > 3 * cus);
+            best = FcTile{f.tm, f.tn, rounds > 1 || (four && f.tm == 2) ? f.wk : f.wk1};
             least = cost;
         }
     }
     return best;
 }
 
-hipError_t fc_split_prepare() { return prepare_dot<4>(); }
+hipError_t fc_split_prepare()
+{
+    hipError_t e = prepare_in<IN_BF16>();
+    if (e == hipSuccess) e = prepare_in<IN_F32>();
+    if (e == hipSuccess) e = prepare_in<IN_F32_ANY>();
+    return e;
+}
 
 bool fc_split_applies(const FcProblem &a)
 {

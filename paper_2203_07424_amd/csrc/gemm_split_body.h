@@ -77,10 +77,15 @@ struct RowUnit {
     }
 };
 
+// Partial tiles that are in LDS at a time: where all of them are more than 64 KB those of the
+// upper half of the waves are added to the lower half's first.
+template <int TM, int TN, int WN, int WK>
+constexpr int partial_tiles() { return WK >= 8 && WN * WK * TM * TN > 64 ? WK / 2 : WK; }
+
 template <int TM, int TN, int WN, int WK>
 constexpr size_t split_lds_bytes()
 {
-    constexpr size_t stage = (size_t)WN * WK * TM * 16 * SP_LD * 2, sums = (size_t)WN * WK * TM * TN * 1024;
+    constexpr size_t stage = (size_t)WN * WK * TM * 16 * SP_LD * 2, sums = (size_t)WN * partial_tiles<TM, TN, WN, WK>() * TM * TN * 1024;
     return stage > sums ? stage : sums;
 }
 
@@ -186,11 +191,24 @@ __device__ inline void split_block(const SplitLayer &p, const Groups &groups, un
     }
 
     __syncthreads();  // the staged rows are done with
-    f32x4 *sums = reinterpret_cast<f32x4 *>(smem);  // [WK][QUADS]
+    constexpr int PARTS = partial_tiles<TM, TN, WN, WK>();
+    f32x4 *sums = reinterpret_cast<f32x4 *>(smem);  // [PARTS][QUADS]
+    f32x4 *mine = sums + (wk % PARTS) * QUADS + wn * TM * TN * 64 + lane;
+    if (PARTS < WK) {
+        if (wk >= PARTS) {
 #pragma unroll
-    for (int j = 0; j < TM; ++j)
+            for (int i = 0; i < TM * TN; ++i) mine[i * 64] = acc[i / TN][i % TN];
+        }
+        __syncthreads();
+        if (wk < PARTS) {
 #pragma unroll
-        for (int t = 0; t < TN; ++t) sums[wk * QUADS + ((wn * TM + j) * TN + t) * 64 + lane] = acc[j][t];
+            for (int i = 0; i < TM * TN; ++i) acc[i / TN][i % TN] += mine[i * 64];
+        }
+    }
+    if (wk < PARTS) {
+#pragma unroll
+        for (int i = 0; i < TM * TN; ++i) mine[i * 64] = acc[i / TN][i % TN];
+    }
     __syncthreads();
     float part[MINE];
 #pragma unroll
@@ -199,7 +217,7 @@ __device__ inline void split_block(const SplitLayer &p, const Groups &groups, un
         if (i >= QUADS) break;
         f32x4 x = sums[i];
 #pragma unroll
-        for (int k = 1; k < WK; ++k) x += sums[k * QUADS + i];
+        for (int k = 1; k < PARTS; ++k) x += sums[k * QUADS + i];
         const int m = m0 + i / 64 / TN % TM * 16 + (lane & 15), n = quad_n(i);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -281,9 +299,6 @@ inline Rider rider_of(const FcProblem &a, int tm, int tn, void *z, int ldz, int 
     r.g.s[0] = SplitStack{a.frag[0], a.g.bias[0], nullptr, nullptr};
     return r;
 }
-// Waves of a block in tiles of 16 tm rows, as in the layer's own launch: the same sums.
-constexpr int rider_waves(int tm) { return tm >= 2 ? 4 : 8; }
-
 }  // namespace split
 }  // namespace rec
 #endif

@@ -543,6 +543,12 @@ Plan plan_of(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, boo
     p.tail = tail_applies(m, c);
     p.tail_from = p.tail ? tail_bottom_from(m, c.B) : (int)m->bottom.size();
     p.layer = !timed && first_layer_rides(m, u, c, p);
+    if (p.front && !p.layer && !timed) {  // a layer too large to run beside pooling still may beside the scan
+        Plan q = p;
+        q.front = false;
+        q.layer = first_layer_rides(m, u, c, q);
+        if (q.layer) return q;
+    }
     return p;
 }
 

@@ -190,6 +190,7 @@ hipError_t launch_fc(const FcProblem &p, hipStream_t s);
 bool fc_split_applies(const FcProblem &p);
 struct FcTile {
     int tm, tn;  // 16 tm rows x 16 tn columns
+    int wk;      // waves that share its k
 };
 FcTile fc_split_tile(const FcProblem &p);  // without the one-output layer
 bool fc_takes_split(const FcProblem &p);   // does launch_fc() take this path?

@@ -79,8 +79,8 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<MAXC>()) v
 // leave the chip idle.  1536-1024 beside 10 tables x 900 samples 42.5 -> 36.9 us per forward,
 // 500-256 beside 10 x 3000 51.5 -> 45.9; one 64-64 layer of a concatenation model, 26 x 4096
 // 104.8 -> 97.9.  Layers that take 128 x 128 tiles: fc_big_behind_scan_kernel.
-template <int TM, int TN>
-__global__ __launch_bounds__(64 * split::rider_waves(TM), TM * TN >= 8 ? 2 : 4) void scan_offsets_layer_kernel(
+template <int TM, int TN, int WK>
+__global__ __launch_bounds__(64 * WK, TM * TN >= 8 ? 2 : 4) void scan_offsets_layer_kernel(
     const int32_t *__restrict__ len, int32_t *__restrict__ offsets, unsigned long long *words, long long nnz, int n,
     int tiles, int polls, int extra, ErrRecord *err, const ConcatDense job, const split::Rider a)
 {
@@ -90,23 +90,28 @@ __global__ __launch_bounds__(64 * split::rider_waves(TM), TM * TN >= 8 ? 2 : 4) 
         __shared__ ScanShared sh;
         if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, TileLink{words, tiles, polls}, offsets, err, b, sh);
     } else if (b < tiles + extra) {
-        concat_dense_block<64 * split::rider_waves(TM)>(job, b - tiles, extra);
+        concat_dense_block<64 * WK>(job, b - tiles, extra);
     } else {
-        split::split_block<TM, TN, 1, split::rider_waves(TM), split::IN_F32, split::OUT_EITHER>(a.p, a.g, smem,
-                                                                                                b - tiles - extra);
+        split::split_block<TM, TN, 1, WK, split::IN_F32, split::OUT_EITHER>(a.p, a.g, smem, b - tiles - extra);
     }
 }
 
-template <int TM, int TN>
+template <int TM, int TN, int WK>
 hipError_t launch_beside(const ScanBlocks &b, int extra, const ConcatDense &job, const FcProblem &layer, void *z, int ldz,
                          int z_cols, hipStream_t s)
 {
     const split::Rider a = split::rider_of(layer, TM, TN, z, ldz, z_cols);
-    constexpr int WAVES = split::rider_waves(TM);
-    hipLaunchKernelGGL((scan_offsets_layer_kernel<TM, TN>), dim3(b.tiles + extra + 8 * a.p.per_xcd), dim3(64 * WAVES),
-                       (split::split_lds_bytes<TM, TN, 1, WAVES>()), s, b.lengths, b.offsets, b.words, b.nnz, b.n, b.tiles,
+    hipLaunchKernelGGL((scan_offsets_layer_kernel<TM, TN, WK>), dim3(b.tiles + extra + 8 * a.p.per_xcd), dim3(64 * WK),
+                       (split::split_lds_bytes<TM, TN, 1, WK>()), s, b.lengths, b.offsets, b.words, b.nnz, b.n, b.tiles,
                        b.polls, extra, b.err, job, a);
     return hipGetLastError();
+}
+
+template <int TM, int TN, int WK>
+hipError_t grant_layer_lds()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_layer_kernel<TM, TN, WK>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)split::split_lds_bytes<TM, TN, 1, WK>());
 }
 
 int concat_blocks(const ConcatDense &job)
@@ -133,8 +138,11 @@ hipError_t launch_clear_tile_words(unsigned long long *words, int n, hipStream_t
 hipError_t scan_prepare()
 {
     const int most = (int)chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<1>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<1>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e == hipSuccess) e = grant_layer_lds<3, 4, 8>();
+    if (e == hipSuccess) e = grant_layer_lds<4, 4, 8>();
+    if (e == hipSuccess) e = grant_layer_lds<5, 4, 8>();
     if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<4>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, most);
@@ -190,13 +198,19 @@ hipError_t launch_scan_beside_layer(const int32_t *lengths, int n, long long nnz
     if (!fc_split_rides(layer)) return job.x0 ? hipErrorInvalidValue : launch_fc_big_behind_scan(layer, b, s);
     const int extra = concat_blocks(job);
     const FcTile t = fc_split_tile(layer);
-    if (t.tm == 1)
-        return t.tn == 1 ? launch_beside<1, 1>(b, extra, job, layer, z, ldz, z_cols, s)
-                         : launch_beside<1, 2>(b, extra, job, layer, z, ldz, z_cols, s);
-    if (t.tm == 2)
-        return t.tn == 2 ? launch_beside<2, 2>(b, extra, job, layer, z, ldz, z_cols, s)
-                         : launch_beside<2, 4>(b, extra, job, layer, z, ldz, z_cols, s);
-    return launch_beside<4, 4>(b, extra, job, layer, z, ldz, z_cols, s);
+    switch (t.tm * 100 + t.tn * 10 + t.wk) {
+    case 118: return launch_beside<1, 1, 8>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 128: return launch_beside<1, 2, 8>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 224: return launch_beside<2, 2, 4>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 228: return launch_beside<2, 2, 8>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 244: return launch_beside<2, 4, 4>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 248: return launch_beside<2, 4, 8>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 348: return launch_beside<3, 4, 8>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 444: return launch_beside<4, 4, 4>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 448: return launch_beside<4, 4, 8>(b, extra, job, layer, z, ldz, z_cols, s);
+    case 548: return launch_beside<5, 4, 8>(b, extra, job, layer, z, ldz, z_cols, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace rec

@@ -69,6 +69,10 @@ def compare(binding, m, batch, concat=False):
     (9, 64, np.float16, 797, 500, (256,), 12),          # one tile of lengths more: beside the scan alone
     (10, 32, np.float32, 901, 1536, (1024, 256), 8),
     (30, 32, np.float16, 601, 1000, (1024, 256), 9),    # 9 tiles of lengths: their sums handed on
+    (9, 32, np.float16, 195, 2560, (1024, 256), 9),     # 32 x 32, eight waves
+    (10, 32, np.float32, 751, 2560, (1024, 256), 8),    # 48 x 64
+    (5, 32, np.float32, 1187, 1000, (1024, 256), 8),    # 80 x 64
+    (2, 64, np.float32, 1024, 1000, (512, 64), 9),      # 64 x 64, eight waves
     (12, 16, np.float32, 100, 640, (1024, 32), 9),      # rows of 64 bytes
     (12, 8, np.float16, 100, 640, (1024, 32), 9),       # 16-byte rows: never with pooling
     (5, 32, np.float32, 3500, 1536, (1024, 256), 8),    # 128 x 128, 224 tiles

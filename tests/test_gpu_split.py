@@ -55,6 +55,9 @@ def both(binding, m, batch):
     (31, 12, 64, 10, (640, 256), 2),
     (65, 30, 64, 100, (1100, 1000, 72), 2),
     (300, 26, 64, 64, (1024, 512, 256), 4),
+    (200, 26, 64, 64, (1024, 512, 256), 4),    # 64 rows a block, eight waves
+    (320, 26, 64, 64, (1024, 512, 256), 4),    # 80 rows, the last block full
+    (257, 10, 64, 40, (1100, 1000, 72), 3),    # 48 rows
     (300, 10, 64, 7, (448,), 8),               # the layer leaves fp32 for a dot kernel
     (1000, 20, 64, 33, (600, 200), 3),
 ])
