@@ -353,8 +353,8 @@ __global__ __launch_bounds__(256) void pack_fc_kernel(const float *__restrict__ 
 // Launches that do not fill the chip with 128 x 128 tiles deal the k of smaller tiles to
 // the waves of a block, and so does, at any size, a layer with the one-output layer behind
 // it (16384 samples, 512 -> 128 -> 1 10.7 / 7.6 us, 4096 x four of 512 -> 256 -> 1
-// 13 / 10.7).  Where the 128 x 128 tiles do fill it they win: 1000 samples, four of
-// 1728 -> 1024 26.8 / 28.1, 4096 samples 53 / 96.
+// 13 / 10.7).  Where larger tiles fill it they win (four of 1728 -> 1024, 4096 samples 53 / 96):
+// fc_big_applies() says from where on.
 bool fc_takes_split(const FcProblem &a)
 {
     if (!fc_split_applies(a)) return false;

@@ -344,10 +344,10 @@ hipError_t grant_lds()
 }
 
 // Which block tile, if any: 256 x 256, 256 x 128 (bf16 input) or 128 x 128, the
-// largest whose tiles still cover three quarters of the compute units.
+// largest whose tiles still cover three quarters of the compute units (the last: half, against many small ones).
 int big_tile_choice(const FcProblem &a, int num_cus)
 {
-    if (a.dot_out || a.M < 1024 || a.Kpad % BK != 0 || a.groups < 1 || a.groups > MAX_GROUPS) return 0;
+    if (a.dot_out || a.M < 512 || a.Kpad % BK != 0 || a.groups < 1 || a.groups > MAX_GROUPS) return 0;
     if (a.a_f32 && (a.K % 8 != 0 || a.lda % 4 != 0 || a.a_stride % 4 != 0 ||
                     reinterpret_cast<uintptr_t>(a.A) % 16 != 0))
         return 0;
@@ -355,7 +355,14 @@ int big_tile_choice(const FcProblem &a, int num_cus)
     const long long m256 = (a.M + 255) / 256, m128 = (a.M + 127) / 128;
     if (!a.a_f32 && a.Npad % 256 == 0 && a.groups * m256 * (a.Npad / 256) >= need) return 1;
     if (!a.a_f32 && a.Npad % 128 == 0 && a.groups * m256 * (a.Npad / 128) >= need) return 2;
-    if (a.Npad % 128 == 0 && a.groups * m128 * (a.Npad / 128) >= need) return 3;
+    const long long tiles = a.groups * m128 * (a.Npad / 128);
+    if (a.Npad % 128 == 0 && tiles >= need) return 3;
+    // One round of these, at least half full, against three and more of 64 x 64 tiles
+    // (csrc/gemm_split.hip).  us per forward, those / these: 2560 fp32 -> 1024, 2060 samples 66.8 / 61.4
+    // (136 tiles), 2400 69.7 / 62.5, 2900 70.6 / 64.2; four towers of 1728 -> 1024, 520 samples 42.5 /
+    // 42.1 (160), 600 47.7 / 44.0, 800 51.6 / 46.2; three, 900 51.7 / 44.7; with two rounds of 64 x 64
+    // (400 samples, 448 of them, 14 us a launch) half a round of these is no shorter.
+    if (a.Npad % 128 == 0 && 2 * tiles > num_cus && a.groups * ((a.M + 63) / 64) * (a.Npad / 64) > 2 * num_cus) return 3;
     return 0;
 }
 

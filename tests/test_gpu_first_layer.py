@@ -76,6 +76,7 @@ def compare(binding, m, batch, concat=False):
     (12, 16, np.float32, 100, 640, (1024, 32), 9),      # rows of 64 bytes
     (12, 8, np.float16, 100, 640, (1024, 32), 9),       # 16-byte rows: never with pooling
     (5, 32, np.float32, 3500, 1536, (1024, 256), 8),    # 128 x 128, 224 tiles
+    (4, 32, np.float32, 2049, 1000, (1024, 256), 7),    # 136
     (9, 32, np.float32, 4097, 1000, (1024, 256), 6),    # and with 19 tiles of lengths
     (3, 64, np.float32, 65, 300, (), 7),                # the layer is the whole stack
     (6, 32, np.float32, 70, 1501, (1024, 256), 7),      # rows that are not read in vectors

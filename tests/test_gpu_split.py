@@ -60,6 +60,7 @@ def both(binding, m, batch):
     (257, 10, 64, 40, (1100, 1000, 72), 3),    # 48 rows
     (300, 10, 64, 7, (448,), 8),               # the layer leaves fp32 for a dot kernel
     (1000, 20, 64, 33, (600, 200), 3),
+    (520, 26, 64, 64, (1024, 512, 256), 4),    # 160 tiles of 128 x 128 instead, then one round of 80 rows
 ])
 def test_towers_layer_by_layer(binding, B, T, D, F, hidden, towers):
     print("split towers", B, T, D, F, hidden, towers, flush=True)
