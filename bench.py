@@ -51,9 +51,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 matrix rate
 # of this run, and hold only for the kernel source the counters were taken with:
 # reported as null once csrc/pool.hip or csrc/pool_body.h differs.
 POOL_TRAFFIC = {
-    "sha256": "285c7f940111602c4608e88779e111ae1131e1c77cd717c2579d87a8bfd0146f",
-    ("rmc2", 4096): {"fetch_bytes": 553864462.4, "write_bytes": 41943680.0},
-    ("rmc2-uniform", 4096): {"fetch_bytes": 1721396654.3, "write_bytes": 41943680.0},
+    "sha256": "76d3a5fa6e11831727a962e385a03a9e8b71eed2491fbf1fb0063f793f40be35",
+    ("rmc2", 4096): {"fetch_bytes": 554007598.0, "write_bytes": 41943680.0},
+    ("rmc2-uniform", 4096): {"fetch_bytes": 1721427296.9, "write_bytes": 41943680.0},
 }
 
 
