@@ -12,6 +12,8 @@
  * the published peak and beside its own GEMMs.
  *
  * The offsets scan by itself, with the bound on its waits in the caller's hand.
+ *
+ * Which kernel a layer's launch takes (host code, no device).
  */
 #ifndef REC_PROBE_H
 #define REC_PROBE_H
@@ -48,6 +50,24 @@ REC_API rec_status rec_probe_mfma(int32_t random_operands, int32_t blocks, int32
  * [0, REC_SCAN_POLLS]. */
 REC_API rec_status rec_probe_scan(const int32_t *dev_lengths, int32_t n, int64_t nnz, int32_t *dev_offsets,
                           uint64_t *dev_words, int32_t polls, void *dev_err, void *stream);
+
+/* What rec_probe_fc_form() asks about (bits of `flags`) ... */
+enum {
+    REC_FC_F32_ROWS = 1,       /* the dense input: fp32 rows, 16-byte aligned */
+    REC_FC_DOT = 2,            /* the one-output layer folded into the launch */
+    REC_FC_BESIDE_POOLING = 4, /* a pipelined model's */
+    REC_FC_ANY_ORDER = 8       /* sums over k in any order: REC_OPT_FUSE_MLP 1, in order */
+};
+/* ... and form[0] of its answer: k-tile by k-tile; in tiles of 128 columns and more; the
+ * k of a tile dealt to the waves of a block. */
+enum { REC_FORM_TILES = 0, REC_FORM_WIDE = 1, REC_FORM_SPLIT = 2 };
+
+/* The form a launch of one FC layer takes: `rows` samples, `inputs` -> `outputs`
+ * features, `stacks` of them side by side, on a device of `compute_units`.
+ * form[1..2]: rows and columns of a block's tile, form[3]: waves that share its k
+ * (REC_FORM_TILES: zeros).  REC_ERR_ARG on a null pointer or counts that no layer has. */
+REC_API rec_status rec_probe_fc_form(int32_t rows, int32_t inputs, int32_t outputs, int32_t stacks, uint32_t flags,
+                          int32_t compute_units, int32_t *form);
 
 #ifdef __cplusplus
 }

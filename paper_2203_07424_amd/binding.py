@@ -40,12 +40,14 @@ REC_OPT_STREAM_ROWS = 1
 REC_OPT_FUSE_MLP = 2
 REC_OPT_PIPELINE = 3
 REC_NUM_STAGES = 7
+REC_FC_F32_ROWS, REC_FC_DOT, REC_FC_BESIDE_POOLING, REC_FC_ANY_ORDER = 1, 2, 4, 8
+REC_FORM_TILES, REC_FORM_WIDE, REC_FORM_SPLIT = 0, 1, 2
 STAGE_NAMES = ("scan", "pool", "bottom_first", "bottom_rest", "interact", "top_first", "top_rest")
 
 EXPORTS = ("rec_create", "rec_destroy", "rec_workspace_bytes", "rec_bind_workspace",
            "rec_load_tables", "rec_load_hot_rows", "rec_mlp_packed_bytes", "rec_load_mlp", "rec_forward", "rec_forward_static", "rec_check",
            "rec_debug_get", "rec_set_option", "rec_set_dense_stream", "rec_set_pool_streams", "rec_drain", "rec_set_profiling", "rec_stage_ms", "rec_stage_shared", "rec_status_string",
-           "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan")
+           "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan", "rec_probe_fc_form")
 
 
 class rec_config(C.Structure):
@@ -106,6 +108,8 @@ _lib.rec_probe_mfma.restype = C.c_int
 _lib.rec_probe_mfma.argtypes = [C.c_int32, C.c_int32, C.c_int32, _vp, _vp]
 _lib.rec_probe_scan.restype = C.c_int
 _lib.rec_probe_scan.argtypes = [_vp, C.c_int32, C.c_int64, _vp, _vp, C.c_int32, _vp, _vp]
+_lib.rec_probe_fc_form.restype = C.c_int
+_lib.rec_probe_fc_form.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_uint32, C.c_int32, C.POINTER(C.c_int32)]
 
 
 class RecError(RuntimeError):
@@ -252,6 +256,14 @@ def rec_probe_scan(dev_lengths: torch.Tensor, nnz: int, dev_offsets: torch.Tenso
     """The offsets scan alone; dev_words int64, one per 2048 lengths, zero on entry; dev_err 64 bytes."""
     return _lib.rec_probe_scan(_ptr(dev_lengths), dev_lengths.numel(), int(nnz), _ptr(dev_offsets), _ptr(dev_words),
                                int(polls), _ptr(dev_err), _stream())
+
+
+def rec_probe_fc_form(rows: int, inputs: int, outputs: int, stacks: int = 1, flags: int = 0,
+                      compute_units: int = 256) -> Tuple[int, Tuple[int, int, int, int]]:
+    """(status, (REC_FORM_*, rows and columns of a block's tile, waves that share its k))."""
+    form = (C.c_int32 * 4)()
+    st = _lib.rec_probe_fc_form(int(rows), int(inputs), int(outputs), int(stacks), int(flags), int(compute_units), form)
+    return st, tuple(form)
 
 
 class RecModel:

@@ -345,9 +345,16 @@ hipError_t grant_lds()
 
 // Which block tile, if any: 256 x 256, 256 x 128 (bf16 input) or 128 x 128, the
 // largest whose tiles still cover three quarters of the compute units (the last: half, against many small ones).
+// One stack of bf16 rows beside a pooling launch that is there for long keeps to 1024 rows and three
+// quarters: below, launch_fc() has a form of four waves for it that finds room beside pooling's (pipelined
+// forwards, us per batch, that form / half a round of these: 40 tables of 80 ids, 4500 samples 281.1 / 283.5; 20
+// ids 122.3 / 120.4; 884 -> 1024, 2100 samples, 40 ids 103.0 / 106.8, 80 157.3 / 160.9, 8 57.8 / 53.1).  Several
+// stacks and fp32 rows win with these beside any pooling (four of 1728 -> 1024, 600 samples, 1 id 71.8 / 58.9, 80
+// 91.4 / 78.1; 2560 fp32 -> 1024, 2100 samples, 20 ids 82.3 / 74.3, 80 103.1 / 92.6).
 int big_tile_choice(const FcProblem &a, int num_cus)
 {
-    if (a.dot_out || a.M < 512 || a.Kpad % BK != 0 || a.groups < 1 || a.groups > MAX_GROUPS) return 0;
+    const bool keeps = a.corun && !a.a_f32 && a.groups == 1;
+    if (a.dot_out || a.M < (keeps ? 1024 : 512) || a.Kpad % BK != 0 || a.groups < 1 || a.groups > MAX_GROUPS) return 0;
     if (a.a_f32 && (a.K % 8 != 0 || a.lda % 4 != 0 || a.a_stride % 4 != 0 ||
                     reinterpret_cast<uintptr_t>(a.A) % 16 != 0))
         return 0;
@@ -362,13 +369,23 @@ int big_tile_choice(const FcProblem &a, int num_cus)
     // (136 tiles), 2400 69.7 / 62.5, 2900 70.6 / 64.2; four towers of 1728 -> 1024, 520 samples 42.5 /
     // 42.1 (160), 600 47.7 / 44.0, 800 51.6 / 46.2; three, 900 51.7 / 44.7; with two rounds of 64 x 64
     // (400 samples, 448 of them, 14 us a launch) half a round of these is no shorter.
-    if (a.Npad % 128 == 0 && 2 * tiles > num_cus && a.groups * ((a.M + 63) / 64) * (a.Npad / 64) > 2 * num_cus) return 3;
+    if (!keeps && a.Npad % 128 == 0 && 2 * tiles > num_cus && a.groups * ((a.M + 63) / 64) * (a.Npad / 64) > 2 * num_cus) return 3;
     return 0;
 }
 
 }  // namespace
 
 bool fc_big_applies(const FcProblem &a, int num_cus) { return big_tile_choice(a, num_cus) != 0; }
+
+FcTile fc_big_tile(const FcProblem &a, int num_cus)
+{
+    switch (big_tile_choice(a, num_cus)) {
+    case 1: return FcTile{16, 16, 1};
+    case 2: return FcTile{16, 8, 1};
+    case 3: return FcTile{8, 8, 1};
+    }
+    return FcTile{0, 0, 0};
+}
 
 bool fc_big_rides(const FcProblem &a, int num_cus)
 {

@@ -76,17 +76,18 @@ hipError_t launch_tiles(const FcProblem &a, hipStream_t s)
     return hipErrorInvalidValue;
 }
 
-// With the one-output layer: a block has all columns, and as many rows as still give
-// every compute unit a block.
 template <int IN>
 hipError_t launch_dot(const FcProblem &a, hipStream_t s)
 {
-    const long long cus = a.num_cus > 0 ? a.num_cus : 256, blocks16 = (a.M + 15) / 16 * (long long)a.groups;
-    if (a.Npad == 64) return launch_as<1, 4, 1, 8, IN, CHAIN_OUT_DOT>(a, s);
-    if (a.Npad == 128)
-        return blocks16 < 3 * cus ? launch_as<1, 4, 2, 4, IN, CHAIN_OUT_DOT>(a, s) : launch_as<2, 4, 2, 4, IN, CHAIN_OUT_DOT>(a, s);
-    if (blocks16 <= cus) return launch_as<1, 4, 4, 2, IN, CHAIN_OUT_DOT>(a, s);
-    return blocks16 <= 2 * cus ? launch_as<2, 4, 4, 2, IN, CHAIN_OUT_DOT>(a, s) : launch_as<4, 4, 4, 2, IN, CHAIN_OUT_DOT>(a, s);
+    switch (a.Npad + fc_split_dot_tile(a).tm) {
+    case 64 + 1: return launch_as<1, 4, 1, 8, IN, CHAIN_OUT_DOT>(a, s);
+    case 128 + 1: return launch_as<1, 4, 2, 4, IN, CHAIN_OUT_DOT>(a, s);
+    case 128 + 2: return launch_as<2, 4, 2, 4, IN, CHAIN_OUT_DOT>(a, s);
+    case 256 + 1: return launch_as<1, 4, 4, 2, IN, CHAIN_OUT_DOT>(a, s);
+    case 256 + 2: return launch_as<2, 4, 4, 2, IN, CHAIN_OUT_DOT>(a, s);
+    case 256 + 4: return launch_as<4, 4, 4, 2, IN, CHAIN_OUT_DOT>(a, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int IN>
@@ -156,6 +157,16 @@ FcTile fc_split_tile(const FcProblem &a)
         }
     }
     return best;
+}
+
+// With the one-output layer: a block has all columns, and as many rows as still give
+// every compute unit a block.
+FcTile fc_split_dot_tile(const FcProblem &a)
+{
+    const long long cus = a.num_cus > 0 ? a.num_cus : 256, blocks16 = (a.M + 15) / 16 * (long long)a.groups;
+    if (a.Npad == 64) return FcTile{1, 4, 8};
+    if (a.Npad == 128) return FcTile{blocks16 < 3 * cus ? 1 : 2, 8, 4};
+    return FcTile{blocks16 <= cus ? 1 : blocks16 <= 2 * cus ? 2 : 4, 16, 2};
 }
 
 hipError_t fc_split_prepare()

@@ -91,3 +91,34 @@ extern "C" rec_status rec_probe_scan(const int32_t *dev_lengths, int32_t n, int6
                                           static_cast<hipStream_t>(stream), polls);
     return e == hipSuccess ? REC_OK : REC_ERR_DEVICE;
 }
+
+// launch_fc()'s choice, on pointers that nothing follows.
+extern "C" rec_status rec_probe_fc_form(int32_t rows, int32_t inputs, int32_t outputs, int32_t stacks, uint32_t flags,
+                                        int32_t compute_units, int32_t *form)
+{
+    using namespace rec;
+    static char some[16] __attribute__((aligned(16)));
+    const bool dot = (flags & REC_FC_DOT) != 0;
+    if (!form || rows < 1 || inputs < 1 || outputs < 1 || inputs > (1 << 20) || outputs > (1 << 20) || stacks < 1 ||
+        stacks > MAX_GROUPS || compute_units < 1)
+        return REC_ERR_ARG;
+    FcProblem p{};
+    p.A = some; p.a_f32 = (flags & REC_FC_F32_ROWS) != 0;
+    p.M = rows; p.K = inputs; p.Kpad = (inputs + 63) / 64 * 64; p.Npad = (outputs + 63) / 64 * 64;
+    p.lda = p.a_f32 ? p.K : stacks * p.Kpad;
+    p.groups = stacks; p.num_cus = compute_units; p.corun = (flags & REC_FC_BESIDE_POOLING) != 0;
+    for (int g = 0; g < stacks && (flags & REC_FC_ANY_ORDER); ++g) p.frag[g] = some;
+    if (dot) p.dot_out = reinterpret_cast<float *>(some);
+    if (dot && !fc_can_fuse_dot(p.Npad)) return REC_ERR_ARG;
+    FcTile t{0, 0, 0};
+    form[0] = REC_FORM_TILES;
+    if (fc_takes_split(p)) {
+        form[0] = REC_FORM_SPLIT;
+        t = dot ? fc_split_dot_tile(p) : fc_split_tile(p);
+    } else if (!dot && fc_big_applies(p, compute_units)) {
+        form[0] = REC_FORM_WIDE;
+        t = fc_big_tile(p, compute_units);
+    }
+    form[1] = 16 * t.tm; form[2] = 16 * t.tn; form[3] = t.wk;
+    return REC_OK;
+}

@@ -192,7 +192,8 @@ struct FcTile {
     int tm, tn;  // 16 tm rows x 16 tn columns
     int wk;      // waves that share its k
 };
-FcTile fc_split_tile(const FcProblem &p);  // without the one-output layer
+FcTile fc_split_tile(const FcProblem &p);      // without the one-output layer
+FcTile fc_split_dot_tile(const FcProblem &p);  // with it
 bool fc_takes_split(const FcProblem &p);   // does launch_fc() take this path?
 // May the layer's blocks share a launch with others' (fp32 rows read in vectors)?
 bool fc_split_rides(const FcProblem &p);
@@ -205,6 +206,7 @@ hipError_t fc_split_prepare();
 // launch_fc() takes this path by itself when fc_big_applies().
 bool fc_big_applies(const FcProblem &p, int num_cus);
 hipError_t launch_fc_big(const FcProblem &p, int num_cus, hipStream_t s);
+FcTile fc_big_tile(const FcProblem &p, int num_cus);  // no tile: does not apply
 // Does the layer take tiles of which two blocks fit a compute unit (128 x 128, fp32
 // input), so that a scan's blocks may stand in front of them?
 bool fc_big_rides(const FcProblem &p, int num_cus);

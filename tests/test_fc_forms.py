@@ -1,0 +1,36 @@
+"""Which kernel the launch of an FC layer takes, by the shapes at which the choice was
+measured.  Host code only: no device."""
+import pytest
+
+from paper_2203_07424_amd import binding as b
+
+CUS = 256
+ALONE = b.REC_FC_ANY_ORDER
+PIPELINED = b.REC_FC_BESIDE_POOLING
+
+
+def form(rows, inputs, outputs, stacks=1, flags=ALONE):
+    st, f = b.rec_probe_fc_form(rows, inputs, outputs, stacks, flags, CUS)
+    assert st == b.REC_OK
+    return f
+
+
+def test_what_is_no_layer_is_refused():
+    for bad in ((0, 64, 64, 1), (1, 0, 64, 1), (1, 64, 0, 1), (1, 64, 64, 0), (1, 64, 64, b.REC_MAX_TOWERS + 1), (1, 2 ** 20 + 1, 64, 1)):
+        assert b.rec_probe_fc_form(*bad)[0] == b.REC_ERR_ARG
+    assert b.rec_probe_fc_form(1, 64, 64, 1, 0, 0)[0] == b.REC_ERR_ARG
+    assert b.rec_probe_fc_form(1, 64, 320, 1, b.REC_FC_DOT)[0] == b.REC_ERR_ARG
+
+
+@pytest.mark.parametrize("rows", [4097, 4500, 6016])
+def test_one_stack_beside_pooling_keeps_its_small_blocks(rows):
+    """132 to 188 tiles of 128 x 128: eight waves and 72 KB each, no room beside pooling."""
+    assert form(rows, 884, 512, flags=PIPELINED)[0] == b.REC_FORM_TILES
+    assert form(rows, 884, 512)[0] == b.REC_FORM_WIDE
+    assert form(6200, 884, 512, flags=PIPELINED)[0] == b.REC_FORM_WIDE  # three quarters of a round
+
+
+@pytest.mark.parametrize("rows,inputs,outputs,stacks,flags", [
+    (2049, 2560, 1024, 1, b.REC_FC_F32_ROWS), (2944, 2560, 1024, 1, b.REC_FC_F32_ROWS), (520, 1728, 1024, 4, 0), (1000, 1728, 1024, 4, 0)])
+def test_fp32_rows_and_several_stacks_take_wide_tiles_beside_pooling(rows, inputs, outputs, stacks, flags):
+    assert form(rows, inputs, outputs, stacks, flags | PIPELINED)[0] == b.REC_FORM_WIDE
