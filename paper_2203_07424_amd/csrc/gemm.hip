@@ -94,8 +94,12 @@ template <int BM, int BN, int WAVES_M, int P, bool A_F32, bool OUT_F32, bool FUS
 __global__ __launch_bounds__(FC_THREADS, ((P == 2 && BM * BN <= 4096) || P == 1) ? 4 : 1) void fc_kernel(
     const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_n,
     int tiles_per_group, int per_xcd, int vec_ok, long long a_stride, int relu, void *__restrict__ C0, int ldc,
-    long long c_stride, float *__restrict__ dot_out, int dot_ld, const FcGroups groups)
+    long long c_stride, float *__restrict__ dot_out, int dot_ld, const FcGroups groups, int blocks, const FaultReport report)
 {
+    if (FUSE_DOT && (int)blockIdx.x == blocks) {
+        report_fault(report.err, report.fault);
+        return;
+    }
     constexpr int WAVES_N = 4 / WAVES_M;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // per-wave tile
     constexpr int TM = WM / 32, TN = WN / 32;            // 32 x 32 MFMA tiles per wave
@@ -257,15 +261,16 @@ hipError_t launch_tile(const FcProblem &a, hipStream_t s)
 {
     const int grid_n = a.Npad / BN;
     const int tiles = grid_n * ((a.M + BM - 1) / BM);
-    const dim3 grid(tiles * a.groups), block(FC_THREADS);
+    const int blocks = tiles * a.groups;
+    const dim3 grid(blocks + (a.dot_out ? report_blocks(a.report) : 0)), block(FC_THREADS);
     // 16-byte loads of fp32 rows need lda and the stack stride % 4 == 0 and an aligned base.
     const int vec_ok = a.a_f32 && (a.lda % 4 == 0) && (a.a_stride % 4 == 0) &&
                        (reinterpret_cast<uintptr_t>(a.A) % 16 == 0);
-    const int r = a.relu ? 1 : 0, per_xcd = grid.x % 8 == 0 ? grid.x / 8 : 0;
+    const int r = a.relu ? 1 : 0, per_xcd = blocks % 8 == 0 ? blocks / 8 : 0;
 #define REC_FC_LAUNCH(AF, OF, FD)                                                                  \
     hipLaunchKernelGGL((fc_kernel<BM, BN, WAVES_M, P, AF, OF, FD>), grid, block, 0, s, a.A, a.g.W[0], \
                        a.lda, a.M, a.K, a.Kpad, grid_n, tiles, per_xcd, vec_ok, a.a_stride, r, a.C, a.ldc,   \
-                       a.c_stride, a.dot_out, a.dot_ld, a.g)
+                       a.c_stride, a.dot_out, a.dot_ld, a.g, blocks, a.report)
     if (a.dot_out) {
         if (a.a_f32) REC_FC_LAUNCH(true, false, true);
         else REC_FC_LAUNCH(false, false, true);
@@ -350,15 +355,27 @@ __global__ __launch_bounds__(256) void pack_fc_kernel(const float *__restrict__ 
 
 }  // namespace
 
+// A layer with the one-output layer behind it has every column in a block: few rows a block,
+// and what bounds it is the weights, which each block brings in whole.  Up to two rounds of blocks of
+// 16 rows (blocks of 64 take one round of 256 columns up to four of those) the trips of dealt k
+// weigh more; beyond, the k-tile kernel's 64 rows share a weight tile (128 columns: 32 rows, in both the
+// same, and dealt k wins at any size).  us per launch, k-tile by k-tile / dealt: 1024 -> 64, 8192
+// samples 9.8 / 8.8, 9216 10.0 / 9.9, 16384 10.2 / 11.8, 65536 24.2 / 32.6; 512 -> 256, 8192 12.2 /
+// 10.1, 16384 12.4 / 12.3, 18432 16.4 / 19.8; 2048 -> 256, 16384 30.0 / 25.6, 65536 97 / 124; 256 ->
+// 256, 8192 9.2 / 8.3, 9216 9.2 / 9.7, 65536 19.6 / 28.1; 1024 -> 128, 16384 14.3 / 13.8, 65536 42.6 / 37.4.
+static bool split_dot_pays(const FcProblem &a)
+{
+    const long long cus = a.num_cus > 0 ? a.num_cus : 256, blocks16 = (a.M + 15) / 16 * (long long)a.groups;
+    return a.Npad == 128 || blocks16 <= (a.Npad == 256 && a.Kpad >= 512 ? 4 : 2) * cus;
+}
+
 // Launches that do not fill the chip with 128 x 128 tiles deal the k of smaller tiles to
-// the waves of a block, and so does, at any size, a layer with the one-output layer behind
-// it (16384 samples, 512 -> 128 -> 1 10.7 / 7.6 us, 4096 x four of 512 -> 256 -> 1
-// 13 / 10.7).  Where larger tiles fill it they win (four of 1728 -> 1024, 4096 samples 53 / 96):
+// the waves of a block.  Where larger tiles fill it they win (four of 1728 -> 1024, 4096 samples 53 / 96):
 // fc_big_applies() says from where on.
 bool fc_takes_split(const FcProblem &a)
 {
     if (!fc_split_applies(a)) return false;
-    if (a.dot_out) return fc_can_fuse_dot(a.Npad);
+    if (a.dot_out) return fc_can_fuse_dot(a.Npad) && split_dot_pays(a);
     if (a.num_cus > 0 && fc_big_applies(a, a.num_cus)) return false;
     const long long big_blocks = (long long)a.groups * (a.Npad / 128) * ((a.M + 127) / 128);
     if (a.corun && !a.a_f32 && a.Npad % 128 == 0 && big_blocks >= 64) return false;

@@ -746,7 +746,7 @@ hipError_t enqueue_tail(const rec_model *m, const Bufs &u, const Call &c, const 
             if (feeds_dot && fc_can_fuse_dot(l.Npad)) {
                 p.C = nullptr; p.out_f32 = false; p.ldc = 0; p.c_stride = 0;
                 p.dot_out = c.logits; p.dot_ld = G;
-                if (fc_takes_split(p)) p.report = take_report(c);
+                p.report = take_report(c);
                 REC_TRY(launch_fc(p, s));
                 done = true;
             } else {

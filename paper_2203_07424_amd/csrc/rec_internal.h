@@ -177,7 +177,7 @@ struct FcProblem {
     float *dot_out; int dot_ld;
     int num_cus;  // compute units of the device; 0 = unknown (never picks the wide-tile kernels)
     bool corun;   // the launch will share the device with a pooling launch: keep register use low
-    FaultReport report;  // with dot_out and fc_takes_split(): made on the way
+    FaultReport report;  // with dot_out: made on the way
     // Each stack's weights in the order of launch_pack_chain(), for the kernels that deal
     // a tile's k to the waves of a block (sums in another order); null: not these.
     const void *frag[MAX_GROUPS];

@@ -34,3 +34,17 @@ def test_one_stack_beside_pooling_keeps_its_small_blocks(rows):
     (2049, 2560, 1024, 1, b.REC_FC_F32_ROWS), (2944, 2560, 1024, 1, b.REC_FC_F32_ROWS), (520, 1728, 1024, 4, 0), (1000, 1728, 1024, 4, 0)])
 def test_fp32_rows_and_several_stacks_take_wide_tiles_beside_pooling(rows, inputs, outputs, stacks, flags):
     assert form(rows, inputs, outputs, stacks, flags | PIPELINED)[0] == b.REC_FORM_WIDE
+
+
+@pytest.mark.parametrize("inputs,outputs,stacks,most", [
+    (256, 64, 1, 8192), (2048, 64, 4, 8192), (1024, 50, 1, 8192),   # two rounds of blocks of 16 rows
+    (256, 256, 1, 8192), (448, 256, 1, 8192), (512, 256, 4, 16384), (2048, 250, 1, 16384)])
+def test_the_dot_layer_on_many_samples_is_left_to_the_k_tiles(inputs, outputs, stacks, most):
+    assert form(most // stacks, inputs, outputs, stacks, ALONE | b.REC_FC_DOT)[0] == b.REC_FORM_SPLIT
+    for rows in (most + 16 * stacks, 2 * most, 8 * most):
+        assert form(rows // stacks, inputs, outputs, stacks, ALONE | b.REC_FC_DOT)[0] == b.REC_FORM_TILES
+
+
+@pytest.mark.parametrize("rows,tile", [(1, 16), (4096, 16), (4097, 32), (8192, 32), (65536, 32)])
+def test_blocks_of_the_dot_layer_with_128_columns(rows, tile):
+    assert form(rows, 512, 128, flags=ALONE | b.REC_FC_DOT) == (b.REC_FORM_SPLIT, tile, 128, 4)

@@ -29,7 +29,8 @@ def stack(g, ws):
     (False, (64,), 1, 1, 1), (False, (64,), 1, 3000, 1),         # joint launch
     (True, (96, 72), 2, 50, 1), (True, (96, 72), 2, 2100, 1),    # chain
     (True, (512, 256), 2, 50, 1), (True, (512, 100), 1, 2100, 1),  # k dealt to waves, dot folded in
-    (False, (64,), 1, 70, 0), (True, (448,), 2, 70, 1), (True, (), 1, 33, 1)])  # a launch of its own
+    (False, (64,), 1, 70, 0), (True, (50,), 2, 5000, 1), (True, (64,), 4, 4096, 1),  # k-tile by k-tile, dot folded in
+    (True, (448,), 2, 70, 1), (True, (), 1, 33, 1)])  # a launch of its own
 def test_faults_of_a_static_forward(binding, concat, hidden, towers, B, fuse):
     print("static report", concat, hidden, towers, B, fuse, flush=True)
     g = np.random.default_rng(1700 + B)
