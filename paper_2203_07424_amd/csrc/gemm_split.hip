@@ -133,20 +133,23 @@ hipError_t prepare_in()
 // round.  us per launch (64 x 64 or 32 x 64 with four waves, the choice without these two /
 // now): 300 samples, four of 1728 -> 1024 14.8 / 11.2 (80 rows, 256 blocks), 1024 -> 512
 // 7.4 / 6.3 (48 rows, 224), two of 1728 -> 1024 10.7 / 8.4; 2560 fp32 -> 1024, 300 samples 11.8 / 10.2,
-// 700 17.7 / 14.6, 1200 24.2 / 20.8.  Blocks of 96 rows never won.
+// 700 17.7 / 14.6, 1200 24.2 / 20.8.  Blocks of 96 rows never won, and those of 80 only in one
+// round: in many each block's loads, sums and stores lie bare (64 rows / 80; 256 -> 192, 40960 samples 20.4
+// / 30.2; 1024 -> 704, 32768 96 / 118).
 FcTile fc_split_tile(const FcProblem &a)
 {
     struct Form {
-        int tm, tn, wk1, wk, once1, once;  // waves and uncovered part (tenths of a round), in one round and in several
+        int tm, tn, wk1, wk, once1, once;  // waves and uncovered part (tenths of a round), in one round and in several (0: not)
     };
     static const Form forms[] = {{1, 1, 8, 8, 10, 11}, {1, 2, 8, 8, 10, 11}, {2, 2, 8, 4, 10, 11}, {2, 4, 8, 4, 10, 11},
-                                 {3, 4, 8, 8, 11, 14}, {4, 4, 8, 4, 11, 11}, {5, 4, 8, 8, 11, 18}};
+                                 {3, 4, 8, 8, 11, 14}, {4, 4, 8, 4, 11, 11}, {5, 4, 8, 8, 11, 0}};
     const int cus = a.num_cus > 0 ? a.num_cus : 256;
     FcTile best{0, 0, 0};
     long long least = 0;
     for (const Form &f : forms) {
         const long long blocks = (long long)((a.M + 16 * f.tm - 1) / (16 * f.tm)) * (a.Npad / (16 * f.tn)) * a.groups;
         const long long rounds = (blocks + cus - 1) / cus;
+        if (rounds > 1 && f.once == 0) continue;
         const long long cost = (f.tm * (a.a_f32 ? 2 : 1) + f.tn) * (10 * rounds + (rounds == 1 ? f.once1 : f.once));
         if (best.tm == 0 || cost < least) {
             // Eight waves with a unit each gain nothing, and most fp32 layers run beside pooling,

@@ -48,3 +48,11 @@ def test_the_dot_layer_on_many_samples_is_left_to_the_k_tiles(inputs, outputs, s
 @pytest.mark.parametrize("rows,tile", [(1, 16), (4096, 16), (4097, 32), (8192, 32), (65536, 32)])
 def test_blocks_of_the_dot_layer_with_128_columns(rows, tile):
     assert form(rows, 512, 128, flags=ALONE | b.REC_FC_DOT) == (b.REC_FORM_SPLIT, tile, 128, 4)
+
+
+@pytest.mark.parametrize("rows,inputs,outputs,stacks", [
+    (40960, 256, 192, 1), (40960, 256, 448, 1), (32768, 1024, 704, 1), (16384, 2048, 448, 4), (65536, 256, 704, 1)])
+def test_blocks_of_80_rows_only_in_one_round(rows, inputs, outputs, stacks):
+    f = form(rows, inputs, outputs, stacks)
+    assert f[0] != b.REC_FORM_SPLIT or f[1] == 64
+    assert form(300, 1728, 1024, 4) == (b.REC_FORM_SPLIT, 80, 64, 8)
