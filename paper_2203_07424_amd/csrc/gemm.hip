@@ -369,6 +369,31 @@ static bool split_dot_pays(const FcProblem &a)
     return a.Npad == 128 || blocks16 <= (a.Npad == 256 && a.Kpad >= 512 ? 4 : 2) * cus;
 }
 
+// Tiles of more than 32 rows have to be paid for with enough k: a wave that has one unit of
+// 64 or none waits for its loads once in either form, and the sums of eight such waves, 16 KB
+// each in tiles of 64 x 64, cost more than the barriers of the k-tiles.  Four waves with a unit
+// each win again where several rounds of blocks cover that, and with up to 128 columns (of 48
+// rows, up to 64) a row tile is read by one or two blocks alone.  us per launch, k-tile by k-tile /
+// dealt: 256 -> 512, 3000 samples 8.5 / 8.8 (48 rows), 512 inputs 10.0 / 9.7; 256 -> 1024, 1000 samples 7.3
+// / 9.4 (64 rows, eight waves), 512 8.6 / 10.1, 1024 -> 448, 2048 10.8 / 9.8; 320 -> 704, 4096 11.5 / 12.2
+// (64 rows, four waves), 256 10.8 / 10.8, 1024 -> 448, 4096 14.0 / 12.8; 320 -> 704, 1536 8.2 / 8.8 (80 rows),
+// 512 -> 512, 2100 10.6 / 9.8; 2048 -> 64, 16384 15.6 / 18.5, 8192 14.4 / 11.5 (32 rows).
+// bf16 rows only: a layer of fp32 rows is the first of its stack, which runs beside the scan
+// in these tiles, and its own launch is to give the same bits.
+static bool split_tile_pays(const FcProblem &a)
+{
+    const FcTile t = fc_split_tile(a);
+    if (a.a_f32 || t.tm <= 2) return true;
+    const int units = a.Kpad / 64;
+    if (t.tm == 3) return units >= (a.Npad > 64 ? 6 : 18);
+    if (t.tm == 5) return units >= 8;
+    if (a.Npad <= 128) return a.Npad == 128 && units >= 24;
+    if (t.wk == 8) return units >= 9;
+    const int cus = a.num_cus > 0 ? a.num_cus : 256;
+    const long long blocks = (long long)((a.M + 63) / 64) * (a.Npad / 64) * a.groups;
+    return units >= 8 || (units == 4 && blocks > 2 * cus);
+}
+
 // Launches that do not fill the chip with 128 x 128 tiles deal the k of smaller tiles to
 // the waves of a block.  Where larger tiles fill it they win (four of 1728 -> 1024, 4096 samples 53 / 96):
 // fc_big_applies() says from where on.
@@ -379,7 +404,7 @@ bool fc_takes_split(const FcProblem &a)
     if (a.num_cus > 0 && fc_big_applies(a, a.num_cus)) return false;
     const long long big_blocks = (long long)a.groups * (a.Npad / 128) * ((a.M + 127) / 128);
     if (a.corun && !a.a_f32 && a.Npad % 128 == 0 && big_blocks >= 64) return false;
-    return a.Npad % 128 != 0 || big_blocks < 256;
+    return (a.Npad % 128 != 0 || big_blocks < 256) && split_tile_pays(a);
 }
 
 bool fc_can_fuse_dot(int Npad) { return Npad == 64 || Npad == 128 || Npad == 256; }

@@ -56,3 +56,29 @@ def test_blocks_of_80_rows_only_in_one_round(rows, inputs, outputs, stacks):
     f = form(rows, inputs, outputs, stacks)
     assert f[0] != b.REC_FORM_SPLIT or f[1] == 64
     assert form(300, 1728, 1024, 4) == (b.REC_FORM_SPLIT, 80, 64, 8)
+
+
+@pytest.mark.parametrize("rows,outputs,tile,from_inputs", [
+    (3000, 512, 48, 384), (10000, 64, 48, 1152), (1536, 704, 80, 512), (20480, 64, 80, 512),
+    (1000, 1024, 64, 576), (2048, 448, 64, 576), (16384, 64, 64, None), (16384, 128, 64, 1536)])
+def test_tiles_of_more_than_32_rows_need_enough_k(rows, outputs, tile, from_inputs):
+    for inputs in (64, 128, 192, 256, 320, 384, 448, 512, 576, 704, 768, 1088, 1152, 1472, 1536, 2048):
+        f = form(rows, inputs, outputs)
+        if from_inputs and inputs >= from_inputs:
+            assert f[:3] == (b.REC_FORM_SPLIT, tile, 64), (inputs, f)
+        else:
+            assert f[0] == b.REC_FORM_TILES, (inputs, f)
+
+
+@pytest.mark.parametrize("rows,outputs,takes", [(4096, 448, {512, 576, 768, 2048}), (16384, 448, {256, 512, 576, 768, 2048})])
+def test_64_rows_and_four_waves_by_units_of_k(rows, outputs, takes):
+    for inputs in (64, 128, 192, 256, 320, 384, 448, 512, 576, 768, 2048):
+        assert form(rows, inputs, outputs)[0] == (b.REC_FORM_SPLIT if inputs in takes else b.REC_FORM_TILES), inputs
+
+
+def test_up_to_32_rows_and_fp32_rows_at_any_k():
+    for inputs in (64, 320, 2560):
+        f = form(300, inputs, 512)
+        assert f[0] == b.REC_FORM_SPLIT and f[1] <= 32
+        for rows, outputs in ((3000, 256), (4096, 448), (2100, 512)):
+            assert form(rows, inputs, outputs, flags=ALONE | b.REC_FC_F32_ROWS)[0] == b.REC_FORM_SPLIT
