@@ -259,9 +259,9 @@ enum {
     REC_OPT_STREAM_ROWS = 1,
     /* Consecutive FC layers of at most 1024 (padded) inputs and outputs can run
      * as one kernel per stack (a chain), their activations held on chip between
-     * layers; a Bottom-FC that is one chain rides on the launch of the scan, and
-     * with it scan and pooling of small batches become one launch.  The
-     * interaction and Predict-FC of a model with pairwise dots and one tower
+     * layers; a Bottom-FC that is one chain rides on the launch of the scan, of any
+     * other its first layer, and with it scan and pooling of small batches become
+     * one launch.  The interaction and Predict-FC of a model with pairwise dots and one tower
      * (emb_dim 32 or 64, up to 63 tables, Predict-FC input up to 2048) can run as
      * one launch too, the last narrow Bottom-FC layers in front.
      * 2: both wherever the shapes allow; 0: neither, every layer is a kernel of

@@ -13,7 +13,8 @@
  *
  * The offsets scan by itself, with the bound on its waits in the caller's hand.
  *
- * Which kernel a layer's launch takes (host code, no device).
+ * Which kernel a layer's launch takes, and which stages of a forward share a launch
+ * (host code, no device).
  */
 #ifndef REC_PROBE_H
 #define REC_PROBE_H
@@ -68,6 +69,19 @@ enum { REC_FORM_TILES = 0, REC_FORM_WIDE = 1, REC_FORM_SPLIT = 2 };
  * (REC_FORM_TILES: zeros).  REC_ERR_ARG on a null pointer or counts that no layer has. */
 REC_API rec_status rec_probe_fc_form(int32_t rows, int32_t inputs, int32_t outputs, int32_t stacks, uint32_t flags,
                           int32_t compute_units, int32_t *form);
+
+/* Bits of rec_probe_plan()'s mask. */
+enum {
+    REC_PLAN_RIDE = 1,  /* Bottom-FC in the launch of the scan */
+    REC_PLAN_FRONT = 2, /* scan and pooling in one launch */
+    REC_PLAN_LAYER = 4, /* Bottom-FC's first layer in the launch of the scan */
+    REC_PLAN_TAIL = 8   /* interaction and Predict-FC in one launch */
+};
+/* What an untimed rec_forward() of `batch` samples and nnz ids, its buffers 16-byte
+ * aligned, would run with the options as set (no workspace needed): *mask, and in
+ * *tail_from the first Bottom-FC layer that the launch of REC_PLAN_TAIL takes (the number
+ * of layers: none).  REC_ERR_ARG on a null pointer or a batch that the model does not take. */
+REC_API rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz, uint32_t *mask, int32_t *tail_from);
 
 #ifdef __cplusplus
 }

@@ -42,12 +42,13 @@ REC_OPT_PIPELINE = 3
 REC_NUM_STAGES = 7
 REC_FC_F32_ROWS, REC_FC_DOT, REC_FC_BESIDE_POOLING, REC_FC_ANY_ORDER = 1, 2, 4, 8
 REC_FORM_TILES, REC_FORM_WIDE, REC_FORM_SPLIT = 0, 1, 2
+REC_PLAN_RIDE, REC_PLAN_FRONT, REC_PLAN_LAYER, REC_PLAN_TAIL = 1, 2, 4, 8
 STAGE_NAMES = ("scan", "pool", "bottom_first", "bottom_rest", "interact", "top_first", "top_rest")
 
 EXPORTS = ("rec_create", "rec_destroy", "rec_workspace_bytes", "rec_bind_workspace",
            "rec_load_tables", "rec_load_hot_rows", "rec_mlp_packed_bytes", "rec_load_mlp", "rec_forward", "rec_forward_static", "rec_check",
            "rec_debug_get", "rec_set_option", "rec_set_dense_stream", "rec_set_pool_streams", "rec_drain", "rec_set_profiling", "rec_stage_ms", "rec_stage_shared", "rec_status_string",
-           "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan", "rec_probe_fc_form")
+           "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan", "rec_probe_fc_form", "rec_probe_plan")
 
 
 class rec_config(C.Structure):
@@ -108,6 +109,8 @@ _lib.rec_probe_mfma.restype = C.c_int
 _lib.rec_probe_mfma.argtypes = [C.c_int32, C.c_int32, C.c_int32, _vp, _vp]
 _lib.rec_probe_scan.restype = C.c_int
 _lib.rec_probe_scan.argtypes = [_vp, C.c_int32, C.c_int64, _vp, _vp, C.c_int32, _vp, _vp]
+_lib.rec_probe_plan.restype = C.c_int
+_lib.rec_probe_plan.argtypes = [_vp, C.c_int32, C.c_int64, C.POINTER(C.c_uint32), C.POINTER(C.c_int32)]
 _lib.rec_probe_fc_form.restype = C.c_int
 _lib.rec_probe_fc_form.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_uint32, C.c_int32, C.POINTER(C.c_int32)]
 
@@ -264,6 +267,13 @@ def rec_probe_fc_form(rows: int, inputs: int, outputs: int, stacks: int = 1, fla
     form = (C.c_int32 * 4)()
     st = _lib.rec_probe_fc_form(int(rows), int(inputs), int(outputs), int(stacks), int(flags), int(compute_units), form)
     return st, tuple(form)
+
+
+def rec_probe_plan(m: int, batch: int, nnz: int) -> Tuple[int, int, int]:
+    """(status, REC_PLAN_* bits, first Bottom-FC layer that the joint Predict-FC launch takes)."""
+    mask, tail_from = C.c_uint32(0), C.c_int32(0)
+    st = _lib.rec_probe_plan(m, int(batch), int(nnz), C.byref(mask), C.byref(tail_from))
+    return st, mask.value, tail_from.value
 
 
 class RecModel:

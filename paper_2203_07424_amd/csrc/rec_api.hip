@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "rec_internal.h"
+#include "rec_probe.h"
 
 using namespace rec;
 
@@ -484,11 +485,13 @@ struct Plan {
 };
 
 // S0 and S1 (and Bottom-FC, with_bottom) of a small in-order batch as one launch,
-// where csrc/front.hip has one for it.
+// where csrc/front.hip has one for it.  With layer by layer prescribed (fuse_mlp 0) only
+// where no layer is involved, in a concatenation model without Bottom-FC.
 bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with_bottom)
 {
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
     if (m->pipeline || (m->overlap_dense && !m->bottom.empty()) || (concat && with_bottom)) return false;
+    if (m->fuse_mlp == 0 && !concat_rides_on_scan(m)) return false;
     if (!concat && longest_hot_list(m, use_hot) > 0) return false;
     if (with_bottom)
         for (const Layer &l : m->bottom)
@@ -502,7 +505,8 @@ bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with
 bool first_layer_rides(const rec_model *m, const Bufs &u, const Call &c, const Plan &p)
 {
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
-    if (m->pipeline || m->overlap_dense || p.ride || m->bottom.empty() || (concat && m->bottom.size() > 1)) return false;
+    if (m->fuse_mlp == 0 || m->pipeline || m->overlap_dense || p.ride || m->bottom.empty() || (concat && m->bottom.size() > 1))
+        return false;
     if (chain_end(m, m->bottom.data(), 0, p.tail_from, 1, c.B, true, false) > 0) return false;
     const FcProblem first = first_bottom_layer(m, u, c);
     return p.front ? front_layer_rides(first, concat) : scan_layer_rides(first, concat ? u.act[0] : nullptr);
@@ -1358,6 +1362,28 @@ rec_status rec_stage_shared(const rec_model *m, int32_t slot, uint32_t *mask)
     const long long timed = (m->forwards + m->period - 1) / m->period;
     if (m->slots <= 0 || slot < 0 || slot >= m->slots || slot >= timed) return REC_ERR_STATE;
     *mask = m->slot_shared[slot];
+    return REC_OK;
+}
+
+rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz, uint32_t *mask, int32_t *tail_from)
+{
+    if (!m || !mask || !tail_from || batch < 1 || batch > m->max_batch || nnz < 0 || nnz > m->max_nnz) return REC_ERR_ARG;
+    alignas(16) float some[4] = {};  // nothing follows these pointers
+    try {
+        rec_model loaded = *m;
+        for (std::vector<Layer> *stack : {&loaded.bottom, &loaded.top})
+            for (Layer &l : *stack) l.Wc = some;
+        Bufs u{};
+        u.x0 = some;
+        for (void *&a : u.act) a = some;
+        const Call c{some, nullptr, nullptr, batch, nnz, some, nullptr};
+        const Plan p = plan_of(&loaded, u, c, true, false);
+        *mask = (p.ride ? REC_PLAN_RIDE : 0) | (p.front ? REC_PLAN_FRONT : 0) | (p.layer ? REC_PLAN_LAYER : 0) |
+                (p.tail ? REC_PLAN_TAIL : 0);
+        *tail_from = p.tail_from;
+    } catch (const std::bad_alloc &) {
+        return REC_ERR_STATE;
+    }
     return REC_OK;
 }
 
