@@ -392,7 +392,7 @@ int tail_bottom_from(const rec_model *m, int B)
     if (m->overlap_dense || m->pipeline || bottom_rides_on_scan(m)) return n;
     int i = n;
     while (i > 1 && m->bottom[i - 1].chain && n - i < CHAIN_MAX_LAYERS &&
-           m->bottom[i - 1].chain_bytes() <= tail_layer_bytes(m, B))
+           (m->fuse_mlp == 2 || m->bottom[i - 1].chain_bytes() <= tail_layer_bytes(m, B)))
         --i;
     return i;
 }

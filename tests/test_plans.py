@@ -40,3 +40,10 @@ def test_layer_by_layer_every_layer_has_its_own_launch(batch, overlap):
 def test_first_layer_beside_the_sparse_side(batch, mask):
     assert plan(batch)[0] == mask
 
+
+@pytest.mark.parametrize("batch", [1, 300, 3000, 4096])
+def test_wherever_the_shapes_allow_is_not_a_matter_of_weights(batch):
+    """1024 -> 256 is 512 KiB: left to itself the joint Predict-FC launch takes it from some
+    samples a compute unit on; told to, at any batch."""
+    assert plan(batch, fuse=2)[1] == 1
+    assert plan(batch)[1] == (2 if batch <= 8 * 256 else 1)
