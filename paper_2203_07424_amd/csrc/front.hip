@@ -143,7 +143,7 @@ constexpr int short_groups() { return POOL_WAVES * (64 / LPR); }
 template <int LPR>
 constexpr int short_block_bags() { return short_groups<LPR>() * SHORT_BAGS; }
 
-// FC: with a layer, in tiles of 16 x 32 (a dense part of at most a few units of k).
+// FC: with a layer, in tiles of 16 x 32.
 template <int LPR, bool HALF, bool FC>
 __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
     const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
@@ -153,6 +153,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
 {
     constexpr int THREADS = POOL_WAVES * 64, GROUPS = short_groups<LPR>(), BAGS = short_block_bags<LPR>();
     static_assert(THREADS == SCAN_THREADS && BAGS <= THREADS, "a thread per bag of the block");
+    static_assert(POOL_WAVES == FRONT_SHORT_WAVES, "the layer's sums in the order of its own launch");
     int b = blockIdx.x;
     if (b < tiles) {
         __shared__ ScanShared sh;

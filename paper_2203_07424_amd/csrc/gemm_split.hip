@@ -149,13 +149,13 @@ FcTile fc_split_tile(const FcProblem &a)
     for (const Form &f : forms) {
         const long long blocks = (long long)((a.M + 16 * f.tm - 1) / (16 * f.tm)) * (a.Npad / (16 * f.tn)) * a.groups;
         const long long rounds = (blocks + cus - 1) / cus;
-        if (rounds > 1 && f.once == 0) continue;
+        if ((rounds > 1 && f.once == 0) || (a.waves > 0 && f.wk != a.waves)) continue;
         const long long cost = (f.tm * (a.a_f32 ? 2 : 1) + f.tn) * (10 * rounds + (rounds == 1 ? f.once1 : f.once));
         if (best.tm == 0 || cost < least) {
             // Eight waves with a unit each gain nothing, and most fp32 layers run beside pooling,
             // whose waves four leave more room (500 samples, 256 blocks 32.8 / 30.8 us per forward).
             const bool four = a.Kpad <= 8 * UNIT || (a.a_f32 && f.tn == 4 && 4 * blocks > 3 * cus);
-            best = FcTile{f.tm, f.tn, rounds > 1 || (four && f.tm == 2) ? f.wk : f.wk1};
+            best = FcTile{f.tm, f.tn, rounds > 1 || a.waves > 0 || (four && f.tm == 2) ? f.wk : f.wk1};
             least = cost;
         }
     }

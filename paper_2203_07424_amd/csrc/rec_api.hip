@@ -297,23 +297,28 @@ int chain_end(const rec_model *m, const Layer *layers, int i, int n, int G, int 
 bool splits(const rec_model *m) { return m->fuse_mlp == 1 && !m->pipeline; }
 
 // Layer i of Bottom-FC as a launch of its own, on rows A.
-FcProblem bottom_layer(const rec_model *m, int i, int B, const void *A, bool a_f32, int lda, void *C, int ldc)
+FcProblem bottom_layer(const rec_model *m, int i, const Call &c, const void *A, bool a_f32, int lda, void *C, int ldc)
 {
     const Layer &l = m->bottom[i];
     FcProblem p{};
     p.A = A; p.a_f32 = a_f32; p.lda = lda;
-    p.M = B; p.relu = true; p.groups = 1; p.num_cus = m->num_cus; p.corun = m->pipeline;
+    p.M = c.B; p.relu = true; p.groups = 1; p.num_cus = m->num_cus; p.corun = m->pipeline;
     p.K = l.K; p.Kpad = l.Kpad; p.Npad = l.Npad;
     p.g.W[0] = l.W; p.g.bias[0] = l.bias;
     if (splits(m)) p.frag[0] = l.Wc;
     p.C = C; p.out_f32 = i + 1 == (int)m->bottom.size(); p.ldc = ldc;
+    // Beside the short bags of a small batch a layer is in blocks of four waves; where it has a
+    // launch to itself all the same (a timed forward, REC_OPT_OVERLAP_DENSE) its sums are to be the same bits.
+    if (m->interaction == REC_INTERACT_CONCAT && m->bottom.size() == 1 &&
+        front_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows, true) && front_layer_rides(p, true))
+        p.waves = FRONT_SHORT_WAVES;
     return p;
 }
 // Its first layer.
 FcProblem first_bottom_layer(const rec_model *m, const Bufs &u, const Call &c)
 {
     const bool last = m->bottom.size() == 1;
-    return bottom_layer(m, 0, c.B, c.dense, true, m->F, last ? static_cast<void *>(u.x0) : u.act[1], last ? m->x0_ld : m->act_ld);
+    return bottom_layer(m, 0, c, c.dense, true, m->F, last ? static_cast<void *>(u.x0) : u.act[1], last ? m->x0_ld : m->act_ld);
 }
 
 // S2: ReLU after every layer; the last one leaves fp32 for the interaction.  Of
@@ -348,7 +353,7 @@ hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipS
             cp.C = C; cp.ldc = ldc; cp.c_stride = 0;
             REC_TRY(launch_mlp_chain(cp, s));
         } else {
-            REC_TRY(launch_fc(bottom_layer(m, i, c.B, A, a_f32, lda, C, ldc), s));
+            REC_TRY(launch_fc(bottom_layer(m, i, c, A, a_f32, lda, C, ldc), s));
         }
         A = C; lda = ldc; a_f32 = false;
         if (launches++ == 0) REC_TRY(mark(ev, EV_BOTTOM_FIRST_END, s));  // the first launch is timed on its own

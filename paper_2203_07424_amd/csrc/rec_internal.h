@@ -181,6 +181,7 @@ struct FcProblem {
     // Each stack's weights in the order of launch_pack_chain(), for the kernels that deal
     // a tile's k to the waves of a block (sums in another order); null: not these.
     const void *frag[MAX_GROUPS];
+    int waves;    // that share the k of a tile then, where that is prescribed: 4, or 0
 };
 bool fc_can_fuse_dot(int Npad);
 hipError_t launch_fc(const FcProblem &p, hipStream_t s);
@@ -316,6 +317,7 @@ struct FrontProblem {
     int z_cols;
 };
 bool front_layer_rides(const FcProblem &p, bool concat);
+constexpr int FRONT_SHORT_WAVES = 4;  // that share the k of such a layer's tiles in a concatenation model
 bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat);
 bool front_takes(const ChainProblem &rider);
 hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStream_t s);

@@ -118,7 +118,9 @@ def test_layer_of_a_pooled_model(binding, T, D, dtype, B, F, bottom, mean):
     (5, 32, np.float32, 1, 24, 40), (16, 32, np.float16, 38, 100, 42), (26, 64, np.float16, 300, 64, 64),
     (4, 32, np.float32, 3072, 16, 13), (3, 64, np.float16, 17, 128, 250), (1, 32, np.float16, 8200, 8, 64),  # many tiles: apart
     (1, 64, np.float16, 12289, 20, 64), (26, 64, np.float16, 1501, 64, 33), (6, 16, np.float32, 50, 37, 40),
-    (5, 128, np.float32, 40, 64, 40)])
+    (5, 128, np.float32, 40, 64, 40), (26, 64, np.float16, 300, 256, 64),  # a unit of k for each of four waves
+    (26, 64, np.float16, 300, 257, 64), (26, 64, np.float16, 300, 260, 64), (26, 64, np.float16, 100, 1000, 200),
+    (5, 32, np.float32, 2001, 512, 64)])  # more than one
 def test_layer_of_a_concatenation_model(binding, T, D, dtype, B, F, w0):
     print("first layer, concat", T, D, np.dtype(dtype).name, B, F, w0, flush=True)
     g = np.random.default_rng(1600 + T + B)
