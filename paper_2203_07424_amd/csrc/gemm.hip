@@ -271,11 +271,15 @@ hipError_t launch_tile(const FcProblem &a, hipStream_t s)
     hipLaunchKernelGGL((fc_kernel<BM, BN, WAVES_M, P, AF, OF, FD>), grid, block, 0, s, a.A, a.g.W[0], \
                        a.lda, a.M, a.K, a.Kpad, grid_n, tiles, per_xcd, vec_ok, a.a_stride, r, a.C, a.ldc,   \
                        a.c_stride, a.dot_out, a.dot_ld, a.g, blocks, a.report)
-    if (a.dot_out) {
-        if (a.a_f32) REC_FC_LAUNCH(true, false, true);
-        else REC_FC_LAUNCH(false, false, true);
-    } else if (a.a_f32 && a.out_f32) REC_FC_LAUNCH(true, true, false);
-    else if (a.a_f32) REC_FC_LAUNCH(true, false, false);
+    if (a.a_f32 && (a.dot_out || P == 1)) return hipErrorInvalidValue;  // launch_fc() has none of these
+    if constexpr (P > 1) {
+        if (a.a_f32) {
+            if (a.out_f32) REC_FC_LAUNCH(true, true, false);
+            else REC_FC_LAUNCH(true, false, false);
+            return hipGetLastError();
+        }
+    }
+    if (a.dot_out) REC_FC_LAUNCH(false, false, true);
     else if (a.out_f32) REC_FC_LAUNCH(false, true, false);
     else REC_FC_LAUNCH(false, false, false);
 #undef REC_FC_LAUNCH

@@ -101,7 +101,9 @@ __device__ inline void big_block(const BigLayer &p, const Groups &groups, __bf16
     // and W in that XCD's L2.
     int v = block;
     if (per_xcd > 0) v = (block & 7) * per_xcd + (block >> 3);
-    const int grp = v / tiles_per_group;
+    // Of a single stack the compiler is to know the index: a table of one looked up with a number
+    // from the launch's arguments would be a copy in scratch memory.
+    const int grp = sizeof(groups.W) == sizeof(void *) ? 0 : v / tiles_per_group;
     v -= grp * tiles_per_group;
     int bm, bn;
     if ((grid_m & 3) == 0) {
@@ -317,10 +319,13 @@ hipError_t launch_big_as(const FcProblem &a, hipStream_t s)
 template <int BM, int BN, int WAVES_M, int WAVES_N>
 hipError_t launch_big(const FcProblem &a, hipStream_t s)
 {
-    if (a.a_f32) {
-        if (a.out_f32) return launch_big_as<BM, BN, WAVES_M, WAVES_N, true, true>(a, s);
-        return launch_big_as<BM, BN, WAVES_M, WAVES_N, true, false>(a, s);
+    if constexpr (BM == 128) {
+        if (a.a_f32) {
+            if (a.out_f32) return launch_big_as<BM, BN, WAVES_M, WAVES_N, true, true>(a, s);
+            return launch_big_as<BM, BN, WAVES_M, WAVES_N, true, false>(a, s);
+        }
     }
+    if (a.a_f32) return hipErrorInvalidValue;  // big_tile_choice() has bf16 rows only in these tiles
     if (a.out_f32) return launch_big_as<BM, BN, WAVES_M, WAVES_N, false, true>(a, s);
     return launch_big_as<BM, BN, WAVES_M, WAVES_N, false, false>(a, s);
 }
@@ -331,16 +336,16 @@ hipError_t grant_lds()
 {
     constexpr size_t lds = big_lds_bytes<BM, BN>();
     if (lds <= 64 * 1024) return hipSuccess;
-    const void *kernels[4] = {
-        reinterpret_cast<const void *>(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, false, false>),
-        reinterpret_cast<const void *>(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, false, true>),
-        reinterpret_cast<const void *>(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, true, false>),
-        reinterpret_cast<const void *>(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, true, true>)};
-    for (const void *k : kernels) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
+    const auto grant = [lds](auto k) {
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    };
+    hipError_t e = grant(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, false, false>);
+    if (e == hipSuccess) e = grant(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, false, true>);
+    if constexpr (BM == 128) {
+        if (e == hipSuccess) e = grant(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, true, false>);
+        if (e == hipSuccess) e = grant(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, true, true>);
     }
-    return hipSuccess;
+    return e;
 }
 
 // Which block tile, if any: 256 x 256, 256 x 128 (bf16 input) or 128 x 128, the
