@@ -57,7 +57,7 @@ enum {
     REC_FC_F32_ROWS = 1,       /* the dense input: fp32 rows, 16-byte aligned */
     REC_FC_DOT = 2,            /* the one-output layer folded into the launch */
     REC_FC_BESIDE_POOLING = 4, /* a pipelined model's */
-    REC_FC_ANY_ORDER = 8       /* sums over k in any order: REC_OPT_FUSE_MLP 1, in order */
+    REC_FC_ANY_ORDER = 8       /* sums over k in any order: REC_OPT_FUSE_MLP 1 (beside pooling never) */
 };
 /* ... and form[0] of its answer: k-tile by k-tile; in tiles of 128 columns and more; the
  * k of a tile dealt to the waves of a block. */

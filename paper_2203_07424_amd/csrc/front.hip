@@ -326,7 +326,7 @@ bool front_layer_rides(const FcProblem &a, bool concat)
     if (!fc_split_rides(a)) return false;
     if (concat) return (long long)((a.M + 15) / 16) * (a.Npad / 32) <= 512;
     const FcTile t = fc_split_tile(a);
-    return t.tm == 1 || t.tm == 2 || (t.tm == 4 && t.wk == 4);
+    return t.tm == 1 || t.tm == 2 || t.tm == 4;
 }
 
 bool front_takes(const ChainProblem &rider) { return chain::narrow_run(rider); }

@@ -407,7 +407,6 @@ bool fc_takes_split(const FcProblem &a)
     if (a.dot_out) return fc_can_fuse_dot(a.Npad) && split_dot_pays(a);
     if (a.num_cus > 0 && fc_big_applies(a, a.num_cus)) return false;
     const long long big_blocks = (long long)a.groups * (a.Npad / 128) * ((a.M + 127) / 128);
-    if (a.corun && !a.a_f32 && a.Npad % 128 == 0 && big_blocks >= 64) return false;
     return (a.Npad % 128 != 0 || big_blocks < 256) && split_tile_pays(a);
 }
 

@@ -70,15 +70,18 @@ hipError_t launch_tiles(const FcProblem &a, hipStream_t s)
     case 248: return launch_as<2, 4, 1, 8, IN, OUT>(a, s);
     case 348: return launch_as<3, 4, 1, 8, IN, OUT>(a, s);
     case 444: return launch_as<4, 4, 1, 4, IN, OUT>(a, s);
-    case 448: return launch_as<4, 4, 1, 8, IN, OUT>(a, s);
     case 548: return launch_as<5, 4, 1, 8, IN, OUT>(a, s);
+    }
+    if constexpr (IN == IN_BF16) {  // fp32 rows cost twice as much: 32 x 64 in two rounds is always less
+        if (t.tm == 4 && t.wk == 8) return launch_as<4, 4, 1, 8, IN, OUT>(a, s);
     }
     return hipErrorInvalidValue;
 }
 
-template <int IN>
+// In front of the one-output layer rows are bf16.
 hipError_t launch_dot(const FcProblem &a, hipStream_t s)
 {
+    constexpr int IN = IN_BF16;
     switch (a.Npad + fc_split_dot_tile(a).tm) {
     case 64 + 1: return launch_as<1, 4, 1, 8, IN, CHAIN_OUT_DOT>(a, s);
     case 128 + 1: return launch_as<1, 4, 2, 4, IN, CHAIN_OUT_DOT>(a, s);
@@ -93,7 +96,6 @@ hipError_t launch_dot(const FcProblem &a, hipStream_t s)
 template <int IN>
 hipError_t launch_in(const FcProblem &a, hipStream_t s)
 {
-    if (a.dot_out) return launch_dot<IN>(a, s);
     return a.out_f32 ? launch_tiles<IN, CHAIN_OUT_F32>(a, s) : launch_tiles<IN, CHAIN_OUT_BF16>(a, s);
 }
 
@@ -116,11 +118,8 @@ hipError_t prepare_tiles()
 template <int IN>
 hipError_t prepare_in()
 {
-    hipError_t e = grant_lds<4, 4, 4, 2, IN, CHAIN_OUT_DOT>();
-    if (e == hipSuccess) e = prepare_tiles<3, IN>();
-    if (e == hipSuccess) e = prepare_tiles<4, IN>();
-    if (e == hipSuccess) e = prepare_tiles<5, IN>();
-    return e;
+    const hipError_t e = prepare_tiles<3, IN>();
+    return e == hipSuccess ? prepare_tiles<5, IN>() : e;
 }
 
 }  // namespace
@@ -175,7 +174,9 @@ FcTile fc_split_dot_tile(const FcProblem &a)
 
 hipError_t fc_split_prepare()
 {
-    hipError_t e = prepare_in<IN_BF16>();
+    hipError_t e = grant_lds<4, 4, 4, 2, IN_BF16, CHAIN_OUT_DOT>();
+    if (e == hipSuccess) e = prepare_tiles<4, IN_BF16>();
+    if (e == hipSuccess) e = prepare_in<IN_BF16>();
     if (e == hipSuccess) e = prepare_in<IN_F32>();
     if (e == hipSuccess) e = prepare_in<IN_F32_ANY>();
     return e;
@@ -191,11 +192,12 @@ bool fc_split_applies(const FcProblem &a)
 
 bool fc_split_rides(const FcProblem &a)
 {
-    return a.a_f32 && a.groups == 1 && !a.dot_out && !a.corun && fc_takes_split(a) && rows_in_vectors(a);
+    return a.a_f32 && a.groups == 1 && !a.dot_out && fc_takes_split(a) && rows_in_vectors(a);
 }
 
 hipError_t launch_fc_split(const FcProblem &a, hipStream_t s)
 {
+    if (a.dot_out) return a.a_f32 ? hipErrorInvalidValue : launch_dot(a, s);
     if (!a.a_f32) return launch_in<IN_BF16>(a, s);
     return rows_in_vectors(a) ? launch_in<IN_F32>(a, s) : launch_in<IN_F32_ANY>(a, s);
 }

@@ -107,7 +107,7 @@ extern "C" rec_status rec_probe_fc_form(int32_t rows, int32_t inputs, int32_t ou
     p.M = rows; p.K = inputs; p.Kpad = (inputs + 63) / 64 * 64; p.Npad = (outputs + 63) / 64 * 64;
     p.lda = p.a_f32 ? p.K : stacks * p.Kpad;
     p.groups = stacks; p.num_cus = compute_units; p.corun = (flags & REC_FC_BESIDE_POOLING) != 0;
-    for (int g = 0; g < stacks && (flags & REC_FC_ANY_ORDER); ++g) p.frag[g] = some;
+    for (int g = 0; g < stacks && (flags & REC_FC_ANY_ORDER) && !p.corun; ++g) p.frag[g] = some;
     if (dot) p.dot_out = reinterpret_cast<float *>(some);
     if (dot && !fc_can_fuse_dot(p.Npad)) return REC_ERR_ARG;
     FcTile t{0, 0, 0};

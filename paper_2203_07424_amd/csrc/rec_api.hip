@@ -336,8 +336,7 @@ hipError_t enqueue_bottom(const rec_model *m, const Bufs &u, const Call &c, hipS
     if (first_done) {
         const FcProblem p = first_bottom_layer(m, u, c);
         A = p.C; lda = p.ldc; a_f32 = false;
-        launches = i = 1;
-        REC_TRY(mark(ev, EV_BOTTOM_FIRST_END, s));
+        launches = i = 1;  // of a forward that is not timed
     }
     while (i < n) {
         const int j = chain_end(m, layers, i, n, 1, c.B, a_f32, false);

@@ -141,7 +141,6 @@ hipError_t scan_prepare()
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<1>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, most);
     if (e == hipSuccess) e = grant_layer_lds<3, 4, 8>();
-    if (e == hipSuccess) e = grant_layer_lds<4, 4, 8>();
     if (e == hipSuccess) e = grant_layer_lds<5, 4, 8>();
     if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<4>),
@@ -207,7 +206,6 @@ hipError_t launch_scan_beside_layer(const int32_t *lengths, int n, long long nnz
     case 248: return launch_beside<2, 4, 8>(b, extra, job, layer, z, ldz, z_cols, s);
     case 348: return launch_beside<3, 4, 8>(b, extra, job, layer, z, ldz, z_cols, s);
     case 444: return launch_beside<4, 4, 4>(b, extra, job, layer, z, ldz, z_cols, s);
-    case 448: return launch_beside<4, 4, 8>(b, extra, job, layer, z, ldz, z_cols, s);
     case 548: return launch_beside<5, 4, 8>(b, extra, job, layer, z, ldz, z_cols, s);
     }
     return hipErrorInvalidValue;

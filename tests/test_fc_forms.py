@@ -82,3 +82,12 @@ def test_up_to_32_rows_and_fp32_rows_at_any_k():
         assert f[0] == b.REC_FORM_SPLIT and f[1] <= 32
         for rows, outputs in ((3000, 256), (4096, 448), (2100, 512)):
             assert form(rows, inputs, outputs, flags=ALONE | b.REC_FC_F32_ROWS)[0] == b.REC_FORM_SPLIT
+
+
+@pytest.mark.parametrize("cus", [64, 120, 256, 304])
+def test_fp32_rows_never_in_64_rows_and_eight_waves(cus):
+    """The kernel is not compiled for it."""
+    for rows in [2 ** k + d for k in range(0, 17) for d in (-1, 0, 1, 2 ** k // 3) if 2 ** k + d > 0]:
+        for outputs in (64, 192, 320, 512, 704, 1024, 2048, 4032):
+            st, f = b.rec_probe_fc_form(rows, 2560, outputs, 1, ALONE | b.REC_FC_F32_ROWS, cus)
+            assert st == b.REC_OK and f != (b.REC_FORM_SPLIT, 64, 64, 8)
