@@ -285,15 +285,24 @@ hipError_t launch_short(const FrontProblem &f, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int LPR, bool HALF, int TM, int TN, int WAVES>
+hipError_t prepare_fc_beside()
+{
+    constexpr size_t lds = split::split_lds_bytes<TM, TN, 1, WAVES>();
+    const hipError_t e = grant_lds(front_fc_kernel<LPR, HALF, false, TM, TN, WAVES>, lds);
+    return e == hipSuccess ? grant_lds(front_fc_kernel<LPR, HALF, true, TM, TN, WAVES>, lds) : e;
+}
+
 template <int LPR, bool HALF>
 hipError_t prepare_long()
 {
-    const int most = (int)chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(front_kernel<LPR, HALF, false>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(front_kernel<LPR, HALF, true>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    constexpr size_t most = chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
+    hipError_t e = grant_lds(front_kernel<LPR, HALF, false>, most);
+    if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, true>, most);
+    if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 2, 2, 8>();
+    if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 2, 4, 8>();
+    if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 4, 4, 4>();
+    return e;
 }
 
 }  // namespace

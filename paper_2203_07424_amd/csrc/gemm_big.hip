@@ -330,20 +330,15 @@ hipError_t launch_big(const FcProblem &a, hipStream_t s)
     return launch_big_as<BM, BN, WAVES_M, WAVES_N, false, false>(a, s);
 }
 
-// More than 64 KB of dynamic LDS has to be granted to a kernel before its first launch.
 template <int BM, int BN, int WAVES_M, int WAVES_N>
-hipError_t grant_lds()
+hipError_t prepare_tiles()
 {
     constexpr size_t lds = big_lds_bytes<BM, BN>();
-    if (lds <= 64 * 1024) return hipSuccess;
-    const auto grant = [lds](auto k) {
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    };
-    hipError_t e = grant(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, false, false>);
-    if (e == hipSuccess) e = grant(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, false, true>);
+    hipError_t e = grant_lds(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, false, false>, lds);
+    if (e == hipSuccess) e = grant_lds(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, false, true>, lds);
     if constexpr (BM == 128) {
-        if (e == hipSuccess) e = grant(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, true, false>);
-        if (e == hipSuccess) e = grant(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, true, true>);
+        if (e == hipSuccess) e = grant_lds(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, true, false>, lds);
+        if (e == hipSuccess) e = grant_lds(fc_big_kernel<BM, BN, WAVES_M, WAVES_N, true, true>, lds);
     }
     return e;
 }
@@ -408,15 +403,11 @@ hipError_t launch_fc_big_behind_scan(const FcProblem &a, const ScanBlocks &scan,
 
 hipError_t fc_big_prepare()
 {
-    const void *behind[] = {reinterpret_cast<const void *>(fc_big_behind_scan_kernel<true>),
-                            reinterpret_cast<const void *>(fc_big_behind_scan_kernel<false>)};
-    for (const void *k : behind) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)big_lds_bytes<128, 128>());
-        if (e != hipSuccess) return e;
-    }
-    hipError_t e = grant_lds<256, 256, 2, 4>();
-    if (e == hipSuccess) e = grant_lds<256, 128, 4, 2>();
-    if (e == hipSuccess) e = grant_lds<128, 128, 2, 4>();
+    hipError_t e = grant_lds(fc_big_behind_scan_kernel<true>, big_lds_bytes<128, 128>());
+    if (e == hipSuccess) e = grant_lds(fc_big_behind_scan_kernel<false>, big_lds_bytes<128, 128>());
+    if (e == hipSuccess) e = prepare_tiles<256, 256, 2, 4>();
+    if (e == hipSuccess) e = prepare_tiles<256, 128, 4, 2>();
+    if (e == hipSuccess) e = prepare_tiles<128, 128, 2, 4>();
     return e;
 }
 

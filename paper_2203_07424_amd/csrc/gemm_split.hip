@@ -100,19 +100,16 @@ hipError_t launch_in(const FcProblem &a, hipStream_t s)
 }
 
 template <int TM, int TN, int WN, int WK, int IN, int OUT>
-hipError_t grant_lds()
+hipError_t prepare_as()
 {
-    constexpr size_t lds = split_lds_bytes<TM, TN, WN, WK>();
-    if (lds <= 64 * 1024) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(fc_split_kernel<TM, TN, WN, WK, IN, OUT>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    return grant_lds(fc_split_kernel<TM, TN, WN, WK, IN, OUT>, split_lds_bytes<TM, TN, WN, WK>());
 }
 
 template <int TM, int IN>
 hipError_t prepare_tiles()
 {
-    const hipError_t e = grant_lds<TM, 4, 1, 8, IN, CHAIN_OUT_BF16>();
-    return e == hipSuccess ? grant_lds<TM, 4, 1, 8, IN, CHAIN_OUT_F32>() : e;
+    const hipError_t e = prepare_as<TM, 4, 1, 8, IN, CHAIN_OUT_BF16>();
+    return e == hipSuccess ? prepare_as<TM, 4, 1, 8, IN, CHAIN_OUT_F32>() : e;
 }
 
 template <int IN>
@@ -174,7 +171,7 @@ FcTile fc_split_dot_tile(const FcProblem &a)
 
 hipError_t fc_split_prepare()
 {
-    hipError_t e = grant_lds<4, 4, 4, 2, IN_BF16, CHAIN_OUT_DOT>();
+    hipError_t e = prepare_as<4, 4, 4, 2, IN_BF16, CHAIN_OUT_DOT>();
     if (e == hipSuccess) e = prepare_tiles<4, IN_BF16>();
     if (e == hipSuccess) e = prepare_in<IN_BF16>();
     if (e == hipSuccess) e = prepare_in<IN_F32>();

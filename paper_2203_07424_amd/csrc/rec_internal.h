@@ -45,6 +45,18 @@ __device__ inline void report_fault(const ErrRecord *err, long long *fault)
     fault[1] = pos;
 }
 
+// A block's LDS beyond 64 KB, what the kernel declares itself included, has to be granted to the
+// kernel before its first launch (not under stream capture).
+template <class Kernel>
+hipError_t grant_lds(Kernel kernel, size_t dynamic)
+{
+    const void *k = reinterpret_cast<const void *>(kernel);
+    hipFuncAttributes has;
+    const hipError_t e = hipFuncGetAttributes(&has, k);
+    if (e != hipSuccess || has.sharedSizeBytes + dynamic <= 64 * 1024) return e;
+    return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dynamic);
+}
+
 struct TableDesc {
     const void *base;
     long long rows;

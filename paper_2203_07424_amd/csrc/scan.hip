@@ -110,8 +110,7 @@ hipError_t launch_beside(const ScanBlocks &b, int extra, const ConcatDense &job,
 template <int TM, int TN, int WK>
 hipError_t grant_layer_lds()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_layer_kernel<TM, TN, WK>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)split::split_lds_bytes<TM, TN, 1, WK>());
+    return grant_lds(scan_offsets_layer_kernel<TM, TN, WK>, split::split_lds_bytes<TM, TN, 1, WK>());
 }
 
 int concat_blocks(const ConcatDense &job)
@@ -137,14 +136,15 @@ hipError_t launch_clear_tile_words(unsigned long long *words, int n, hipStream_t
 
 hipError_t scan_prepare()
 {
-    const int most = (int)chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<1>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    constexpr size_t most = chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
+    hipError_t e = grant_lds(scan_offsets_ride_kernel<1>, most);
+    if (e == hipSuccess) e = grant_lds(scan_offsets_ride_kernel<4>, most);
+    if (e == hipSuccess) e = grant_layer_lds<2, 2, 8>();
+    if (e == hipSuccess) e = grant_layer_lds<2, 4, 8>();
     if (e == hipSuccess) e = grant_layer_lds<3, 4, 8>();
+    if (e == hipSuccess) e = grant_layer_lds<4, 4, 4>();
     if (e == hipSuccess) e = grant_layer_lds<5, 4, 8>();
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(scan_offsets_ride_kernel<4>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    return e;
 }
 
 // With a stack riding along the launch lasts as long as the stack, so for a few
