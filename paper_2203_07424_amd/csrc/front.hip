@@ -254,7 +254,6 @@ hipError_t launch_fc_front(const FrontProblem &f, hipStream_t s)
     case 228: return launch_fc_beside<LPR, HALF, 2, 2, 8>(f, s);
     case 248: return launch_fc_beside<LPR, HALF, 2, 4, 8>(f, s);
     case 244: return launch_fc_beside<LPR, HALF, 2, 4, 4>(f, s);
-    case 444: return launch_fc_beside<LPR, HALF, 4, 4, 4>(f, s);
     }
     return hipErrorInvalidValue;
 }
@@ -301,7 +300,6 @@ hipError_t prepare_long()
     if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, true>, most);
     if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 2, 2, 8>();
     if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 2, 4, 8>();
-    if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 4, 4, 4>();
     return e;
 }
 
@@ -328,14 +326,16 @@ hipError_t front_prepare()
 }
 
 // Beside short bags a layer rides along in tiles of 16 x 32, where these are few; else
-// in the tiles whose LDS, which every block of a launch gets, leaves pooling more than
-// a block a compute unit.
+// in tiles of up to 32 rows.  Those of 48 and 80 would leave pooling one block a compute unit by their
+// LDS, which every block of a launch gets, and those of 64 two: the layer beside the scan alone is the
+// shorter forward (us, beside pooling / beside the scan; 1024 columns and 4 tables x 1790 samples, 600 inputs 38.1
+// / 34.5, 1536 43.1 / 39.9, 2560 49.2 / 48.1; 2560, x 1600 45.8 / 48.2, the one that lost).
 bool front_layer_rides(const FcProblem &a, bool concat)
 {
     if (!fc_split_rides(a)) return false;
     if (concat) return (long long)((a.M + 15) / 16) * (a.Npad / 32) <= 512;
     const FcTile t = fc_split_tile(a);
-    return t.tm == 1 || t.tm == 2 || t.tm == 4;
+    return t.tm <= 2;
 }
 
 bool front_takes(const ChainProblem &rider) { return chain::narrow_run(rider); }

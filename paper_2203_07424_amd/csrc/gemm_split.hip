@@ -149,7 +149,8 @@ FcTile fc_split_tile(const FcProblem &a)
         const long long cost = (f.tm * (a.a_f32 ? 2 : 1) + f.tn) * (10 * rounds + (rounds == 1 ? f.once1 : f.once));
         if (best.tm == 0 || cost < least) {
             // Eight waves with a unit each gain nothing, and most fp32 layers run beside pooling,
-            // whose waves four leave more room (500 samples, 256 blocks 32.8 / 30.8 us per forward).
+            // whose waves four leave more room (us per forward, eight / four: 500 samples beside 10 tables, 600 -> 1024
+            // 27.0 / 26.1, 2560 33.3 / 31.3; 1000 beside 4, 1000 -> 512 26.4 / 24.2, beside 6, 1536 29.3 / 28.0).
             const bool four = a.Kpad <= 8 * UNIT || (a.a_f32 && f.tn == 4 && 4 * blocks > 3 * cus);
             best = FcTile{f.tm, f.tn, rounds > 1 || a.waves > 0 || (four && f.tm == 2) ? f.wk : f.wk1};
             least = cost;

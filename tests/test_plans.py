@@ -47,3 +47,9 @@ def test_wherever_the_shapes_allow_is_not_a_matter_of_weights(batch):
     samples a compute unit on; told to, at any batch."""
     assert plan(batch, fuse=2)[1] == 1
     assert plan(batch)[1] == (2 if batch <= 8 * 256 else 1)
+
+
+@pytest.mark.parametrize("batch,dense,mask", [(1536, 1536, FRONT | LAYER | TAIL), (1600, 1536, LAYER | TAIL), (1790, 2560, LAYER | TAIL)])
+def test_a_layer_in_tiles_of_64_rows_leaves_pooling_its_launch(batch, dense, mask):
+    assert b.rec_probe_fc_form(batch, dense, 1024, 1, b.REC_FC_ANY_ORDER | b.REC_FC_F32_ROWS)[1][1] == (64 if batch > 1536 else 32)
+    assert plan(batch, tables=4, dense=dense)[0] == mask
