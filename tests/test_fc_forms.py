@@ -91,3 +91,25 @@ def test_fp32_rows_never_in_64_rows_and_eight_waves(cus):
         for outputs in (64, 192, 320, 512, 704, 1024, 2048, 4032):
             st, f = b.rec_probe_fc_form(rows, 2560, outputs, 1, ALONE | b.REC_FC_F32_ROWS, cus)
             assert st == b.REC_OK and f != (b.REC_FORM_SPLIT, 64, 64, 8)
+
+
+def test_the_device_tests_run_every_form():
+    """On 256 compute units: the shapes of the towers' tests take each tile that deals k, and those
+    of the first layer each tile it rides in."""
+    import test_gpu_first_layer as first
+    import test_gpu_split as split
+    plain, dots = set(), set()
+    for rows, tables, dim, dense, hidden, towers in split.TOWERS:
+        widths = (dense + tables * dim,) + hidden
+        for i, n in enumerate(hidden):
+            dot = i + 1 == len(hidden) and -(-n // 64) in (1, 2, 4)
+            f = form(rows, widths[i], n, towers, ALONE | (b.REC_FC_DOT if dot else 0))
+            if f[0] == b.REC_FORM_SPLIT:
+                (dots if dot else plain).add(f[1:])
+    assert plain == {(16, 16, 8), (16, 32, 8), (32, 32, 4), (32, 32, 8), (32, 64, 4), (32, 64, 8), (48, 64, 8), (64, 64, 4),
+                     (64, 64, 8), (80, 64, 8)}
+    assert dots == {(16, 64, 8), (16, 128, 4), (32, 128, 4), (16, 256, 2), (32, 256, 2), (64, 256, 2)}
+    ride = {(r[7], r[8]) for r in first.POOLED}
+    small = {(16, 16, 8), (16, 32, 8), (32, 32, 4), (32, 32, 8), (32, 64, 4), (32, 64, 8)}
+    assert {t for w, t in ride if w == "pooling"} == small
+    assert {t for w, t in ride if w == "scan"} >= {(32, 32, 4), (32, 64, 4), (48, 64, 8), (64, 64, 4), (80, 64, 8), (128, 128, 1)}

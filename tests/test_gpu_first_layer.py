@@ -58,30 +58,38 @@ def compare(binding, m, batch, concat=False):
     return joint
 
 
-@pytest.mark.parametrize("T,D,dtype,B,F,bottom,mean", [
-    (1, 32, np.float32, 1, 2560, (1024, 256), 20),      # beside scan and pooling, tiles of 16 x 16
-    (10, 32, np.float16, 17, 1000, (1024, 256), 20),
-    (10, 64, np.float32, 113, 1000, (1024, 256), 8),    # 16 x 32
-    (11, 32, np.float32, 223, 1000, (1024, 256), 10),   # 32 x 32
-    (10, 32, np.float32, 301, 2560, (1024, 256), 9),    # 32 x 64
-    (7, 32, np.float32, 1001, 1536, (1024, 256), 8),    # 64 x 64
-    (8, 64, np.float16, 895, 500, (256,), 12),          # the largest batches
-    (9, 64, np.float16, 797, 500, (256,), 12),          # one tile of lengths more: beside the scan alone
-    (10, 32, np.float32, 901, 1536, (1024, 256), 8),
-    (30, 32, np.float16, 601, 1000, (1024, 256), 9),    # 9 tiles of lengths: their sums handed on
-    (9, 32, np.float16, 195, 2560, (1024, 256), 9),     # 32 x 32, eight waves
-    (10, 32, np.float32, 751, 2560, (1024, 256), 8),    # 48 x 64
-    (5, 32, np.float32, 1187, 1000, (1024, 256), 8),    # 80 x 64
-    (2, 64, np.float32, 1024, 1000, (512, 64), 9),      # 64 x 64, eight waves
-    (12, 16, np.float32, 100, 640, (1024, 32), 9),      # rows of 64 bytes
-    (12, 8, np.float16, 100, 640, (1024, 32), 9),       # 16-byte rows: never with pooling
-    (5, 32, np.float32, 3500, 1536, (1024, 256), 8),    # 128 x 128, 224 tiles
-    (4, 32, np.float32, 2049, 1000, (1024, 256), 7),    # 136
-    (9, 32, np.float32, 4097, 1000, (1024, 256), 6),    # and with 19 tiles of lengths
-    (3, 64, np.float32, 65, 300, (), 7),                # the layer is the whole stack
-    (6, 32, np.float32, 70, 1501, (1024, 256), 7),      # rows that are not read in vectors
-])
-def test_layer_of_a_pooled_model(binding, T, D, dtype, B, F, bottom, mean):
+# where: the launch that has the layer; tile: its rows, columns and the waves that share its
+# k on 256 compute units (128 x 128: csrc/gemm_big.hip).
+POOLED = [
+    (1, 32, np.float32, 1, 2560, (1024, 256), 20, "pooling", (16, 16, 8)),
+    (10, 32, np.float16, 17, 1000, (1024, 256), 20, "pooling", (16, 16, 8)),
+    (10, 64, np.float32, 113, 1000, (1024, 256), 8, "pooling", (16, 32, 8)),
+    (11, 32, np.float32, 223, 1000, (1024, 256), 10, "pooling", (32, 32, 8)),
+    (9, 32, np.float16, 195, 2560, (1024, 256), 9, "pooling", (32, 32, 8)),
+    (8, 64, np.float16, 895, 500, (256,), 12, "pooling", (32, 32, 4)),          # the largest batches
+    (10, 32, np.float32, 301, 2560, (1024, 256), 9, "pooling", (32, 64, 8)),
+    (7, 32, np.float32, 1001, 1536, (1024, 256), 8, "pooling", (32, 64, 4)),
+    (2, 64, np.float32, 1024, 1000, (512, 64), 9, "pooling", (32, 64, 4)),
+    (9, 64, np.float16, 797, 500, (256,), 12, "scan", (32, 32, 4)),             # one tile of lengths more
+    (10, 32, np.float32, 901, 1536, (1024, 256), 8, "scan", (32, 64, 4)),
+    (30, 32, np.float16, 601, 1000, (1024, 256), 9, "scan", (48, 64, 8)),       # 9 tiles of lengths: their sums handed on
+    (10, 32, np.float32, 751, 2560, (1024, 256), 8, "scan", (48, 64, 8)),
+    (4, 32, np.float32, 1601, 1536, (1024, 256), 8, "scan", (64, 64, 4)),       # few bags, but 64 KB of LDS a block
+    (4, 32, np.float16, 1793, 1000, (1024, 256), 8, "scan", (64, 64, 4)),
+    (10, 64, np.float32, 2047, 600, (1024, 256), 8, "scan", (64, 64, 4)),
+    (5, 32, np.float32, 1187, 1000, (1024, 256), 8, "scan", (80, 64, 8)),
+    (12, 16, np.float32, 100, 640, (1024, 32), 9, "pooling", (16, 32, 8)),      # rows of 64 bytes
+    (12, 8, np.float16, 100, 640, (1024, 32), 9, "scan", (16, 32, 8)),          # 16-byte rows: never with pooling
+    (5, 32, np.float32, 3500, 1536, (1024, 256), 8, "scan", (128, 128, 1)),     # 224 tiles
+    (4, 32, np.float32, 2049, 1000, (1024, 256), 7, "scan", (128, 128, 1)),     # 136
+    (9, 32, np.float32, 4097, 1000, (1024, 256), 6, "scan", (128, 128, 1)),     # and with 19 tiles of lengths
+    (3, 64, np.float32, 65, 300, (), 7, "pooling", (16, 16, 8)),                # the layer is the whole stack
+    (6, 32, np.float32, 70, 1501, (1024, 256), 7, None, None),                  # rows that are not read in vectors
+]
+
+
+@pytest.mark.parametrize("T,D,dtype,B,F,bottom,mean,where,tile", POOLED)
+def test_layer_of_a_pooled_model(binding, T, D, dtype, B, F, bottom, mean, where, tile):
     print("first layer", T, D, np.dtype(dtype).name, B, F, bottom, flush=True)
     g = np.random.default_rng(1500 + T + B)
     R = 300
@@ -91,6 +99,13 @@ def test_layer_of_a_pooled_model(binding, T, D, dtype, B, F, bottom, mean):
     idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
     mlp, top = stack(g, (F,) + bottom + (D,)), stack(g, (D + T * (T + 1) // 2, 200, 72, 1))
     m = H.make_model(binding, tabs, mlp, top, B, idx.size, F)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if cus == 256:
+        _, mask, _ = binding.rec_probe_plan(m.handle, B, idx.size)
+        assert bool(mask & binding.REC_PLAN_LAYER) == (where is not None)
+        assert bool(mask & binding.REC_PLAN_FRONT) == (where != "scan")
+        form = binding.rec_probe_fc_form(B, F, (bottom + (D,))[0], 1, binding.REC_FC_ANY_ORDER | binding.REC_FC_F32_ROWS)[1]
+        assert tile is None or form[1:] == tile
     dense = g.standard_normal((B, F)).astype(np.float32)
     batch = synth.Batch(dense, idx, lens)
     logits, _, x0, _, pooled = compare(binding, m, batch)

@@ -48,20 +48,27 @@ def both(binding, m, batch):
     return got, plain
 
 
-@pytest.mark.parametrize("B,T,D,F,hidden,towers", [
-    (1, 10, 64, 64, (512, 128), 1),
-    (16, 10, 64, 40, (512, 64), 3),
-    (17, 26, 64, 64, (1024, 512, 256), 4),
+TOWERS = [  # with the tiles of the layers on 256 compute units
+    (1, 10, 64, 64, (512, 128), 1),            # 16 x 16, dot 16 x 128
+    (16, 10, 64, 40, (512, 64), 3),            # 16 x 16, dot 16 x 64
+    (17, 26, 64, 64, (1024, 512, 256), 4),     # 16 x 32, 16 x 16, dot 16 x 256
     (31, 12, 64, 10, (640, 256), 2),
-    (65, 30, 64, 100, (1100, 1000, 72), 2),
-    (300, 26, 64, 64, (1024, 512, 256), 4),
-    (200, 26, 64, 64, (1024, 512, 256), 4),    # 64 rows a block, eight waves
-    (320, 26, 64, 64, (1024, 512, 256), 4),    # 80 rows, the last block full
-    (257, 10, 64, 40, (1100, 1000, 72), 3),    # 48 rows
+    (65, 30, 64, 100, (1100, 1000, 72), 2),    # 32 x 32 twice, eight waves
+    (300, 26, 64, 64, (1024, 512, 256), 4),    # 80 x 64, 48 x 64
+    (200, 26, 64, 64, (1024, 512, 256), 4),    # 64 x 64 and 32 x 64, eight waves
+    (320, 26, 64, 64, (1024, 512, 256), 4),    # 80 x 64, the last block full
+    (257, 10, 64, 40, (1100, 1000, 72), 3),    # 32 x 64, four waves, 64 x 64, eight
     (300, 10, 64, 7, (448,), 8),               # the layer leaves fp32 for a dot kernel
-    (1000, 20, 64, 33, (600, 200), 3),
+    (1000, 20, 64, 33, (600, 200), 3),         # 64 x 64, four waves
     (520, 26, 64, 64, (1024, 512, 256), 4),    # 160 tiles of 128 x 128 instead, then one round of 80 rows
-])
+    (520, 3, 64, 64, (250, 1100), 1),          # 32 x 32, four waves
+    (2100, 8, 64, 64, (256,), 4),              # dot 64 x 256
+    (600, 8, 64, 64, (256,), 8),               # dot 32 x 256
+    (2500, 4, 64, 64, (128,), 3),              # dot 32 x 128
+]
+
+
+@pytest.mark.parametrize("B,T,D,F,hidden,towers", TOWERS)
 def test_towers_layer_by_layer(binding, B, T, D, F, hidden, towers):
     print("split towers", B, T, D, F, hidden, towers, flush=True)
     g = np.random.default_rng(1000 + B + T)
