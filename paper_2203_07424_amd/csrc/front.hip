@@ -20,13 +20,16 @@
 // layer's, which write its columns of the Predict-FC input rows too), then pooling.
 // 64-64 in front of four towers, 26 tables x 300 42.6 -> 32.5 us, x 1 28.3 -> 17.3.
 //
-// The pooling waves of front_kernel get the 122 registers Bottom-FC's need, so 16
+// front_fc_kernel's pooling blocks get the registers and the LDS of the layer's tile: tiles of up to 32 rows,
+// between 68 and 123 registers.  The pooling waves of front_kernel get the 122 registers Bottom-FC's need, so 16
 // of them share a compute unit instead of 32.  Up to LONG_BAGS that costs less
 // than the launch (us per forward, two launches / one: 8 tables x 800 samples 15.7 / 12.8, 40 x 160
 // 26.9 / 23.2, 10 x 700 22.2 / 20.2); beyond it some shapes lose (10 x 800 22.9 / 23.2, with 20 fp16
-// rows a bag 10 x 1000 17.8 / 18.2).  front_fc_kernel has no such waves, but beyond that
-// the layer beside the scan alone (csrc/scan.hip) wins as often (12 000 bags: 50.5 / 49.7, 57.9
-// as three launches; 14 000 and more 59.8 / 52.2, 41.6 / 24.8).  front_short_kernel: 26 tables x 300 samples 47.4 -> 44.8 us, x 16
+// rows a bag 10 x 1000 17.8 / 18.2).  For front_fc_kernel the line lies
+// there too: below, the layer beside the scan alone (csrc/scan.hip) is the longer forward in most shapes and
+// near the line as often the shorter one (beside pooling / beside the scan: 30 x 200, 2560 -> 1024 36.0 / 38.3; 14 x
+// 500, 600 -> 512 with 8 ids 27.1 / 25.5, with 60 31.3 / 31.6); beyond it that is the shorter (12 000 bags: 50.5 /
+// 49.7, 57.9 as three launches; 14 000 and more 59.8 / 52.2, 41.6 / 24.8).  front_short_kernel: 26 tables x 300 samples 47.4 -> 44.8 us, x 16
 // 36.7 -> 34.0, even at 16380 bags, where adding up the lengths takes as long as the launches it saves.
 #include <algorithm>
 
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
     }
     b -= tiles;
     if (b < chain_blocks) {
-        chain::touch_args<72 + sizeof(out) + sizeof(a)>();
+        chain::touch_args<80 + sizeof(out) + sizeof(a)>();
         const int share = chain::touch_share(chain_blocks);
         chain::mlp_chain_block<true, 1, 1>(a, smem, b, 0, (b >> 3) % share, share);
         return;

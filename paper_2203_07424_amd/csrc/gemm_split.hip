@@ -13,12 +13,12 @@
 // lines into a corner of LDS that only this wave uses (read as fragments from memory
 // each lane of a load would touch another line).  The partial tiles are added up through LDS
 // in the order of the waves, once.  us per launch, k-tile by k-tile / here:
-// 16 samples, 1728 -> 1024 four towers 12.2 / 4.4; 300 samples 17.3 / 12.6, 1024 -> 512 8.5 / 6.6,
+// 16 samples, 1728 -> 1024 four towers 12.2 / 4.4; 300 samples 17.3 / 11.2, 1024 -> 512 8.5 / 6.3,
 // 512 -> 256 -> 1 10.5 / 6.2; 256 samples, 884 -> 512 8.5 / 3.5, 512 -> 128 -> 1 6.0 / 4.2;
 // one sample of 2560 fp32 -> 1024 16.8 / 4.6.
 //
-// More waves or more units in flight a wave change nothing or lose: two or more blocks
-// on a compute unit cover one another's trips.
+// Where two or more blocks share a compute unit they cover one another's trips, and more waves a
+// block or more units in flight a wave change nothing or lose; a block by itself has eight waves for it.
 #include "gemm_split_body.h"
 
 namespace rec {
@@ -121,9 +121,10 @@ hipError_t prepare_in()
 
 }  // namespace
 
-// A compute unit spends its time bringing both operands of its blocks through its L1
-// (about 40 bytes a clock) and, once, on the trips of a first block that nothing covers: rounds
-// of blocks plus about one, times the rows and columns of a tile.  With one block a
+// A compute unit spends its time bringing both operands of its blocks through its L1 (25 bytes a
+// clock where it has one block of eight waves, 36 where two cover one another) and, once, on the launch and
+// the trips of a first block that nothing covers, about 3 us: rounds of blocks plus about one, times the
+// rows and columns of a tile.  With one block a
 // compute unit eight waves share its k, else four, and two blocks cover one another's trips;
 // tiles of 48 and 80 rows, one block a compute unit at a time, pay that once more in every
 // round.  us per launch (64 x 64 or 32 x 64 with four waves, the choice without these two /

@@ -440,7 +440,7 @@ __device__ inline void narrow_layers(const Run &a, const RunCtx &t, Ahead<1> &ah
 // or, with two row tiles and at most four chunks, one chunk of one tile.
 // red: [CH_WAVES][rows] floats of LDS.
 // MAXC: the most chunks a wave has in any layer, 4 (up to 1024 columns) or 1 (up to
-// 256: 106 registers instead of 174 to 236, so that two blocks share a compute
+// 256: 122 registers instead of 174 to 227, so that two blocks share a compute
 // unit and a launch of more blocks than compute units does not take a second
 // round for it: towers of 96-72, 264 blocks, 24.0 -> 19.4 us per forward).
 // `ahead` holds the first layer's request.
