@@ -12,7 +12,8 @@ Default run (workload rmc2, the configuration the metric is quoted on):
   in_order            the same K steps with everything in order on one stream
   sustained           the pipelined loop kept up for at least two seconds
   latency_ms          one batch at a time, host launch and synchronisation included
-  stage_ms, mlp_mfma  HIP-event brackets around every stage of in-order forwards
+  stage_ms, mlp_mfma  HIP-event brackets around every stage of in-order forwards (timed,
+                      these give a first Bottom-FC layer a launch of its own)
   roofline            the pooling kernel on the uniform-id twin (no reuse for the
                       caches to serve): algorithmic bytes / launch time against the
                       HBM peak
