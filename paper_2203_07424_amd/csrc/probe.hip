@@ -99,7 +99,7 @@ extern "C" rec_status rec_probe_fc_form(int32_t rows, int32_t inputs, int32_t ou
     using namespace rec;
     static char some[16] __attribute__((aligned(16)));
     const bool dot = (flags & REC_FC_DOT) != 0;
-    if (!form || rows < 1 || inputs < 1 || outputs < 1 || inputs > (1 << 20) || outputs > (1 << 20) || stacks < 1 ||
+    if (!form || rows < 1 || rows > (1 << 30) || inputs < 1 || outputs < 1 || inputs > (1 << 20) || outputs > (1 << 20) || stacks < 1 ||
         stacks > MAX_GROUPS || compute_units < 1)
         return REC_ERR_ARG;
     FcProblem p{};

@@ -16,10 +16,15 @@ def form(rows, inputs, outputs, stacks=1, flags=ALONE):
 
 
 def test_what_is_no_layer_is_refused():
-    for bad in ((0, 64, 64, 1), (1, 0, 64, 1), (1, 64, 0, 1), (1, 64, 64, 0), (1, 64, 64, b.REC_MAX_TOWERS + 1), (1, 2 ** 20 + 1, 64, 1)):
+    for bad in ((0, 64, 64, 1), (1, 0, 64, 1), (1, 64, 0, 1), (1, 64, 64, 0), (1, 64, 64, b.REC_MAX_TOWERS + 1), (1, 2 ** 20 + 1, 64, 1),
+                (2 ** 30 + 1, 64, 64, 1)):
         assert b.rec_probe_fc_form(*bad)[0] == b.REC_ERR_ARG
     assert b.rec_probe_fc_form(1, 64, 64, 1, 0, 0)[0] == b.REC_ERR_ARG
     assert b.rec_probe_fc_form(1, 64, 320, 1, b.REC_FC_DOT)[0] == b.REC_ERR_ARG
+    assert form(2 ** 30, 2 ** 20, 2 ** 20, b.REC_MAX_TOWERS)[0] != b.REC_FORM_SPLIT  # offsets beyond 32 bits
+    for rows in (1, 2 ** 30):
+        for flags in range(16):
+            b.rec_probe_fc_form(rows, 2048, 256, 1, flags, 1)
 
 
 @pytest.mark.parametrize("rows", [4097, 4500, 6016])

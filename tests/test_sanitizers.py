@@ -49,8 +49,9 @@ def test_oracle_pins_hold_under_address_and_ub_sanitizers():
 
 
 def test_library_host_code_under_address_and_ub_sanitizers():
-    """The device library with instrumented host code: model creation and every
-    argument check that needs no GPU (tests/test_abi.py) must run clean."""
+    """The device library with instrumented host code: model creation, every argument
+    check that needs no GPU (tests/test_abi.py) and the choice of kernels and launches must
+    run clean."""
     from paper_2203_07424_amd import build
     lib = build.build_host_sanitized()
     runtime = build.sanitizer_runtime()
@@ -60,5 +61,6 @@ def test_library_host_code_under_address_and_ub_sanitizers():
     env["REC_MI355X_LIBRARY"] = lib
     which = _run([sys.executable, "-c", "from paper_2203_07424_amd import binding as b; print(b._lib._name)"], env)
     assert which.strip().endswith("librec_mi355x_hostsan.so"), which
-    out = _run([sys.executable, "-m", "pytest", "-x", "-q", "-p", "no:cacheprovider", "tests/test_abi.py"], env)
+    out = _run([sys.executable, "-m", "pytest", "-x", "-q", "-p", "no:cacheprovider", "tests/test_abi.py",
+                "tests/test_fc_forms.py", "tests/test_plans.py"], env)
     assert " passed" in out and "failed" not in out, out[-2000:]
