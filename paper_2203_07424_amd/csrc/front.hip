@@ -21,11 +21,10 @@
 // 64-64 in front of four towers, 26 tables x 300 42.6 -> 32.5 us, x 1 28.3 -> 17.3.
 //
 // front_fc_kernel's pooling blocks get the registers and the LDS of the layer's tile: tiles of up to 32 rows,
-// between 68 and 123 registers.  The pooling waves of front_kernel get the 122 registers Bottom-FC's need, so 16
-// of them share a compute unit instead of 32.  Up to LONG_BAGS that costs less
-// than the launch (us per forward, two launches / one: 8 tables x 800 samples 15.7 / 12.8, 40 x 160
-// 26.9 / 23.2, 10 x 700 22.2 / 20.2); beyond it some shapes lose (10 x 800 22.9 / 23.2, with 20 fp16
-// rows a bag 10 x 1000 17.8 / 18.2).  For front_fc_kernel the line lies
+// between 68 and 123 registers.  The pooling waves of front_kernel get the registers Bottom-FC's need: 122, and 16
+// waves share a compute unit instead of 32, or 64 in the light form (front_takes_light()).
+// LONG_BAGS: with 122 registers some shapes lose beyond it against two launches (us per forward, two launches / one: 8
+// tables x 800 samples 15.7 / 12.8, 40 x 160 26.9 / 23.2, 10 x 700 22.2 / 20.2; 10 x 800 22.9 / 23.2).  For front_fc_kernel the line lies
 // there too: below, the layer beside the scan alone (csrc/scan.hip) is the longer forward in most shapes and
 // near the line as often the shorter one (beside pooling / beside the scan: 30 x 200, 2560 -> 1024 36.0 / 38.3; 14 x
 // 500, 600 -> 512 with 8 ids 27.1 / 25.5, with 60 31.3 / 31.6); beyond it that is the shorter (12 000 bags: 50.5 /
@@ -47,6 +46,20 @@ using namespace pool;
 using split::Rider;
 
 constexpr int LONG_BAGS = 7 * SCAN_TILE / 2, SHORT_FORM_BAGS = 6 * SCAN_TILE;
+// With the light form of a whole Bottom-FC: us per forward, two launches / one, 10 tables of 80 fp32 rows x 1024
+// samples 31.1 / 27.7, 40 of 80 fp16 rows x 256 30.6 / 25.9, 13 x 966 of 10 ids 18.0 / 15.4 (12 558 bags), 14 x 949 of 42
+// 29.9 / 26.3 (13 286).  Each block of eight bags reads all earlier lengths, so beyond it shapes lose: 12 x 1276 24.1 /
+// 25.0 (15 312), 5 x 3155 26.6 / 28.0 (15 775), 40 x 800 43.2 / 52.7.
+constexpr int LIGHT_BAGS = 7 * SCAN_TILE;
+constexpr int LIGHT_INPUT = 512;  // inputs of such a stack at most: four blocks a compute unit by its LDS
+
+// The light form of Bottom-FC, beside twice the pooling waves, beyond LONG_BAGS and up to there where
+// pooling is the longer part: by the bytes of rows a compute unit gathers (us per forward, other form / light; 320 KB
+// 19.4 / 18.3, 450 21.9 / 20.1; 256 23.4 / 23.9, 64 12.6 / 13.4).
+inline bool front_takes_light(int n, long long nnz, int rowbytes, int num_cus)
+{
+    return n > LONG_BAGS || nnz * rowbytes > (long long)num_cus * (288 * 1024);
+}
 
 // Sum over max(len, 0) of lengths [0, n) by all threads of the block; s_w: a word
 // per wave.
@@ -89,8 +102,9 @@ __device__ inline void pool_from_lengths(const int32_t *__restrict__ len, const 
                                              (int)min(end, nnz), one, err);
 }
 
-template <int LPR, bool HALF, bool STREAM>
-__global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void front_kernel(
+// LIGHT: Bottom-FC within 64 registers, so that 32 pooling waves share a compute unit.
+template <int LPR, bool HALF, bool STREAM, bool LIGHT>
+__global__ __launch_bounds__(chain::CH_THREADS, LIGHT ? 8 : chain::waves_per_simd<1>()) void front_kernel(
     const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     long long nnz, int n, int tiles, int chain_blocks, int per, unsigned B, unsigned magic, int T, float one,
     int32_t *__restrict__ offsets, ErrRecord *err, const PoolOut out, const ChainArgs<1> a)
@@ -98,15 +112,23 @@ __global__ __launch_bounds__(chain::CH_THREADS, chain::waves_per_simd<1>()) void
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int b = blockIdx.x;
     if (b < tiles) {
-        __shared__ ScanShared sh;
-        if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b, sh);
+        if constexpr (LIGHT) {
+            ScanShared &sh = *reinterpret_cast<ScanShared *>(smem);
+            if (threadIdx.x < SCAN_THREADS) scan_offsets_tile<true>(len, n, nnz, TileLink{}, offsets, err, b, sh);
+        } else {
+            __shared__ ScanShared sh;
+            if (threadIdx.x < SCAN_THREADS) scan_offsets_tile(len, n, nnz, TileLink{}, offsets, err, b, sh);
+        }
         return;
     }
     b -= tiles;
     if (b < chain_blocks) {
         chain::touch_args<80 + sizeof(out) + sizeof(a)>();
         const int share = chain::touch_share(chain_blocks);
-        chain::mlp_chain_block<true, 1, 1>(a, smem, b, 0, (b >> 3) % share, share);
+        if constexpr (LIGHT)
+            chain::light_chain_block<true>(a, smem, b, 0, (b >> 3) % share, share);
+        else
+            chain::mlp_chain_block<true, 1, 1>(a, smem, b, 0, (b >> 3) % share, share);
         return;
     }
     pool_from_lengths<chain::CH_WAVES, LPR, HALF, STREAM>(len, tables, indices, nnz, n, b - chain_blocks, per,
@@ -219,9 +241,11 @@ hipError_t launch_long(const FrontProblem &f, const ChainProblem &a, hipStream_t
     const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE, chain_blocks = (a.M + 31) / 32;
     const int pool_blocks = ((n + chain::CH_WAVES - 1) / chain::CH_WAVES + 7) / 8 * 8;
     const BagTable div = BagTable::of_batch(f.B);
-    auto k = f.stream_rows ? front_kernel<LPR, HALF, true> : front_kernel<LPR, HALF, false>;
+    auto k = front_takes_light(n, f.nnz, LPR * 16, a.num_cus)
+                 ? (f.stream_rows ? front_kernel<LPR, HALF, true, true> : front_kernel<LPR, HALF, false, true>)
+                 : (f.stream_rows ? front_kernel<LPR, HALF, true, false> : front_kernel<LPR, HALF, false, false>);
     hipLaunchKernelGGL(k, dim3(tiles + chain_blocks + pool_blocks), dim3(chain::CH_THREADS),
-                       chain::chain_lds_bytes<1>(a.ld_lds), s, f.lengths, f.tables, f.indices, f.nnz, n, tiles, chain_blocks,
+                       std::max(chain::chain_lds_bytes<1>(a.ld_lds), sizeof(ScanShared)), s, f.lengths, f.tables, f.indices, f.nnz, n, tiles, chain_blocks,
                        pool_blocks / 8, div.B, div.magic, f.T, 1.0f, f.offsets, f.err, f.out, one_stack(a));
     return hipGetLastError();
 }
@@ -299,8 +323,10 @@ template <int LPR, bool HALF>
 hipError_t prepare_long()
 {
     constexpr size_t most = chain::chain_lds_bytes<1>(CHAIN_MAX_WIDTH + chain::CH_LDS_PAD);
-    hipError_t e = grant_lds(front_kernel<LPR, HALF, false>, most);
-    if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, true>, most);
+    hipError_t e = grant_lds(front_kernel<LPR, HALF, false, false>, most);
+    if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, true, false>, most);
+    if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, false, true>, most);
+    if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, true, true>, most);
     if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 2, 2, 8>();
     if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 2, 4, 8>();
     return e;
@@ -308,11 +334,12 @@ hipError_t prepare_long()
 
 }  // namespace
 
-bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat)
+bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat, int ride_input)
 {
     const long long n = (long long)T * B;
     const int rowbytes = D * (dtype == REC_F16 ? 2 : 4);
-    if (n > (concat ? SHORT_FORM_BAGS : LONG_BAGS) || (rowbytes != 64 && rowbytes != 128 && rowbytes != 256)) return false;
+    const int most = concat ? SHORT_FORM_BAGS : ride_input > 0 && ride_input <= LIGHT_INPUT ? LIGHT_BAGS : LONG_BAGS;
+    if (n > most || (rowbytes != 64 && rowbytes != 128 && rowbytes != 256)) return false;
     const bool sh = pool_short_applies(rowbytes, nnz, n);
     return concat ? sh : !sh && pool_narrow(max_rows, rowbytes);
 }

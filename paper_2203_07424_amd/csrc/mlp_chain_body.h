@@ -117,9 +117,9 @@ constexpr int fetch_ahead() { return CNT <= 2 ? 8 : 4; }
 // fragments straight from global memory (L2) into operand registers, requested
 // fetch_ahead() steps before their use in straight-line code (a branch around a
 // request makes the compiler wait for all of them).
-template <int CNT>
+template <int CNT, int AHEAD = fetch_ahead<CNT>()>
 struct WeightStream {
-    static constexpr int PF = fetch_ahead<CNT>();
+    static constexpr int PF = AHEAD;
     const char *w;   // chunk 0's first fragment (the same in all lanes), chunk c wstep bytes further on
     unsigned wstep, lane16;
     int KS;          // k-steps in all, a multiple of 4
@@ -144,12 +144,10 @@ struct WeightStream {
 // lane's part of row tile 0.  The activation fragments are read from LDS a group
 // of XG steps before their products, so that neither their latency nor the
 // weights' is met at a product.
-template <int CNT, int RT>
-__device__ inline void chunk_product(WeightStream<CNT> &ws, const __bf16 *x, int xstep, int KS,
+template <int CNT, int RT, int PF, int XG = CNT * RT >= 8 ? 1 : CNT * RT >= 4 ? 2 : 4>
+__device__ inline void chunk_product(WeightStream<CNT, PF> &ws, const __bf16 *x, int xstep, int KS,
                                      f32x16 (&acc)[CNT][RT])
 {
-    constexpr int PF = WeightStream<CNT>::PF;
-    constexpr int XG = CNT * RT >= 8 ? 1 : CNT * RT >= 4 ? 2 : 4;
     const auto rows = [&](bf16x8 (&f)[XG][RT], int k) {
 #pragma unroll
         for (int p = 0; p < XG; ++p)
@@ -433,6 +431,51 @@ __device__ inline void narrow_layers(const Run &a, const RunCtx &t, Ahead<1> &ah
     }
 }
 
+// The same within 64 registers, for blocks beside others that want all wave slots of a
+// compute unit: weights four steps ahead, nothing requested in front of the barriers.  The
+// layers of a block of 256-128-64 take about 1 us longer for it (8 tables of 20 ids x 800 samples, where
+// nothing else lasts as long, 12.6 -> 13.4 us per forward).
+constexpr int LIGHT_AHEAD = 4, LIGHT_XG = 2, LIGHT_BATCH = 4;
+template <class Run>
+__device__ inline void light_layers(const Run &a, const RunCtx &t)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    for (int L = 0; L < a.n_layers; ++L) {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));  // else every address below is kept in registers across all layers
+        const int m = lane & 31, half = lane >> 5;
+        const bool last = L + 1 == a.n_layers, has = wave < a.Npad[L] / 32;
+        const int n0 = wave * 32 + 4 * half, KS = a.Kpad[L] / 16;
+        f32x16 acc[1][1];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.0f;
+        if (has) {
+            WeightStream<1, LIGHT_AHEAD> ws(static_cast<const char *>(a.W[t.g][L]) + (size_t)wave * KS * 1024, 0, KS);
+            chunk_product<1, 1, LIGHT_AHEAD, LIGHT_XG>(ws, t.X + m * t.ld + half * 8, 0, KS, acc);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (!last) __syncthreads();  // every wave has read the input: the output may replace it
+        if (has) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = n0 + 8 * q;
+                const f32x4 bv = *reinterpret_cast<const f32x4 *>(a.bias[t.g][L] + n);
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float s = acc[0][0][4 * q + e] + bv[e];
+                    v[e] = a.relu[L] != 0 && s < 0.0f ? 0.0f : s;
+                }
+                if (last)
+                    store_last(a, t, m, n, v);
+                else
+                    *reinterpret_cast<bf16x4 *>(t.X + m * t.ld + n) = narrowed(v);
+            }
+        }
+        if (!last) __syncthreads();
+    }
+}
+
 // The layers of run `a` on the rows in t.X (the first layer's Kpad columns valid,
 // visible to the whole block).  Each layer's output replaces its input in place:
 // a wave keeps its sums in registers until every wave has read the input.  A
@@ -531,6 +574,19 @@ __device__ inline void mlp_chain_block(const Run &a, unsigned char *smem, int bx
     touched.done();
     __syncthreads();
     run_layers<RT, MAXC>(a, t, ahead, red);
+}
+
+// The same for a narrow run into rows (no CHAIN_OUT_DOT), within 64 registers.
+template <bool A_F32, class Run>
+__device__ inline void light_chain_block(const Run &a, unsigned char *smem, int bx, int g, int mine, int share)
+{
+    __bf16 *X = reinterpret_cast<__bf16 *>(smem);
+    const RunCtx t{X, nullptr, a.ld_lds, 0, g, bx * rows_of<1>(), 31};
+    const Touched touched = touch_weights(a, g, mine, share);
+    stage_input<A_F32, LIGHT_BATCH>(a, g, t.row0, rows_of<1>(), X, a.ld_lds);
+    touched.done();
+    __syncthreads();
+    light_layers(a, t);
 }
 
 }  // namespace chain

@@ -310,7 +310,7 @@ FcProblem bottom_layer(const rec_model *m, int i, const Call &c, const void *A, 
     // Beside the short bags of a small batch a layer is in blocks of four waves; where it has a
     // launch to itself all the same (a timed forward, REC_OPT_OVERLAP_DENSE) its sums are to be the same bits.
     if (m->interaction == REC_INTERACT_CONCAT && m->bottom.size() == 1 &&
-        front_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows, true) && front_layer_rides(p, true))
+        front_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows, true, 0) && front_layer_rides(p, true))
         p.waves = FRONT_SHORT_WAVES;
     return p;
 }
@@ -489,9 +489,10 @@ struct Plan {
 };
 
 // S0 and S1 (and Bottom-FC, with_bottom) of a small in-order batch as one launch,
-// where csrc/front.hip has one for it.  With layer by layer prescribed (fuse_mlp 0) only
+// where csrc/front.hip has one for it (timed: of the more bags that a stack's light form is for, scan
+// and pooling are to have an interval each).  With layer by layer prescribed (fuse_mlp 0) only
 // where no layer is involved, in a concatenation model without Bottom-FC.
-bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with_bottom)
+bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with_bottom, bool timed)
 {
     const bool concat = m->interaction == REC_INTERACT_CONCAT;
     if (m->pipeline || (m->overlap_dense && !m->bottom.empty()) || (concat && with_bottom)) return false;
@@ -500,7 +501,7 @@ bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with
     if (with_bottom)
         for (const Layer &l : m->bottom)
             if (l.Npad > CHAIN_NARROW_WIDTH) return false;
-    return front_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows, concat);
+    return front_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows, concat, with_bottom && !timed ? m->bottom[0].Kpad : 0);
 }
 
 // Does Bottom-FC's first layer, which waits for nothing, run beside the scan (and
@@ -546,7 +547,7 @@ Plan plan_of(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, boo
 {
     Plan p;
     p.ride = bottom_rides_on_scan(m);
-    p.front = front_applies_to(m, c, use_hot, p.ride);
+    p.front = front_applies_to(m, c, use_hot, p.ride, timed);
     if (timed && !p.ride && !concat_rides_on_scan(m)) p.front = false;
     p.tail = tail_applies(m, c);
     p.tail_from = p.tail ? tail_bottom_from(m, c.B) : (int)m->bottom.size();

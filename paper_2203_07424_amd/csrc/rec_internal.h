@@ -330,7 +330,8 @@ struct FrontProblem {
 };
 bool front_layer_rides(const FcProblem &p, bool concat);
 constexpr int FRONT_SHORT_WAVES = 4;  // that share the k of such a layer's tiles in a concatenation model
-bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat);
+// ride_input: padded inputs of the stack that is to ride along, 0: none.
+bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat, int ride_input);
 bool front_takes(const ChainProblem &rider);
 hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).

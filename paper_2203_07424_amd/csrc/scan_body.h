@@ -115,7 +115,9 @@ struct ScanShared {
 
 // Offsets of tile `tile`; the threads with threadIdx.x < SCAN_THREADS call it,
 // all of them.  The sum of earlier tiles comes by `link`, or (no words: a few
-// tiles) from their lengths.
+// tiles) from their lengths.  LEAN: in few registers, about 0.2 us longer where nothing else lasts as long (one
+// sample of 8 tables 11.1 -> 11.3 us per forward).
+template <bool LEAN = false>
 __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n, long long nnz, const TileLink &link,
                                          int32_t *__restrict__ offsets, ErrRecord *err, int tile, ScanShared &sh)
 {
@@ -196,9 +198,11 @@ __device__ inline void scan_offsets_tile(const int32_t *__restrict__ len, int n,
         if (total != nnz) atomicOr(&err->flags, ERR_TOTAL_MISMATCH);
     }
     __syncthreads();
+    int at = tid;
+    if (LEAN) asm volatile("" : "+v"(at));  // else the addresses of the first loop are kept in registers until here
 #pragma unroll
     for (int i = 0; i < SCAN_ITEMS; ++i) {
-        const int p = i * SCAN_THREADS + tid;
+        const int p = i * SCAN_THREADS + at;
         const long long k = base + p;
         if (k < n) offsets[k] = s_tile[p + (p >> 5)];
     }
