@@ -146,6 +146,56 @@ __device__ inline float add_ror(float v)
     return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, x, 0x120 + R, 0xf, 0xf, false));
 }
 
+// Columns a lane ends up with when the partial sums of a wave are folded.
+template <int LPR, bool HALF>
+constexpr int folded_columns()
+{
+    constexpr int N = HALF ? 8 : 4, N1 = LPR <= 32 ? N / 2 : N;
+    return LPR <= 16 ? N1 / 2 : N1;
+}
+
+// Folds the RPW partial sums, lanes l and l ^ m holding the same columns; the lane's columns
+// are then acc.v[0 ...] from the one returned on.  While
+// m is 32 or 16 a lane passes half of its columns to l ^ m and keeps the sum of
+// the other half; within a row of 16 lanes the rest are rotate-and-add.  None of
+// it goes through the LDS: folding with __shfl_xor, 24 of the 34 permutes a
+// bag of 80 fp16 rows of 64 needed, queued on it.  In terms of the rows of a
+// load the order is r with r ^ 1, then r ^ 2, r ^ 4, ...: fp32 sums depend on it.
+template <int LPR, bool HALF>
+__device__ inline int fold_sums(Acc<HALF> &acc)
+{
+    const int lane = threadIdx.x & 63;
+    float *v = acc.v;
+    int col = lane % LPR * Acc<HALF>::N;
+    constexpr int N1 = LPR <= 32 ? Acc<HALF>::N / 2 : Acc<HALF>::N, N2 = folded_columns<LPR, HALF>();
+    if constexpr (LPR <= 32) {
+#pragma unroll
+        for (int i = 0; i < N1; ++i) v[i] = fold_pair<32>(v[i], v[i + N1]);
+        col += (lane >> 5) * N1;
+    }
+    if constexpr (LPR <= 16) {
+#pragma unroll
+        for (int i = 0; i < N2; ++i) v[i] = fold_pair<16>(v[i], v[i + N2]);
+        col += (lane >> 4 & 1) * N2;
+    }
+#pragma unroll
+    for (int i = 0; i < N2; ++i) {
+        if (LPR <= 8) v[i] = add_ror<8>(v[i]);
+        if (LPR <= 4) v[i] = add_ror<4>(v[i]);
+        if (LPR <= 2) v[i] = add_ror<2>(v[i]);
+        if (LPR <= 1) v[i] = add_ror<1>(v[i]);
+    }
+    return col;
+}
+
+// Which of the 64 / LPR rows of a wave-wide load a lane fetches a part of: lane / LPR with its
+// bits in reverse, so that neighbouring rows sit 32 lanes apart, the next pair 16, and so on.
+template <int LPR>
+__device__ inline int row_of_lane()
+{
+    return (int)(__builtin_bitreverse32(threadIdx.x & 63u) >> 26) & (64 / LPR - 1);
+}
+
 // The sum of bag (t, b), ids [start, end), by one wave.
 template <int LPR, bool HALF, bool CONCAT, bool STREAM, bool NARROW>
 __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
@@ -160,9 +210,7 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
     const int lane = threadIdx.x & 63;
     const long long rows = tables[t].rows;
 
-    // Which of the RPW rows of a wave-wide load: lane / LPR with its bits in reverse, so
-    // that neighbouring rows sit 32 lanes apart, the next pair 16, and so on.
-    const int sub = (int)(__builtin_bitreverse32((unsigned)lane) >> 26) & (RPW - 1);
+    const int sub = row_of_lane<LPR>();
     const int chunk = lane % LPR;
     const Rows src(tables[t].base, rows, chunk);
 
@@ -211,33 +259,9 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
         }
     }
 
-    // Fold the RPW partial sums, lanes l and l ^ m holding the same columns.  While
-    // m is 32 or 16 a lane passes half of its columns to l ^ m and keeps the sum of
-    // the other half; within a row of 16 lanes the rest are rotate-and-add.  None of
-    // it goes through the LDS: folding with __shfl_xor, 24 of the 34 permutes a
-    // bag of 80 fp16 rows of 64 needed, queued on it.  In terms of the rows of a
-    // load the order is r with r ^ 1, then r ^ 2, r ^ 4, ...: fp32 sums depend on it.
-    float *v = acc.v;
-    int col = chunk * NACC;
-    constexpr int N1 = LPR <= 32 ? NACC / 2 : NACC, N2 = LPR <= 16 ? N1 / 2 : N1;
-    if constexpr (LPR <= 32) {
-#pragma unroll
-        for (int i = 0; i < N1; ++i) v[i] = fold_pair<32>(v[i], v[i + N1]);
-        col += (lane >> 5) * N1;
-    }
-    if constexpr (LPR <= 16) {
-#pragma unroll
-        for (int i = 0; i < N2; ++i) v[i] = fold_pair<16>(v[i], v[i + N2]);
-        col += (lane >> 4 & 1) * N2;
-    }
-#pragma unroll
-    for (int i = 0; i < N2; ++i) {
-        if (LPR <= 8) v[i] = add_ror<8>(v[i]);
-        if (LPR <= 4) v[i] = add_ror<4>(v[i]);
-        if (LPR <= 2) v[i] = add_ror<2>(v[i]);
-        if (LPR <= 1) v[i] = add_ror<1>(v[i]);
-    }
-    if (LPR > 8 || (lane & 15) < LPR) store_sums<N2, CONCAT>(v, out, vec_ok, b, t, T, D, col);
+    const int col = fold_sums<LPR, HALF>(acc);
+    constexpr int N = folded_columns<LPR, HALF>();
+    if (LPR > 8 || (lane & 15) < LPR) store_sums<N, CONCAT>(acc.v, out, vec_ok, b, t, T, D, col);
 }
 
 // SHORT_BAGS bags per group of LPR lanes, their load chains (ids -> rows) running

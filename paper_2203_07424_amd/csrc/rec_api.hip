@@ -631,7 +631,7 @@ hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool u
                                 m->num_cus, left, u.err, s));
     } else {
         REC_TRY(launch_pool(u.tables, m->dtype, T, D, B, c.indices, u.offsets, pool_out(m, u), c.nnz, m->stream_rows,
-                            m->max_rows, left, u.err, s));
+                            m->max_rows, m->num_cus, m->pipeline || m->overlap_dense, left, u.err, s));
     }
     return hipSuccess;
 }

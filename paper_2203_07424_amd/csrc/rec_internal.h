@@ -147,13 +147,16 @@ struct PoolOut {
 // words in `left` are cleared on the way.
 // stream_rows: load rows with the non-temporal hint (id streams without reuse).
 // max_rows: row count of the largest table (tables under 4 GiB take 32-bit offsets).
+// corun: other launches share the device with this one and want wave slots.
 hipError_t launch_pool(const TableDesc *tables, int dtype, int T, int D, int B,
                        const int32_t *indices, const int32_t *offsets, PoolOut out, long long nnz,
-                       bool stream_rows, long long max_rows, const TileWords &left, ErrRecord *err, hipStream_t s);
+                       bool stream_rows, long long max_rows, int num_cus, bool corun, const TileWords &left, ErrRecord *err,
+                       hipStream_t s);
 
-// Which form launch_pool() takes: bags of a few ids side by side in a wave; 32-bit
+// Which form launch_pool() takes: bags of a few ids side by side in a wave; two bags in turn in a wave; 32-bit
 // byte offsets into the tables.
 bool pool_short_applies(int rowbytes, long long nnz, long long bags);
+bool pool_two_applies(int rowbytes, long long nnz, long long bags, bool narrow, int num_cus);
 bool pool_narrow(long long max_rows, int rowbytes);
 
 // S1 with the tables' hot rows served from an LDS copy (hcap: power of two >= the
