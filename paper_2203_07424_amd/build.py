@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "librec_mi355x.so")
 
-SOURCES = ["scan.hip", "pool.hip", "pool_hot.hip", "gemm.hip", "gemm_big.hip", "gemm_split.hip", "mlp_chain.hip", "tail.hip", "front.hip", "interact.hip", "synth_fill.hip", "probe.hip", "rec_api.hip"]
+SOURCES = ["scan.hip", "pool.hip", "pool_hot.hip", "gemm.hip", "gemm_big.hip", "gemm_split.hip", "mlp_chain.hip", "tail.hip", "front.hip", "lookup.hip", "interact.hip", "synth_fill.hip", "probe.hip", "rec_api.hip"]
 
 # The packed-fp32 target feature is switched off for all device code.  A wave starts
 # with the first 16 words of its kernel's arguments in registers instead of loading

@@ -45,7 +45,7 @@ using namespace scan;
 using namespace pool;
 using split::Rider;
 
-constexpr int LONG_BAGS = 7 * SCAN_TILE / 2, SHORT_FORM_BAGS = 6 * SCAN_TILE;
+constexpr int LONG_BAGS = 7 * SCAN_TILE / 2;
 // With the light form of a whole Bottom-FC: us per forward, two launches / one, 10 tables of 80 fp32 rows x 1024
 // samples 31.1 / 27.7, 40 of 80 fp16 rows x 256 30.6 / 25.9, 13 x 966 of 10 ids 18.0 / 15.4 (12 558 bags), 14 x 949 of 42
 // 29.9 / 26.3 (13 286).  Each block of eight bags reads all earlier lengths, so beyond it shapes lose: 12 x 1276 24.1 /
@@ -398,6 +398,7 @@ hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStr
     }
     if (!f.out.z) REC_FRONT_BY_ROW(launch_fc_front)
     if (!f.dense.x0) return hipErrorInvalidValue;
+    if (f.T * f.B > SHORT_FORM_BAGS) return launch_lookups(f, s);
     REC_FRONT_BY_ROW(launch_short)
 #undef REC_FRONT_BY_ROW
 }

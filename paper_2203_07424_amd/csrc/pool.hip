@@ -126,7 +126,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_two_kernel(
             keys[c * 64 + lane] = Rows::key(id[c]);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        const int sub = row_of_lane<LPR>();
+        const int sub = row_of_lane<LPR>(lane);
         const Rows src(tables[t].base, rows, lane % LPR);
         Acc<HALF> acc[2];
         int col = 0;
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_two_kernel(
                 for (int u = 0; u < POOL_UNROLL; ++u)
                     if ((j + u) * RPW < n) accumulate<HALF>(acc[i], raw[u], one);
             }
-            col = fold_sums<LPR, HALF>(acc[i]);
+            col = fold_sums<LPR, HALF>(acc[i], lane, lane % LPR);
         }
         if (LPR > 8 || (lane & 15) < LPR) {
             store_sums<folded_columns<LPR, HALF>(), false>(acc[0].v, out, 0, b, t, T, D, col);

@@ -162,11 +162,10 @@ constexpr int folded_columns()
 // bag of 80 fp16 rows of 64 needed, queued on it.  In terms of the rows of a
 // load the order is r with r ^ 1, then r ^ 2, r ^ 4, ...: fp32 sums depend on it.
 template <int LPR, bool HALF>
-__device__ inline int fold_sums(Acc<HALF> &acc)
+__device__ inline int fold_sums(Acc<HALF> &acc, int lane, int chunk)
 {
-    const int lane = threadIdx.x & 63;
     float *v = acc.v;
-    int col = lane % LPR * Acc<HALF>::N;
+    int col = chunk * Acc<HALF>::N;
     constexpr int N1 = LPR <= 32 ? Acc<HALF>::N / 2 : Acc<HALF>::N, N2 = folded_columns<LPR, HALF>();
     if constexpr (LPR <= 32) {
 #pragma unroll
@@ -191,9 +190,9 @@ __device__ inline int fold_sums(Acc<HALF> &acc)
 // Which of the 64 / LPR rows of a wave-wide load a lane fetches a part of: lane / LPR with its
 // bits in reverse, so that neighbouring rows sit 32 lanes apart, the next pair 16, and so on.
 template <int LPR>
-__device__ inline int row_of_lane()
+__device__ inline int row_of_lane(int lane)
 {
-    return (int)(__builtin_bitreverse32(threadIdx.x & 63u) >> 26) & (64 / LPR - 1);
+    return (int)(__builtin_bitreverse32((unsigned)lane) >> 26) & (64 / LPR - 1);
 }
 
 // The sum of bag (t, b), ids [start, end), by one wave.
@@ -210,7 +209,7 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
     const int lane = threadIdx.x & 63;
     const long long rows = tables[t].rows;
 
-    const int sub = row_of_lane<LPR>();
+    const int sub = row_of_lane<LPR>(lane);
     const int chunk = lane % LPR;
     const Rows src(tables[t].base, rows, chunk);
 
@@ -259,33 +258,32 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
         }
     }
 
-    const int col = fold_sums<LPR, HALF>(acc);
+    const int col = fold_sums<LPR, HALF>(acc, lane, chunk);
     constexpr int N = folded_columns<LPR, HALF>();
     if (LPR > 8 || (lane & 15) < LPR) store_sums<N, CONCAT>(acc.v, out, vec_ok, b, t, T, D, col);
 }
 
-// SHORT_BAGS bags per group of LPR lanes, their load chains (ids -> rows) running
+// BAGS bags per group of LPR lanes, their load chains (ids -> rows, PER_BAG at a time) running
 // side by side.  bag[g] with ids [pos[g], end[g]); groups without a bag work on a
 // copy of another (live[g] false) and store nothing.
-template <int LPR, bool HALF, bool CONCAT>
+template <int LPR, bool HALF, bool CONCAT, int BAGS = SHORT_BAGS, int PER_BAG = SHORT_UNROLL / SHORT_BAGS>
 __device__ inline void pool_short_bags(const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
-                                       const PoolOut &out, int vec_ok, const BagTable &div, int T, const bool (&live)[SHORT_BAGS],
-                                       const int (&bag)[SHORT_BAGS], int (&pos)[SHORT_BAGS],
-                                       const int (&end)[SHORT_BAGS], float one, ErrRecord *err)
+                                       const PoolOut &out, int vec_ok, const BagTable &div, int T, const bool (&live)[BAGS],
+                                       const int (&bag)[BAGS], int (&pos)[BAGS],
+                                       const int (&end)[BAGS], float one, ErrRecord *err)
 {
     typedef const __attribute__((address_space(1))) char *table_ptr;
     typedef const __attribute__((address_space(1))) u32x4 *row_ptr;
     constexpr int ROWBYTES = LPR * 16;
     constexpr int NACC = HALF ? 8 : 4;
     constexpr int D = ROWBYTES / (HALF ? 2 : 4);
-    constexpr int PER_BAG = SHORT_UNROLL / SHORT_BAGS;  // row loads in flight per bag
     const int chunk = (threadIdx.x & 63) % LPR;
-    int t[SHORT_BAGS], b[SHORT_BAGS];
-    table_ptr lane_base[SHORT_BAGS];
-    long long rows[SHORT_BAGS];
-    Acc<HALF> acc[SHORT_BAGS];
+    int t[BAGS], b[BAGS];
+    table_ptr lane_base[BAGS];
+    long long rows[BAGS];
+    Acc<HALF> acc[BAGS];
 #pragma unroll
-    for (int g = 0; g < SHORT_BAGS; ++g) {
+    for (int g = 0; g < BAGS; ++g) {
         t[g] = div.of(bag[g]);
         b[g] = bag[g] - t[g] * (int)div.B;
         lane_base[g] = (table_ptr)tables[t[g]].base + chunk * 16;
@@ -296,11 +294,11 @@ __device__ inline void pool_short_bags(const TableDesc *__restrict__ tables, con
 
     bool more = false;
 #pragma unroll
-    for (int g = 0; g < SHORT_BAGS; ++g) more |= pos[g] < end[g];
+    for (int g = 0; g < BAGS; ++g) more |= pos[g] < end[g];
     while (more) {
-        u32x4 raw[SHORT_BAGS][PER_BAG];
+        u32x4 raw[BAGS][PER_BAG];
 #pragma unroll
-        for (int g = 0; g < SHORT_BAGS; ++g) {
+        for (int g = 0; g < BAGS; ++g) {
 #pragma unroll
             for (int u = 0; u < PER_BAG; ++u) {
                 const int k = pos[g] + u;
@@ -324,7 +322,7 @@ __device__ inline void pool_short_bags(const TableDesc *__restrict__ tables, con
         }
         more = false;
 #pragma unroll
-        for (int g = 0; g < SHORT_BAGS; ++g) {
+        for (int g = 0; g < BAGS; ++g) {
 #pragma unroll
             for (int u = 0; u < PER_BAG; ++u) accumulate<HALF>(acc[g], raw[g][u], one);
             pos[g] = min(pos[g] + PER_BAG, end[g]);
@@ -332,7 +330,7 @@ __device__ inline void pool_short_bags(const TableDesc *__restrict__ tables, con
         }
     }
 #pragma unroll
-    for (int g = 0; g < SHORT_BAGS; ++g)
+    for (int g = 0; g < BAGS; ++g)
         if (live[g]) store_sums<NACC, CONCAT>(acc[g].v, out, vec_ok, b[g], t[g], T, D, chunk * NACC);
 }
 

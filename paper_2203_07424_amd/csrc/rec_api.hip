@@ -498,6 +498,8 @@ bool front_applies_to(const rec_model *m, const Call &c, bool use_hot, bool with
     if (m->pipeline || (m->overlap_dense && !m->bottom.empty()) || (concat && with_bottom)) return false;
     if (m->fuse_mlp == 0 && !concat_rides_on_scan(m)) return false;
     if (!concat && longest_hot_list(m, use_hot) > 0) return false;
+    if (concat_rides_on_scan(m) && m->fuse_mlp != 0 && !timed && front_lookup_applies(m->T, c.B, m->D, m->dtype, c.nnz, m->num_cus))
+        return true;
     if (with_bottom)
         for (const Layer &l : m->bottom)
             if (l.Npad > CHAIN_NARROW_WIDTH) return false;
@@ -524,6 +526,7 @@ hipError_t enqueue_front(const rec_model *m, const Bufs &u, const Call &c, const
     f.offsets = u.offsets; f.tables = u.tables; f.err = u.err;
     f.dtype = m->dtype; f.T = m->T; f.D = m->D; f.B = c.B;
     f.stream_rows = m->stream_rows;
+    f.num_cus = m->num_cus;
     f.out = pool_out(m, u);
     if (m->interaction == REC_INTERACT_CONCAT) {
         f.dense = concat_job(m, u, c);

@@ -330,11 +330,16 @@ struct FrontProblem {
     ConcatDense dense;
     const FcProblem *layer;
     int z_cols;
+    int num_cus;
 };
 bool front_layer_rides(const FcProblem &p, bool concat);
 constexpr int FRONT_SHORT_WAVES = 4;  // that share the k of such a layer's tiles in a concatenation model
 // ride_input: padded inputs of the stack that is to ride along, 0: none.
 bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat, int ride_input);
+// More lookups than that, about one id a bag, of a concatenation model without Bottom-FC (no layer).
+constexpr int SHORT_FORM_BAGS = 6 * SCAN_TILE;  // up to which bags of a few ids take csrc/front.hip's launch
+hipError_t launch_lookups(const FrontProblem &f, hipStream_t s);
+bool front_lookup_applies(int T, int B, int D, int dtype, long long nnz, int num_cus);
 bool front_takes(const ChainProblem &rider);
 hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).

@@ -58,21 +58,28 @@ __device__ inline long long part_of_sum(const int32_t *__restrict__ len, int n)
 }
 
 // Dense part of the Predict-FC input rows of a concatenation model, narrowed,
-// and the zero padding behind each row: block `b` of `nb` blocks of THREADS threads.
+// and the zero padding behind each row: block `b` of `nb` blocks of THREADS threads, a
+// wave a row at a time, the loads of four rows in flight.
 template <int THREADS>
 __device__ inline void concat_dense_block(const ConcatDense &job, int b, int nb)
 {
+    constexpr int WAVES = THREADS / 64, U = 4;
     __bf16 *z = static_cast<__bf16 *>(job.z_bf16);
-    const int per_row = job.w0 + (job.ldz - job.width);
-    const long long total = (long long)job.B * per_row;
-    const long long stride = (long long)nb * THREADS;
-    for (long long i = (long long)b * THREADS + threadIdx.x; i < total; i += stride) {
-        const long long r = i / per_row;
-        const int c = (int)(i - r * per_row);
-        if (c < job.w0)
-            z[r * job.ldz + c] = (__bf16)job.x0[r * job.ldx0 + c];
-        else
-            z[r * job.ldz + job.width + (c - job.w0)] = (__bf16)0.0f;
+    const int lane = threadIdx.x & 63, step = nb * WAVES, pad = job.ldz - job.width;
+    for (int r0 = b * WAVES + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); r0 < job.B; r0 += U * step) {
+        for (int c = lane; c < job.w0; c += 64) {
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = job.x0[(long long)min(r0 + u * step, job.B - 1) * job.ldx0 + c];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (r0 + u * step < job.B) z[(long long)(r0 + u * step) * job.ldz + c] = (__bf16)v[u];
+        }
+        if (lane < pad) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (r0 + u * step < job.B) z[(long long)(r0 + u * step) * job.ldz + job.width + lane] = (__bf16)0.0f;
+        }
     }
 }
 
