@@ -33,32 +33,29 @@ constexpr int LDS_LD = BK + 8;  // 144-byte row stride: 16-byte reads of 16 cons
 template <int BM, int BN>
 constexpr size_t big_lds_bytes() { return 2 * (size_t)(BM + BN) * LDS_LD * sizeof(__bf16); }
 
-// 8 consecutive k of one activation row as fetched: bf16, or raw fp32 (the model's
-// dense input) that is narrowed only when it is written to LDS.
+// 16 bytes of one activation row as fetched: 8 k in bf16, or 4 of raw fp32 (the model's
+// dense input) that are narrowed only when they are written to LDS.  Neighbouring lanes fetch
+// neighbouring 16 bytes: as 8 k a lane, 16 bytes of every 32 in one load, 4096 samples of 2560 -> 1024 beside the
+// scan took 35.6 us and not 33.5 (from cold memory 50.1 and 47.3).
 template <bool A_F32>
 struct AReg;
 template <>
 struct AReg<false> {
+    static constexpr int K = 8;
     bf16x8 v;
     __device__ inline void fetch(const char *p) { v = *reinterpret_cast<const bf16x8 *>(p); }
     __device__ inline bf16x8 narrow(bool) const { return v; }
 };
 template <>
 struct AReg<true> {
-    f32x4 lo, hi;
-    __device__ inline void fetch(const char *p)
+    static constexpr int K = 4;
+    f32x4 v;
+    __device__ inline void fetch(const char *p) { v = *reinterpret_cast<const f32x4 *>(p); }
+    __device__ inline bf16x4 narrow(bool valid) const
     {
-        lo = *reinterpret_cast<const f32x4 *>(p);
-        hi = *reinterpret_cast<const f32x4 *>(p + 16);
-    }
-    __device__ inline bf16x8 narrow(bool valid) const
-    {
-        bf16x8 o;
+        bf16x4 o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            o[i] = (__bf16)(valid ? lo[i] : 0.0f);
-            o[i + 4] = (__bf16)(valid ? hi[i] : 0.0f);
-        }
+        for (int i = 0; i < 4; ++i) o[i] = (__bf16)(valid ? v[i] : 0.0f);
         return o;
     }
 };
@@ -88,10 +85,12 @@ __device__ inline void big_block(const BigLayer &p, const Groups &groups, __bf16
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // per-wave tile
     constexpr int TM = WM / 32, TN = WN / 32;            // 32 x 32 MFMA tiles per wave
     constexpr int ROWS_PER_PASS = THREADS / 8;           // 8 threads fetch the 64 k of one row
-    constexpr int A_LOADS = BM / ROWS_PER_PASS, W_LOADS = BN / ROWS_PER_PASS;
+    constexpr int AK = AReg<A_F32>::K, A_THREADS = BK / AK;  // k of a load, threads that fetch a row of A
+    constexpr int A_ROWS = THREADS / A_THREADS;
+    constexpr int A_LOADS = BM / A_ROWS, W_LOADS = BN / ROWS_PER_PASS;
     constexpr int BUF = (BM + BN) * LDS_LD;              // elements of one tile pair
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be whole MFMA tiles");
-    static_assert(BM % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0, "staging passes must tile the block");
+    static_assert(BM % A_ROWS == 0 && BN % ROWS_PER_PASS == 0, "staging passes must tile the block");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
@@ -121,11 +120,12 @@ __device__ inline void big_block(const BigLayer &p, const Groups &groups, __bf16
     const float *__restrict__ bias = groups.bias[grp];
 
     const int ld_row = tid >> 3, ld_chunk = tid & 7;
+    const int a_row = tid / A_THREADS, a_k = tid % A_THREADS * AK;
     const char *a_src[A_LOADS];  // this thread's chunk of k-tile 0 in each of its rows
     const __bf16 *w_src[W_LOADS];
 #pragma unroll
     for (int i = 0; i < A_LOADS; ++i) {
-        int row = m0 + ld_row + ROWS_PER_PASS * i;
+        int row = m0 + a_row + A_ROWS * i;
         row = row < M ? row : M - 1;  // rows past M are computed and dropped
         a_src[i] = A + (long long)row * lda * A_ELT;
     }
@@ -152,8 +152,8 @@ __device__ inline void big_block(const BigLayer &p, const Groups &groups, __bf16
     constexpr int A_PART = (A_LOADS + KSTEPS - 1) / KSTEPS, W_PART = (W_LOADS + KSTEPS - 1) / KSTEPS;
 #define REC_BIG_FETCH_PART(kt, part)                                                       \
     do {                                                                                   \
-        int k_ = (kt) * BK + ld_chunk * 8;                                                 \
-        if (A_F32) k_ = k_ < K ? k_ : K - 8;                                               \
+        int k_ = (kt) * BK + a_k;                                                          \
+        if (A_F32) k_ = k_ < K ? k_ : K - AK;                                              \
         _Pragma("unroll") for (int i = (part) * A_PART; i < ((part) + 1) * A_PART && i < A_LOADS; ++i) \
             ra[i].fetch(a_src[i] + (long long)k_ * A_ELT);                                 \
         _Pragma("unroll") for (int i = (part) * W_PART; i < ((part) + 1) * W_PART && i < W_LOADS; ++i) \
@@ -162,9 +162,9 @@ __device__ inline void big_block(const BigLayer &p, const Groups &groups, __bf16
 #define REC_BIG_STASH_PART(kt, buf, part)                                                  \
     do {                                                                                   \
         __bf16 *sa_ = smem + (buf) * BUF, *sw_ = sa_ + BM * LDS_LD;                        \
-        const bool valid_ = !A_F32 || (kt) * BK + ld_chunk * 8 < K; /* the chunk held in ra lies below K */ \
+        const bool valid_ = !A_F32 || (kt) * BK + a_k < K; /* the chunk held in ra lies below K */ \
         _Pragma("unroll") for (int i = (part) * A_PART; i < ((part) + 1) * A_PART && i < A_LOADS; ++i) \
-            *reinterpret_cast<bf16x8 *>(&sa_[(ld_row + ROWS_PER_PASS * i) * LDS_LD + ld_chunk * 8]) = ra[i].narrow(valid_); \
+            *reinterpret_cast<decltype(ra[i].narrow(true)) *>(&sa_[(a_row + A_ROWS * i) * LDS_LD + a_k]) = ra[i].narrow(valid_); \
         _Pragma("unroll") for (int i = (part) * W_PART; i < ((part) + 1) * W_PART && i < W_LOADS; ++i) \
             *reinterpret_cast<bf16x8 *>(&sw_[(ld_row + ROWS_PER_PASS * i) * LDS_LD + ld_chunk * 8]) = rw[i]; \
     } while (0)
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
 }
 
 // One stack's layer of fp32 rows behind the blocks of a scan, which are done before the
-// layer is a quarter through: two blocks of 128 x 128 tiles fit a compute unit (111
+// layer is a quarter through: two blocks of 128 x 128 tiles fit a compute unit (115
 // registers, 72 KB of LDS, the scan's inside it), so no tile waits for them: 4096 samples,
 // 2560-1024 beside 10 tables 76.4 -> 71.2 us per forward, 2400 beside 8 74.2 -> 66.7.  What bounds it is the chain
 // of trips and barriers of one block in lock-step: 22 bytes of operands a clock and compute unit, 64 lines in
