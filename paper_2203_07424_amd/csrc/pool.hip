@@ -74,13 +74,15 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
 // life of the last ones does not show: 40 x 4096, 20 rounds, 160.5 -> 161.3.
 // Waves share nothing, so a block is one of them: its slot is taken again when it ends and
 // not when the last of four does (632 -> 618).  Waves that live for one bag, and for short ones above
-// all, come faster in fours (12 x 1737 of 9 ids, a wave a bag, 21.7 -> 23.2 in ones).  Beside launches that want wave slots
-// these blocks are four waves as well: between blocks of one wave the others find none (eight pipelined batches of
-// 40 x 4096 1272 -> 1404 us).
+// all, come faster in fours (12 x 1737 of 9 ids, a wave a bag, 21.7 -> 23.2 in ones).  Beside launches that want wave
+// slots these blocks are larger, or the others find none between them: eight waves, and four in a launch so long that the
+// others are the smaller part of it.  Eight pipelined batches, us with a wave a bag / two bags in blocks of one wave, four, eight:
+// 40 x 4096 of 80 ids 1273 / 1422, 1419, 1275, of 20 727 / -, 789, 706; 60 x 4096 1809 / -, 1960, 1805; 40 x 8000 2321 / -,
+// 2268, 2205; 40 x 16384 of 20 2466 / -, 2192, 2390; 60 x 16384 6248 / -, 6079, 6379.
 constexpr int TWO_IDS = 256;  // of the two bags, or they are taken as two waves would
 
 template <int LPR, bool HALF, bool STREAM>
-__global__ __launch_bounds__(POOL_WAVES * 64) void pool_two_kernel(
+__global__ __launch_bounds__(512) void pool_two_kernel(
     const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     const int32_t *__restrict__ offsets, int per, int npairs, unsigned pairs, unsigned magic, int T, float one,
     int B, int log_waves, ErrRecord *err, const PoolOut out, const TileWords left)
@@ -200,6 +202,7 @@ struct PoolProblem {
     TileWords left;
     ErrRecord *err;
     bool short_bags, two_bags, stream_rows, narrow, corun;
+    int num_cus;
 };
 
 template <int LPR, bool HALF, bool CONCAT>
@@ -222,7 +225,7 @@ hipError_t launch_shape(const PoolProblem &p, hipStream_t s)
     if constexpr (!CONCAT && LPR >= 4 && LPR <= 16) {
         if (p.two_bags) {
             const BagTable by_pair = BagTable::of_batch((p.B + 1) / 2);
-            const int npairs = p.T * (int)by_pair.B, log_waves = p.corun ? 2 : 0, waves = 1 << log_waves;
+            const int npairs = p.T * (int)by_pair.B, log_waves = !p.corun ? 0 : nbags < 64 * 32 * p.num_cus ? 3 : 2, waves = 1 << log_waves;
             const dim3 grid = blocks_of(npairs, waves);
             auto k = p.stream_rows ? pool_two_kernel<LPR, HALF, true> : pool_two_kernel<LPR, HALF, false>;
             hipLaunchKernelGGL(k, grid, dim3(waves * 64), waves * TWO_IDS * sizeof(unsigned), s, p.tables, p.indices, p.offsets,
@@ -280,7 +283,7 @@ hipError_t launch_pool(const TableDesc *tables, int dtype, int T, int D, int B,
     const long long bags = (long long)T * B;
     const bool narrow = pool_narrow(max_rows, rowbytes), short_bags = pool_short_applies(rowbytes, nnz, bags);
     const PoolProblem p{tables, T, B, indices, offsets, out, left, err, short_bags,
-                        pool_two_applies(rowbytes, nnz, bags, narrow, num_cus), stream_rows, narrow, corun};
+                        pool_two_applies(rowbytes, nnz, bags, narrow, num_cus), stream_rows, narrow, corun, num_cus};
     switch (rowbytes / 16) {
     case 1: return launch_lpr<1>(half, p, s);
     case 2: return launch_lpr<2>(half, p, s);

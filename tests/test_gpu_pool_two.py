@@ -1,5 +1,6 @@
 """Two bags of a table by one wave: every row size that takes it, an odd and an even number of samples,
-pairs whose ids just fit and do not, empty bags, faults; in blocks of one wave and (pipelined) of four."""
+pairs whose ids just fit and do not, empty bags, faults; in blocks of one wave and (pipelined) of eight and, of
+many more bags, four."""
 import numpy as np
 import pytest
 import torch
@@ -20,14 +21,15 @@ def binding():
     return b
 
 
-@pytest.mark.parametrize("pipeline", [False, True])
-@pytest.mark.parametrize("rowbytes,dtype,odd", [(64, np.float16, 0), (64, np.float32, 1), (128, np.float16, 1), (128, np.float32, 0),
-                                                (256, np.float16, 0), (256, np.float32, 1)])
-def test_two_bags_by_a_wave(binding, rowbytes, dtype, odd, pipeline):
-    print("two bags", rowbytes, np.dtype(dtype).name, odd, pipeline, flush=True)
+ROWS = [(64, np.float16, 0), (64, np.float32, 1), (128, np.float16, 1), (128, np.float32, 0), (256, np.float16, 0), (256, np.float32, 1)]
+
+
+@pytest.mark.parametrize("rowbytes,dtype,odd,pipeline,rounds", [(*r, p, 5) for r in ROWS for p in (False, True)] + [(64, np.float32, 1, True, 64)])
+def test_two_bags_by_a_wave(binding, rowbytes, dtype, odd, pipeline, rounds):
+    print("two bags", rowbytes, np.dtype(dtype).name, odd, pipeline, rounds, flush=True)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     D, T, R, F = rowbytes // np.dtype(dtype).itemsize, 2, 300, 6
-    B = (5 * 32 * cus + T - 1) // T  # the smallest batch, of bags of up to 2 KB of rows
+    B = (rounds * 32 * cus + T - 1) // T  # 5: the smallest batch, of bags of up to 2 KB of rows
     B += B % 2 != odd
     g = np.random.default_rng(300 + rowbytes + odd)
     # magnitudes over eight octaves, so that the order of a sum shows in fp16 rows as well
