@@ -137,11 +137,10 @@ hipError_t launch_lookup(const FrontProblem &f, hipStream_t s)
     constexpr int NACC = HALF ? 8 : 4, BAGS = lookup_block_bags<LPR>();
     const int n = f.T * f.B;
     const int vec_ok = f.out.col0 % NACC == 0 && reinterpret_cast<uintptr_t>(f.out.z) % 16 == 0;
-    const long long total = (long long)f.dense.B * (f.dense.w0 + f.dense.ldz - f.dense.width);
     const BagTable div = BagTable::of_batch(f.B);
     const int blocks = ((n + BAGS - 1) / BAGS + 7) / 8 * 8;
     // as many as the compute units that the others leave, a block each
-    const int extra = (int)std::min<long long>((total + 4 * LOOKUP_THREADS - 1) / (4 * LOOKUP_THREADS), std::max(16, f.num_cus - blocks));
+    const int extra = concat_dense_blocks(f.dense, LOOKUP_THREADS / 64, std::max(16, f.num_cus - blocks));
     hipLaunchKernelGGL((front_lookup_kernel<LPR, HALF>), dim3(blocks + extra), dim3(LOOKUP_THREADS), 0, s, f.lengths, f.tables,
                        f.indices, f.nnz, n, blocks, extra, blocks / 8, div.B, div.magic, f.T, 1.0f, vec_ok, f.offsets, f.err,
                        f.out, f.dense);

@@ -83,6 +83,14 @@ __device__ inline void concat_dense_block(const ConcatDense &job, int b, int nb)
     }
 }
 
+// Blocks for it: two trips for a wave's rows.
+inline int concat_dense_blocks(const ConcatDense &job, int waves, int most)
+{
+    if (!job.x0 || job.w0 + (job.ldz - job.width) == 0) return 0;
+    const int rows = 8 * waves, blocks = (job.B + rows - 1) / rows;
+    return blocks < most ? blocks : most;
+}
+
 // How the blocks of a scan that is one launch learn what lies before their tile:
 // each publishes the sum of its own (value * 2 + 1, so that the word says by itself
 // that it is there), except the last, whose sum nobody reads, and adds up those of
