@@ -82,6 +82,8 @@ enum {
  * *tail_from the first Bottom-FC layer that the launch of REC_PLAN_TAIL takes (the number
  * of layers: none).  REC_ERR_ARG on a null pointer or a batch that the model does not take. */
 REC_API rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz, uint32_t *mask, int32_t *tail_from);
+/* The same, *joined = 1 where pooling is in the launch of REC_PLAN_LAYER too, a layer of large tiles. */
+REC_API rec_status rec_probe_plan_joined(const rec_model *m, int32_t batch, int64_t nnz, int32_t *joined);
 
 #ifdef __cplusplus
 }

@@ -48,7 +48,8 @@ STAGE_NAMES = ("scan", "pool", "bottom_first", "bottom_rest", "interact", "top_f
 EXPORTS = ("rec_create", "rec_destroy", "rec_workspace_bytes", "rec_bind_workspace",
            "rec_load_tables", "rec_load_hot_rows", "rec_mlp_packed_bytes", "rec_load_mlp", "rec_forward", "rec_forward_static", "rec_check",
            "rec_debug_get", "rec_set_option", "rec_set_dense_stream", "rec_set_pool_streams", "rec_drain", "rec_set_profiling", "rec_stage_ms", "rec_stage_shared", "rec_status_string",
-           "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan", "rec_probe_fc_form", "rec_probe_plan")
+           "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan", "rec_probe_fc_form", "rec_probe_plan",
+           "rec_probe_plan_joined")
 
 
 class rec_config(C.Structure):
@@ -111,6 +112,8 @@ _lib.rec_probe_scan.restype = C.c_int
 _lib.rec_probe_scan.argtypes = [_vp, C.c_int32, C.c_int64, _vp, _vp, C.c_int32, _vp, _vp]
 _lib.rec_probe_plan.restype = C.c_int
 _lib.rec_probe_plan.argtypes = [_vp, C.c_int32, C.c_int64, C.POINTER(C.c_uint32), C.POINTER(C.c_int32)]
+_lib.rec_probe_plan_joined.restype = C.c_int
+_lib.rec_probe_plan_joined.argtypes = [_vp, C.c_int32, C.c_int64, C.POINTER(C.c_int32)]
 _lib.rec_probe_fc_form.restype = C.c_int
 _lib.rec_probe_fc_form.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_uint32, C.c_int32, C.POINTER(C.c_int32)]
 
@@ -274,6 +277,13 @@ def rec_probe_plan(m: int, batch: int, nnz: int) -> Tuple[int, int, int]:
     mask, tail_from = C.c_uint32(0), C.c_int32(0)
     st = _lib.rec_probe_plan(m, int(batch), int(nnz), C.byref(mask), C.byref(tail_from))
     return st, mask.value, tail_from.value
+
+
+def rec_probe_plan_joined(m: int, batch: int, nnz: int) -> Tuple[int, bool]:
+    """(status, whether pooling shares the launch of scan and a first layer of large tiles)."""
+    joined = C.c_int32(0)
+    st = _lib.rec_probe_plan_joined(m, int(batch), int(nnz), C.byref(joined))
+    return st, bool(joined.value)
 
 
 class RecModel:

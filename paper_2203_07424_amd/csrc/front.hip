@@ -386,6 +386,7 @@ hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStr
         default: return hipErrorInvalidValue;
         }
     }
+    if (f.layer && !fc_split_rides(*f.layer)) return launch_fc_big_beside_pool(f, s);
     if (f.layer && (!front_layer_rides(*f.layer, f.out.z != nullptr) || (f.out.z && f.out.ldz % 4 != 0)))
         return hipErrorInvalidValue;
 #define REC_FRONT_BY_ROW(LAUNCH)                                          \

@@ -16,6 +16,9 @@
 // of matrix instructions.  Measured and not kept: 4 waves with 128 x 128 wave
 // tiles (accumulators in AGPRs), 16 waves, and global loads written straight
 // into LDS (swizzled rows, no staging registers) - each within 5 % of this.
+#include <algorithm>
+
+#include "pool_body.h"
 #include "scan_body.h"
 
 namespace rec {
@@ -277,6 +280,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void fc_big_kernel(
         smem, blockIdx.x);
 }
 
+// Bags of a pooling block beside a wide layer: one block a compute unit, whole rounds of four
+// bags for each of its waves; a thread for each bag, and its sums in LDS.
+constexpr int BESIDE_WIDE_BAGS = 256, BESIDE_WIDE_COLUMNS = 15360;
+inline long long beside_wide_bags(long long n, int num_cus) { return ((n + num_cus - 1) / num_cus + 31) / 32 * 32; }
+inline bool beside_wide_fits(long long n, int D, int num_cus)
+{
+    const long long bags = beside_wide_bags(n, num_cus);
+    return bags <= BESIDE_WIDE_BAGS && bags * D <= BESIDE_WIDE_COLUMNS;
+}
+
 // One stack's layer of fp32 rows behind the blocks of a scan, which are done before the
 // layer is a quarter through: two blocks of 128 x 128 tiles fit a compute unit (115
 // registers, 72 KB of LDS, the scan's inside it), so no tile waits for them: 4096 samples,
@@ -303,6 +316,87 @@ __global__ __launch_bounds__(512, 4) void fc_big_behind_scan_kernel(
     big_block<128, 128, 2, 4, true, OUT_F32>(
         BigLayer{A0, W0, lda, M, K, Kpad, grid_m, grid_n, tiles_per_group, per_xcd, 0, relu, C0, ldc, 0}, groups, smem,
         blockIdx.x - b.tiles);
+}
+
+// The same with scan and pooling in further blocks of the launch, for which the layer leaves
+// half of a compute unit's registers and LDS, and most of the time of its memory pipes: the layer takes 35 to 38 us
+// beside them, 33.5 with the scan alone.  What bounds a pooling block, eight waves on its compute unit: the
+// earlier lengths, which it adds up itself (6 us for 80 KB, 10 for 160), then a trip for each of its waves' rounds of
+// four bags (3 us with hot rows, 5.8 with cold ones).  us per forward, scan with layer and then pooling / one launch: 10
+// tables of 20 fp32 rows of 128 bytes, uniform ids x 4096 samples behind 2560 -> 1024 71.0 / 60.7.
+struct PoolBlocks {
+    long long nnz;
+    int n, per, bags;  // per: blocks of an XCD
+    pool::BagTable div;
+    int T;
+    float one;
+    int32_t *offsets;
+    ErrRecord *err;
+    PoolOut out;
+};
+struct PoolShared {
+    unsigned keys[8 * pool::QUAD_IDS];
+    long long sum[8], scan[8];
+    int off[BESIDE_WIDE_BAGS + 4];
+    float sums[BESIDE_WIDE_COLUMNS];
+};
+
+template <int LPR, bool HALF, bool STREAM>
+__global__ __launch_bounds__(512, 4) void fc_big_beside_pool_kernel(
+    const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
+    int tiles, int per_xcd, int relu, void *__restrict__ C0, int ldc, const float *__restrict__ bias,
+    const int32_t *__restrict__ lengths, const int32_t *__restrict__ indices, const TableDesc *__restrict__ tables, const PoolBlocks p)
+{
+    extern __shared__ __attribute__((aligned(16))) __bf16 smem[];
+    static_assert(sizeof(PoolShared) <= big_lds_bytes<128, 128>(), "pooling's LDS is part of the tiles'");
+    if ((int)blockIdx.x < tiles) {
+        struct {
+            const void *W[1];
+            const float *bias[1];
+        } groups{{W0}, {bias}};
+        big_block<128, 128, 2, 4, true, false>(
+            BigLayer{A0, W0, lda, M, K, Kpad, grid_m, grid_n, tiles, per_xcd, 0, relu, C0, ldc, 0}, groups, smem, blockIdx.x);
+        return;
+    }
+    const int b = blockIdx.x - tiles, first = ((b & 7) * p.per + (b >> 3)) * p.bags;
+    if (first >= p.n) return;
+    PoolShared &sh = *reinterpret_cast<PoolShared *>(smem);
+    scan::offsets_of_block<512, 8>(lengths, p.n, p.nnz, first, p.bags, p.offsets, p.err, sh.sum, sh.scan, sh.off);
+    pool::pool_quads<8, LPR, HALF, STREAM>(tables, indices, p.out, p.div, p.T, p.n, first, p.bags, sh.off, sh.keys, sh.sums, p.one,
+                                           p.err);
+}
+
+template <int LPR, bool HALF, bool STREAM>
+hipError_t launch_beside_pool(const FrontProblem &f, const FcProblem &a, hipStream_t s)
+{
+    const int n = f.T * f.B, bags = (int)beside_wide_bags(n, f.num_cus);
+    const int blocks = ((n + bags - 1) / bags + 7) / 8 * 8;
+    const int grid_m = (a.M + 127) / 128, grid_n = a.Npad / 128, tiles = grid_m * grid_n;
+    const PoolBlocks p{f.nnz, n, blocks / 8, bags, pool::BagTable::of_batch(f.B), f.T, 1.0f,
+                       f.offsets, f.err, f.out};
+    hipLaunchKernelGGL((fc_big_beside_pool_kernel<LPR, HALF, STREAM>), dim3(tiles + blocks), dim3(512),
+                       (big_lds_bytes<128, 128>()), s, a.A, a.g.W[0], a.lda, a.M, a.K, a.Kpad, grid_m, grid_n, tiles,
+                       tiles % 8 == 0 ? tiles / 8 : 0, a.relu ? 1 : 0, a.C, a.ldc, a.g.bias[0], f.lengths, f.indices, f.tables, p);
+    return hipGetLastError();
+}
+
+template <int LPR>
+hipError_t launch_beside_pool(const FrontProblem &f, const FcProblem &a, hipStream_t s)
+{
+    if (f.dtype == REC_F16)
+        return f.stream_rows ? launch_beside_pool<LPR, true, true>(f, a, s) : launch_beside_pool<LPR, true, false>(f, a, s);
+    return f.stream_rows ? launch_beside_pool<LPR, false, true>(f, a, s) : launch_beside_pool<LPR, false, false>(f, a, s);
+}
+
+template <int LPR>
+hipError_t prepare_beside_pool()
+{
+    constexpr size_t lds = big_lds_bytes<128, 128>();
+    hipError_t e = grant_lds(fc_big_beside_pool_kernel<LPR, true, true>, lds);
+    if (e == hipSuccess) e = grant_lds(fc_big_beside_pool_kernel<LPR, true, false>, lds);
+    if (e == hipSuccess) e = grant_lds(fc_big_beside_pool_kernel<LPR, false, true>, lds);
+    if (e == hipSuccess) e = grant_lds(fc_big_beside_pool_kernel<LPR, false, false>, lds);
+    return e;
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_F32, bool OUT_F32>
@@ -394,6 +488,34 @@ bool fc_big_rides(const FcProblem &a, int num_cus)
     return a.a_f32 && a.groups == 1 && !a.corun && num_cus > 0 && big_tile_choice(a, num_cus) == 3;
 }
 
+// Where a pooling block, with a quarter of the waves of a launch of its own, is done about when the layer is: by
+// its bags, which the layer's depth allows (10 a k-tile), and by its rows (6400 a compute unit).  us per forward, two
+// launches / one, Zipf ids; 2560 -> 1024, 10 tables of 20 rows of 128 bytes x 6000 samples 89.8 / 79.5, of 40 of 256 x 4096
+// 76.4 / 75.9, 14 of 28 of 64 bytes x 4096 67.2 / 64.2; 1000 -> 1024, 10 of 20 of 128 x 4096 47.6 / 44.4, 4 of 55 x 6000 57.2 /
+// 55.7.  Beyond: 2560, 14 of 40 of 256 x 4096 (8960 rows) 93.3 / 96.4, 14 of 50 of 64 x 2500 (6836) 61.8 / 63.4, 30 of 8 x 4096
+// (480 bags) 84.2 / 87.8; 1000, 14 of 20 of 64 bytes x 4096 (224 bags) 50.8 / 53.8, 14 of 10 x 6000 64.8 / 72.5.
+bool fc_big_beside_pool_applies(const FcProblem &a, int T, int B, int D, int dtype, long long nnz, long long max_rows)
+{
+    const long long n = (long long)T * B;
+    const int rowbytes = D * (dtype == REC_F16 ? 2 : 4);
+    if (a.out_f32 || !fc_big_rides(a, a.num_cus) || (rowbytes != 64 && rowbytes != 128 && rowbytes != 256)) return false;
+    if (!beside_wide_fits(n, D, a.num_cus) || pool_short_applies(rowbytes, nnz, n) || !pool_narrow(max_rows, rowbytes)) return false;
+    return n <= (long long)a.num_cus * std::min(240, 10 * (a.Kpad / BK)) && nnz <= 6400ll * a.num_cus && nnz <= 56 * n;
+}
+
+hipError_t launch_fc_big_beside_pool(const FrontProblem &f, hipStream_t s)
+{
+    const FcProblem &a = *f.layer;
+    if (f.out.z || f.num_cus <= 0 || a.out_f32 || !fc_big_rides(a, f.num_cus) || !beside_wide_fits((long long)f.T * f.B, f.D, f.num_cus))
+        return hipErrorInvalidValue;
+    switch (f.D * (f.dtype == REC_F16 ? 2 : 4) / 16) {
+    case 4: return launch_beside_pool<4>(f, a, s);
+    case 8: return launch_beside_pool<8>(f, a, s);
+    case 16: return launch_beside_pool<16>(f, a, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_fc_big_behind_scan(const FcProblem &a, const ScanBlocks &scan, hipStream_t s)
 {
     const int grid_m = (a.M + 127) / 128, grid_n = a.Npad / 128, tiles = grid_m * grid_n;
@@ -407,6 +529,9 @@ hipError_t fc_big_prepare()
 {
     hipError_t e = grant_lds(fc_big_behind_scan_kernel<true>, big_lds_bytes<128, 128>());
     if (e == hipSuccess) e = grant_lds(fc_big_behind_scan_kernel<false>, big_lds_bytes<128, 128>());
+    if (e == hipSuccess) e = prepare_beside_pool<4>();
+    if (e == hipSuccess) e = prepare_beside_pool<8>();
+    if (e == hipSuccess) e = prepare_beside_pool<16>();
     if (e == hipSuccess) e = prepare_tiles<256, 256, 2, 4>();
     if (e == hipSuccess) e = prepare_tiles<256, 128, 4, 2>();
     if (e == hipSuccess) e = prepare_tiles<128, 128, 2, 4>();

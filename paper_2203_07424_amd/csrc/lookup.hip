@@ -23,49 +23,6 @@ using namespace pool;
 constexpr int LOOKUP_THREADS = 1024, LOOKUP_BAGS = 4;
 constexpr int MOST_LOOKUPS = 64 * SCAN_TILE;
 
-// As part_of_sum(), over up to 2048 lengths a thread, n not zero: loads past n read zeros (a buffer's range
-// check), and of each length there is an addition and an "or", in 32 bits; a thread that has seen a bit from the
-// 20th on (a sign among them) adds its lengths up again in 64.  426 KB by a block of 1024 threads: 104 lengths
-// a thread, some 5 vector instructions each in part_of_sum() (a launch of 13.2 us, 11.8 with this).
-template <int THREADS, int U>
-__device__ inline long long part_of_long_sum(const int32_t *__restrict__ len, int n)
-{
-    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(len), 0, n * 4, 0x00020000);
-    unsigned sum = 0, seen = 0;
-    for (int k0 = 4 * (int)threadIdx.x; k0 < n; k0 += 4 * THREADS * U) {
-        u32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(src, (k0 + u * 4 * THREADS) * 4, 0, 0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            sum += v[u][0] + v[u][1];
-            sum += v[u][2] + v[u][3];
-            seen |= v[u][0] | v[u][1];
-            seen |= v[u][2] | v[u][3];
-        }
-    }
-    if (seen >> 20 == 0) return sum;
-    long long exact = 0;
-    for (int k0 = 4 * (int)threadIdx.x; k0 < n; k0 += 4 * THREADS)
-        for (int e = 0; e < 4; ++e) exact += max(len[k0 + e], 0);
-    return exact;
-}
-
-// Sum over max(len, 0) of lengths [0, n) by all threads of the block, in one trip where these are up to
-// 104 a thread; s_w: a word per wave.
-template <int THREADS>
-__device__ inline long long sum_before(const int32_t *__restrict__ len, int n, long long *s_w)
-{
-    const long long sum = wave_sum(n <= 4 * 8 * THREADS ? part_of_long_sum<THREADS, 8>(len, n) : part_of_long_sum<THREADS, 26>(len, n));
-    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    long long all = 0;
-#pragma unroll
-    for (int w = 0; w < THREADS / 64; ++w) all += s_w[w];
-    return all;
-}
-
 // Bags of one block: consecutive, each group of LPR lanes taking
 // LOOKUP_BAGS of them a block's groups apart.
 template <int LPR>
@@ -89,35 +46,8 @@ __global__ __launch_bounds__(LOOKUP_THREADS) void front_lookup_kernel(
     if (first >= n) return;
     __shared__ long long s_w[WAVES], s_scan[WAVES];
     __shared__ int s_off[BAGS + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int k = first + tid;
-    int own = tid < BAGS && k < n ? len[k] : 0;
-    if (own < 0) {  // counts as 0
-        atomicMin(&err->first_bad_len, (unsigned long long)k);
-        atomicOr(&err->flags, ERR_NEG_LENGTH);
-        own = 0;
-    }
-    long long incl = own;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const long long up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
-    }
-    if (lane == 63) s_scan[wave] = incl;
-    long long run = sum_before<THREADS>(len, first, s_w);  // its barrier makes s_scan visible too
-    for (int w = 0; w < wave; ++w) run += s_scan[w];
-    run += incl;
-    if (tid < BAGS) {
-        s_off[tid] = (int)min(run - own, nnz);
-        if (k < n) offsets[k] = (int)min(run - own, nnz);
-        if (tid == BAGS - 1) s_off[BAGS] = (int)min(run, nnz);
-        if (k == n - 1) {
-            offsets[n] = (int)min(run, nnz);
-            if (run != nnz) atomicOr(&err->flags, ERR_TOTAL_MISMATCH);
-        }
-    }
-    __syncthreads();
-    const int group = tid / LPR;
+    offsets_of_block<THREADS, 26>(len, n, nnz, first, BAGS, offsets, err, s_w, s_scan, s_off);
+    const int group = threadIdx.x / LPR;
     bool live[LOOKUP_BAGS];
     int bag[LOOKUP_BAGS], pos[LOOKUP_BAGS], end[LOOKUP_BAGS];
 #pragma unroll

@@ -263,6 +263,123 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
     if (LPR > 8 || (lane & 15) < LPR) store_sums<N, CONCAT>(acc.v, out, vec_ok, b, t, T, D, col);
 }
 
+// Bags [first, first + bags) of the n of a launch by a block of WAVES waves, offsets in s_off[0 ... bags]: four
+// neighbouring bags a wave at a time, their rows requested together, and the ids of its next four
+// in front of these, all sums stored at the end (behind a store the next rows wait until it has reached memory);
+// for waves that have few others on their compute unit.  Sums in pool_bag()'s order.
+// keys: QUAD_IDS words a wave; sums: D a bag.  Four bags of two tables, or with more ids, are taken one by one
+// at the end (in the loop, their loads cost the others waits).
+constexpr int QUAD = 4, QUAD_IDS = 256;
+
+template <int WAVES, int LPR, bool HALF, bool STREAM>
+__device__ inline void pool_quads(const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
+                                  const PoolOut &out, const BagTable &div, int T, int n, int first, int bags, const int *s_off,
+                                  unsigned *keys, float *sums, float one, ErrRecord *err)
+{
+    typedef RowSource<LPR * 16, true, STREAM> Rows;
+    constexpr int RPW = 64 / LPR, CHUNKS = QUAD_IDS / 64, D = LPR * 16 / (HALF ? 2 : 4), U = 3;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int sub = row_of_lane<LPR>(lane);
+    const auto read_offsets = [&](int q, int (&offs)[QUAD + 1]) {
+        const int v = s_off[q + min(lane, QUAD)];
+#pragma unroll
+        for (int i = 0; i <= QUAD; ++i) offs[i] = __builtin_amdgcn_readlane(v, i);
+    };
+    int id[CHUNKS];
+    const auto request = [&](int q) {  // the ids of four bags
+        int offs[QUAD + 1];
+        read_offsets(q, offs);
+        const int from = offs[0], count = offs[QUAD] - from;
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) {
+            id[c] = -1;
+            if (c * 64 + lane < count) id[c] = indices[from + c * 64 + lane];
+        }
+    };
+    keys += wave * QUAD_IDS;
+    const int mine = min(bags, n - first);  // n - first > 0
+    if (wave * QUAD < mine) request(wave * QUAD);
+    for (int q = wave * QUAD; q < mine; q += WAVES * QUAD) {
+        const int live = min(QUAD, mine - q), bag = first + q;
+        int offs[QUAD + 1];
+        read_offsets(q, offs);
+        const int t = div.of(bag), from = offs[0], total = offs[QUAD] - from;
+        const bool joint = total <= QUAD_IDS && bag + live <= (t + 1) * (int)div.B;
+        const long long rows = tables[t].rows;
+        if (joint) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int c = 0; c < CHUNKS; ++c) {
+                // Ids outside the table contribute zero and leave a record.
+                if (c * 64 + lane < total && (unsigned long long)(long long)id[c] >= (unsigned long long)rows) {
+                    atomicMin(&err->first_bad_idx, (unsigned long long)(from + c * 64 + lane));
+                    atomicOr(&err->flags, ERR_INDEX_RANGE);
+                    id[c] = -1;
+                }
+                keys[c * 64 + lane] = Rows::key(id[c]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        if (q + WAVES * QUAD < mine) request(q + WAVES * QUAD);
+        if (!joint) continue;
+        const Rows src(tables[t].base, rows, lane % LPR);
+        Acc<HALF> acc[QUAD];
+        int at0[QUAD], len[QUAD], most = 0;  // of bags past the last one no ids
+#pragma unroll
+        for (int i = 0; i < QUAD; ++i) {
+#pragma unroll
+            for (int e = 0; e < Acc<HALF>::N; ++e) acc[i].v[e] = 0.0f;
+            at0[i] = offs[i] - from;
+            len[i] = offs[i + 1] - offs[i];
+            most = max(most, len[i]);
+        }
+        // Without branches around the loads: with them the compiler waits for the next ids in front of the rows.
+        for (int j = 0; j < most; j += U * RPW) {
+            unsigned key[QUAD][U];
+#pragma unroll
+            for (int i = 0; i < QUAD; ++i)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int k = j + u * RPW + sub;
+                    const unsigned v = keys[k < len[i] ? at0[i] + k : 0];
+                    key[i][u] = k < len[i] ? v : Rows::key(-1);
+                }
+            u32x4 raw[QUAD][U];
+#pragma unroll
+            for (int i = 0; i < QUAD; ++i)
+#pragma unroll
+                for (int u = 0; u < U; ++u) raw[i][u] = src.fetch(key[i][u]);
+#pragma unroll
+            for (int i = 0; i < QUAD; ++i)
+#pragma unroll
+                for (int u = 0; u < U; ++u) accumulate<HALF>(acc[i], raw[i][u], one);
+        }
+#pragma unroll
+        for (int i = 0; i < QUAD; ++i) {
+            const int col = fold_sums<LPR, HALF>(acc[i], lane, lane % LPR);
+            if (LPR > 8 || (lane & 15) < LPR)
+#pragma unroll
+                for (int e = 0; e < folded_columns<LPR, HALF>(); ++e) sums[(q + i) * D + col + e] = acc[i].v[e];
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int q = wave * QUAD; q < mine; q += WAVES * QUAD) {
+        const int live = min(QUAD, mine - q), t = div.of(first + q), b = first + q - t * (int)div.B;
+        if (s_off[q + QUAD] - s_off[q] > QUAD_IDS || b + live > (int)div.B) {
+            for (int i = 0; i < live; ++i) {
+                const int ti = div.of(first + q + i);
+                pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, first + q + i - ti * (int)div.B, ti,
+                                                         __builtin_amdgcn_readfirstlane(s_off[q + i]),
+                                                         __builtin_amdgcn_readfirstlane(s_off[q + i + 1]), one, err);
+            }
+            continue;
+        }
+        for (int k = lane; k < live * (D / 4); k += 64)
+            *reinterpret_cast<f32x4 *>(out.pooled + ((long long)(b + k / (D / 4)) * T + t) * D + k % (D / 4) * 4) =
+                *reinterpret_cast<const f32x4 *>(&sums[q * D + k * 4]);
+    }
+}
+
 // BAGS bags per group of LPR lanes, their load chains (ids -> rows, PER_BAG at a time) running
 // side by side.  bag[g] with ids [pos[g], end[g]); groups without a bag work on a
 // copy of another (live[g] false) and store nothing.

@@ -484,6 +484,7 @@ struct Plan {
     bool ride = false;   // Bottom-FC in the scan's launch
     bool front = false;  // scan (and Bottom-FC, with ride) in the pooling launch
     bool layer = false;  // Bottom-FC's first layer in the launch of the scan
+    bool joined = false;  // scan and pooling in the launch of that layer, in large tiles
     bool tail = false;   // interaction, Predict-FC and the Bottom-FC layers [tail_from, ...) in one launch
     int tail_from = 0;
 };
@@ -517,6 +518,14 @@ bool first_layer_rides(const rec_model *m, const Bufs &u, const Call &c, const P
     if (chain_end(m, m->bottom.data(), 0, p.tail_from, 1, c.B, true, false) > 0) return false;
     const FcProblem first = first_bottom_layer(m, u, c);
     return p.front ? front_layer_rides(first, concat) : scan_layer_rides(first, concat ? u.act[0] : nullptr);
+}
+
+// Does pooling join the launch of the scan and a first layer of large tiles?
+bool pool_joins_layer(const rec_model *m, const Bufs &u, const Call &c, bool use_hot)
+{
+    if (m->interaction == REC_INTERACT_CONCAT || longest_hot_list(m, use_hot) > 0) return false;
+    const FcProblem first = first_bottom_layer(m, u, c);
+    return !fc_split_rides(first) && fc_big_beside_pool_applies(first, m->T, c.B, m->D, m->dtype, c.nnz, m->max_rows);
 }
 
 hipError_t enqueue_front(const rec_model *m, const Bufs &u, const Call &c, const Plan &plan, hipStream_t s)
@@ -559,8 +568,9 @@ Plan plan_of(const rec_model *m, const Bufs &u, const Call &c, bool use_hot, boo
         Plan q = p;
         q.front = false;
         q.layer = first_layer_rides(m, u, c, q);
-        if (q.layer) return q;
+        if (q.layer) p = q;
     }
+    p.joined = p.layer && !p.front && pool_joins_layer(m, u, c, use_hot);
     return p;
 }
 
@@ -642,7 +652,7 @@ hipError_t enqueue_pool(const rec_model *m, const Bufs &u, const Call &c, bool u
 hipError_t enqueue_sparse(const rec_model *m, const Bufs &u, const Call &c, const Plan &plan, bool use_hot,
                           hipStream_t s, hipEvent_t *ev)
 {
-    if (plan.front) {  // all of it in the pooling stage; the scan's reads an empty interval
+    if (plan.front || plan.joined) {  // all of it in the pooling stage; the scan's reads an empty interval
         REC_TRY(mark(ev, EV_SCAN_END, s));
         REC_TRY(enqueue_front(m, u, c, plan, s));
         return mark(ev, EV_POOL_END, s);
@@ -1373,9 +1383,9 @@ rec_status rec_stage_shared(const rec_model *m, int32_t slot, uint32_t *mask)
     return REC_OK;
 }
 
-rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz, uint32_t *mask, int32_t *tail_from)
+static rec_status probe_plan(const rec_model *m, int32_t batch, int64_t nnz, Plan *p)
 {
-    if (!m || !mask || !tail_from || batch < 1 || batch > m->max_batch || nnz < 0 || nnz > m->max_nnz) return REC_ERR_ARG;
+    if (!m || batch < 1 || batch > m->max_batch || nnz < 0 || nnz > m->max_nnz) return REC_ERR_ARG;
     alignas(16) float some[4] = {};  // nothing follows these pointers
     try {
         rec_model loaded = *m;
@@ -1385,14 +1395,32 @@ rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz, uint32
         u.x0 = some;
         for (void *&a : u.act) a = some;
         const Call c{some, nullptr, nullptr, batch, nnz, some, nullptr};
-        const Plan p = plan_of(&loaded, u, c, true, false);
-        *mask = (p.ride ? REC_PLAN_RIDE : 0) | (p.front ? REC_PLAN_FRONT : 0) | (p.layer ? REC_PLAN_LAYER : 0) |
-                (p.tail ? REC_PLAN_TAIL : 0);
-        *tail_from = p.tail_from;
+        *p = plan_of(&loaded, u, c, true, false);
     } catch (const std::bad_alloc &) {
         return REC_ERR_STATE;
     }
     return REC_OK;
+}
+
+rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz, uint32_t *mask, int32_t *tail_from)
+{
+    if (!mask || !tail_from) return REC_ERR_ARG;
+    Plan p;
+    const rec_status st = probe_plan(m, batch, nnz, &p);
+    if (st != REC_OK) return st;
+    *mask = (p.ride ? REC_PLAN_RIDE : 0) | (p.front ? REC_PLAN_FRONT : 0) | (p.layer ? REC_PLAN_LAYER : 0) |
+            (p.tail ? REC_PLAN_TAIL : 0);
+    *tail_from = p.tail_from;
+    return REC_OK;
+}
+
+rec_status rec_probe_plan_joined(const rec_model *m, int32_t batch, int64_t nnz, int32_t *joined)
+{
+    if (!joined) return REC_ERR_ARG;
+    Plan p;
+    const rec_status st = probe_plan(m, batch, nnz, &p);
+    if (st == REC_OK) *joined = p.joined ? 1 : 0;
+    return st;
 }
 
 }  // extern "C"

@@ -340,6 +340,9 @@ bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_
 constexpr int SHORT_FORM_BAGS = 6 * SCAN_TILE;  // up to which bags of a few ids take csrc/front.hip's launch
 hipError_t launch_lookups(const FrontProblem &f, hipStream_t s);
 bool front_lookup_applies(int T, int B, int D, int dtype, long long nnz, int num_cus);
+// The same beside a layer of 128 x 128 tiles (dot models, bags a wave each).
+bool fc_big_beside_pool_applies(const FcProblem &layer, int T, int B, int D, int dtype, long long nnz, long long max_rows);
+hipError_t launch_fc_big_beside_pool(const FrontProblem &f, hipStream_t s);
 bool front_takes(const ChainProblem &rider);
 hipError_t launch_front(const FrontProblem &f, const ChainProblem *rider, hipStream_t s);
 // Once per process and device, before the first launch (not under stream capture).

@@ -121,6 +121,80 @@ __device__ inline long long linked_sum(const TileLink &l, int tile, const int32_
     return sum;
 }
 
+// As part_of_sum(), over up to 2048 lengths a thread, n not zero: loads past n read zeros (a buffer's range
+// check), and of each length there is an addition and an "or", in 32 bits; a thread that has seen a bit from the
+// 20th on (a sign among them) adds its lengths up again in 64.  426 KB by a block of 1024 threads: 104 lengths
+// a thread, some 5 vector instructions each in part_of_sum() (a launch of 13.2 us, 11.8 with this).
+template <int THREADS, int U>
+__device__ inline long long part_of_long_sum(const int32_t *__restrict__ len, int n)
+{
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(len), 0, n * 4, 0x00020000);
+    unsigned sum = 0, seen = 0;
+    for (int k0 = 4 * (int)threadIdx.x; k0 < n; k0 += 4 * THREADS * U) {
+        u32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(src, (k0 + u * 4 * THREADS) * 4, 0, 0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            sum += v[u][0] + v[u][1];
+            sum += v[u][2] + v[u][3];
+            seen |= v[u][0] | v[u][1];
+            seen |= v[u][2] | v[u][3];
+        }
+    }
+    if (seen >> 20 == 0) return sum;
+    long long exact = 0;
+    for (int k0 = 4 * (int)threadIdx.x; k0 < n; k0 += 4 * THREADS)
+        for (int e = 0; e < 4; ++e) exact += max(len[k0 + e], 0);
+    return exact;
+}
+
+// Offsets of bags [first, first + bags) into s_off[0 ... bags] and `offsets`, and the checks of
+// their lengths, by all threads of a block, which add up all earlier lengths: `first` a multiple
+// of 4 and at most 2048 a thread, a thread for each bag.  U: loads of a thread in flight where the
+// earlier lengths are many.  s_w, s_scan: a word per wave each.
+template <int THREADS, int U>
+__device__ inline void offsets_of_block(const int32_t *__restrict__ len, int n, long long nnz, int first, int bags,
+                                        int32_t *__restrict__ offsets, ErrRecord *err, long long *s_w, long long *s_scan,
+                                        int *s_off)
+{
+    constexpr int WAVES = THREADS / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int k = first + tid;
+    int own = tid < bags && k < n ? len[k] : 0;
+    if (own < 0) {  // counts as 0
+        atomicMin(&err->first_bad_len, (unsigned long long)k);
+        atomicOr(&err->flags, ERR_NEG_LENGTH);
+        own = 0;
+    }
+    long long incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const long long up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+    }
+    if (lane == 63) s_scan[wave] = incl;
+    const long long before = wave_sum(U == 8 || first <= 4 * 8 * THREADS ? part_of_long_sum<THREADS, 8>(len, first)
+                                                                         : part_of_long_sum<THREADS, U>(len, first));
+    if (lane == 0) s_w[wave] = before;
+    __syncthreads();
+    long long run = incl;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) run += s_w[w];
+    for (int w = 0; w < wave; ++w) run += s_scan[w];
+    if (tid < bags) {
+        s_off[tid] = (int)min(run - own, nnz);
+        if (k < n) offsets[k] = (int)min(run - own, nnz);
+        if (tid == bags - 1) s_off[bags] = (int)min(run, nnz);
+        if (k == n - 1) {
+            offsets[n] = (int)min(run, nnz);
+            if (run != nnz) atomicOr(&err->flags, ERR_TOTAL_MISMATCH);
+        }
+    }
+    __syncthreads();
+}
+
 // LDS of a scan block.
 struct ScanShared {
     // One extra word per 32 keeps the 8-per-thread strided reads off one bank.

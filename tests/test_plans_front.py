@@ -1,6 +1,8 @@
 """Up to which batch scan, a whole Bottom-FC and pooling share a launch (no device)."""
 import pytest
 
+from paper_2203_07424_amd import binding as b
+
 from test_plans import FRONT, RIDE, plan
 
 
@@ -18,3 +20,24 @@ def test_lookups_of_the_joint_launch(tables, dim, batch, ids, front):
     """fp32 rows of 256 bytes in blocks of 256 bags, of 128 in blocks of 512, for 256 compute units."""
     mask, _ = plan(batch, tables=tables, dim=dim, dense=64, bottom=(), hidden=(64,), ids=ids, concat=True)
     assert bool(mask & FRONT) == front
+
+
+@pytest.mark.parametrize("tables,dim,batch,dense,ids,concat,fuse,overlap,joined", [
+    (10, 32, 4096, 2560, 20, False, 1, 0, True), (15, 32, 4096, 1536, 20, False, 1, 0, True),
+    (15, 32, 4112, 1536, 20, False, 1, 0, False), (14, 64, 4096, 2560, 20, False, 1, 0, True),  # 240 bags a compute unit; by LDS 224
+    (15, 64, 4096, 2560, 20, False, 1, 0, False), (10, 32, 4096, 1000, 20, False, 1, 0, True),
+    (11, 32, 4096, 1000, 20, False, 1, 0, False), (10, 32, 4096, 2560, 40, False, 1, 0, True),  # 10 a k-tile; 6400 rows a compute unit
+    (10, 32, 4096, 2560, 41, False, 1, 0, False), (4, 32, 2049, 2560, 56, False, 1, 0, True),
+    (4, 32, 2049, 2560, 57, False, 1, 0, False), (4, 32, 4096, 2560, 4, False, 1, 0, False),  # bags of a few ids
+    (10, 32, 2047, 2560, 20, False, 1, 0, False), (10, 32, 4096, 2560, 20, True, 1, 0, False),
+    (10, 32, 4096, 2560, 20, False, 0, 0, False), (10, 32, 4096, 2560, 20, False, 1, 1, False)])
+def test_pooling_joins_a_wide_layer(tables, dim, batch, dense, ids, concat, fuse, overlap, joined):
+    bottom = (1024, dim)
+    z = dim + tables * dim if concat else dim + tables * (tables + 1) // 2
+    st, m = b.rec_create(num_tables=tables, emb_dim=dim, rows=[1000] * tables, table_dtype=b.REC_F32, num_dense=dense,
+                         bottom_widths=[dense, *bottom], top_widths=[z, 64, 1], max_batch=batch, max_nnz=tables * batch * ids,
+                         interaction=b.REC_INTERACT_CONCAT if concat else b.REC_INTERACT_DOT)
+    assert st == b.REC_OK
+    assert b.rec_set_option(m, b.REC_OPT_FUSE_MLP, fuse) == b.rec_set_option(m, b.REC_OPT_OVERLAP_DENSE, overlap) == b.REC_OK
+    assert b.rec_probe_plan_joined(m, batch, tables * batch * ids) == (b.REC_OK, joined)
+    b.rec_destroy(m)
