@@ -294,8 +294,8 @@ inline bool beside_wide_fits(long long n, int D, int num_cus)
 // layer is a quarter through: two blocks of 128 x 128 tiles fit a compute unit (115
 // registers, 72 KB of LDS, the scan's inside it), so no tile waits for them: 4096 samples,
 // 2560-1024 beside 10 tables 76.4 -> 71.2 us per forward, 2400 beside 8 74.2 -> 66.7.  What bounds it is the chain
-// of trips and barriers of one block in lock-step: 22 bytes of operands a clock and compute unit, 64 lines in
-// flight at 421 cycles, the matrix pipe busy 23 % of the launch.
+// of trips and barriers of one block in lock-step: 24 bytes of operands a clock and compute unit at 388 cycles a
+// line, the matrix pipe busy 25 % of the launch.
 template <bool OUT_F32>
 __global__ __launch_bounds__(512, 4) void fc_big_behind_scan_kernel(
     const void *__restrict__ A0, const void *__restrict__ W0, int lda, int M, int K, int Kpad, int grid_m, int grid_n,
