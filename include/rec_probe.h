@@ -85,6 +85,12 @@ REC_API rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz
 /* The same, *joined = 1 where pooling is in the launch of REC_PLAN_LAYER too, a layer of large tiles. */
 REC_API rec_status rec_probe_plan_joined(const rec_model *m, int32_t batch, int64_t nnz, int32_t *joined);
 
+/* How a launch that copies the dense part of a concatenation model without Bottom-FC (`rows`
+ * samples of `columns` features, then `pad` zeros a row) deals it: deal[0] blocks of deal[1]
+ * waves, deal[2] units a wave at most, a unit four wave-wide accesses.  left: -1, the launch of the scan or of
+ * scan and a few lookups; else compute units without a block of the launch of many lookups. */
+REC_API rec_status rec_probe_dense_copy(int32_t rows, int32_t columns, int32_t pad, int32_t left, int32_t *deal);
+
 #ifdef __cplusplus
 }
 #endif

@@ -49,7 +49,7 @@ EXPORTS = ("rec_create", "rec_destroy", "rec_workspace_bytes", "rec_bind_workspa
            "rec_load_tables", "rec_load_hot_rows", "rec_mlp_packed_bytes", "rec_load_mlp", "rec_forward", "rec_forward_static", "rec_check",
            "rec_debug_get", "rec_set_option", "rec_set_dense_stream", "rec_set_pool_streams", "rec_drain", "rec_set_profiling", "rec_stage_ms", "rec_stage_shared", "rec_status_string",
            "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan", "rec_probe_fc_form", "rec_probe_plan",
-           "rec_probe_plan_joined")
+           "rec_probe_plan_joined", "rec_probe_dense_copy")
 
 
 class rec_config(C.Structure):
@@ -114,6 +114,8 @@ _lib.rec_probe_plan.restype = C.c_int
 _lib.rec_probe_plan.argtypes = [_vp, C.c_int32, C.c_int64, C.POINTER(C.c_uint32), C.POINTER(C.c_int32)]
 _lib.rec_probe_plan_joined.restype = C.c_int
 _lib.rec_probe_plan_joined.argtypes = [_vp, C.c_int32, C.c_int64, C.POINTER(C.c_int32)]
+_lib.rec_probe_dense_copy.restype = C.c_int
+_lib.rec_probe_dense_copy.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
 _lib.rec_probe_fc_form.restype = C.c_int
 _lib.rec_probe_fc_form.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_uint32, C.c_int32, C.POINTER(C.c_int32)]
 
@@ -284,6 +286,13 @@ def rec_probe_plan_joined(m: int, batch: int, nnz: int) -> Tuple[int, bool]:
     joined = C.c_int32(0)
     st = _lib.rec_probe_plan_joined(m, int(batch), int(nnz), C.byref(joined))
     return st, bool(joined.value)
+
+
+def rec_probe_dense_copy(rows: int, columns: int, pad: int, left: int = -1) -> Tuple[int, int, int, int]:
+    """(status, blocks, waves of a block, units a wave) for the copy of a concatenation model's dense part."""
+    deal = (C.c_int32 * 3)()
+    st = _lib.rec_probe_dense_copy(int(rows), int(columns), int(pad), int(left), deal)
+    return st, *deal
 
 
 class RecModel:

@@ -291,7 +291,7 @@ hipError_t launch_short(const FrontProblem &f, hipStream_t s)
     constexpr int NACC = HALF ? 8 : 4;
     const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
     const int vec_ok = f.out.col0 % NACC == 0 && reinterpret_cast<uintptr_t>(f.out.z) % 16 == 0;
-    const int extra = concat_dense_blocks(f.dense, POOL_WAVES, 256);
+    const int extra = concat_dense_blocks(f.dense, POOL_WAVES);
     constexpr int BAGS = short_block_bags<LPR>();
     const BagTable div = BagTable::of_batch(f.B);
     const int pool_blocks = ((n + BAGS - 1) / BAGS + 7) / 8 * 8;

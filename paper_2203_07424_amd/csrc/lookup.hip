@@ -69,8 +69,7 @@ hipError_t launch_lookup(const FrontProblem &f, hipStream_t s)
     const int vec_ok = f.out.col0 % NACC == 0 && reinterpret_cast<uintptr_t>(f.out.z) % 16 == 0;
     const BagTable div = BagTable::of_batch(f.B);
     const int blocks = ((n + BAGS - 1) / BAGS + 7) / 8 * 8;
-    // as many as the compute units that the others leave, a block each
-    const int extra = concat_dense_blocks(f.dense, LOOKUP_THREADS / 64, std::max(16, f.num_cus - blocks));
+    const int extra = lookup_dense_blocks(f.dense, f.num_cus - blocks);
     hipLaunchKernelGGL((front_lookup_kernel<LPR, HALF>), dim3(blocks + extra), dim3(LOOKUP_THREADS), 0, s, f.lengths, f.tables,
                        f.indices, f.nnz, n, blocks, extra, blocks / 8, div.B, div.magic, f.T, 1.0f, vec_ok, f.offsets, f.err,
                        f.out, f.dense);
@@ -78,6 +77,13 @@ hipError_t launch_lookup(const FrontProblem &f, hipStream_t s)
 }
 
 }  // namespace
+
+// As many as the compute units that the others leave, a block each, or what a wave does in the others' time.
+int lookup_dense_blocks(const ConcatDense &job, int left)
+{
+    constexpr int WAVES = LOOKUP_THREADS / 64;
+    return std::min(concat_dense_blocks(job, WAVES, 2), std::max({16, left, concat_dense_blocks(job, WAVES, 8)}));
+}
 
 bool front_lookup_applies(int T, int B, int D, int dtype, long long nnz, int num_cus)
 {

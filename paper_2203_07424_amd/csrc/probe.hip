@@ -4,8 +4,8 @@
 // operands, on constant or on pseudo-random values.  With every compute unit
 // busy the chip is power-limited and the rate depends on the operand bits; a
 // benchmark puts it beside the published peak.
-#include "rec_internal.h"
 #include "rec_probe.h"
+#include "scan_body.h"
 
 namespace {
 
@@ -120,5 +120,20 @@ extern "C" rec_status rec_probe_fc_form(int32_t rows, int32_t inputs, int32_t ou
         t = fc_big_tile(p, compute_units);
     }
     form[1] = 16 * t.tm; form[2] = 16 * t.tn; form[3] = t.wk;
+    return REC_OK;
+}
+
+extern "C" rec_status rec_probe_dense_copy(int32_t rows, int32_t columns, int32_t pad, int32_t left, int32_t *deal)
+{
+    using namespace rec;
+    static float some[1];
+    if (!deal || rows < 1 || rows > (1 << 24) || columns < 0 || columns > (1 << 16) || pad < 0 || pad >= PAD || left < -1) return REC_ERR_ARG;
+    ConcatDense job;
+    job.x0 = some; job.w0 = columns; job.B = rows;
+    job.width = columns; job.ldz = columns + pad;
+    deal[1] = left < 0 ? SCAN_THREADS / 64 : 16;
+    deal[0] = left < 0 ? scan::concat_dense_blocks(job, deal[1]) : lookup_dense_blocks(job, left);
+    const int all = scan::dense_units(rows, columns, pad).all, waves = deal[0] * deal[1];
+    deal[2] = waves > 0 ? (all + waves - 1) / waves : 0;
     return REC_OK;
 }

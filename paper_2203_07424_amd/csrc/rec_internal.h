@@ -339,6 +339,7 @@ bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_
 // More lookups than that, about one id a bag, of a concatenation model without Bottom-FC (no layer).
 constexpr int SHORT_FORM_BAGS = 6 * SCAN_TILE;  // up to which bags of a few ids take csrc/front.hip's launch
 hipError_t launch_lookups(const FrontProblem &f, hipStream_t s);
+int lookup_dense_blocks(const ConcatDense &job, int left);  // its blocks for the dense part, `left` compute units without another
 bool front_lookup_applies(int T, int B, int D, int dtype, long long nnz, int num_cus);
 // The same beside a layer of 128 x 128 tiles (dot models, bags a wave each).
 bool fc_big_beside_pool_applies(const FcProblem &layer, int T, int B, int D, int dtype, long long nnz, long long max_rows);

@@ -154,7 +154,7 @@ hipError_t launch_scan(const int32_t *lengths, int n, long long nnz, int32_t *of
 {
     if (n <= 0) return hipSuccess;
     const int tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
-    const int extra = concat_dense_blocks(job, SCAN_THREADS / 64, 256);
+    const int extra = concat_dense_blocks(job, SCAN_THREADS / 64);
     const bool has_rider = rider && rider->M > 0;
     unsigned long long *words = scan_linked_words(n, has_rider) > 0 ? tile_words : nullptr;
     if (has_rider) {
@@ -188,7 +188,7 @@ hipError_t launch_scan_beside_layer(const int32_t *lengths, int n, long long nnz
     const ScanBlocks b{lengths, offsets, scan_linked_words(n, true) > 0 ? tile_words : nullptr, nnz, n,
                        (n + SCAN_TILE - 1) / SCAN_TILE, SCAN_LINK_POLLS, err};
     if (!fc_split_rides(layer)) return job.x0 ? hipErrorInvalidValue : launch_fc_big_behind_scan(layer, b, s);
-    const int extra = concat_dense_blocks(job, SCAN_THREADS / 64, 256);
+    const int extra = concat_dense_blocks(job, SCAN_THREADS / 64);
     const FcTile t = fc_split_tile(layer);
     switch (t.tm * 100 + t.tn * 10 + t.wk) {
     case 118: return launch_beside<1, 1, 8>(b, extra, job, layer, z, ldz, z_cols, s);
