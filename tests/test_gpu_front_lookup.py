@@ -63,3 +63,50 @@ def test_front_of_many_lookups(binding, T, D, dtype, B, F):
         run(odd, idx)
         assert m.check() == (binding.REC_ERR_LENGTHS, first)
     m.close()
+
+
+def test_long_bags(binding):
+    """Bags of more ids than most: one that is nearly all of the forward takes no longer than in a launch of
+    lookups alone (with an id at a time it took 1.8 times as long, with four 0.5), and every length around the ids of
+    a trip gives the same sums; an id out of range in a late trip is found."""
+    print("front lookup long bags", flush=True)
+    g = np.random.default_rng(5)
+    T, D, B, R, F = 26, 64, 600, 300, 8
+    tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(np.float16) for _ in range(T)]
+    n = T * B
+    lens = np.where(g.random(n) < 0.03, g.integers(0, 12, n), 1).astype(np.int32)
+    lens[512:700], lens[5000:5100] = 6, 3
+    lens[n // 3] = 0
+    lens[n // 3] = n + n // 4 - lens.sum()
+    assert lens[n // 3] > 400
+    idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
+    m = H.make_model(binding, tabs, [], stack(g, (F + T * D, 1)), B, idx.size, F, interaction="concat")
+    assert binding.rec_probe_plan(m.handle, B, idx.size)[1] & binding.REC_PLAN_FRONT
+    dense = g.standard_normal((B, F)).astype(np.float32)
+    H.run(m, synth.Batch(dense, idx, lens))
+    assert m.check() == (binding.REC_OK, -1)
+    z = m.debug_interact()[:, F:F + T * D].float().cpu().numpy().astype(np.float64).reshape(B, T, D)
+    P, A, _, _ = orc.pool(tabs, idx, lens, B, want_abs=True)
+    assert (np.abs(z - P) <= 2.0 ** -8 * (np.abs(P) + 1e-5 * A) + 1e-5 * A).all()
+    bad, at = idx.copy(), int(lens[:n // 3 + 1].sum()) - 2
+    bad[at] = R
+    H.run(m, synth.Batch(dense, bad, lens))
+    assert m.check() == (binding.REC_ERR_INDEX_RANGE, at)
+
+    lens = np.ones(n, np.int32)
+    lens[n // 3] = 3500
+    idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
+    args = [torch.from_numpy(a).cuda() for a in (dense, idx, lens)]
+    out, best = torch.empty(B, device="cuda"), {}
+    for fuse in (1, 0, 1, 0):
+        m.set_option(binding.REC_OPT_FUSE_MLP, fuse)
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                m.forward(*args, out)
+            b.record()
+            b.synchronize()
+            best[fuse] = min(best.get(fuse, 1e9), a.elapsed_time(b))
+    assert best[1] <= 1.2 * best[0], best
+    m.close()
