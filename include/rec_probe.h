@@ -85,6 +85,17 @@ REC_API rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz
 /* The same, *joined = 1 where pooling is in the launch of REC_PLAN_LAYER too, a layer of large tiles. */
 REC_API rec_status rec_probe_plan_joined(const rec_model *m, int32_t batch, int64_t nnz, int32_t *joined);
 
+/* Forms of pooling: launches of their own (a bag a wave, two bags a wave, several bags of a few ids a wave, hot
+ * rows from LDS) ... */
+enum {
+    REC_POOL_BAG = 0, REC_POOL_TWO = 1, REC_POOL_SHORT = 2, REC_POOL_HOT = 3,
+    /* ... and with the scan in one: beside Bottom-FC or its first layer in small tiles, a whole Bottom-FC within 64
+     * registers, a few lookups of a concatenation model, many of them, beside a first layer of large tiles. */
+    REC_POOL_FRONT = 4, REC_POOL_FRONT_LIGHT = 5, REC_POOL_FEW_LOOKUPS = 6, REC_POOL_MANY_LOOKUPS = 7, REC_POOL_BESIDE_WIDE = 8
+};
+/* The one that rec_forward() would take, as rec_probe_plan(). */
+REC_API rec_status rec_probe_plan_pooling(const rec_model *m, int32_t batch, int64_t nnz, int32_t *form);
+
 /* How a launch that copies the dense part of a concatenation model without Bottom-FC (`rows`
  * samples of `columns` features, then `pad` zeros a row) deals it: deal[0] blocks of deal[1]
  * waves, deal[2] units a wave at most, a unit four wave-wide accesses.  left: -1, the launch of the scan or of

@@ -43,13 +43,15 @@ REC_NUM_STAGES = 7
 REC_FC_F32_ROWS, REC_FC_DOT, REC_FC_BESIDE_POOLING, REC_FC_ANY_ORDER = 1, 2, 4, 8
 REC_FORM_TILES, REC_FORM_WIDE, REC_FORM_SPLIT = 0, 1, 2
 REC_PLAN_RIDE, REC_PLAN_FRONT, REC_PLAN_LAYER, REC_PLAN_TAIL = 1, 2, 4, 8
+(REC_POOL_BAG, REC_POOL_TWO, REC_POOL_SHORT, REC_POOL_HOT, REC_POOL_FRONT, REC_POOL_FRONT_LIGHT, REC_POOL_FEW_LOOKUPS,
+ REC_POOL_MANY_LOOKUPS, REC_POOL_BESIDE_WIDE) = range(9)
 STAGE_NAMES = ("scan", "pool", "bottom_first", "bottom_rest", "interact", "top_first", "top_rest")
 
 EXPORTS = ("rec_create", "rec_destroy", "rec_workspace_bytes", "rec_bind_workspace",
            "rec_load_tables", "rec_load_hot_rows", "rec_mlp_packed_bytes", "rec_load_mlp", "rec_forward", "rec_forward_static", "rec_check",
            "rec_debug_get", "rec_set_option", "rec_set_dense_stream", "rec_set_pool_streams", "rec_drain", "rec_set_profiling", "rec_stage_ms", "rec_stage_shared", "rec_status_string",
            "rec_synth_fill_table", "rec_probe_mfma", "rec_probe_scan", "rec_probe_fc_form", "rec_probe_plan",
-           "rec_probe_plan_joined", "rec_probe_dense_copy")
+           "rec_probe_plan_joined", "rec_probe_plan_pooling", "rec_probe_dense_copy")
 
 
 class rec_config(C.Structure):
@@ -114,6 +116,8 @@ _lib.rec_probe_plan.restype = C.c_int
 _lib.rec_probe_plan.argtypes = [_vp, C.c_int32, C.c_int64, C.POINTER(C.c_uint32), C.POINTER(C.c_int32)]
 _lib.rec_probe_plan_joined.restype = C.c_int
 _lib.rec_probe_plan_joined.argtypes = [_vp, C.c_int32, C.c_int64, C.POINTER(C.c_int32)]
+_lib.rec_probe_plan_pooling.restype = C.c_int
+_lib.rec_probe_plan_pooling.argtypes = [_vp, C.c_int32, C.c_int64, C.POINTER(C.c_int32)]
 _lib.rec_probe_dense_copy.restype = C.c_int
 _lib.rec_probe_dense_copy.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
 _lib.rec_probe_fc_form.restype = C.c_int
@@ -286,6 +290,13 @@ def rec_probe_plan_joined(m: int, batch: int, nnz: int) -> Tuple[int, bool]:
     joined = C.c_int32(0)
     st = _lib.rec_probe_plan_joined(m, int(batch), int(nnz), C.byref(joined))
     return st, bool(joined.value)
+
+
+def rec_probe_plan_pooling(m: int, batch: int, nnz: int) -> Tuple[int, int]:
+    """(status, REC_POOL_*: the form of pooling that a forward takes)."""
+    form = C.c_int32(-1)
+    st = _lib.rec_probe_plan_pooling(m, int(batch), int(nnz), C.byref(form))
+    return st, form.value
 
 
 def rec_probe_dense_copy(rows: int, columns: int, pad: int, left: int = -1) -> Tuple[int, int, int, int]:

@@ -53,14 +53,6 @@ constexpr int LONG_BAGS = 7 * SCAN_TILE / 2;
 constexpr int LIGHT_BAGS = 7 * SCAN_TILE;
 constexpr int LIGHT_INPUT = 512;  // inputs of such a stack at most: four blocks a compute unit by its LDS
 
-// The light form of Bottom-FC, beside twice the pooling waves, beyond LONG_BAGS and up to there where
-// pooling is the longer part: by the bytes of rows a compute unit gathers (us per forward, other form / light; 320 KB
-// 19.4 / 18.3, 450 21.9 / 20.1; 256 23.4 / 23.9, 64 12.6 / 13.4).
-inline bool front_takes_light(int n, long long nnz, int rowbytes, int num_cus)
-{
-    return n > LONG_BAGS || nnz * rowbytes > (long long)num_cus * (288 * 1024);
-}
-
 // Sum over max(len, 0) of lengths [0, n) by all threads of the block; s_w: a word
 // per wave.
 template <int THREADS>
@@ -241,7 +233,7 @@ hipError_t launch_long(const FrontProblem &f, const ChainProblem &a, hipStream_t
     const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE, chain_blocks = (a.M + 31) / 32;
     const int pool_blocks = ((n + chain::CH_WAVES - 1) / chain::CH_WAVES + 7) / 8 * 8;
     const BagTable div = BagTable::of_batch(f.B);
-    auto k = front_takes_light(n, f.nnz, LPR * 16, a.num_cus)
+    auto k = front_takes_light(n, f.nnz, LPR * 16, a.Kpad[0], a.num_cus)
                  ? (f.stream_rows ? front_kernel<LPR, HALF, true, true> : front_kernel<LPR, HALF, false, true>)
                  : (f.stream_rows ? front_kernel<LPR, HALF, true, false> : front_kernel<LPR, HALF, false, false>);
     hipLaunchKernelGGL(k, dim3(tiles + chain_blocks + pool_blocks), dim3(chain::CH_THREADS),
@@ -332,6 +324,16 @@ hipError_t prepare_long()
 }
 
 }  // namespace
+
+// The light form of Bottom-FC, beside twice the pooling waves, beyond LONG_BAGS and up to there where
+// pooling is the longer part: by the bytes of rows a compute unit gathers (us per forward, other form / light; 320 KB
+// 19.4 / 18.3, 450 21.9 / 20.1; 256 23.4 / 23.9, 64 12.6 / 13.4).  Stacks of wider inputs have two blocks a compute unit by
+// their LDS in either form and gain no wave (28 tables of 80 fp32 rows x 256 samples in front of x-64-64, 560 KB: 256 inputs
+// 23.9 / 22.4, 500 24.0 / 24.1, 576 24.0 / 24.6, 1000 24.2 / 26.4).
+bool front_takes_light(long long n, long long nnz, int rowbytes, int input, int num_cus)
+{
+    return n > LONG_BAGS || (input <= LIGHT_INPUT && nnz * rowbytes > (long long)num_cus * (288 * 1024));
+}
 
 bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat, int ride_input)
 {

@@ -1414,6 +1414,30 @@ rec_status rec_probe_plan(const rec_model *m, int32_t batch, int64_t nnz, uint32
     return REC_OK;
 }
 
+rec_status rec_probe_plan_pooling(const rec_model *m, int32_t batch, int64_t nnz, int32_t *form)
+{
+    if (!form) return REC_ERR_ARG;
+    Plan p;
+    const rec_status st = probe_plan(m, batch, nnz, &p);
+    if (st != REC_OK) return st;
+    const long long bags = (long long)m->T * batch;
+    const int rowbytes = m->D * (m->dtype == REC_F16 ? 2 : 4);
+    const bool concat = m->interaction == REC_INTERACT_CONCAT;
+    if (p.joined)
+        *form = REC_POOL_BESIDE_WIDE;
+    else if (p.front && concat)
+        *form = bags > SHORT_FORM_BAGS ? REC_POOL_MANY_LOOKUPS : REC_POOL_FEW_LOOKUPS;
+    else if (p.front)
+        *form = p.ride && front_takes_light(bags, nnz, rowbytes, m->bottom[0].Kpad, m->num_cus) ? REC_POOL_FRONT_LIGHT : REC_POOL_FRONT;
+    else if (longest_hot_list(m, true) > 0 && !concat)
+        *form = REC_POOL_HOT;
+    else if (pool_short_applies(rowbytes, nnz, bags))
+        *form = REC_POOL_SHORT;
+    else
+        *form = !concat && pool_two_applies(rowbytes, nnz, bags, pool_narrow(m->max_rows, rowbytes), m->num_cus) ? REC_POOL_TWO : REC_POOL_BAG;
+    return REC_OK;
+}
+
 rec_status rec_probe_plan_joined(const rec_model *m, int32_t batch, int64_t nnz, int32_t *joined)
 {
     if (!joined) return REC_ERR_ARG;

@@ -334,6 +334,8 @@ struct FrontProblem {
 };
 bool front_layer_rides(const FcProblem &p, bool concat);
 constexpr int FRONT_SHORT_WAVES = 4;  // that share the k of such a layer's tiles in a concatenation model
+// Does a whole stack of `input` padded inputs run there within 64 registers?
+bool front_takes_light(long long bags, long long nnz, int rowbytes, int input, int num_cus);
 // ride_input: padded inputs of the stack that is to ride along, 0: none.
 bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_rows, bool concat, int ride_input);
 // More lookups than that, about one id a bag, of a concatenation model without Bottom-FC (no layer).

@@ -22,6 +22,29 @@ def test_lookups_of_the_joint_launch(tables, dim, batch, ids, front):
     assert bool(mask & FRONT) == front
 
 
+def pooling(tables, dim, batch, ids, dense, bottom, hidden=(64,), concat=False, dtype=b.REC_F32):
+    z = (list(bottom) or [dense])[-1] + tables * dim if concat else dim + tables * (tables + 1) // 2
+    st, m = b.rec_create(num_tables=tables, emb_dim=dim, rows=[1000] * tables, table_dtype=dtype, num_dense=dense,
+                         bottom_widths=[dense, *bottom], top_widths=[z, *hidden, 1], max_batch=batch, max_nnz=tables * batch * ids,
+                         interaction=b.REC_INTERACT_CONCAT if concat else b.REC_INTERACT_DOT)
+    assert st == b.REC_OK
+    assert b.rec_probe_plan_pooling(m, batch + 1, 0)[0] == b.rec_probe_plan_pooling(None, 1, 1)[0] == b.REC_ERR_ARG
+    st, form = b.rec_probe_plan_pooling(m, batch, tables * batch * ids)
+    assert st == b.REC_OK
+    b.rec_destroy(m)
+    return form
+
+
+@pytest.mark.parametrize("tables,batch,ids,dense,bottom,form", [
+    (28, 256, 80, 512, (64, 64), b.REC_POOL_FRONT_LIGHT), (28, 256, 80, 513, (64, 64), b.REC_POOL_FRONT),  # 560 KB of rows a compute unit
+    (28, 256, 80, 1000, (64, 64), b.REC_POOL_FRONT), (28, 256, 40, 512, (64, 64), b.REC_POOL_FRONT),       # 280 KB
+    (8, 896, 10, 512, (64, 64), b.REC_POOL_FRONT), (8, 897, 10, 512, (64, 64), b.REC_POOL_FRONT_LIGHT),    # 7168 bags
+    (8, 1792, 10, 512, (64, 64), b.REC_POOL_FRONT_LIGHT), (8, 1793, 10, 512, (64, 64), b.REC_POOL_BAG),    # 14 336
+    (8, 897, 10, 1000, (64, 64), b.REC_POOL_BAG)])
+def test_light_form_of_a_stack(tables, batch, ids, dense, bottom, form):
+    assert pooling(tables, 64, batch, ids, dense, bottom) == form
+
+
 @pytest.mark.parametrize("tables,dim,batch,dense,ids,concat,fuse,overlap,joined", [
     (10, 32, 4096, 2560, 20, False, 1, 0, True), (15, 32, 4096, 1536, 20, False, 1, 0, True),
     (15, 32, 4112, 1536, 20, False, 1, 0, False), (14, 64, 4096, 2560, 20, False, 1, 0, True),  # 240 bags a compute unit; by LDS 224
