@@ -337,6 +337,7 @@ struct PoolBlocks {
 struct PoolShared {
     unsigned keys[8 * pool::QUAD_IDS];
     long long sum[8], scan[8];
+    int next[4];
     int off[BESIDE_WIDE_BAGS + 4];
     float sums[BESIDE_WIDE_COLUMNS];
 };
@@ -349,6 +350,7 @@ __global__ __launch_bounds__(512, 4) void fc_big_beside_pool_kernel(
 {
     extern __shared__ __attribute__((aligned(16))) __bf16 smem[];
     static_assert(sizeof(PoolShared) <= big_lds_bytes<128, 128>(), "pooling's LDS is part of the tiles'");
+    static_assert(BESIDE_WIDE_BAGS <= 64 * pool::QUAD, "a lane to four bags");
     if ((int)blockIdx.x < tiles) {
         struct {
             const void *W[1];
@@ -361,8 +363,9 @@ __global__ __launch_bounds__(512, 4) void fc_big_beside_pool_kernel(
     const int b = blockIdx.x - tiles, first = ((b & 7) * p.per + (b >> 3)) * p.bags;
     if (first >= p.n) return;
     PoolShared &sh = *reinterpret_cast<PoolShared *>(smem);
+    if (threadIdx.x < 2) sh.next[threadIdx.x] = threadIdx.x == 0 ? 8 : 0;  // read behind the barriers below
     scan::offsets_of_block<512, 8>(lengths, p.n, p.nnz, first, p.bags, p.offsets, p.err, sh.sum, sh.scan, sh.off);
-    pool::pool_quads<8, LPR, HALF, STREAM>(tables, indices, p.out, p.div, p.T, p.n, first, p.bags, sh.off, sh.keys, sh.sums, p.one,
+    pool::pool_quads<8, LPR, HALF, STREAM>(tables, indices, p.out, p.div, p.T, p.n, first, p.bags, sh.off, sh.keys, sh.sums, sh.next, p.one,
                                            p.err);
 }
 
@@ -494,6 +497,8 @@ bool fc_big_rides(const FcProblem &a, int num_cus)
 // 76.4 / 75.9, 14 of 28 of 64 bytes x 4096 67.2 / 64.2; 1000 -> 1024, 10 of 20 of 128 x 4096 47.6 / 44.4, 4 of 55 x 6000 57.2 /
 // 55.7.  Beyond: 2560, 14 of 40 of 256 x 4096 (8960 rows) 93.3 / 96.4, 14 of 50 of 64 x 2500 (6836) 61.8 / 63.4, 30 of 8 x 4096
 // (480 bags) 84.2 / 87.8; 1000, 14 of 20 of 64 bytes x 4096 (224 bags) 50.8 / 53.8, 14 of 10 x 6000 64.8 / 72.5.
+// For lengths near each other; of geometric ones four bags wait for their longest, which shows where the bags are long and
+// their rows hot (Zipf of 1.2): 10 of 20 x 2560 behind 1000 43.5 / 44.2, of 40 46.5 / 51.3, of 40 behind 2560 60.9 / 61.1.
 bool fc_big_beside_pool_applies(const FcProblem &a, int T, int B, int D, int dtype, long long nnz, long long max_rows)
 {
     const long long n = (long long)T * B;

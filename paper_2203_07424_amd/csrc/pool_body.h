@@ -269,14 +269,16 @@ __device__ inline void pool_bag(const TableDesc *__restrict__ tables, const int3
 // neighbouring bags a wave at a time, their rows requested together, and the ids of its next four
 // in front of these, all sums stored at the end (behind a store the next rows wait until it has reached memory);
 // for waves that have few others on their compute unit.  Sums in pool_bag()'s order.
-// keys: QUAD_IDS words a wave; sums: D a bag.  Four bags of two tables, or with more ids, are taken one by one
-// at the end (in the loop, their loads cost the others waits).
+// keys: QUAD_IDS words a wave; sums: D a bag; next: WAVES and 0.  Waves take fours as they are done with others, and at
+// the end (in the loop, their loads cost the others waits) the bags of fours of two tables or of more ids one by one.  With
+// every eighth four a wave's own, beside 1536 -> 1024 on 4096 samples of 10 tables, us per forward: all lengths 29 but 2 % of 300
+// 80.3 -> 66.6 (72.0 in two launches), geometric of mean 35 75.2 -> 68.0 (70.8); 20 ids beside 2560 -> 1024 59.4 as before.
 constexpr int QUAD = 4, QUAD_IDS = 256;
 
 template <int WAVES, int LPR, bool HALF, bool STREAM>
 __device__ inline void pool_quads(const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
                                   const PoolOut &out, const BagTable &div, int T, int n, int first, int bags, const int *s_off,
-                                  unsigned *keys, float *sums, float one, ErrRecord *err)
+                                  unsigned *keys, float *sums, int *next, float one, ErrRecord *err)
 {
     typedef RowSource<LPR * 16, true, STREAM> Rows;
     constexpr int RPW = 64 / LPR, CHUNKS = QUAD_IDS / 64, D = LPR * 16 / (HALF ? 2 : 4), U = 3;
@@ -298,17 +300,25 @@ __device__ inline void pool_quads(const TableDesc *__restrict__ tables, const in
             if (c * 64 + lane < count) id[c] = indices[from + c * 64 + lane];
         }
     };
+    const auto joint = [&](int ids, int bag, int live, int t) { return ids <= QUAD_IDS && bag + live <= (t + 1) * (int)div.B; };
     keys += wave * QUAD_IDS;
     const int mine = min(bags, n - first);  // n - first > 0
+    const auto ticket = [&](int *count) {
+        int v = 0;
+        if (lane == 0) v = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return __builtin_amdgcn_readfirstlane(v);
+    };
+    unsigned long long own = 0;  // fours whose sums this wave has in LDS
     if (wave * QUAD < mine) request(wave * QUAD);
-    for (int q = wave * QUAD; q < mine; q += WAVES * QUAD) {
+    for (int q = wave * QUAD, after; q < mine; q = after) {
+        after = ticket(next) * QUAD;
         const int live = min(QUAD, mine - q), bag = first + q;
         int offs[QUAD + 1];
         read_offsets(q, offs);
         const int t = div.of(bag), from = offs[0], total = offs[QUAD] - from;
-        const bool joint = total <= QUAD_IDS && bag + live <= (t + 1) * (int)div.B;
+        const bool together = joint(total, bag, live, t);
         const long long rows = tables[t].rows;
-        if (joint) {
+        if (together) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
             for (int c = 0; c < CHUNKS; ++c) {
@@ -322,8 +332,9 @@ __device__ inline void pool_quads(const TableDesc *__restrict__ tables, const in
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-        if (q + WAVES * QUAD < mine) request(q + WAVES * QUAD);
-        if (!joint) continue;
+        if (after < mine) request(after);
+        if (!together) continue;
+        own |= 1ull << q / QUAD;
         const Rows src(tables[t].base, rows, lane % LPR);
         Acc<HALF> acc[QUAD];
         int at0[QUAD], len[QUAD], most = 0;  // of bags past the last one no ids
@@ -364,18 +375,24 @@ __device__ inline void pool_quads(const TableDesc *__restrict__ tables, const in
                 for (int e = 0; e < folded_columns<LPR, HALF>(); ++e) sums[(q + i) * D + col + e] = acc[i].v[e];
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    for (int q = wave * QUAD; q < mine; q += WAVES * QUAD) {
-        const int live = min(QUAD, mine - q), t = div.of(first + q), b = first + q - t * (int)div.B;
-        if (s_off[q + QUAD] - s_off[q] > QUAD_IDS || b + live > (int)div.B) {
-            for (int i = 0; i < live; ++i) {
-                const int ti = div.of(first + q + i);
-                pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, first + q + i - ti * (int)div.B, ti,
-                                                         __builtin_amdgcn_readfirstlane(s_off[q + i]),
-                                                         __builtin_amdgcn_readfirstlane(s_off[q + i + 1]), one, err);
-            }
-            continue;
+    // The bags of all other fours of the block, dealt to its waves: a lane looks at a four (their number fits a wave).
+    const int at = min(lane * QUAD, mine - 1) / QUAD * QUAD;
+    unsigned long long left = __builtin_amdgcn_ballot_w64(
+        lane * QUAD < mine && !joint(s_off[at + QUAD] - s_off[at], first + at, min(QUAD, mine - at), div.of(first + at)));
+    for (int turn = 0, my = left != 0 ? ticket(next + 1) : 0; left != 0; left &= left - 1) {
+        const int q = __builtin_ctzll(left) * QUAD;
+        for (int i = 0; i < min(QUAD, mine - q); ++i, ++turn) {
+            if (turn != my) continue;
+            const int bag = first + q + i, t = div.of(bag);
+            pool_bag<LPR, HALF, false, STREAM, true>(tables, indices, out, 0, T, bag - t * (int)div.B, t,
+                                                     __builtin_amdgcn_readfirstlane(s_off[q + i]),
+                                                     __builtin_amdgcn_readfirstlane(s_off[q + i + 1]), one, err);
+            my = ticket(next + 1);
         }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (; own != 0; own &= own - 1) {
+        const int q = __builtin_ctzll(own) * QUAD, live = min(QUAD, mine - q), t = div.of(first + q), b = first + q - t * (int)div.B;
         for (int k = lane; k < live * (D / 4); k += 64)
             *reinterpret_cast<f32x4 *>(out.pooled + ((long long)(b + k / (D / 4)) * T + t) * D + k % (D / 4) * 4) =
                 *reinterpret_cast<const f32x4 *>(&sums[q * D + k * 4]);
