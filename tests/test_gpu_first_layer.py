@@ -58,7 +58,7 @@ def compare(binding, m, batch, concat=False):
     return joint
 
 
-# where: the launch that has the layer; tile: its rows, columns and the waves that share its
+# where: the launch that has the layer, "joined": that of the scan with pooling in it too; tile: its rows, columns and the waves that share its
 # k on 256 compute units (128 x 128: csrc/gemm_big.hip).
 POOLED = [
     (1, 32, np.float32, 1, 2560, (1024, 256), 20, "pooling", (16, 16, 8)),
@@ -80,9 +80,12 @@ POOLED = [
     (5, 32, np.float32, 1187, 1000, (1024, 256), 8, "scan", (80, 64, 8)),
     (12, 16, np.float32, 100, 640, (1024, 32), 9, "pooling", (16, 32, 8)),      # rows of 64 bytes
     (12, 8, np.float16, 100, 640, (1024, 32), 9, "scan", (16, 32, 8)),          # 16-byte rows: never with pooling
-    (5, 32, np.float32, 3500, 1536, (1024, 256), 8, "scan", (128, 128, 1)),     # 224 tiles
-    (4, 32, np.float32, 2049, 1000, (1024, 256), 7, "scan", (128, 128, 1)),     # 136
-    (9, 32, np.float32, 4097, 1000, (1024, 256), 6, "scan", (128, 128, 1)),     # and with 19 tiles of lengths
+    (5, 32, np.float32, 3500, 1536, (1024, 256), 8, "joined", (128, 128, 1)),   # 224 tiles, pooling in the launch too
+    (4, 32, np.float32, 2049, 1000, (1024, 256), 7, "joined", (128, 128, 1)),   # 136
+    (9, 32, np.float32, 4097, 1000, (1024, 256), 6, "joined", (128, 128, 1)),
+    (30, 32, np.float32, 2100, 2560, (1024, 256), 6, "scan", (128, 128, 1)),    # 247 bags a compute unit, 31 tiles of lengths: their sums handed on
+    (12, 32, np.float16, 2049, 1000, (1024, 256), 2, "scan", (128, 128, 1)),    # a few ids a bag, 13 tiles
+    (3, 32, np.float32, 2500, 1536, (1024, 256), 60, "scan", (128, 128, 1)),    # long bags, 4 tiles: all earlier lengths added up
     (3, 64, np.float32, 65, 300, (), 7, "pooling", (16, 16, 8)),                # the layer is the whole stack
     (6, 32, np.float32, 70, 1501, (1024, 256), 7, None, None),                  # rows that are not read in vectors
 ]
@@ -103,7 +106,8 @@ def test_layer_of_a_pooled_model(binding, T, D, dtype, B, F, bottom, mean, where
     if cus == 256:
         _, mask, _ = binding.rec_probe_plan(m.handle, B, idx.size)
         assert bool(mask & binding.REC_PLAN_LAYER) == (where is not None)
-        assert bool(mask & binding.REC_PLAN_FRONT) == (where != "scan")
+        assert bool(mask & binding.REC_PLAN_FRONT) == (where not in ("scan", "joined"))
+        assert binding.rec_probe_plan_joined(m.handle, B, idx.size) == (binding.REC_OK, where == "joined")
         form = binding.rec_probe_fc_form(B, F, (bottom + (D,))[0], 1, binding.REC_FC_ANY_ORDER | binding.REC_FC_F32_ROWS)[1]
         assert tile is None or form[1:] == tile
     dense = g.standard_normal((B, F)).astype(np.float32)

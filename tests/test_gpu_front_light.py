@@ -1,6 +1,6 @@
 """Scan, Bottom-FC and pooling in one launch where Bottom-FC keeps within 64 registers: from the
-smallest batch that takes this form by its bags to the largest and one bag more, a Bottom-FC
-of one to three layers, the widest input."""
+smallest batch that takes this form by its bags to the largest and one bag more, and by its rows, every row size, type
+and way of loading rows, a Bottom-FC of one to three layers, the widest input, faults."""
 import numpy as np
 import pytest
 import torch
@@ -20,24 +20,41 @@ def binding():
     return b
 
 
-@pytest.mark.parametrize("T,D,dtype,B,bottom", [(7, 64, np.float16, 1025, (30, 64)), (23, 32, np.float32, 312, (512, 256, 32)),
-                                                (8, 64, np.float16, 1792, (13, 256, 128, 64)), (3, 64, np.float32, 4779, (257, 100, 64)),
-                                                (10, 16, np.float32, 1003, (500, 16))])
-def test_front_of_more_bags(binding, T, D, dtype, B, bottom):
-    print("front light case", T, D, np.dtype(dtype).name, B, bottom, flush=True)
+@pytest.mark.parametrize("T,D,dtype,B,bottom,mean,stream,light", [
+    (7, 64, np.float16, 1025, (30, 64), 8, False, True), (23, 32, np.float32, 312, (512, 256, 32), 8, True, True),
+    (8, 64, np.float16, 1792, (13, 256, 128, 64), 8, True, True), (3, 64, np.float32, 4779, (257, 100, 64), 8, False, False),  # a bag too many
+    (10, 16, np.float32, 1003, (500, 16), 8, True, True), (7, 128, np.float16, 1030, (64, 256, 128), 6, False, True),          # 256-byte rows
+    (5, 128, np.float16, 2001, (100, 128), 6, True, True), (3, 64, np.float32, 4778, (257, 100, 64), 6, False, True),
+    (9, 64, np.float32, 800, (33, 64), 6, True, True), (12, 32, np.float16, 650, (20, 40, 32), 9, False, True),                # 64
+    (10, 32, np.float16, 1400, (512, 32), 9, True, True), (10, 16, np.float32, 1003, (500, 16), 8, False, True),
+    (10, 64, np.float32, 520, (300, 128, 64), 60, False, True),   # few bags, 300 KB of rows a compute unit
+    (10, 64, np.float32, 520, (300, 128, 64), 50, False, False)])  # 250
+def test_front_of_more_bags(binding, T, D, dtype, B, bottom, mean, stream, light):
+    print("front light case", T, D, np.dtype(dtype).name, B, bottom, mean, stream, flush=True)
     g = np.random.default_rng(700 + T + B)
-    R, F = 500, bottom[0]
+    R, F, n = 500, bottom[0], T * B
     tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(dtype) for _ in range(T)]
-    lens = g.integers(0, 16, T * B).astype(np.int32)
+    lens = g.integers(0, 2 * mean, n).astype(np.int32)
     lens[-1] = 131
     idx = g.integers(0, R, int(lens.sum())).astype(np.int32)
     m = H.make_model(binding, tabs, stack(g, bottom), stack(g, (D + T * (T + 1) // 2, 1)), B, idx.size, F)
+    m.set_option(binding.REC_OPT_STREAM_ROWS, int(stream))
+    if not binding.rec_probe_plan(m.handle, B, idx.size)[1] & binding.REC_PLAN_RIDE:  # one layer, or of many weights
+        m.set_option(binding.REC_OPT_FUSE_MLP, 2)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert (binding.rec_probe_plan_pooling(m.handle, B, idx.size)[1] == binding.REC_POOL_FRONT_LIGHT) == light
     dense = g.standard_normal((B, F)).astype(np.float32)
-    for l, i in ((lens, idx), (lens, idx[:-70])):  # as stated, and too few ids: bags cut off at their number
+    bad, neg = idx.copy(), lens.copy()
+    bad[[700, idx.size - 1]] = (R, -1)
+    neg[n - 5] = -3
+    for l, i, want in ((lens, idx, (binding.REC_OK, -1)), (lens, idx[:-70], (binding.REC_ERR_LENGTHS, -1)),  # too few ids: bags cut off at their number
+                       (lens, bad, (binding.REC_ERR_INDEX_RANGE, 700)), (neg, idx, (binding.REC_ERR_LENGTHS, n - 5))):
         H.run(m, synth.Batch(dense, i, l))
-        assert m.check() == ((binding.REC_OK, -1) if i is idx else (binding.REC_ERR_LENGTHS, -1))
+        assert m.check() == want
         assert np.array_equal(m.debug_offsets().cpu().numpy().astype(np.int64), np.minimum(orc.offsets(l)[0], i.size))
         pooled, x0 = m.debug_pooled().clone(), m.debug_bottom_out().clone()
+        if want[0] != binding.REC_ERR_LENGTHS:
+            H.check_pooled(pooled.cpu().numpy(), *orc.pool(tabs, i, l, B, want_abs=True)[:2])
         m.set_option(binding.REC_OPT_OVERLAP_DENSE, 1)  # scan, pooling and Bottom-FC as launches of their own
         H.run(m, synth.Batch(dense, i, l))
         m.check()

@@ -28,6 +28,8 @@ def test_front_of_many_lookups(binding, T, D, dtype, B, F):
     R, n = 300, T * B
     tabs = [g.uniform(-0.05, 0.05, (R, D)).astype(dtype) for _ in range(T)]
     m = H.make_model(binding, tabs, [], stack(g, (F + T * D, 1)), B, 2 * n, F, interaction="concat")
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert binding.rec_probe_plan_pooling(m.handle, B, n) == (binding.REC_OK, binding.REC_POOL_MANY_LOOKUPS)
     dense = g.standard_normal((B, F)).astype(np.float32)
 
     def run(lens, idx):

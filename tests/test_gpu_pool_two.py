@@ -43,6 +43,7 @@ def test_two_bags_by_a_wave(binding, rowbytes, dtype, odd, pipeline, rounds):
     m = binding.RecModel(T, D, [R] * T, "f16" if dtype == np.float16 else "f32", F, [F, D], [D + 3, 1], B, idx.size, pipeline=pipeline)
     for t, tab in enumerate(tabs):
         m.load_table(t, torch.from_numpy(tab).cuda())
+    assert cus != 256 or binding.rec_probe_plan_pooling(m.handle, B, idx.size) == (binding.REC_OK, binding.REC_POOL_TWO)
     H.load_mlps(binding, m, stack(g, (F, D)), stack(g, (D + 3, 1)))
     dense = g.standard_normal((B, F)).astype(np.float32)
     H.run(m, synth.Batch(dense, idx, lens))

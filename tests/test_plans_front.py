@@ -45,6 +45,16 @@ def test_light_form_of_a_stack(tables, batch, ids, dense, bottom, form):
     assert pooling(tables, 64, batch, ids, dense, bottom) == form
 
 
+@pytest.mark.parametrize("tables,dim,batch,ids,dtype,form", [
+    (10, 64, 4096, 8, b.REC_F32, b.REC_POOL_TWO), (10, 64, 4095, 8, b.REC_F32, b.REC_POOL_BAG),    # 5 rounds of waves, 2 KB a bag
+    (16, 64, 4096, 16, b.REC_F32, b.REC_POOL_TWO), (16, 64, 4095, 16, b.REC_F32, b.REC_POOL_BAG),  # 8, 4 KB
+    (48, 64, 4096, 17, b.REC_F32, b.REC_POOL_TWO), (48, 64, 4095, 17, b.REC_F32, b.REC_POOL_BAG),  # 24
+    (48, 64, 4096, 88, b.REC_F16, b.REC_POOL_TWO), (48, 64, 4096, 89, b.REC_F16, b.REC_POOL_BAG),
+    (48, 128, 4096, 20, b.REC_F32, b.REC_POOL_BAG), (48, 64, 4096, 4, b.REC_F16, b.REC_POOL_SHORT)])
+def test_two_bags_by_a_wave(tables, dim, batch, ids, dtype, form):
+    assert pooling(tables, dim, batch, ids, 100, (128, dim), dtype=dtype) == form
+
+
 @pytest.mark.parametrize("tables,dim,batch,dense,ids,concat,fuse,overlap,joined", [
     (10, 32, 4096, 2560, 20, False, 1, 0, True), (15, 32, 4096, 1536, 20, False, 1, 0, True),
     (15, 32, 4112, 1536, 20, False, 1, 0, False), (14, 64, 4096, 2560, 20, False, 1, 0, True),  # 240 bags a compute unit; by LDS 224
