@@ -199,19 +199,7 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void front_short_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k = first + tid;
     const long long mine = tid < BAGS && k < n ? max(len[k], 0) : 0;
-    long long incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const long long up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
-    }
-    if (lane == 63) s_scan[wave] = incl;
-    long long run = sum_before<THREADS>(len, first, s_w);  // its barrier makes s_scan visible too
-    for (int w = 0; w < wave; ++w) run += s_scan[w];
-    if (tid < BAGS) {
-        s_off[tid] = (int)min(run + incl - mine, nnz);
-        if (tid == BAGS - 1) s_off[BAGS] = (int)min(run + incl, nnz);
-    }
+    block_offsets<THREADS>(mine, part_of_sum<THREADS>(len, first), nnz, BAGS, s_w, s_scan, s_off);
     __syncthreads();
     const int group = wave * (64 / LPR) + lane / LPR;
     bool live[SHORT_BAGS];

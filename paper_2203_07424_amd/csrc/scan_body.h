@@ -157,7 +157,7 @@ __device__ inline long long linked_sum(const TileLink &l, int tile, const int32_
     return sum;
 }
 
-// As part_of_sum(), over up to 2048 lengths a thread, n not zero: loads past n read zeros (a buffer's range
+// As part_of_sum(), over up to 2048 lengths a thread, n a multiple of 4 or zero: loads past n read zeros (a buffer's range
 // check), and of each length there is an addition and an "or", in 32 bits; a thread that has seen a bit from the
 // 20th on (a sign among them) adds its lengths up again in 64.  426 KB by a block of 1024 threads: 104 lengths
 // a thread, some 5 vector instructions each in part_of_sum() (a launch of 13.2 us, 11.8 with this).
@@ -186,24 +186,15 @@ __device__ inline long long part_of_long_sum(const int32_t *__restrict__ len, in
     return exact;
 }
 
-// Offsets of bags [first, first + bags) into s_off[0 ... bags] and `offsets`, and the checks of
-// their lengths, by all threads of a block, which add up all earlier lengths: `first` a multiple
-// of 4 and at most 2048 a thread, a thread for each bag.  U: loads of a thread in flight where the
-// earlier lengths are many.  s_w, s_scan: a word per wave each.
-template <int THREADS, int U>
-__device__ inline void offsets_of_block(const int32_t *__restrict__ len, int n, long long nnz, int first, int bags,
-                                        int32_t *__restrict__ offsets, ErrRecord *err, long long *s_w, long long *s_scan,
-                                        int *s_off)
+// Offsets of a block's bags, a thread for each of the first `bags`, into s_off[0 ... bags], by all threads of the
+// block.  own: the thread's length, not negative; before: its part of the sum of all earlier lengths.  Returned
+// where the thread's bag ends.  s_w, s_scan: a word per wave each.
+template <int THREADS>
+__device__ inline long long block_offsets(long long own, long long before, long long nnz, int bags, long long *s_w, long long *s_scan,
+                                          int *s_off)
 {
     constexpr int WAVES = THREADS / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int k = first + tid;
-    int own = tid < bags && k < n ? len[k] : 0;
-    if (own < 0) {  // counts as 0
-        atomicMin(&err->first_bad_len, (unsigned long long)k);
-        atomicOr(&err->flags, ERR_NEG_LENGTH);
-        own = 0;
-    }
     long long incl = own;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -211,8 +202,7 @@ __device__ inline void offsets_of_block(const int32_t *__restrict__ len, int n, 
         if (lane >= o) incl += up;
     }
     if (lane == 63) s_scan[wave] = incl;
-    const long long before = wave_sum(U == 8 || first <= 4 * 8 * THREADS ? part_of_long_sum<THREADS, 8>(len, first)
-                                                                         : part_of_long_sum<THREADS, U>(len, first));
+    before = wave_sum(before);
     if (lane == 0) s_w[wave] = before;
     __syncthreads();
     long long run = incl;
@@ -221,8 +211,31 @@ __device__ inline void offsets_of_block(const int32_t *__restrict__ len, int n, 
     for (int w = 0; w < wave; ++w) run += s_scan[w];
     if (tid < bags) {
         s_off[tid] = (int)min(run - own, nnz);
-        if (k < n) offsets[k] = (int)min(run - own, nnz);
         if (tid == bags - 1) s_off[bags] = (int)min(run, nnz);
+    }
+    return run;
+}
+
+// Offsets of bags [first, first + bags) into s_off[0 ... bags] and `offsets`, and the checks of
+// their lengths, by all threads of a block, which add up all earlier lengths: `first` a multiple
+// of 4 and at most 2048 a thread, a thread for each bag.  U: loads of a thread in flight where the
+// earlier lengths are many.
+template <int THREADS, int U>
+__device__ inline void offsets_of_block(const int32_t *__restrict__ len, int n, long long nnz, int first, int bags,
+                                        int32_t *__restrict__ offsets, ErrRecord *err, long long *s_w, long long *s_scan,
+                                        int *s_off)
+{
+    const int tid = threadIdx.x, k = first + tid;
+    int own = tid < bags && k < n ? len[k] : 0;
+    if (own < 0) {  // counts as 0
+        atomicMin(&err->first_bad_len, (unsigned long long)k);
+        atomicOr(&err->flags, ERR_NEG_LENGTH);
+        own = 0;
+    }
+    const long long before = U == 8 || first <= 4 * 8 * THREADS ? part_of_long_sum<THREADS, 8>(len, first) : part_of_long_sum<THREADS, U>(len, first);
+    const long long run = block_offsets<THREADS>(own, before, nnz, bags, s_w, s_scan, s_off);
+    if (tid < bags && k < n) {
+        offsets[k] = (int)min(run - own, nnz);
         if (k == n - 1) {
             offsets[n] = (int)min(run, nnz);
             if (run != nnz) atomicOr(&err->flags, ERR_TOTAL_MISMATCH);
