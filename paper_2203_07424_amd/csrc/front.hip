@@ -49,16 +49,20 @@ constexpr int LONG_BAGS = 7 * SCAN_TILE / 2;
 // With the light form of a whole Bottom-FC: us per forward, two launches / one, 10 tables of 80 fp32 rows x 1024
 // samples 31.1 / 27.7, 40 of 80 fp16 rows x 256 30.6 / 25.9, 13 x 966 of 10 ids 18.0 / 15.4 (12 558 bags), 14 x 949 of 42
 // 29.9 / 26.3 (13 286).  Each block of eight bags reads all earlier lengths, so beyond it shapes lose: 12 x 1276 24.1 /
-// 25.0 (15 312), 5 x 3155 26.6 / 28.0 (15 775), 40 x 800 43.2 / 52.7.
-constexpr int LIGHT_BAGS = 7 * SCAN_TILE;
+// 25.0 (15 312), 5 x 3155 26.6 / 28.0 (15 775), 40 x 800 43.2 / 52.7.  In front of one to three tables Bottom-FC's
+// blocks are so many that the line lies lower (8 ids, fp32 and fp16 rows: 1 x 12 300 29.4 / 28.2 and 26.7 / 26.3, 1 x 13 000 29.5 / 29.2 and 26.8 /
+// 27.4, 1 x 14 300 29.8 / 30.5 and 27.3 / 28.8, 2 x 7150 23.4 / 23.9 and 21.4 / 22.4; but 4 x 3575 21.0 / 20.5, 8 x 1787 18.8 / 18.3).
+constexpr int LIGHT_BAGS = 7 * SCAN_TILE, LIGHT_BAGS_FEW = 25 * SCAN_TILE / 4;
 constexpr int LIGHT_INPUT = 512;  // inputs of such a stack at most: four blocks a compute unit by its LDS
 
 // Sum over max(len, 0) of lengths [0, n) by all threads of the block; s_w: a word
 // per wave.
-template <int THREADS>
+// MANY: of those beyond what six loads a thread take in one trip as well (a seventh is 1 % of a launch without them, two
+// trips 4 %: 8 tables of 8 ids x 1787 samples 19.6 -> 19.2 us per forward).
+template <int THREADS, bool MANY = false>
 __device__ inline long long sum_before(const int32_t *__restrict__ len, int n, long long *s_w)
 {
-    const long long sum = wave_sum(part_of_sum<THREADS>(len, n));
+    const long long sum = wave_sum(MANY && n > 6 * 4 * THREADS ? part_of_sum<THREADS, 7>(len, n) : part_of_sum<THREADS>(len, n));
     if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = sum;
     __syncthreads();
     long long all = 0;
@@ -68,7 +72,7 @@ __device__ inline long long sum_before(const int32_t *__restrict__ len, int n, l
 }
 
 // Block `b` of the pooling blocks, WAVES bags a block, one a wave.
-template <int WAVES, int LPR, bool HALF, bool STREAM>
+template <int WAVES, int LPR, bool HALF, bool STREAM, bool MANY = false>
 __device__ inline void pool_from_lengths(const int32_t *__restrict__ len, const TableDesc *__restrict__ tables,
                                          const int32_t *__restrict__ indices, long long nnz, int n, int b, int per,
                                          const BagTable &div, int T, float one, ErrRecord *err, const PoolOut &out)
@@ -81,7 +85,7 @@ __device__ inline void pool_from_lengths(const int32_t *__restrict__ len, const 
     int own[WAVES];  // the block's lengths, requested with the others
 #pragma unroll
     for (int i = 0; i < WAVES; ++i) own[i] = max(len[min(first + i, n - 1)], 0);
-    long long start = sum_before<WAVES * 64>(len, first, s_w);
+    long long start = sum_before<WAVES * 64, MANY>(len, first, s_w);
     if (bag >= n) return;
     long long end = start;
 #pragma unroll
@@ -123,8 +127,9 @@ __global__ __launch_bounds__(chain::CH_THREADS, LIGHT ? 8 : chain::waves_per_sim
             chain::mlp_chain_block<true, 1, 1>(a, smem, b, 0, (b >> 3) % share, share);
         return;
     }
-    pool_from_lengths<chain::CH_WAVES, LPR, HALF, STREAM>(len, tables, indices, nnz, n, b - chain_blocks, per,
-                                                          BagTable{B, magic}, T, one, err, out);
+    static_assert((LIGHT ? LIGHT_BAGS : LONG_BAGS) <= (LIGHT ? 7 : 6) * 4 * chain::CH_THREADS, "one trip");
+    pool_from_lengths<chain::CH_WAVES, LPR, HALF, STREAM, LIGHT>(len, tables, indices, nnz, n, b - chain_blocks, per,
+                                                             BagTable{B, magic}, T, one, err, out);
 }
 
 // A block has the WK waves of the layer's tile.  TM = 0: no layer.
@@ -327,7 +332,8 @@ bool front_applies(int T, int B, int D, int dtype, long long nnz, long long max_
 {
     const long long n = (long long)T * B;
     const int rowbytes = D * (dtype == REC_F16 ? 2 : 4);
-    const int most = concat ? SHORT_FORM_BAGS : ride_input > 0 && ride_input <= LIGHT_INPUT ? LIGHT_BAGS : LONG_BAGS;
+    const int light = T < 4 ? LIGHT_BAGS_FEW : LIGHT_BAGS;
+    const int most = concat ? SHORT_FORM_BAGS : ride_input > 0 && ride_input <= LIGHT_INPUT ? light : LONG_BAGS;
     if (n > most || (rowbytes != 64 && rowbytes != 128 && rowbytes != 256)) return false;
     const bool sh = pool_short_applies(rowbytes, nnz, n);
     return concat ? sh : !sh && pool_narrow(max_rows, rowbytes);

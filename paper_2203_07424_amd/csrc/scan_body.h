@@ -31,14 +31,13 @@ __device__ inline long long block_sum(long long v, long long *s_w)
 }
 
 // This thread's part of the sum over max(len, 0) of lengths [0, n), n a multiple of 4
-// and a few thousand; threads [0, THREADS) of the block.  Up to six 16-byte loads a
+// and a few thousand; threads [0, THREADS) of the block.  Up to U 16-byte loads a
 // thread in flight: with four single ones 7800 lengths were eight trips in a row
 // (26 tables x 300 samples 37.9 -> 33.5 us per forward).
-template <int THREADS>
+template <int THREADS, int U = 6>
 __device__ inline long long part_of_sum(const int32_t *__restrict__ len, int n)
 {
     typedef int i32x4 __attribute__((ext_vector_type(4)));
-    constexpr int U = 6;
     const bool wide = (reinterpret_cast<uintptr_t>(len) & 15) == 0;
     long long sum = 0;
     for (int k0 = 4 * (int)threadIdx.x; k0 < n; k0 += 4 * THREADS * U) {

@@ -24,9 +24,10 @@ def binding():
     (7, 64, np.float16, 1025, (30, 64), 8, False, True), (23, 32, np.float32, 312, (512, 256, 32), 8, True, True),
     (8, 64, np.float16, 1792, (13, 256, 128, 64), 8, True, True), (3, 64, np.float32, 4779, (257, 100, 64), 8, False, False),  # a bag too many
     (10, 16, np.float32, 1003, (500, 16), 8, True, True), (7, 128, np.float16, 1030, (64, 256, 128), 6, False, True),          # 256-byte rows
-    (5, 128, np.float16, 2001, (100, 128), 6, True, True), (3, 64, np.float32, 4778, (257, 100, 64), 6, False, True),
+    (5, 128, np.float16, 2001, (100, 128), 6, True, True), (4, 64, np.float32, 3584, (257, 100, 64), 6, False, True),
     (9, 64, np.float32, 800, (33, 64), 6, True, True), (12, 32, np.float16, 650, (20, 40, 32), 9, False, True),                # 64
     (10, 32, np.float16, 1400, (512, 32), 9, True, True), (10, 16, np.float32, 1003, (500, 16), 8, False, True),
+    (3, 64, np.float32, 4266, (257, 100, 64), 6, False, True), (3, 64, np.float32, 4267, (257, 100, 64), 6, False, False),     # fewer tables
     (10, 64, np.float32, 520, (300, 128, 64), 60, False, True),   # few bags, 300 KB of rows a compute unit
     (10, 64, np.float32, 520, (300, 128, 64), 50, False, False)])  # 250
 def test_front_of_more_bags(binding, T, D, dtype, B, bottom, mean, stream, light):

@@ -40,7 +40,8 @@ def pooling(tables, dim, batch, ids, dense, bottom, hidden=(64,), concat=False, 
     (28, 256, 80, 1000, (64, 64), b.REC_POOL_FRONT), (28, 256, 40, 512, (64, 64), b.REC_POOL_FRONT),       # 280 KB
     (8, 896, 10, 512, (64, 64), b.REC_POOL_FRONT), (8, 897, 10, 512, (64, 64), b.REC_POOL_FRONT_LIGHT),    # 7168 bags
     (8, 1792, 10, 512, (64, 64), b.REC_POOL_FRONT_LIGHT), (8, 1793, 10, 512, (64, 64), b.REC_POOL_BAG),    # 14 336
-    (8, 897, 10, 1000, (64, 64), b.REC_POOL_BAG)])
+    (3, 4266, 10, 512, (64, 64), b.REC_POOL_FRONT_LIGHT), (3, 4267, 10, 512, (64, 64), b.REC_POOL_BAG),    # 12 800
+    (4, 3584, 10, 512, (64, 64), b.REC_POOL_FRONT_LIGHT), (8, 897, 10, 1000, (64, 64), b.REC_POOL_BAG)])
 def test_light_form_of_a_stack(tables, batch, ids, dense, bottom, form):
     assert pooling(tables, 64, batch, ids, dense, bottom) == form
 
