@@ -80,11 +80,15 @@ hipError_t launch_lookup(const FrontProblem &f, hipStream_t s)
 
 }  // namespace
 
-// As many as the compute units that the others leave, a block each, or what a wave does in the others' time.
+// A block for each compute unit that the others leave, as long as a wave is done with its units when these are; else
+// so many that they come behind them, on all compute units (one more than there are compute units is a round: 13 tables x
+// 7000 samples with 300 features, a block a unit that is left / nine more 25.3 / 29.6 us per forward; 26 x 2400, eight left, 12
+// units a wave / four 29.4 / 24.4, 1000 features 32.2 / 26.1).
 int lookup_dense_blocks(const ConcatDense &job, int left)
 {
     constexpr int WAVES = LOOKUP_THREADS / 64;
-    return std::min(concat_dense_blocks(job, WAVES, 2), std::max({16, left, concat_dense_blocks(job, WAVES, 8)}));
+    if (concat_dense_blocks(job, WAVES, 12) <= left) return std::min(concat_dense_blocks(job, WAVES, 2), left);
+    return concat_dense_blocks(job, WAVES, 4);
 }
 
 bool front_lookup_applies(int T, int B, int D, int dtype, long long nnz, int num_cus)
