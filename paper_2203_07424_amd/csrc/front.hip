@@ -20,16 +20,19 @@
 // layer's, which write its columns of the Predict-FC input rows too), then pooling.
 // 64-64 in front of four towers, 26 tables x 300 42.6 -> 32.5 us, x 1 28.3 -> 17.3.
 //
+// The pooling waves of front_kernel get the registers Bottom-FC's need: 122, and 16 of them share a compute unit, or 64
+// in the light form, and all 32 do (front_takes_light()).  LONG_BAGS is its limit in the form with 122, beyond which some shapes
+// lose against two launches (us per forward, two launches / one: 8 tables x 800 samples 15.7 / 12.8, 40 x 160 26.9 / 23.2,
+// 10 x 700 22.2 / 20.2; 10 x 800 22.9 / 23.2); LIGHT_BAGS, below, that of the light one.
+//
 // front_fc_kernel's pooling blocks get the registers and the LDS of the layer's tile: tiles of up to 32 rows,
-// between 68 and 123 registers.  The pooling waves of front_kernel get the registers Bottom-FC's need: 122, and 16
-// waves share a compute unit instead of 32, or 64 in the light form (front_takes_light()).
-// LONG_BAGS: with 122 registers some shapes lose beyond it against two launches (us per forward, two launches / one: 8
-// tables x 800 samples 15.7 / 12.8, 40 x 160 26.9 / 23.2, 10 x 700 22.2 / 20.2; 10 x 800 22.9 / 23.2).  For front_fc_kernel the line lies
-// there too: below, the layer beside the scan alone (csrc/scan.hip) is the longer forward in most shapes and
-// near the line as often the shorter one (beside pooling / beside the scan: 30 x 200, 2560 -> 1024 36.0 / 38.3; 14 x
-// 500, 600 -> 512 with 8 ids 27.1 / 25.5, with 60 31.3 / 31.6); beyond it that is the shorter (12 000 bags: 50.5 /
-// 49.7, 57.9 as three launches; 14 000 and more 59.8 / 52.2, 41.6 / 24.8).  front_short_kernel: 26 tables x 300 samples 47.4 -> 44.8 us, x 16
-// 36.7 -> 34.0, even at 16380 bags, where adding up the lengths takes as long as the launches it saves.
+// between 68 and 123 registers.  Its limit is LONG_BAGS as well: below, the layer beside the scan alone (csrc/scan.hip) is the
+// longer forward in most shapes and near the line as often the shorter one (beside pooling / beside the scan: 30 x 200,
+// 2560 -> 1024 36.0 / 38.3; 14 x 500, 600 -> 512 with 8 ids 27.1 / 25.5, with 60 31.3 / 31.6); beyond it that is the
+// shorter (12 000 bags: 50.5 / 49.7, 57.9 as three launches; 14 000 and more 59.8 / 52.2, 41.6 / 24.8).
+//
+// front_short_kernel, up to SHORT_FORM_BAGS: 26 tables x 300 samples 47.4 -> 44.8 us, x 16 36.7 -> 34.0, even at 16 380 bags,
+// where adding up the lengths takes as long as the launches it saves.
 #include <algorithm>
 
 #include "gemm_split_body.h"
@@ -53,16 +56,15 @@ constexpr int LONG_BAGS = 7 * SCAN_TILE / 2;
 // blocks are so many that the line lies lower (8 ids, fp32 and fp16 rows: 1 x 12 300 29.4 / 28.2 and 26.7 / 26.3, 1 x 13 000 29.5 / 29.2 and 26.8 /
 // 27.4, 1 x 14 300 29.8 / 30.5 and 27.3 / 28.8, 2 x 7150 23.4 / 23.9 and 21.4 / 22.4; but 4 x 3575 21.0 / 20.5, 8 x 1787 18.8 / 18.3).
 constexpr int LIGHT_BAGS = 7 * SCAN_TILE, LIGHT_BAGS_FEW = 25 * SCAN_TILE / 4;
+constexpr int MANY_LOADS = 7, MANY_BAGS = 13 * SCAN_TILE / 2;  // loads of a thread, and beyond which bags
 constexpr int LIGHT_INPUT = 512;  // inputs of such a stack at most: four blocks a compute unit by its LDS
 
 // Sum over max(len, 0) of lengths [0, n) by all threads of the block; s_w: a word
 // per wave.
-// MANY: of those beyond what six loads a thread take in one trip as well (a seventh is 1 % of a launch without them, two
-// trips 4 %: 8 tables of 8 ids x 1787 samples 19.6 -> 19.2 us per forward).
-template <int THREADS, bool MANY = false>
+template <int THREADS, int U>
 __device__ inline long long sum_before(const int32_t *__restrict__ len, int n, long long *s_w)
 {
-    const long long sum = wave_sum(MANY && n > 6 * 4 * THREADS ? part_of_sum<THREADS, 7>(len, n) : part_of_sum<THREADS>(len, n));
+    const long long sum = wave_sum(part_of_sum<THREADS, U>(len, n));
     if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = sum;
     __syncthreads();
     long long all = 0;
@@ -72,7 +74,7 @@ __device__ inline long long sum_before(const int32_t *__restrict__ len, int n, l
 }
 
 // Block `b` of the pooling blocks, WAVES bags a block, one a wave.
-template <int WAVES, int LPR, bool HALF, bool STREAM, bool MANY = false>
+template <int WAVES, int LPR, bool HALF, bool STREAM, int U = SUM_LOADS>
 __device__ inline void pool_from_lengths(const int32_t *__restrict__ len, const TableDesc *__restrict__ tables,
                                          const int32_t *__restrict__ indices, long long nnz, int n, int b, int per,
                                          const BagTable &div, int T, float one, ErrRecord *err, const PoolOut &out)
@@ -85,7 +87,7 @@ __device__ inline void pool_from_lengths(const int32_t *__restrict__ len, const 
     int own[WAVES];  // the block's lengths, requested with the others
 #pragma unroll
     for (int i = 0; i < WAVES; ++i) own[i] = max(len[min(first + i, n - 1)], 0);
-    long long start = sum_before<WAVES * 64, MANY>(len, first, s_w);
+    long long start = sum_before<WAVES * 64, U>(len, first, s_w);
     if (bag >= n) return;
     long long end = start;
 #pragma unroll
@@ -98,8 +100,11 @@ __device__ inline void pool_from_lengths(const int32_t *__restrict__ len, const 
                                              (int)min(end, nnz), one, err);
 }
 
-// LIGHT: Bottom-FC within 64 registers, so that 32 pooling waves share a compute unit.
-template <int LPR, bool HALF, bool STREAM, bool LIGHT>
+// LIGHT: Bottom-FC within 64 registers, so that 32 pooling waves share a compute unit.  U: loads of a thread for the
+// earlier lengths; SUM_LOADS take 12 288 of them in one trip, and seven pay from where many blocks have more (us per
+// forward, six / seven, 8 tables of 8 ids x 1787 samples 19.6 / 18.9, x 1625 18.1 / 18.4, x 1375 17.3 / 17.4; both in one
+// kernel, chosen at run time, cost those 0.2 us that need no seventh).
+template <int LPR, bool HALF, bool STREAM, bool LIGHT, int U = SUM_LOADS>
 __global__ __launch_bounds__(chain::CH_THREADS, LIGHT ? 8 : chain::waves_per_simd<1>()) void front_kernel(
     const int32_t *__restrict__ len, const TableDesc *__restrict__ tables, const int32_t *__restrict__ indices,
     long long nnz, int n, int tiles, int chain_blocks, int per, unsigned B, unsigned magic, int T, float one,
@@ -128,7 +133,7 @@ __global__ __launch_bounds__(chain::CH_THREADS, LIGHT ? 8 : chain::waves_per_sim
         return;
     }
     static_assert((LIGHT ? LIGHT_BAGS : LONG_BAGS) <= (LIGHT ? 7 : 6) * 4 * chain::CH_THREADS, "one trip");
-    pool_from_lengths<chain::CH_WAVES, LPR, HALF, STREAM, LIGHT>(len, tables, indices, nnz, n, b - chain_blocks, per,
+    pool_from_lengths<chain::CH_WAVES, LPR, HALF, STREAM, U>(len, tables, indices, nnz, n, b - chain_blocks, per,
                                                              BagTable{B, magic}, T, one, err, out);
 }
 
@@ -226,9 +231,12 @@ hipError_t launch_long(const FrontProblem &f, const ChainProblem &a, hipStream_t
     const int n = f.T * f.B, tiles = (n + SCAN_TILE - 1) / SCAN_TILE, chain_blocks = (a.M + 31) / 32;
     const int pool_blocks = ((n + chain::CH_WAVES - 1) / chain::CH_WAVES + 7) / 8 * 8;
     const BagTable div = BagTable::of_batch(f.B);
-    auto k = front_takes_light(n, f.nnz, LPR * 16, a.Kpad[0], a.num_cus)
+    static_assert(LONG_BAGS <= SUM_LOADS * 4 * chain::CH_THREADS && LIGHT_BAGS <= MANY_LOADS * 4 * chain::CH_THREADS, "one trip");
+    auto k = !front_takes_light(n, f.nnz, LPR * 16, a.Kpad[0], a.num_cus)
+                 ? (f.stream_rows ? front_kernel<LPR, HALF, true, false> : front_kernel<LPR, HALF, false, false>)
+             : n <= MANY_BAGS
                  ? (f.stream_rows ? front_kernel<LPR, HALF, true, true> : front_kernel<LPR, HALF, false, true>)
-                 : (f.stream_rows ? front_kernel<LPR, HALF, true, false> : front_kernel<LPR, HALF, false, false>);
+                 : (f.stream_rows ? front_kernel<LPR, HALF, true, true, MANY_LOADS> : front_kernel<LPR, HALF, false, true, MANY_LOADS>);
     hipLaunchKernelGGL(k, dim3(tiles + chain_blocks + pool_blocks), dim3(chain::CH_THREADS),
                        std::max(chain::chain_lds_bytes<1>(a.ld_lds), sizeof(ScanShared)), s, f.lengths, f.tables, f.indices, f.nnz, n, tiles, chain_blocks,
                        pool_blocks / 8, div.B, div.magic, f.T, 1.0f, f.offsets, f.err, f.out, one_stack(a));
@@ -311,6 +319,8 @@ hipError_t prepare_long()
     if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, true, false>, most);
     if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, false, true>, most);
     if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, true, true>, most);
+    if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, false, true, MANY_LOADS>, most);
+    if (e == hipSuccess) e = grant_lds(front_kernel<LPR, HALF, true, true, MANY_LOADS>, most);
     if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 2, 2, 8>();
     if (e == hipSuccess) e = prepare_fc_beside<LPR, HALF, 2, 4, 8>();
     return e;

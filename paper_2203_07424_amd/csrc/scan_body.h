@@ -34,7 +34,8 @@ __device__ inline long long block_sum(long long v, long long *s_w)
 // and a few thousand; threads [0, THREADS) of the block.  Up to U 16-byte loads a
 // thread in flight: with four single ones 7800 lengths were eight trips in a row
 // (26 tables x 300 samples 37.9 -> 33.5 us per forward).
-template <int THREADS, int U = 6>
+constexpr int SUM_LOADS = 6;
+template <int THREADS, int U = SUM_LOADS>
 __device__ inline long long part_of_sum(const int32_t *__restrict__ len, int n)
 {
     typedef int i32x4 __attribute__((ext_vector_type(4)));
