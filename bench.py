@@ -52,9 +52,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 matrix rate
 # of this run, and hold only for the kernel source the counters were taken with:
 # reported as null once csrc/pool.hip or csrc/pool_body.h differs.
 POOL_TRAFFIC = {
-    "sha256": "d66582af303d20aebbb1a615834521a3b0c64ae7194d546b4780036c387bcbcd",
-    ("rmc2", 4096): {"fetch_bytes": 554011634.6, "write_bytes": 41943680.0},
-    ("rmc2-uniform", 4096): {"fetch_bytes": 1721484776.9, "write_bytes": 41943680.0},
+    "sha256": "0201d26abce91ff7639c3e45ec8c84f861c600222696945488a26ec49fce0fd8",
+    ("rmc2", 4096): {"fetch_bytes": 554011759.6, "write_bytes": 41943680.0},
+    ("rmc2-uniform", 4096): {"fetch_bytes": 1721478186.5, "write_bytes": 41943680.0},
 }
 
 

@@ -69,8 +69,8 @@ __global__ __launch_bounds__(POOL_WAVES * 64) void pool_kernel(
 // Two neighbouring bags of a table by one wave, one after the other: the ids of both in one
 // trip, and no store before the last row.  (Behind a store the next bag's loads wait until it
 // has reached memory: loads and stores count in one order.)  With a wave a bag the trips
-// to a bag's offsets and ids are about a quarter of its life.  60 tables x 16384 samples 650 -> 610 us per
-// forward (four bags a wave 605, eight 615).  For launches of many rounds of waves, where the longer
+// to a bag's offsets and ids are about a quarter of its life.  60 tables x 16384 samples on changing inputs
+// 645 -> 604 us per forward (in another run, 650 -> 610, four bags a wave 605, eight 615).  For launches of many rounds of waves, where the longer
 // life of the last ones does not show: 40 x 4096, 20 rounds, 160.5 -> 161.3.
 // Waves share nothing, so a block is one of them: its slot is taken again when it ends and
 // not when the last of four does (632 -> 618).  Waves that live for one bag, and for short ones above
