@@ -424,6 +424,8 @@ hipError_t launch_fc(const FcProblem &a, hipStream_t s)
     // registers free.  With four k-tiles in flight these kernels need 184-214 and
     // would wait for a second slot on the same SIMD, which pooling refills first
     // (measured: 123 instead of 14 us); with three they need 130-150.
+    // Beside waves of two bags, 64 registers each with fp16 rows, a slot is 64: their blocks
+    // there are of four or eight waves, which end together (csrc/pool.hip).
     if (fc_takes_split(a)) return launch_fc_split(a, s);
     if (a.dot_out) {
         // The block must own whole rows.
